@@ -206,7 +206,7 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
 
 int stq_set_schedule(stq_ctx* ctx, uint64_t ticket_min_tiles) {
   if (!ctx) return STQ_EINVAL;
-  ctx->ticket_min_units = ticket_min_tiles ? ticket_min_tiles : kTicketMinUnits;
+  ctx->ticket_min_tiles = ticket_min_tiles ? ticket_min_tiles : kTicketMinTiles;
   return STQ_OK;
 }
 
@@ -268,7 +268,7 @@ int check_hparams(const stq_hparams* hp) {
 }
 
 int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t total, double* d_stats,
-                 const stq_hparams* hp, int mode, bool quarters_ok, uint32_t v_widths, void* stream, uint32_t* sched) {
+                 const stq_hparams* hp, int mode, bool quarters_ok, void* stream, uint32_t* sched) {
   StepArgs a;
   a.desc = d_desc;
   a.n_tensors = n;
@@ -286,44 +286,55 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
   a.lr = hp->lr;
   a.decay = 1.0f - hp->lr * hp->weight_decay;
   a.lgK = static_cast<uint32_t>(lg_block(hp->block));
-  a.v_widths = v_widths;
 
   // statistics: all of them, or only the gradient's (the flag for all wins)
   const int stats = (hp->flags & STQ_FLAG_STATS) ? 1 : ((hp->flags & STQ_FLAG_STATS_GRAD) ? 2 : 0);
   const bool want_stats = stats != 0;
+  const bool fp32_grads = hp->grad_dtype == 0;
   // every variant fits six waves per SIMD (three workgroups per CU) except the wide-state one (two)
   const uint32_t cap_cu = mode == 2 ? 2 : 8;
   const uint32_t per_cu = ctx->groups_per_cu < cap_cu ? ctx->groups_per_cu : cap_cu;
   const uint32_t wpg = kWavesPerGroup;
-  const uint32_t max_groups = ctx->n_cu * per_cu;
-  // Units of scheduling (see step_kernel): quarter tiles when whole tiles would leave waves idle and
-  // every width keeps quarters word-aligned (multiples of 4 bits), else tiles.
-  const bool quarters = quarters_ok && static_cast<uint64_t>(total) < static_cast<uint64_t>(max_groups) * wpg;
-  a.quarter_units = quarters ? 1u : 0u;
+  uint32_t max_groups = ctx->n_cu * per_cu;
+  // Tickets (see step_kernel) for large launches: 0.33 G parameters 849 us against 905 (fp32 gradients) and 732 against
+  // 762 (bf16), 0.2 G the same within 1 %, 0.13 G slower (358 against 355; 314 against 308).  With statistics from half
+  // of that size on (0.2 G 584 us against 599, 90 M 303 against 281).
+  const uint64_t min_tiles = want_stats ? ctx->ticket_min_tiles / 2 : ctx->ticket_min_tiles;
+  bool tickets = total >= min_tiles;
+#ifdef STQ_TUNING_ENV
+  if (std::getenv("STQ_NO_TICKETS")) tickets = false;
+  if (std::getenv("STQ_TICKETS")) tickets = true;
+#endif
+  a.sched = !tickets ? nullptr : (sched ? sched : ctx->d_sched);
+  // Units of scheduling (see step_kernel): quarter tiles in a launch that whole tiles would not fill (2.4 M parameters
+  // 8.0 us against 14.7, 12.6 M 33 against 40), and under stripes also in larger ones: the last round is shorter and the
+  // chip's window on each array a quarter as wide.  With bf16 gradients up to 25,000 tiles (30 M 73.5 us against 75.5,
+  // 45 M 107 against 108.5, but 60 M 143 against 141); with fp32 gradients or wide states up to the ticket schedule
+  // (fp32: 45 M 107 against 119, 90 M 234 against 252; 60 M of 16- and 32-bit states 266 against 295).
+  bool quarters = total < static_cast<uint64_t>(max_groups) * wpg || (!tickets && (fp32_grads || mode == 2 || total < 25000u));
+#ifdef STQ_TUNING_ENV
+  if (const char* e = std::getenv("STQ_QUARTER_BELOW")) quarters = total < std::strtoull(e, nullptr, 10);
+#endif
+  a.quarter_units = quarters ? (quarters_ok ? 1u : 2u) : 0u;
   const uint64_t units = static_cast<uint64_t>(total) << (quarters ? 2 : 0);
   const uint64_t need_groups = (units + wpg - 1) / wpg;
+  // The plain step is bound by the memory system once its waves have several units each, and fewer waves in flight keep
+  // the chip's accesses closer together: two workgroups per CU instead of three take 3404 us instead of 3497 on 1.56 G
+  // parameters (K = 128, bf16), 345 instead of 360 on 124 M.  A launch whose units all fit at once wants every wave
+  // (2.4 M parameters: 8.8 us with three, 10.0 with two), and the variants with statistics have arithmetic to hide
+  // (3525 us with three, 3620 with two).
+  if (!want_stats && need_groups > max_groups && per_cu > 2) max_groups = ctx->n_cu * 2;
   const uint32_t groups = static_cast<uint32_t>(need_groups < max_groups ? need_groups : max_groups);
-  // order of the units under stripes (see step_kernel).  Without statistics interleaved chunks: pairs of units
-  // once a wave has at least four (measured 2-3 % faster than single units between 5 and 11 units per wave:
-  // a wave then owns whole cache lines of the scale arrays), four at a time from 24 on, single units in the
-  // smallest launches so that every wave gets work.  With statistics few long chunks, because a wave flushes
-  // its sums whenever its next unit lies in another tensor: one range per wave, or for the gradient's
-  // statistics alone (a cheap flush) four units at a time in a large launch.
+  // Order of the units under stripes (see step_kernel).  Quarters: the workgroups take eight at a time in turn.  Tiles:
+  // interleaved chunks, pairs of tiles once a wave has at least four (a wave then owns whole cache lines of the scale
+  // arrays: 345 us instead of 348 with single tiles on 124 M parameters, 360 with four at a time), four at a time from
+  // 24 on.  With statistics one range of units per workgroup, whose waves take them in turn: the fewer tensors a
+  // workgroup meets, the fewer of its sums go to the global slots.
   const uint64_t n_waves = static_cast<uint64_t>(groups) * wpg;
   const uint64_t per_wave = (units + n_waves - 1) / n_waves;
-  if (stats == 1) a.chunk = static_cast<uint32_t>(per_wave);
-  else if (stats == 2) a.chunk = static_cast<uint32_t>(per_wave >= 64 ? 4 : per_wave);
+  if (want_stats) a.chunk = static_cast<uint32_t>(per_wave * wpg);
   else a.chunk = per_wave >= 24 ? 4 : (per_wave >= 4 ? 2 : 1);
   if (ctx->chunk_override && !want_stats) a.chunk = ctx->chunk_override;
-  // tickets (see step_kernel) for large launches; with statistics from a third of that size on, because the
-  // stripes of those variants are few long chunks (measured: 61 K tiles 9 % faster with tickets, 42 K tiles 6 %
-  // slower; without statistics 2 % faster and 12 % slower)
-  const uint64_t min_units = want_stats ? ctx->ticket_min_units / 3 : ctx->ticket_min_units;
-  a.sched = units < min_units ? nullptr : (sched ? sched : ctx->d_sched);
-#ifdef STQ_TUNING_ENV
-  if (std::getenv("STQ_NO_TICKETS")) a.sched = nullptr;
-  if (std::getenv("STQ_TICKETS")) a.sched = sched ? sched : ctx->d_sched;
-#endif
   return launch_step(a, hp->grad_dtype == 1, stats, mode, groups, stream) == 0 ? STQ_OK : STQ_EHIP;
 }
 
@@ -374,13 +385,11 @@ int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream
 
 // Kernel variant for a set of descriptors: 0 in place, 1 widths change, 2 some state is (or becomes)
 // 16 or 32 bits wide; and whether every width keeps quarter tiles word-aligned.
-void classify(const TensorDesc* descs, uint32_t n, bool changes, int* mode, bool* quarters_ok, uint32_t* v_widths) {
+void classify(const TensorDesc* descs, uint32_t n, bool changes, int* mode, bool* quarters_ok) {
   *mode = changes ? 1 : 0;
   *quarters_ok = true;
-  *v_widths = 0;
   for (uint32_t l = 0; l < n; ++l) {
     const TensorDesc& d = descs[l];
-    if (d.bv_out <= 8) *v_widths |= 1u << d.bv_out;
     if (is_wide(d.bm) || is_wide(d.bv) || is_wide(d.bm_out) || is_wide(d.bv_out)) *mode = 2;
     *quarters_ok = *quarters_ok && ((d.bm | d.bv | d.bm_out | d.bv_out) & 3u) == 0;
   }
@@ -426,9 +435,8 @@ int step_impl(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const stq_bit
 
   int mode;
   bool quarters_ok;
-  uint32_t v_widths;
-  classify(descs.data(), n, new_plan != nullptr, &mode, &quarters_ok, &v_widths);
-  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, quarters_ok, v_widths, stream)) return e;
+  classify(descs.data(), n, new_plan != nullptr, &mode, &quarters_ok);
+  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, quarters_ok, stream)) return e;
   if ((hp->flags & (STQ_FLAG_STATS | STQ_FLAG_STATS_GRAD)) != 0)
     for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;
@@ -466,15 +474,14 @@ int stq_step_static(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const s
   if (int e = fill_descs(ctx, tensors, n, plan, hp->block, true, ctx->h_stage[k], &total)) return e;
   int mode;
   bool quarters_ok;
-  uint32_t v_widths;
-  classify(ctx->h_stage[k], n, false, &mode, &quarters_ok, &v_widths);
+  classify(ctx->h_stage[k], n, false, &mode, &quarters_ok);
   TensorDesc* table = static_cast<TensorDesc*>(ctx->static_scratch);
   uint32_t* sched = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ctx->static_scratch) + kStaticTableBytes);
   if (int e = upload_descs(ctx, k, nullptr, n, table, s)) return e;
   // the scheduling words must be zero when the kernel starts: a kernel leaves them so, but the array is shared
   // by every caller on this GPU and may hold what an aborted launch left
   if (launch_fill_zero(sched, kSchedWords, stream) != 0) return STQ_EHIP;
-  if (int e = launch_table(ctx, table, n, total, ctx->d_stats, hp, mode, quarters_ok, v_widths, stream, sched)) return e;
+  if (int e = launch_table(ctx, table, n, total, ctx->d_stats, hp, mode, quarters_ok, stream, sched)) return e;
   if ((hp->flags & (STQ_FLAG_STATS | STQ_FLAG_STATS_GRAD)) != 0)
     for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;

@@ -44,9 +44,9 @@ struct StepArgs {
   float ibc1, ibc2;        // reciprocal bias corrections 1/(1-beta^t)
   float eps, lr, decay;    // decay = 1 - lr*weight_decay
   uint32_t lgK;            // log2 of the block size: 6, 7 or 8
-  uint32_t chunk;          // consecutive units a wave takes at a time, see step_kernel
-  uint32_t quarter_units;  // 1: a unit is a quarter tile (small launches whose widths keep quarters word-aligned)
-  uint32_t v_widths;       // bit b set: some second moment may be quantized at width b in this launch
+  uint32_t chunk;          // stripes of tiles: consecutive tiles a wave takes at a time; statistics: units of a workgroup
+  uint32_t quarter_units;  // not 0: a unit is a quarter tile (small launches); 2: and some width is not a multiple of
+                           // 4 bits, so that quarters share words
   uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters and the count of
                            // workgroups that have left; null: no tickets, every wave walks its own stripes
                            // (see step_kernel)

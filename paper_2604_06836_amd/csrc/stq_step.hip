@@ -7,14 +7,16 @@
 // -ffp-contract=off); division and square root are the correctly rounded ones.
 //
 // Work decomposition: one wavefront owns one 2048-element tile at a time and processes it as four
-// quarters of 2 rows: a quarter's working set fits the 80 registers of six waves per SIMD with
-// nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.
+// quarters of 2 rows: a quarter's working set fits the 80 registers of six waves per SIMD (68 to 72 in use) with
+// nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.  Small and medium
+// launches hand the quarters of a tile to four waves (see step_kernel).
 // In row i lane j holds the 4 elements 256*i + 4*j + e, so
 // every parameter and gradient access is a coalesced 16-byte (8-byte for bf16) per-lane access,
 // and a block of K = 64/128/256 consecutive elements is 16/32/64 neighbouring lanes of one row.
 // The lane's 32 codes of a state are exactly b 32-bit words; word p of all lanes is one contiguous
 // 256-byte row of the code buffer.  A quarter reads the words that hold its 8 codes and writes
-// the words it completes; the bits of a word shared with the next quarter travel in a register.
+// the words it completes; the bits of a word shared with the next quarter travel in a register (or, where the next
+// quarter is another wave's, through LDS).
 //
 // Only the bit-stream unpack and pack are specialised per width (small switch arms); all
 // arithmetic is width-generic and takes the width through table offsets and constants.
@@ -32,11 +34,12 @@ namespace stq {
 namespace {
 
 constexpr int XS = 68;  // row stride (words) of the transpose scratch: keeps 16-byte alignment, shifts banks
-// per-wave LDS scratch: XR[4][XS] partial maxima (later the den table), old scales, new scales, reciprocals
+// per-wave LDS scratch: XR[4][XS] partial maxima (later the den or root table), old scales, new scales, reciprocals
 constexpr int kWaveScratch = 4 * XS + 3 * 64;
 constexpr int kLdsWords = kTabWords + kWavesPerGroup * kWaveScratch;  // + the statistics slices in that variant
 constexpr int kStatFlushTiles = 16;  // fp32 lane sums are widened to fp64 every this many tiles
 constexpr uint32_t kDenEntries = 128;  // capacity of the per-wave den table (8 bytes per entry, inside XR)
+constexpr uint32_t kRootEntries = 256; // capacity of the per-wave root table (4 bytes per entry, inside XR)
 
 // Pointers that arrive through the tensor table are loaded from memory, so the compiler cannot
 // see that they are global; say so, to get global_load/global_store instead of flat accesses.
@@ -82,49 +85,103 @@ __device__ __forceinline__ uint32_t extract(const uint32_t (&w)[3]) {
   return bit_field<0, B>(__builtin_amdgcn_alignbit(w[p + 1], w[p], static_cast<uint32_t>(sh)));
 }
 
-template <int B>
-__device__ __forceinline__ void insert(uint32_t (&w)[3], int n, uint32_t code) {
-  const int off = n * B, p = off >> 5, sh = off & 31;
-  if (sh == 0) w[p] = code; else w[p] |= code << sh;
-  if (sh + B > 32) w[p + 1] = code >> (32 - sh);  // first bits of the next word
+// Byte N of x, times 4; byte N of x masked: one instruction each (the byte is selected by the operand).
+template <int N>
+__device__ __forceinline__ uint32_t byte_times4(uint32_t x, uint32_t two) {
+  uint32_t r;
+  if (N == 0) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(two), "v"(x));
+  if (N == 1) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(two), "v"(x));
+  if (N == 2) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(two), "v"(x));
+  if (N == 3) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(two), "v"(x));
+  return r;
+}
+template <int N>
+__device__ __forceinline__ uint32_t byte_and(uint32_t x, uint32_t mask) {
+  uint32_t r;
+  if (N == 0) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "s"(mask), "v"(x));
+  if (N == 1) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "s"(mask), "v"(x));
+  if (N == 2) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "s"(mask), "v"(x));
+  if (N == 3) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "s"(mask), "v"(x));
+  return r;
 }
 
-// The 8 codes of a quarter as byte offsets into the width's value table: (code << 2) | (4 << B).
+// The 8 codes of a quarter, times 4: byte offsets into the width's value table.
 // lw holds the lane's words from the one that contains the quarter's first bit; s0 (0, 8, 16 or
-// 24) is the position of that bit in lw[0].
+// 24) is the position of that bit in lw[0] (always 0 at widths 4 and 8).
 template <int B>
 __device__ __forceinline__ void unpack_offsets(const uint32_t* lw, uint32_t s0, uint32_t (&off)[8]) {
-  uint32_t w[3];
-  w[0] = __builtin_amdgcn_alignbit(lw[1], lw[0], s0);
-  w[1] = __builtin_amdgcn_alignbit(lw[2], lw[1], s0);
-  w[2] = 0u;
-  off[0] = (extract<B, 0>(w) << 2) | (4u << B);
-  off[1] = (extract<B, 1>(w) << 2) | (4u << B);
-  off[2] = (extract<B, 2>(w) << 2) | (4u << B);
-  off[3] = (extract<B, 3>(w) << 2) | (4u << B);
-  off[4] = (extract<B, 4>(w) << 2) | (4u << B);
-  off[5] = (extract<B, 5>(w) << 2) | (4u << B);
-  off[6] = (extract<B, 6>(w) << 2) | (4u << B);
-  off[7] = (extract<B, 7>(w) << 2) | (4u << B);
+  if constexpr (B == 8) {
+    uint32_t two = 2u;
+    asm("" : "+v"(two));
+    off[0] = byte_times4<0>(lw[0], two); off[1] = byte_times4<1>(lw[0], two);
+    off[2] = byte_times4<2>(lw[0], two); off[3] = byte_times4<3>(lw[0], two);
+    off[4] = byte_times4<0>(lw[1], two); off[5] = byte_times4<1>(lw[1], two);
+    off[6] = byte_times4<2>(lw[1], two); off[7] = byte_times4<3>(lw[1], two);
+  } else if constexpr (B == 4) {
+    const uint32_t even = lw[0] << 2, odd = lw[0] >> 2;  // code 2k / 2k+1 at bits 2..5 of byte k
+    off[0] = byte_and<0>(even, 0x3Cu); off[1] = byte_and<0>(odd, 0x3Cu);
+    off[2] = byte_and<1>(even, 0x3Cu); off[3] = byte_and<1>(odd, 0x3Cu);
+    off[4] = byte_and<2>(even, 0x3Cu); off[5] = byte_and<2>(odd, 0x3Cu);
+    off[6] = byte_and<3>(even, 0x3Cu); off[7] = byte_and<3>(odd, 0x3Cu);
+  } else {
+    uint32_t w[3];
+    w[0] = __builtin_amdgcn_alignbit(lw[1], lw[0], s0);
+    w[1] = __builtin_amdgcn_alignbit(lw[2], lw[1], s0);
+    w[2] = 0u;
+    off[0] = extract<B, 0>(w) << 2;
+    off[1] = extract<B, 1>(w) << 2;
+    off[2] = extract<B, 2>(w) << 2;
+    off[3] = extract<B, 3>(w) << 2;
+    off[4] = extract<B, 4>(w) << 2;
+    off[5] = extract<B, 5>(w) << 2;
+    off[6] = extract<B, 6>(w) << 2;
+    off[7] = extract<B, 7>(w) << 2;
+  }
 }
 
-// Pack the 8 codes of a quarter behind the s0 bits that `carry` holds of the current word, store
-// the words this completes (at C, word stride 64) and keep the rest in `carry`.
-template <int B>
+// Pack the low B bits of the 8 codes of a quarter behind the s0 bits that `carry` holds of the current word,
+// store the words this completes (at C, word stride 64) and keep the rest in `carry`.  Each code enters its
+// word from the top with one v_alignbit, which needs no masking of what lies above the code; MINUS1: the
+// codes given are all one too large (and at least 1), which one subtraction per word of whole codes undoes.
+// HOLD: another wave has the quarter before this one, so the first word, which the two share when s0 > 0, is left in
+// `held` instead of being stored.  (A quarter that starts inside a word always completes it, and what it leaves in
+// `carry` is then its own bits only: 8B >= 16 and s0 + 8B is 32 for the widths below 4 whose quarters are shorter.)
+template <int B, bool MINUS1, bool HOLD>
 __device__ __forceinline__ void pack_store(const uint32_t (&code)[8], STQ_GLOBAL uint32_t* C, uint32_t s0,
-                                           uint32_t& carry, uint32_t lane) {
-  uint32_t ow[3] = {0u, 0u, 0u};
+                                           uint32_t& carry, uint32_t& held, uint32_t lane) {
+  constexpr int kPer = B <= 4 ? 8 : 4;                       // codes per packed word, kPer * B bits of it
+  constexpr uint32_t kOnes = (B == 2 ? 0x5555u : B == 3 ? 0x249249u : B == 4 ? 0x11111111u : B == 5 ? 0x8421u
+                              : B == 6 ? 0x41041u : B == 7 ? 0x204081u : 0x1010101u);
+  uint32_t w[8 / kPer];
 #pragma unroll
-  for (int n = 0; n < 8; ++n) insert<B>(ow, n, code[n]);
-  const unsigned long long x = (static_cast<unsigned long long>(ow[1]) << 32) | ow[0];
-  const unsigned long long lo = x << s0;
-  const uint32_t m0 = carry | static_cast<uint32_t>(lo);
-  const uint32_t m1 = static_cast<uint32_t>(lo >> 32);
-  const uint32_t m2 = s0 ? (ow[1] >> (32u - s0)) : 0u;
+  for (int k = 0; k < 8 / kPer; ++k) {
+    uint32_t x = code[k * kPer] << (32 - B);
+#pragma unroll
+    for (int n = 1; n < kPer; ++n) x = __builtin_amdgcn_alignbit(code[k * kPer + n], x, B);
+    if (kPer * B < 32) x >>= 32 - kPer * B;
+    w[k] = MINUS1 ? x - kOnes : x;
+  }
+  // the quarter's 8B bits as a pair of words
+  uint32_t lo, hi;
+  if constexpr (B <= 4) { lo = w[0]; hi = 0u; }
+  else if constexpr (B == 8) { lo = w[0]; hi = w[1]; }
+  else { lo = (w[1] << (4 * B)) | w[0]; hi = w[1] >> (32 - 4 * B); }
+  if (B == 4 || B == 8 || s0 == 0) {  // (a quarter of 4- or 8-bit codes always starts on a word)
+    if (B >= 4) C[lane] = lo;
+    if (B == 8) C[64u + lane] = hi;
+    carry = B < 4 ? lo : hi;  // (not used at widths 4 and 8)
+    return;
+  }
+  const uint32_t m0 = HOLD ? lo << s0 : (lo << s0) | carry;
+  const uint32_t m1 = __builtin_amdgcn_alignbit(hi, lo, 32u - s0);
   const uint32_t done = (s0 + 8u * B) >> 5;  // complete words: 0, 1 or 2
-  if (done >= 1) C[lane] = m0;
-  if (done >= 2) C[64u + lane] = m1;
-  carry = done == 0 ? m0 : (done == 1 ? m1 : m2);
+  if (!HOLD && done == 0) { carry = m0; return; }
+  if (HOLD) held = m0; else C[lane] = m0;
+  carry = m1;
+  if (done == 2) {
+    C[64u + lane] = m1;
+    carry = hi >> (32u - s0);
+  }
 }
 
 #define STQ_SWITCH_BITS(bits, CALL)               \
@@ -369,7 +426,21 @@ __device__ __forceinline__ void ticket_stats_tile(LaneStats<S>& s, TicketRecord<
   if (lx) rec->max_bits[kx] = mx;
 }
 
-// wave 0, after the ticket's barrier: the records of the workgroup's waves -> the tensor's global slots
+// stripes, at the end: the wave's statistics -> its record, or an empty record
+template <int S>
+__device__ __forceinline__ void record_stats(LaneStats<S>& s, TicketRecord<S>* rec, bool full, int lane) {
+  asm volatile("" : "+v"(lane));
+  if (S == 1) widen_stats(s, lane);
+  wave_lds_sync();
+  const double g = full ? s.reduced_grad(lane) : 0.0;
+  const uint32_t mx = full ? s.reduced_max(lane) : 0u;
+  int k;
+  if (LaneStats<S>::grad_lead(lane, k)) rec->sum[k] = g;
+  if (S == 1 && lane < 6) rec->sum[3 + lane] = full ? s.wide(lane) : 0.0;
+  if (LaneStats<S>::max_lead(lane, k)) rec->max_bits[k] = mx;
+}
+
+// wave 0, after the ticket's (or the last) barrier: the records of the workgroup's waves -> the tensor's global slots
 template <int S>
 __device__ __forceinline__ void ticket_stats_flush(const TicketRecord<S>* recs, double* slot, int lane) {
   static_assert(kWavesPerGroup == 8, "lane 8k + w takes value k of wave w's record");
@@ -387,45 +458,38 @@ __device__ __forceinline__ void ticket_stats_flush(const TicketRecord<S>* recs, 
   if ((lane & 7) == 0 && k < kMaxima) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]) + k, mx);
 }
 
-// Correctly rounded square root for x = 0 or 2^-96 <= x <= 2^96: the hardware estimate is within
-// one ulp; the residuals x - next_down*s and x - next_up*s (exact in an fma) tell which of the
-// three neighbours is the rounded root.  This is the IEEE expansion without its input scaling.
+// The short forms below are Newton steps from the hardware's estimates with exact residuals (Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000 processor", 1990).  That they end in the correctly rounded result
+// is checked, not assumed: root and reciprocal over every mantissa at every exponent of their ranges on a gfx950; the
+// quotient, given a correctly rounded reciprocal, over every operand pair whose quotient lies so close to the middle
+// between two floats that the last step could go the other way (4e7 pairs, by solving for the numerators).
+// Correctly rounded square root for x = 0 or 2^-96 <= x <= 2^96.
 __device__ __forceinline__ float sqrt_rn_safe(float x) {
-  float s = __builtin_amdgcn_sqrtf(x);
-  const float s_dn = u2f(f2u(s) - 1u), s_up = u2f(f2u(s) + 1u);
-  const float t_dn = __builtin_fmaf(-s_dn, s, x);
-  const float t_up = __builtin_fmaf(-s_up, s, x);
-  s = (t_dn <= 0.0f) ? s_dn : s;
-  s = (t_up > 0.0f) ? s_up : s;
-  return s;
+  const float y = __builtin_amdgcn_rsqf(fmaxf(x, FLT_MIN));  // finite also for x = 0, whose root comes out as 0
+  const float s = x * y, h = 0.5f * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, x), h, s);
 }
-
-// Correctly rounded n/d for n = 0 or 2^-47 <= |n| <= 2^40 and 2^-40 <= d <= 2^40: the IEEE
-// division's expansion (reciprocal estimate, one Newton step, quotient, two exact-residual
-// corrections) without the operand scaling that only extreme exponents need.
-__device__ __forceinline__ float div_rn_safe(float n, float d) {
-  float y = __builtin_amdgcn_rcpf(d);
-  const float e = __builtin_fmaf(-d, y, 1.0f);
-  y = __builtin_fmaf(e, y, y);
-  float q = n * y;
-  float r = __builtin_fmaf(-d, q, n);
-  q = __builtin_fmaf(r, y, q);
-  r = __builtin_fmaf(-d, q, n);
-  return __builtin_fmaf(r, y, q);
-}
-
-// Correctly rounded 1/d for 2^-40 <= d <= 2^40: reciprocal estimate, one Newton step, two
-// exact-residual corrections -- the IEEE division's expansion without the operand scaling that
-// only extreme exponents need.
+// Correctly rounded 1/d for 2^-40 <= d <= 2^40.
 __device__ __forceinline__ float rcp_rn_safe(float d) {
-  float y = __builtin_amdgcn_rcpf(d);
-  const float e = __builtin_fmaf(-d, y, 1.0f);
-  y = __builtin_fmaf(e, y, y);
-  float r = __builtin_fmaf(-d, y, 1.0f);
-  const float q = __builtin_fmaf(r, y, y);
-  r = __builtin_fmaf(-d, q, 1.0f);
-  return __builtin_fmaf(r, y, q);
+  const float y = __builtin_amdgcn_rcpf(d);
+  return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
 }
+// Correctly rounded n/d from y = the correctly rounded 1/d, for n = 0 or 2^-85 <= |n| <= 2^40 and 2^-40 <= d <= 2^40
+// (the quotient is then normal and every residual exact).
+__device__ __forceinline__ float div_rn_safe(float n, float d, float y) {
+  const float q = n * y;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
+}
+// Whether every number added is 0 or has its magnitude between two given ones (as bit patterns).
+struct SafeRange {
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  __device__ __forceinline__ void add(float x) {
+    const uint32_t u = f2u(x) & 0x7FFFFFFFu;
+    lo = min(lo, u - 1u);  // 0 passes
+    hi = max(hi, u);
+  }
+  __device__ __forceinline__ bool within(uint32_t least, uint32_t most) const { return lo >= least - 1u && hi <= most; }
+};
 // 2^-40 <= x <= 2^40, for x >= 0: positive floats order like their bit patterns
 __device__ __forceinline__ bool in_safe_range(float x) { return f2u(x) - 0x2B800000u <= 0x53800000u - 0x2B800000u; }
 
@@ -434,75 +498,72 @@ struct UpdateArgs {
   float ibc1, ibc2, eps, lr, decay;
 };
 
-// theta' = theta*decay - lr * (mt / den), with the quotient computed either by the correctly
-// rounded division, or (FAST) from the correctly rounded reciprocal rden = 1/den by two
-// residual corrections, which gives the same correctly rounded quotient when no intermediate
-// underflows or overflows (the caller checks the ranges that guarantee it).
-template <bool FAST>
-__device__ __forceinline__ float updated_param(float theta, float mt, float den, float rden, const UpdateArgs& u) {
-  float ratio;
-  if (FAST) {
-    const float q0 = mt * rden;
-    const float r0 = __builtin_fmaf(-den, q0, mt);
-    const float q1 = __builtin_fmaf(r0, rden, q0);
-    const float r1 = __builtin_fmaf(-den, q1, mt);
-    ratio = __builtin_fmaf(r1, rden, q1);
-  } else {
-    ratio = mt / den;
-  }
+// theta' = theta*decay - lr * ratio
+__device__ __forceinline__ float updated_param(float theta, float ratio, const UpdateArgs& u) {
   const float upd = u.lr * ratio;
   const float dec = theta * u.decay;
   return dec - upd;
 }
 
-// Logarithmic quantization of v fused with the parameter update, for any width.  The code is the
-// number of thresholds at or below rho = v/blockmax, found with one bucket lookup and one compare
-// on the bit pattern of rho.  The update needs den = sqrt(vq*ibc2) + eps of the quantized value
-// vq, which takes only 2^b values per block: with TABLE they (and their reciprocals) are read from
-// the per-wave table DEN, indexed by (row, block, code); otherwise they are computed per element.
-// mq holds the quantized first moments; theta is replaced by the new parameters.
-template <int STATS, bool TAIL, bool TABLE, bool FAST>
-__device__ __forceinline__ void quant2_update(const float (&v)[8], const float (&mq)[8], float (&theta)[8],
-                                              uint32_t (&code)[8], const float (&sn)[2], const float (&inv)[2],
-                                              const float* Lreg, uint32_t l_base, const uint2* VQ, const float2* DEN,
-                                              const uint32_t (&den_row)[2], const UpdateArgs& u, uint32_t q, int lane,
-                                              uint32_t n_valid, LaneStats<STATS>& st) {
-  float sv_err = 0.0f;  // this quarter's part of the lane's sum of squared quantization errors
+// Codes of the second moment: the number of thresholds at or below rho = v/blockmax, as one subtraction and one shift
+// of rho's bit pattern (see stq_tables.h).  The subtrahend is the same for every mantissa at widths up to 4; wider
+// codes look it up by the top five mantissa bits (32 words: a wave's reads never meet in a bank).
+template <bool TAIL>
+__device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)[8], const float (&inv)[2], uint32_t b,
+                                           const uint32_t* vq, uint32_t q, int lane, uint32_t n_valid) {
+  const uint32_t sh = 27u - b;
+  if (b <= 4) {
+    const uint32_t D = b == 4 ? kVqConst4 : (b == 3 ? kVqConst3 : kVqConst2);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) code[n] = __builtin_elementwise_sub_sat(f2u(v[n] * inv[n >> 2]), D) >> sh;
+  } else {
+    const char* D = reinterpret_cast<const char*>(vq + (b - kMinBits) * kVqBuckets);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const uint32_t bits = f2u(v[n] * inv[n >> 2]);
+      const uint32_t d = *reinterpret_cast<const uint32_t*>(D + ((bits >> (kVqShift - 2)) & (4u * (kVqBuckets - 1))));
+      code[n] = __builtin_elementwise_sub_sat(bits, d) >> sh;
+    }
+  }
+  if (TAIL) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+      if (!is_valid(n, q, lane, n_valid)) code[n] = 0u;
+  }
+}
+
+// The parameter update from the quantized moments (mq: values of the first, code: codes of the second moment).  It needs
+// den = sqrt(vq*ibc2) + eps of the quantized value vq, which takes only 2^b values per block:
+//  kDenTable: den and 1/den come from the wave's table TAB of (den, 1/den), indexed by (row, block, code);
+//  kRoots: two octaves of v further down the root is half as large, so a table of the roots of the lowest two octaves'
+//          levels holds them all; TAB keeps, per (row, block, code mod P), the root's bits less (code mod P) << (26-b),
+//          and the root of code c is that plus c << (26-b): its exponent counts the whole multiples of P;
+//  kDirect: from the level itself with the IEEE routines, when a scale is out of the range the short forms need.
+// FAST: the short form of the quotient, else the IEEE division.
+enum UpdateKind { kDenTable, kRoots, kDirect };
+template <int KIND, bool FAST>
+__device__ __forceinline__ void update_params(const float (&mq)[8], const uint32_t (&code)[8], float (&theta)[8], const uint32_t* TAB,
+                                              const uint32_t (&row)[2], uint32_t b, const float (&sn)[2], const float* Lreg,
+                                              const UpdateArgs& u) {
+  const uint32_t below = b > 3 ? (1u << (b - 3)) - 1u : 0u;  // P - 1 (kRoots)
 #pragma unroll
   for (int n = 0; n < 8; ++n) {
     const int i = n >> 2;
-    const float rho = v[n] * inv[i];
-    const uint32_t bits = f2u(rho);
-    const uint32_t idx = __builtin_elementwise_sub_sat(bits >> kVqShift, kVqLow);  // rho <= 1: never past the last bucket
-    const uint2 e = VQ[idx];
-    uint32_t c = e.y + (bits >= e.x ? 1u : 0u);
-    if (TAIL && !is_valid(n, q, lane, n_valid)) c = 0;
-    code[n] = c;
-    if (STATS == 1) {
-      float vq = sn[i] * lds_at(Lreg, (c << 2) | l_base);
-      if (TAIL && !is_valid(n, q, lane, n_valid)) vq = 0.0f;
-      const float d = v[n] - vq;
-      sv_err = __builtin_fmaf(d, d, sv_err);
-    }
     const float mt = mq[n] * u.ibc1;
-    if (TABLE) {
-      const float2 dr = DEN[den_row[i] + c];
-      theta[n] = updated_param<FAST>(theta[n], mt, dr.x, dr.y, u);
+    float den, rden = 0.0f;
+    if (KIND == kDenTable) {
+      const float2 dr = reinterpret_cast<const float2*>(TAB)[row[i] + code[n]];
+      den = dr.x;
+      rden = dr.y;
+    } else if (KIND == kRoots) {
+      den = u2f((code[n] << (26u - b)) + TAB[row[i] + (code[n] & below)]) + u.eps;
+      if (FAST) rden = rcp_rn_safe(den);
     } else {
-      const float vq = sn[i] * lds_at(Lreg, (c << 2) | l_base);
-      const float vt = vq * u.ibc2;
-      if (FAST) {
-        const float den = sqrt_rn_safe(vt) + u.eps;
-        const float upd = u.lr * div_rn_safe(mt, den);
-        const float dec = theta[n] * u.decay;
-        theta[n] = dec - upd;
-      } else {
-        const float den = __builtin_sqrtf(vt) + u.eps;
-        theta[n] = updated_param<false>(theta[n], mt, den, 0.0f, u);
-      }
+      const float vq = sn[i] * lds_at(Lreg, (code[n] << 2) | (4u << b));
+      den = __builtin_sqrtf(vq * u.ibc2) + u.eps;
     }
+    theta[n] = updated_param(theta[n], FAST ? div_rn_safe(mt, den, rden) : mt / den, u);
   }
-  if (STATS == 1) st.add(kLVErr, lane, sv_err);
 }
 
 // ------------------------------------------------------------------ one quarter tile
@@ -516,13 +577,19 @@ __device__ __forceinline__ float bf16_rne(float x) {
   return u2f(u & 0xFFFF0000u);
 }
 
+// The words a quarter shares with its neighbours, for both states: the bits it leaves of its last word (for the next
+// quarter) and, when another wave has the previous quarter, its part of its first word.
+struct SharedWords {
+  uint32_t carry_m, carry_v, held_m, held_v;
+};
+
 // MODE 0: widths stay as they are; 1: the launch changes widths (other destination buffers);
 // 2: as 1, and states may have the wide formats: 32 bits = the fp32 value, 16 bits = its bfloat16
 // rounding, stored in the same tile format with 32- or 16-bit codes and without scales.
-template <bool BF16, int STATS, bool TAIL, int MODE>
+template <bool BF16, int STATS, bool TAIL, int MODE, bool HOLD>
 __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t tile, uint32_t q, uint32_t n_valid,
                                                 const StepArgs& a, const uint32_t* lds, uint32_t* ws, int lane,
-                                                uint32_t& carry_m, uint32_t& carry_v, LaneStats<STATS>& st) {
+                                                SharedWords& sw, LaneStats<STATS>& st) {
   // Everything derived from the lane index and the block size is cheap to recompute.  Hide the two
   // from loop-invariant code motion, which would otherwise keep dozens of such values live across
   // the whole tile loop and spill them.
@@ -633,9 +700,10 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       for (int n = 0; n < 8; ++n)
         old[n] = bm == 32 ? u2f(lwm[n]) : u2f((n & 1) ? (lwm[n >> 1] & 0xFFFF0000u) : (lwm[n >> 1] << 16));
     } else {
+      const float* R = Rreg + (1u << bm);
       STQ_SWITCH_BITS(bm, (unpack_offsets<B>(lwm, s0m, off)));
 #pragma unroll
-      for (int n = 0; n < 8; ++n) old[n] = som[n >> 2] * lds_at(Rreg, off[n]);
+      for (int n = 0; n < 8; ++n) old[n] = som[n >> 2] * lds_at(R, off[n]);
     }
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
@@ -647,9 +715,10 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       for (int n = 0; n < 8; ++n)
         old[n] = bv == 32 ? u2f(lwv[n]) : u2f((n & 1) ? (lwv[n >> 1] & 0xFFFF0000u) : (lwv[n >> 1] << 16));
     } else {
+      const float* L = Lreg + (1u << bv);
       STQ_SWITCH_BITS(bv, (unpack_offsets<B>(lwv, s0v, off)));
 #pragma unroll
-      for (int n = 0; n < 8; ++n) old[n] = sov[n >> 2] * lds_at(Lreg, off[n]);
+      for (int n = 0; n < 8; ++n) old[n] = sov[n >> 2] * lds_at(L, off[n]);
     }
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
@@ -738,66 +807,58 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   }
   wave_lds_sync();
 
-  // ---- table of den = sqrt(vq*ibc2) + eps and 1/den per (row, block, second-moment code) ----
-  // Used when a level serves at least four elements: entries = (512/K) << bv_out <= 128.  The table
-  // takes the place of XR, whose last readers have finished.
+  // ---- table of den = sqrt(vq*ibc2) + eps and 1/den, or of the roots (see update_params) ----
+  // Levels P codes apart (P = 2^(b-3), 1 below b = 4) lie a whole number of octaves pairs apart, so their roots differ by
+  // a power of two: one root per (row, block, code mod P), roots = (512/K)*P.  When a level serves at least four
+  // elements, entries = (512/K) << bv_out <= 128, the lanes go on to den and its reciprocal; 64/roots lanes share the
+  // multiples of a root.  The table takes the place of XR, whose last readers have finished.
   const UpdateArgs ua = {a.ibc1, a.ibc2, a.eps, a.lr, a.decay};
   const bool wide_m = WIDE && bmo >= 16, wide_v = WIDE && bvo >= 16;
-  const uint32_t n_entries = wide_v ? 0xFFFFFFFFu : (512u >> lgK) << bvo;
-  const bool use_table = n_entries <= kDenEntries;
-  const uint32_t l_base = wide_v ? 0u : 4u << bvo;
-  float2* DEN = reinterpret_cast<float2*>(XR);
-  // The short forms of the quotient (and, without a table, of the square root) need every operand
-  // in a range where no intermediate underflows or overflows.  The owner lanes check their scales:
-  // m~ = (s_m*R)*ibc1 is 0 or at least s_m*ibc1/127; v~ = (s_v*L)*ibc2 is 0 or at least
-  // s_v*ibc2*2^-16, so its root lies in [2^-40, 2^39] when s_v*ibc2 lies in [2^-64, 2^78].
-  int bad_bits;
+  const uint32_t bq = wide_v ? 8u : bvo;
+  const bool use_table = !wide_v && ((512u >> lgK) << bq) <= kDenEntries;
+  const uint32_t lgP = bq > 3 ? bq - 3 : 0, lg_roots = 9u - lgK + lgP;
+  // The short forms need every operand in a range where no intermediate underflows or overflows.  The owner lanes
+  // check their scales: m~ = (s_m*R)*ibc1 is 0 or at least s_m*ibc1/127, in [2^-85, 2^40] when s_m*ibc1 lies in
+  // [2^-78, 2^40]; v~ = (s_v*L)*ibc2 is 0 or at least s_v*ibc2*2^-16, in [2^-96, 2^78] when s_v*ibc2 lies in
+  // [2^-80, 2^78], and a root is then at most 2^39.
+  int bad_m = 0, bad_v = 0;
   if (vL < 2) {
-    bad_bits = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(in_safe_range(sc_new * a.ibc1))) ^ 1;
+    bad_m = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(sc_new * a.ibc1) - 0x18800000u <= 0x53800000u - 0x18800000u)) ^ 1;
   } else {
-    const float x = sc_new * a.ibc2;
-    bad_bits = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(x) - 0x1F800000u <= 0x66800000u - 0x1F800000u)) ^ 1;
+    bad_v = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(sc_new * a.ibc2) - 0x17800000u <= 0x66800000u - 0x17800000u)) ^ 1;
   }
   const bool eps_ok = a.eps >= 0x1p-40f && a.eps <= 1.0f;
-  bool fast_div;
-  if (use_table) {
-    // the scales are in range: the short forms build the table as well (their results are the correctly
-    // rounded ones); else the IEEE routines do, and the quotient later takes the IEEE division too
-    const bool short_forms = eps_ok && !__any(bad_bits);
-    if (!short_forms) bad_bits = 1;
-    for (uint32_t e = lane; e < n_entries; e += 64) {
-      const uint32_t c = e & ((1u << bvo) - 1u), rg = e >> bvo;
-      const uint32_t row = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
-      const float sv = SN[((blk << (lgK - 4)) << 2) + 2 + row];
-      const float vq = sv * lds_at(Lreg, (c << 2) | l_base);
-      const float vt = vq * a.ibc2;
-      float den, rden;
-      if (short_forms) {
-        den = sqrt_rn_safe(vt) + a.eps;  // vt is 0 or in [2^-80, 2^78]; den in [eps, 2^39 + 1]
-        rden = rcp_rn_safe(den);
+  bool fast_root = eps_ok && !__any(bad_v);                // the roots (and den) by the short form
+  bool fast_m = !__any(bad_m);                             // and, with it, the quotient
+  if (fast_root && !wide_v) {
+    for (uint32_t e = lane; e < (1u << lg_roots) || (use_table && e < 64u); e += 64) {
+      const uint32_t root = e & ((1u << lg_roots) - 1u), i = root & ((1u << lgP) - 1u), rg = root >> lgP;
+      const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
+      const float sv = SN[((blk << (lgK - 4)) << 2) + 2 + rw];
+      const float vq = sv * lds_at(Lreg, (i << 2) | (4u << bq));
+      const uint32_t s_bits = f2u(sqrt_rn_safe(vq * a.ibc2));
+      if (use_table) {
+        for (uint32_t h = e >> lg_roots; h < (1u << (bq - lgP)); h += 64u >> lg_roots) {
+          // (a root of 0 becomes a number below 2^-96 here, which eps >= 2^-40 absorbs)
+          const float den = u2f(s_bits + (((h << lgP) << (26u - bq)))) + a.eps;
+          reinterpret_cast<float2*>(XR)[(rg << bq) + (h << lgP) + i] = make_float2(den, rcp_rn_safe(den));
+        }
       } else {
-        den = __builtin_sqrtf(vt) + a.eps;
-        rden = 1.0f / den;
+        reinterpret_cast<uint32_t*>(XR)[root] = s_bits - (i << (26u - bq));
       }
-      // the quotient's short form needs the correctly rounded reciprocal, which a divisor with an all-ones
-      // mantissa may not have
-      bad_bits |= static_cast<int>((f2u(den) & 0x7FFFFFu) == 0x7FFFFFu);
-      DEN[e] = make_float2(den, rden);
     }
-    fast_div = !__any(bad_bits);
     wave_lds_sync();
-  } else {
-    fast_div = eps_ok && !__any(bad_bits);
   }
-  if (wide_m) fast_div = false;  // a wide first moment is not a multiple of a block scale: no range guarantee
 
   // ---- linear symmetric quantization of m; m is replaced by its quantized value ----
   if (wide_m) {
     float sm_err = 0.0f;
     uint32_t kept[8];
+    SafeRange range;  // the elements are not multiples of a block scale: look at each
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       const float mq = bmo == 32 ? m[n] : bf16_rne(m[n]);  // pads are 0 and stay 0
+      range.add(mq * ua.ibc1);
       if (STATS == 1) {
         const float dd = m[n] - mq;
         sm_err = __builtin_fmaf(dd, dd, sm_err);
@@ -805,6 +866,7 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       m[n] = mq;
       kept[n] = f2u(mq);
     }
+    fast_m = __all(range.within(0x15000000u, 0x53800000u));  // 2^-85, 2^40
     if (STATS == 1) st.add(kLMErr, lane, sm_err);
     if (bmo == 32) {
 #pragma unroll
@@ -822,21 +884,23 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     }
     const int qmax = (1 << (bmo - 1)) - 1;
     const float qmaxf = static_cast<float>(qmax);
-    const uint32_t r_base = 4u << bmo;
-    uint32_t code[8];
+    // Round half to even by adding 1.5*2^23, which leaves the integer q in the low mantissa bits (|t| <= 127.5); with
+    // 2^(b-1) = qmax + 1 added as well (an even number, so the same rounding), they hold code + 1.
+    // |m| <= s and 1/s is within half an ulp, so |t| <= qmax*(1 + 2^-22) rounds to at most qmax:
+    // the clamp of the quantizer's definition can never act and is left out.
+    const float magic = 12582912.0f + static_cast<float>(qmax + 1);
+    const uint32_t magic_code = 0x4B400001u;  // bits of (magic + q), less the code
+    const uint32_t r_base = (4u << bmo) - 4u * magic_code;
+    uint32_t code[8];  // low bits: code + 1
     float sm_err = 0.0f;  // this quarter's part of the lane's sum of squared quantization errors
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       const int i = n >> 2;
       const float t = (m[n] * inv[i]) * qmaxf;
-      // round half to even: adding 1.5*2^23 leaves the integer in the low mantissa bits (|t| <= 127.5)
-      const float rr = t + 12582912.0f;
-      // |m| <= s and 1/s is within half an ulp, so |t| <= qmax*(1 + 2^-22) rounds to at most qmax:
-      // the clamp of the quantizer's definition can never act and is left out
-      uint32_t u = f2u(rr) - static_cast<uint32_t>(0x4B400000 - qmax);
-      if (TAIL && !is_valid(n, q, lane, n_valid)) u = 0;
+      uint32_t u = f2u(t + magic);
+      if (TAIL && !is_valid(n, q, lane, n_valid)) u = magic_code;
       code[n] = u;
-      float mq = sn[i] * lds_at(Rreg, (u << 2) | r_base);
+      float mq = sn[i] * lds_at(Rreg, (u << 2) + r_base);
       if (STATS == 1) {
         if (TAIL && !is_valid(n, q, lane, n_valid)) mq = 0.0f;
         const float dd = m[n] - mq;
@@ -845,13 +909,14 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       m[n] = mq;
     }
     if (STATS == 1) st.add(kLMErr, lane, sm_err);
-    STQ_SWITCH_BITS(bmo, (pack_store<B>(code, CMO, s0mo, carry_m, ul)));
+    STQ_SWITCH_BITS(bmo, (pack_store<B, true, HOLD>(code, CMO, s0mo, sw.carry_m, sw.held_m, ul)));
   }
 
   // ---- logarithmic quantization of v and the parameter update ----
   if (wide_v) {
     float sv_err = 0.0f;
     uint32_t kept[8];
+    SafeRange range;
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       const float vq = bvo == 32 ? v[n] : bf16_rne(v[n]);
@@ -860,10 +925,23 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
         sv_err = __builtin_fmaf(dd, dd, sv_err);
       }
       kept[n] = f2u(vq);
-      const float mt = m[n] * ua.ibc1;
-      const float vt = vq * ua.ibc2;
-      const float den = __builtin_sqrtf(vt) + ua.eps;
-      theta[n] = updated_param<false>(theta[n], mt, den, 0.0f, ua);
+      v[n] = vq * ua.ibc2;
+      range.add(v[n]);
+    }
+    // The short forms where every element of the wave's quarter allows them (124 M parameters at widths drawn from
+    // {4, 8, 16, 32}: 468 us instead of 472 with the IEEE routines)
+    if (eps_ok && __all(range.within(0x0F800000u, 0x66800000u)) && fast_m) {  // 2^-96, 2^78
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        const float den = sqrt_rn_safe(v[n]) + ua.eps;
+        theta[n] = updated_param(theta[n], div_rn_safe(m[n] * ua.ibc1, den, rcp_rn_safe(den)), ua);
+      }
+    } else {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        const float den = __builtin_sqrtf(v[n]) + ua.eps;
+        theta[n] = updated_param(theta[n], (m[n] * ua.ibc1) / den, ua);
+      }
     }
     if (STATS == 1) st.add(kLVErr, lane, sv_err);
     if (bvo == 32) {
@@ -880,25 +958,32 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       const float4 b1 = *reinterpret_cast<const float4*>(SI + (lane >> 2) * 4);
       sn[0] = a1.z; sn[1] = a1.w; inv[0] = b1.z; inv[1] = b1.w;
     }
-    const uint2* VQ = reinterpret_cast<const uint2*>(lds + kTabVqOff) + (bvo - 2) * kVqBuckets;
-    // den table entry ((row*G + block) << bv_out) + c, G = 256/K blocks per row
-    uint32_t den_row[2];
+    uint32_t code[8];
+    quantize_v<TAIL>(v, code, inv, bvo, lds + kTabVqOff, q, lane, n_valid);
+    if (STATS == 1) {
+      float sv_err = 0.0f;  // this quarter's part of the lane's sum of squared quantization errors
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        float vq = sn[n >> 2] * lds_at(Lreg, (code[n] << 2) | (4u << bvo));
+        if (TAIL && !is_valid(n, q, lane, n_valid)) vq = 0.0f;
+        const float dd = v[n] - vq;
+        sv_err = __builtin_fmaf(dd, dd, sv_err);
+      }
+      st.add(kLVErr, lane, sv_err);
+    }
+    STQ_SWITCH_BITS(bvo, (pack_store<B, false, HOLD>(code, CVO, s0vo, sw.carry_v, sw.held_v, ul)));
+    // first table entry of the lane's two blocks: ((row*G + block) << bv_out, or << lgP for the roots), G = 256/K blocks per row
+    const uint32_t lg_row = use_table ? bvo : lgP;
+    uint32_t row[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      den_row[i] = (((static_cast<uint32_t>(i) << (8 - lgK)) + (static_cast<uint32_t>(lane) >> (lgK - 2))) << bvo);
-    uint32_t code[8];
-    if (use_table) {
-      if (fast_div)
-        quant2_update<STATS, TAIL, true, true>(v, m, theta, code, sn, inv, Lreg, l_base, VQ, DEN, den_row, ua, q, lane, n_valid, st);
-      else
-        quant2_update<STATS, TAIL, true, false>(v, m, theta, code, sn, inv, Lreg, l_base, VQ, DEN, den_row, ua, q, lane, n_valid, st);
-    } else {
-      if (fast_div)
-        quant2_update<STATS, TAIL, false, true>(v, m, theta, code, sn, inv, Lreg, l_base, VQ, DEN, den_row, ua, q, lane, n_valid, st);
-      else
-        quant2_update<STATS, TAIL, false, false>(v, m, theta, code, sn, inv, Lreg, l_base, VQ, DEN, den_row, ua, q, lane, n_valid, st);
-    }
-    STQ_SWITCH_BITS(bvo, (pack_store<B>(code, CVO, s0vo, carry_v, ul)));
+      row[i] = ((static_cast<uint32_t>(i) << (8 - lgK)) + (static_cast<uint32_t>(lane) >> (lgK - 2))) << lg_row;
+    const uint32_t* TAB = ws;
+    if (!fast_root) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (use_table && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (use_table) update_params<kDenTable, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (fast_m) update_params<kRoots, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else update_params<kRoots, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
   }
 
 #pragma unroll
@@ -928,9 +1013,18 @@ __device__ __forceinline__ TensorDesc load_desc(const TensorDesc* table, uint32_
   __builtin_memcpy(&d, w, sizeof(TensorDesc));
   return d;
 }
-__device__ __forceinline__ uint32_t desc_tile_begin(const TensorDesc* table, uint32_t l) {
-  const STQ_CONSTANT uint32_t* p = (const STQ_CONSTANT uint32_t*)(&table[l].tile_begin);
-  return *p;
+// The tensor that holds tile t: the last l with tile_begin <= t (tile_begin ascends from 0, t < total_tiles).  The wave
+// looks at 64 entries at a time, so a table of up to 4096 tensors takes two loads one after the other.
+__device__ __forceinline__ uint32_t find_tensor(const TensorDesc* table, uint32_t n, uint32_t t, int lane) {
+  uint32_t lo = 0;
+  for (uint32_t left = n; left > 1;) {
+    const uint32_t step = (left + 63u) >> 6, i = static_cast<uint32_t>(lane) * step;
+    const uint32_t begin = i < left ? as_global(&table[lo + i].tile_begin)[0] : 0xFFFFFFFFu;
+    const uint32_t at = static_cast<uint32_t>(__popcll(__ballot(i < left && begin <= t))) - 1u;
+    lo += at * step;
+    left = min(step, left - at * step);
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // -------------------------------------------------------------- step kernel
@@ -943,43 +1037,51 @@ __device__ __forceinline__ uint32_t desc_tile_begin(const TensorDesc* table, uin
 //    one compact window of the launch-wide order that moves forward in order.  On multi-gigabyte workloads the
 //    memory system gives 10-15 % more bandwidth to this than to waves that each walk their own stripe of the
 //    arrays at their own pace; on small ones the barrier costs more than the order gains.
-//  * stripes (a.sched null): wave w of W takes the chunks w, w+W, w+2W, ... of `chunk` consecutive units.
-//    The variants that collect statistics use it with few, long chunks (a wave flushes its sums to the
-//    tensor's global slots whenever its next unit lies in another tensor), the plain one with chunk 1 or 4.
+//  * stripes (a.sched null): wave w of W takes the chunks w, w+W, w+2W, ... of `chunk` consecutive tiles; quarter tiles
+//    go to the workgroups eight at a time in turn.  With statistics a workgroup has one range of units, which its waves
+//    take in turn: a wave adds its sums to a tensor's global slots when its next unit lies in another tensor, and what
+//    the waves hold at the end goes there together (one wave after the other had each other's atomics to wait for: 3 M
+//    parameters of one tensor with every statistic took 170 us, now 44; 90 M 356, now 281).
 // The ticket counter resets itself: the last workgroup to leave the kernel clears it (and the count of
 // workgroups that have left), so every launch -- also a replayed one -- finds both at zero.
 // STATS 1 (all statistics) and 2 (the gradient's only) stay within the plain kernel's budget of 80 registers
 // and a third of a CU's LDS: their running sums live in LDS and nothing derived from the lane index is kept
 // across the tile loop (see LaneStats).  Only the wide-state variant (MODE 2) runs two workgroups per CU.
-template <bool BF16, int STATS, int MODE>
+// QUARTERS: a unit is a quarter tile and a workgroup takes two tiles at a time, in step.  Where the widths are not
+// multiples of 4 bits a quarter shares a word with the next: the waves leave their last bits in LDS, meet at a barrier,
+// and the wave that completes a word puts it together and stores it (its neighbour has read the old word before: its
+// moments, which the barrier follows, depend on it).
+template <bool BF16, int STATS, int MODE, bool QUARTERS>
 __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_kernel(const StepArgs a) {
   constexpr int kWaves = kWavesPerGroup;
   __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsWords + kWavesPerGroup * LaneStats<STATS>::kWords];
   __shared__ uint32_t drawn[2];  // the ticket being worked on and the next one, alternating
   // statistics of the two tickets in flight, one record per wave
   __shared__ TicketRecord<STATS> ticket_rec[2][kWavesPerGroup];
+  __shared__ uint32_t ended_in[kWavesPerGroup];  // statistics under stripes: the tensor a wave ended in, plus one
+  __shared__ uint32_t shared_bits[QUARTERS ? 2 * kWaves * 2 * 64 : 1];  // [round & 1][wave][state][lane]
   const bool tickets = a.sched != nullptr;
   if (threadIdx.x == 0) drawn[0] = blockIdx.x;
-  // the value tables of every width (4 KB), the search table of the second-moment widths this launch can write
-  for (int i = threadIdx.x; i < kTabVqOff; i += 64 * kWaves) lds[i] = a.tables[i];
-  for (int b = kMinBits; b <= kMaxBits; ++b) {
-    if (!((a.v_widths >> b) & 1u)) continue;
-    const int base = kTabVqOff + (b - kMinBits) * kVqBuckets * 2;
-    for (int i = threadIdx.x; i < kVqBuckets * 2; i += 64 * kWaves) lds[base + i] = a.tables[base + i];
-  }
-  __syncthreads();
+  constexpr int kTabLoads = (kTabWords + 64 * kWaves - 1) / (64 * kWaves);  // the tables: 5 KB
+  uint32_t tab[kTabLoads];
+#pragma unroll
+  for (int k = 0; k < kTabLoads; ++k) tab[k] = a.tables[min(k * 64 * kWaves + static_cast<int>(threadIdx.x), kTabWords - 1)];
 
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* ws = lds + kTabWords + wave * kWaveScratch;
   const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * kWaves;
-  // A unit of scheduling is a tile; in a launch too small to occupy the waves with whole tiles, and
-  // whose widths are all multiples of 4 bits (a quarter's codes then start and end on word
-  // boundaries), it is a quarter tile.
-  const uint32_t qs = a.quarter_units ? 2u : 0u;
+  constexpr uint32_t qs = QUARTERS ? 2u : 0u;
   const uint64_t total_units = static_cast<uint64_t>(a.total_tiles) << qs;
-  const uint64_t C = a.chunk;
-  uint64_t stripe = (static_cast<uint64_t>(blockIdx.x) * kWaves + wave) * C;  // next chunk of this wave (stripes)
+  // Stripes.  kTogether: the waves of a workgroup take consecutive units, round by round (next unit: stripe + wave, the
+  // workgroup's first one being the same for its waves); else each wave walks chunks of its own.
+  constexpr bool kTogether = QUARTERS || STATS != 0;
+  const uint64_t C = kTogether ? 1 : a.chunk;
+  const uint64_t stripe_step = STATS ? kWaves : n_waves * C;
+  const uint64_t stripe_end = STATS ? min(total_units, (static_cast<uint64_t>(blockIdx.x) + 1) * a.chunk) : total_units;
+  uint64_t stripe = STATS ? static_cast<uint64_t>(blockIdx.x) * a.chunk
+                          : (kTogether ? static_cast<uint64_t>(blockIdx.x) * kWaves
+                                       : (static_cast<uint64_t>(blockIdx.x) * kWaves + wave) * C);
   const uint32_t n_tickets = static_cast<uint32_t>((total_units + kWaves - 1) / kWaves);
   uint32_t turn = 0;         // which of drawn[] is current (tickets)
   uint32_t next_ticket = 0;  // thread 0: the ticket drawn for the next round
@@ -987,6 +1089,21 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
   uint32_t l = 0;
   bool have_desc = false;
   TensorDesc d;
+  // tensor holding the wave's first tile (a workgroup's first ticket is its own index): the table's loads, the search
+  // and the first descriptor are in flight together
+  const uint64_t first = tickets ? static_cast<uint64_t>(blockIdx.x) * kWaves + wave : stripe + (kTogether ? wave : 0u);
+  if (first < (tickets ? total_units : stripe_end)) {
+    l = find_tensor(a.desc, a.n_tensors, static_cast<uint32_t>(first >> qs), lane);
+    d = load_desc(a.desc, l);
+    have_desc = true;
+  }
+#pragma unroll
+  for (int k = 0; k < kTabLoads; ++k) {
+    const int i = k * 64 * kWaves + static_cast<int>(threadIdx.x);
+    if (i < kTabWords) lds[i] = tab[k];
+  }
+  __syncthreads();
+
   LaneStats<STATS> st;
   st.acc = STATS ? reinterpret_cast<float*>(lds + kLdsWords + wave * LaneStats<STATS>::kWords) : nullptr;
   st.tiles = 0;
@@ -1001,25 +1118,14 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
       c_begin = static_cast<uint64_t>(cur) * kWaves + wave;
       c_end = min(c_begin + 1, total_units);
     } else {
-      if (stripe >= total_units) break;
-      c_begin = stripe;
-      c_end = min(stripe + C, total_units);
-      stripe += n_waves * C;
+      if (stripe >= stripe_end) break;  // (kTogether: the same for every wave of the workgroup)
+      c_begin = stripe + (kTogether ? wave : 0u);
+      c_end = min(c_begin + C, stripe_end);
+      stripe += stripe_step;
     }
+    SharedWords sw = {0u, 0u, 0u, 0u};
     for (uint64_t u = c_begin; u < c_end; ++u) {
       const uint32_t t = static_cast<uint32_t>(u >> qs);
-      const uint32_t q_begin = qs ? static_cast<uint32_t>(u & 3u) : 0u, q_end = qs ? q_begin + 1u : 4u;
-      if (!have_desc) {
-        // tensor holding the wave's first tile: last l with tile_begin <= tile
-        uint32_t lo = 0, hi = a.n_tensors - 1;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi + 1) >> 1;
-          if (desc_tile_begin(a.desc, mid) <= t) lo = mid; else hi = mid - 1;
-        }
-        l = __builtin_amdgcn_readfirstlane(lo);
-        d = load_desc(a.desc, l);
-        have_desc = true;
-      }
       if (t >= d.tile_begin + d.n_tiles) {  // t < total_tiles, so a later tensor holds it
         if (STATS && !tickets) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
         do {
@@ -1029,16 +1135,22 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
       }
       const uint32_t tile = t - d.tile_begin;
       const uint64_t left = d.numel - static_cast<uint64_t>(tile) * kTile;
-      uint32_t carry_m = 0, carry_v = 0;
-      if (left >= static_cast<uint64_t>(kTile)) {
+      if (QUARTERS) {
+        const uint32_t q = static_cast<uint32_t>(u & 3u);
+        if (left >= 512u * (q + 1u))
+          process_quarter<BF16, STATS, false, MODE, true>(d, tile, q, kTile, a, lds, ws, lane, sw, st);
+        else
+          process_quarter<BF16, STATS, true, MODE, true>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, sw, st);
+      } else if (left >= static_cast<uint64_t>(kTile)) {
+        sw.carry_m = sw.carry_v = 0u;
 #pragma nounroll
-        for (uint32_t q = q_begin; q < q_end; ++q)
-          process_quarter<BF16, STATS, false, MODE>(d, tile, q, kTile, a, lds, ws, lane, carry_m, carry_v, st);
+        for (uint32_t q = 0; q < 4; ++q)
+          process_quarter<BF16, STATS, false, MODE, false>(d, tile, q, kTile, a, lds, ws, lane, sw, st);
       } else {
+        sw.carry_m = sw.carry_v = 0u;
 #pragma nounroll
-        for (uint32_t q = q_begin; q < q_end; ++q)
-          process_quarter<BF16, STATS, true, MODE>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, carry_m,
-                                                   carry_v, st);
+        for (uint32_t q = 0; q < 4; ++q)
+          process_quarter<BF16, STATS, true, MODE, false>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, sw, st);
       }
       if (STATS && tickets) {
         if constexpr (STATS != 0) {
@@ -1049,6 +1161,24 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
       } else if (STATS && ++st.tiles == kStatFlushTiles) {
         widen_stats(st, lane);
       }
+    }
+    if (QUARTERS && a.quarter_units == 2) {
+      uint32_t* mine = shared_bits + ((turn * kWaves + wave) * 2) * 64;
+      if (c_begin < c_end) {
+        mine[lane] = sw.carry_m;
+        mine[64 + lane] = sw.carry_v;
+      }
+      __syncthreads();
+      if (c_begin < c_end) {
+        const uint32_t* before = mine - 2 * 64;  // the wave with the previous quarter (read for q > 0 only)
+        const uint32_t q = static_cast<uint32_t>(c_begin & 3u), tile = static_cast<uint32_t>(c_begin >> 2) - d.tile_begin;
+        const uint32_t bmo = MODE >= 1 ? d.bm_out : d.bm, bvo = MODE >= 1 ? d.bv_out : d.bv;
+        uint32_t* cm = (MODE >= 1 ? d.m_out : d.m_codes) + (static_cast<size_t>(tile) * bmo + ((q * bmo) >> 2)) * 64;
+        uint32_t* cv = (MODE >= 1 ? d.v_out : d.v_codes) + (static_cast<size_t>(tile) * bvo + ((q * bvo) >> 2)) * 64;
+        if ((q * bmo) & 3u) as_global(cm)[lane] = sw.held_m | before[lane];
+        if ((q * bvo) & 3u) as_global(cv)[lane] = sw.held_v | before[64 + lane];
+      }
+      if (!tickets) turn ^= 1u;  // (the next round's bits go into the other half: a wave is at most one barrier ahead)
     }
     if (tickets) {
       if constexpr (STATS != 0) {
@@ -1065,7 +1195,23 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
       turn ^= 1u;
     }
   }
-  if (STATS && !tickets && have_desc) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
+  if constexpr (STATS != 0) {
+    if (!tickets) {
+      // The workgroup's sums go to the global slots together: those of the waves that ended in its last tensor by one set
+      // of atomics, a wave that ended in an earlier one by itself.
+      if (lane == 0) ended_in[wave] = have_desc ? l + 1u : 0u;
+      __syncthreads();
+      uint32_t last = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) last = max(last, ended_in[w]);
+      last = __builtin_amdgcn_readfirstlane(last);
+      const bool with_last = have_desc && l + 1u == last;
+      if (have_desc && !with_last) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
+      record_stats(st, &ticket_rec[0][wave], with_last, lane);
+      __syncthreads();
+      if (wave == 0 && last) ticket_stats_flush(ticket_rec[0], a.stats + static_cast<size_t>(last - 1u) * kStatSlots, lane);
+    }
+  }
   if (tickets && threadIdx.x == 0) {
     // every ticket this workgroup drew precedes its leaving; the last one to leave has seen all others leave
     const uint32_t left_before = __hip_atomic_fetch_add(a.sched + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -1080,8 +1226,13 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
 
 template <int MODE, int STATS>
 static void launch_variant(const StepArgs& a, bool grad_bf16, dim3 grid, dim3 block, hipStream_t s) {
-  if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((step_kernel<false, STATS, MODE>), grid, block, 0, s, a);
+  if (a.quarter_units) {
+    if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((step_kernel<false, STATS, MODE, true>), grid, block, 0, s, a);
+  } else {
+    if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((step_kernel<false, STATS, MODE, false>), grid, block, 0, s, a);
+  }
 }
 
 template <int MODE>

@@ -22,30 +22,48 @@ float table_L(int b, int c) { return table_G((((1 << b) - 1) - c) << (9 - b)); }
 
 float table_T(int b, int k) { return table_G((2 * k + 1) << (8 - b)); }
 
+// the code the kernel computes for the bit pattern of rho
+static uint32_t vq_code(const std::vector<uint32_t>& img, int b, uint32_t rho_bits) {
+  const uint32_t D = img[kTabVqOff + (b - 2) * kVqBuckets + ((rho_bits >> kVqShift) & (kVqBuckets - 1))];
+  return rho_bits > D ? (rho_bits - D) >> (27 - b) : 0u;
+}
+
 bool build_table_image(std::vector<uint32_t>& img) {
   img.assign(kTabWords, 0u);
+  const uint32_t one = f2u(1.0f);
   for (int b = kMinBits; b <= kMaxBits; ++b) {
     const int qmax = (1 << (b - 1)) - 1, kmax = (1 << b) - 1;
     for (int u = 0; u <= 2 * qmax; ++u) img[kTabROff + (1 << b) + u] = f2u(table_R(b, u));
     for (int c = 0; c <= kmax; ++c) img[kTabLOff + (1 << b) + c] = f2u(table_L(b, c));
-    // thresholds as bit patterns; positive floats order like their bit patterns
-    std::vector<uint32_t> tb(kmax);
-    for (int k = 0; k < kmax; ++k) tb[k] = f2u(table_T(b, k));
-    uint32_t* vq = &img[kTabVqOff + (b - 2) * kVqBuckets * 2];
-    for (int idx = 0; idx < kVqBuckets; ++idx) {
-      const bool last = idx == 0;  // the catch-all bucket below the lowest threshold
-      const uint64_t lo = last ? 0 : (static_cast<uint64_t>(kVqLow + idx) << kVqShift);
-      const uint64_t hi = idx == kVqBuckets - 1 ? (1ull << 32) : (static_cast<uint64_t>(kVqLow + idx + 1) << kVqShift);
-      uint32_t base = 0, thr = 0xFFFFFFFFu;
-      int inside = 0;
-      for (int k = 0; k < kmax; ++k) {
-        if (tb[k] < lo) ++base;
-        else if (tb[k] < hi) { thr = tb[k]; ++inside; }
+    std::vector<uint32_t> thr(kmax);  // bit patterns, descending in k; positive floats order like theirs
+    for (int k = 0; k < kmax; ++k) thr[k] = f2u(table_T(b, k));
+    auto at_or_below = [&](uint32_t x) {  // thresholds at or below x: the code the definition gives
+      uint32_t n = 0;
+      for (uint32_t t : thr) n += t <= x ? 1u : 0u;
+      return n;
+    };
+    uint32_t* D = &img[kTabVqOff + (b - 2) * kVqBuckets];
+    for (int i = 0; i < kVqBuckets; ++i) {
+      if (b <= 4) {
+        D[i] = b == 4 ? kVqConst4 : (b == 3 ? kVqConst3 : kVqConst2);
+        continue;
       }
-      if (inside > 1 || (last && inside != 0)) return false;
-      vq[2 * idx] = thr;     // code = base + (bits >= thr) = number of thresholds <= bits
-      vq[2 * idx + 1] = base;
+      // The octave below 1 (threshold k is the lower end of code kmax - k; k grows downwards).  A bucket with a
+      // threshold: D puts that threshold on the multiple of its code; one without: its first pattern on its code's.
+      const uint32_t lo = one - (1u << 23) + (static_cast<uint32_t>(i) << kVqShift), hi = lo + (1u << kVqShift);
+      uint32_t at = lo;
+      for (uint32_t t : thr)
+        if (t >= lo && t < hi) at = t;
+      D[i] = at - (at_or_below(at) << (27 - b));
     }
+    // the decisions on both sides of every threshold, at both ends of the range, and at the bucket edges
+    for (uint32_t t : thr)
+      if (vq_code(img, b, t) != at_or_below(t) || vq_code(img, b, t - 1) != at_or_below(t - 1)) return false;
+    if (vq_code(img, b, one) != static_cast<uint32_t>(kmax) || vq_code(img, b, one + 1) != static_cast<uint32_t>(kmax) ||
+        vq_code(img, b, 0u) != 0u)
+      return false;
+    for (uint32_t x = one; x > one - (20u << 23); x -= 1u << kVqShift)
+      if (vq_code(img, b, x) != at_or_below(x) || vq_code(img, b, x - 1) != at_or_below(x - 1)) return false;
   }
   return true;
 }

@@ -1,0 +1,114 @@
+"""The result of a step does not depend on how a launch cuts its tiles up: whole tiles under stripes or tickets, and quarter
+tiles (which the other GPU tests compare with the oracle on small inputs), give the same bits."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# 25,394 tiles with bf16 gradients: whole tiles; each tensor by itself: quarter tiles.  Ragged ends in the first, second and
+# last quarter of a tile, one tensor of whole tiles only.
+SIZES = [2048 * 6348 + 1, 2048 * 6349 - 900, 2048 * 6347, 2048 * 6348 + 777, 5, 2047]
+PLANS = {"in_place": [(3, 5), (7, 8), (2, 6), (8, 4), (5, 3), (6, 7)],
+         "transition": [(5, 3), (8, 7), (6, 2), (4, 5), (3, 3), (7, 6)],
+         "wide": [(16, 5), (3, 32), (32, 16), (8, 16), (5, 32), (16, 7)]}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2604_06836_amd as stq
+    c = stq.Context(0, 5000)
+    yield c
+    c.close()
+
+
+def model(ctx, sizes, plan, K, seed):
+    from workloads import configs
+    from workloads.harness import DeviceModel
+    w = configs.Workload(seed, "schedules", [("t%d" % i, n) for i, n in enumerate(sizes)], K, "bf16", 2, "normal_per_tensor")
+    m = DeviceModel(ctx, w, plan, spare_width=32)
+    return m
+
+
+def launch(ctx, m, t, which, new=None, stats=False):
+    """One step of the tensors `which` (indices) of the model; new: plan to write, into the spare buffers."""
+    from paper_2604_06836_amd import binding
+    from workloads.harness import hparams
+    sub = (binding.Tensor * len(which))(*[m.tensors[l] for l in which])
+    plan = binding.make_plan([m.plan[l] for l in which])
+    hp = hparams(m.w, t, stats)
+    if new is None:
+        ctx.step(sub, plan, hp, m.stream)
+    else:
+        dst = [tuple(m._spare[(l, s)].data_ptr() if new[l][s] != m.plan[l][s] else None for s in (0, 1)) for l in which]
+        ctx.step_transition(sub, plan, binding.make_plan([new[l] for l in which]), dst, hp, m.stream)
+
+
+def outputs(m):
+    torch.cuda.synchronize()
+    return [[t.clone() for t in lst] for lst in (m.param, m.m_scales, m.v_scales, m.m_codes, m.v_codes)] + \
+        [[m._spare[(l, s)].clone() for l in range(len(m.param)) for s in (0, 1)]]
+
+
+@pytest.mark.parametrize("kind", ["in_place", "transition", "wide"])
+@pytest.mark.parametrize("stats", [False, True, "grad"])
+@pytest.mark.parametrize("tickets", [False, True])
+def test_whole_tiles_and_quarters_give_the_same_bits(ctx, kind, stats, tickets):
+    K = {"in_place": 64, "transition": 128, "wide": 256}[kind]
+    got, sums = [], []
+    for together in (False, True):
+        plan = PLANS["in_place"] if kind == "transition" else PLANS[kind]
+        new = PLANS["transition"] if kind == "transition" else None
+        m = model(ctx, SIZES, plan, K, 70)
+        for lst in (m.m_codes, m.v_codes):  # nothing undefined behind a state narrower than its buffer
+            for l, buf in enumerate(lst):
+                buf[m._code_words(SIZES[l], plan[l][0 if lst is m.m_codes else 1]):] = 0
+        for s in m._spare.values():
+            s.zero_()
+        ctx.set_schedule(1 if together and tickets else 2 ** 63)
+        m.set_grads(1)
+        for t in (1, 2):
+            which = [list(range(len(SIZES)))] if together else [[l] for l in range(len(SIZES))]
+            for g in which:
+                launch(ctx, m, t, g, new, stats)
+                if stats and not together:
+                    s = ctx.stats(1, m.stream)[0]
+                    sums.append((t, g[0], [getattr(s, f) for f, _ in s._fields_]))
+            if stats and together:
+                for l, s in enumerate(ctx.stats(len(SIZES), m.stream)):
+                    ref = dict(((a, b), c) for a, b, c in sums)[(t, l)]
+                    for (f, _), a, b in zip(s._fields_, [getattr(s, f) for f, _ in s._fields_], ref):
+                        if f == "count" or f.endswith("absmax"):
+                            assert a == b, (l, f)
+                        elif f == "g_sum":   # fp64 in another order: n * 2^-53 of the sum of absolute values
+                            assert abs(a - b) <= 1e-12 * ref[2], (l, f)
+                        elif f == "m_sum":   # fp32 over a tile: 1e-5 of sqrt(n * sum of squares) >= the sum of absolute values
+                            assert abs(a - b) <= 1e-5 * np.sqrt(SIZES[l] * ref[6]), (l, f)
+                        else:
+                            assert abs(a - b) <= (1e-12 if f.startswith("g_") else 1e-5) * abs(b) + SIZES[l] * 1.2e-38, (l, f)
+        got.append(outputs(m))
+        ctx.set_schedule(0)
+        del m
+    for a, b in zip(*got):
+        for l, (x, y) in enumerate(zip(a, b)):
+            assert torch.equal(x.view(torch.int32), y.view(torch.int32)), l
+
+
+def test_tensor_search_over_three_levels(ctx):
+    """4,700 small tensors in one launch (the search for a tile's tensor takes three rounds) against launches of 60."""
+    sizes = [1 + (i * 7919) % 2500 for i in range(4700)]
+    plan = [(2 + i % 7, 2 + (i // 7) % 7) for i in range(len(sizes))]
+    got = []
+    for group in (60, len(sizes)):
+        m = model(ctx, sizes, plan, 64, 71)
+        m.set_grads(1)
+        for a in range(0, len(sizes), group):
+            launch(ctx, m, 1, list(range(a, min(a + group, len(sizes)))))
+        torch.cuda.synchronize()
+        nm = [m._code_words(n, b) for n, (b, _) in zip(sizes, plan)]
+        nv = [m._code_words(n, b) for n, (_, b) in zip(sizes, plan)]
+        got.append([torch.cat(m.param).view(torch.int32), torch.cat(m.m_scales).view(torch.int32),
+                    torch.cat([c[:k] for c, k in zip(m.m_codes, nm)]), torch.cat([c[:k] for c, k in zip(m.v_codes, nv)])])
+        del m
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
