@@ -499,7 +499,7 @@ int stq_grad_stats(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, uint32_t
   if (!g.ok) return STQ_EHIP;
   int table = -1;
   if (int e = resident_table(ctx, descs, static_cast<hipStream_t>(stream), &table)) return e;
-  if (launch_grad_stats(ctx->d_desc[table], n, total, ctx->d_stats, grad_dtype == 1, grad_stats_groups(ctx->n_cu, total), stream) != 0)
+  if (launch_grad_stats(ctx->d_desc[table], n, total, ctx->d_stats, grad_dtype == 1, ctx->n_cu, stream) != 0)
     return STQ_EHIP;
   for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;
@@ -511,9 +511,8 @@ int stq_stats(stq_ctx* ctx, stq_layer_stats* out, uint32_t n, void* stream) {
   DeviceGuard g(ctx->device);
   if (!g.ok) return STQ_EHIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t bytes = sizeof(double) * kStatSlots * n;
-  if (hipMemcpyAsync(ctx->h_stats, ctx->d_stats, bytes, hipMemcpyDeviceToHost, s) != hipSuccess) return STQ_EHIP;
-  if (launch_fill_zero(reinterpret_cast<uint32_t*>(ctx->d_stats), bytes / 4, stream) != 0) return STQ_EHIP;
+  // (pinned memory of hipHostMalloc is the device's to write too)
+  if (launch_take_stats(ctx->h_stats, ctx->d_stats, static_cast<uint64_t>(kStatSlots) * n, stream) != 0) return STQ_EHIP;
   if (hipStreamSynchronize(s) != hipSuccess) return STQ_EHIP;
   for (uint32_t l = 0; l < n; ++l) {
     const double* a = ctx->h_stats + static_cast<size_t>(l) * kStatSlots;

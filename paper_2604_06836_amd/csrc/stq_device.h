@@ -7,6 +7,7 @@ namespace stq {
 constexpr int kTile = 2048;         // elements per tile = 64 lanes x 32 codes
 constexpr uint32_t kRepackChunk = 8;  // consecutive tiles a wave of repack_many_kernel converts at a time (1..16 measured alike)
 constexpr int kWavesPerGroup = 8;   // 512-thread workgroups
+constexpr int kGradWaves = 8;       // waves of a workgroup of grad_stats_kernel
 constexpr int kStatSlots = 16;      // 8-byte accumulator slots per tensor
 constexpr uint32_t kSchedWords = 2;  // the ticket counter of a launch and the count of workgroups that have left
 
@@ -83,7 +84,8 @@ int launch_step(const StepArgs& a, bool grad_bf16, int stats, int mode, uint32_t
 int launch_zero(const ZeroArgs& a, void* stream);
 int launch_repack_many(const RepackManyArgs& a, uint32_t groups, void* stream);
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
-                      uint32_t groups, void* stream);
+                      uint32_t n_cu, void* stream);
+int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);
 int launch_fill_zero(uint32_t* p, uint64_t words, void* stream);
 
 }  // namespace stq

@@ -330,8 +330,7 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
     // Algorithm 1 as written: statistics of g_t and Map first, then this step's layer loop at the new widths
     h.flags = 0u;
     if (due) {
-      if (launch_grad_stats(e->d_desc, e->n, e->total_tiles, e->d_stats, hp->grad_dtype == 1,
-                            grad_stats_groups(e->ctx->n_cu, e->total_tiles), stream) != 0)
+      if (launch_grad_stats(e->d_desc, e->n, e->total_tiles, e->d_stats, hp->grad_dtype == 1, e->ctx->n_cu, stream) != 0)
         return STQ_EHIP;
       if (int err = plan(true)) return err;
     }

@@ -99,10 +99,4 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
                  const stq_hparams* hp, int mode, bool quarters_ok, void* stream,
                  uint32_t* sched = nullptr);
 
-// Workgroups (of four waves) for the gradient-statistics kernel: at most eight per CU, at least one tile per wave.
-inline uint32_t grad_stats_groups(uint32_t n_cu, uint32_t total_tiles) {
-  const uint64_t need = (static_cast<uint64_t>(total_tiles) + 3) / 4, cap = static_cast<uint64_t>(n_cu) * 8;
-  return static_cast<uint32_t>(need < cap ? need : cap);
-}
-
 }  // namespace stq

@@ -10,6 +10,7 @@
 
 #include "stq_device.h"
 #include "stq_tables.h"
+#include "stq_wave.h"
 
 #pragma clang fp contract(off)
 
@@ -47,9 +48,6 @@ __global__ __launch_bounds__(256) void zero_kernel(const ZeroArgs a) {
 // --------------------------------------------------------------- re-pack kernel
 // Width change of stored states: every code goes through a 256-entry table; pad codes stay 0.
 // The lane's 32 codes of width B out of / into its B stream words; all shifts are compile-time.
-// Pointers that arrive through the job table are loaded from memory, so the compiler cannot see that they
-// are global; say so, to get global_load/global_store instead of flat accesses.
-#define STQ_GLOBAL __attribute__((address_space(1)))
 // Bits [SH, SH+B) of x in one instruction (from the plain expression the compiler makes a shift and a mask).
 template <int SH, int B>
 __device__ __forceinline__ uint32_t bit_field(uint32_t x) {
@@ -107,7 +105,6 @@ __device__ __forceinline__ void pack32(const uint32_t (&code)[32], STQ_GLOBAL ui
 
 // The job table is not written while the kernel runs: reading it through the constant address
 // space gives scalar loads.
-#define STQ_CONSTANT __attribute__((address_space(4)))
 __device__ __forceinline__ RepackJob load_job(const RepackJob* table, uint32_t j) {
   const STQ_CONSTANT uint64_t* p = (const STQ_CONSTANT uint64_t*)(table + j);
   static_assert(sizeof(RepackJob) == 48, "job layout");
@@ -188,105 +185,162 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, uint64_t wo
 // --------------------------------------------------- gradient statistics kernel
 // The per-layer sums the bit-width decision reads (Eq. 2, 3, 8: sum g, sum |g|, sum g^2) and max |g|,
 // from the gradients alone: for the order in which Algorithm 1 is written, where the decision of step t
-// precedes that step's layer loop.  Streams the gradients once (HBM-bound).  Each wave takes one
-// contiguous range of the launch-wide tile order; a lane keeps fp64 totals of its elements, and a wave adds
-// its totals to the layer's accumulators once per layer it touched.
-__device__ __forceinline__ void flush_grad_stats(double* slot, double s0, double s1, double s2, float mx, int lane) {
+// precedes that step's layer loop.  One read of the gradients, and bound by it as long as the sums do not wait for each
+// other: a workgroup takes one contiguous range of tiles, its eight waves in turn, with the next tile's loads in flight
+// while a tile is added up; a lane keeps fp64 totals; what the waves hold at the end goes to the layer's accumulators
+// by one set of atomics per workgroup (one set per wave, 8192 of them on the
+// same words, took 127 us for 0.25 GB of bf16 gradients; now 45).
+struct GradSums {
+  double sum, abs, sq;
+  float top;
+};
+
+// over the wave; complete in lane 0
+__device__ __forceinline__ GradSums wave_sums(GradSums s) {
+  s.sum = row_sum(s.sum);
+  s.abs = row_sum(s.abs);
+  s.sq = row_sum(s.sq);
+  uint32_t top = row_max(f2u(s.top));  // non-negative floats order like their bit patterns
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    s0 += __shfl_xor(s0, o, 64);
-    s1 += __shfl_xor(s1, o, 64);
-    s2 += __shfl_xor(s2, o, 64);
-    mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  for (int o = 16; o <= 32; o <<= 1) {
+    s.sum += __shfl_xor(s.sum, o, 64);
+    s.abs += __shfl_xor(s.abs, o, 64);
+    s.sq += __shfl_xor(s.sq, o, 64);
+    top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), o, 64)));
   }
-  if (lane == 0) {
-    atomicAdd(&slot[kGSum], s0);
-    atomicAdd(&slot[kGAbsSum], s1);
-    atomicAdd(&slot[kGSqSum], s2);
-    // non-negative floats order like their bit patterns
-    atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]), __builtin_bit_cast(uint32_t, mx));
-  }
+  s.top = u2f(top);
+  return s;
+}
+
+__device__ __forceinline__ void add_grad_sums(double* slot, const GradSums& s) {
+  atomicAdd(&slot[kGSum], s.sum);
+  atomicAdd(&slot[kGAbsSum], s.abs);
+  atomicAdd(&slot[kGSqSum], s.sq);
+  atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]), f2u(s.top));
 }
 
 typedef uint32_t gs_u32x2 __attribute__((ext_vector_type(2)));
 typedef float gs_f32x4 __attribute__((ext_vector_type(4)));
+template <bool BF16>
+struct GradRow {  // four neighbouring gradients
+  typedef gs_f32x4 type;
+};
+template <>
+struct GradRow<true> {
+  typedef gs_u32x2 type;
+};
+
+__device__ __forceinline__ void add_grad(GradSums& s, float g) {
+  // fp64 from the first addition: the decision compares scores with thresholds, and the variance of Eq. 3
+  // is a difference of two of these sums
+  const double gd = static_cast<double>(g);
+  s.sum += gd;
+  s.abs += __builtin_fabs(gd);
+  s.sq = __builtin_fma(gd, gd, s.sq);
+  s.top = fmaxf(s.top, fabsf(g));
+}
+__device__ __forceinline__ void add_row(GradSums& s, gs_f32x4 r) {
+  add_grad(s, r.x); add_grad(s, r.y); add_grad(s, r.z); add_grad(s, r.w);
+}
+__device__ __forceinline__ void add_row(GradSums& s, gs_u32x2 r) {
+  add_grad(s, u2f(r.x << 16)); add_grad(s, u2f(r.x & 0xFFFF0000u));
+  add_grad(s, u2f(r.y << 16)); add_grad(s, u2f(r.y & 0xFFFF0000u));
+}
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void grad_stats_kernel(const TensorDesc* desc, uint32_t n_tensors,
-                                                         uint32_t total_tiles, double* stats) {
+__global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const TensorDesc* desc, uint32_t n_tensors,
+                                                                     uint32_t total_tiles, uint32_t per_group, double* stats) {
+  typedef typename GradRow<BF16>::type Row;
+  __shared__ GradSums held[kGradWaves];
+  __shared__ uint32_t ended_in[kGradWaves];  // the tensor a wave ended in, plus one
   const int lane = threadIdx.x & 63;
-  const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * 4;
-  const uint64_t gw = static_cast<uint64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const uint64_t per_wave = (total_tiles + n_waves - 1) / n_waves;
-  const uint64_t begin = gw * per_wave;
-  const uint64_t end = begin + per_wave < total_tiles ? begin + per_wave : total_tiles;
-  if (begin >= end) return;
-  uint32_t lo = 0, hi = n_tensors - 1;  // last l with tile_begin <= begin
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (desc[mid].tile_begin <= static_cast<uint32_t>(begin)) lo = mid; else hi = mid - 1;
-  }
-  uint32_t l = lo;
-  uint32_t t_begin = desc[l].tile_begin, t_count = desc[l].n_tiles;
-  uint64_t numel = desc[l].numel;
-  const void* grad = desc[l].grad;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  float mx = 0.0f;
-  for (uint64_t t = begin; t < end; ++t) {
-    if (t >= static_cast<uint64_t>(t_begin) + t_count) {  // t < total_tiles, so a later tensor holds it
-      flush_grad_stats(stats + static_cast<size_t>(l) * kStatSlots, s0, s1, s2, mx, lane);
-      s0 = s1 = s2 = 0.0; mx = 0.0f;
-      do {
-        ++l;
-        t_begin = desc[l].tile_begin; t_count = desc[l].n_tiles;
-      } while (t >= static_cast<uint64_t>(t_begin) + t_count);
-      numel = desc[l].numel;
-      grad = desc[l].grad;
-    }
-    const uint64_t base = (t - t_begin) * kTile;
-    const uint64_t left = numel - base;  // >= 1
-    float g[32];
-    if (left >= static_cast<uint64_t>(kTile)) {  // a whole tile: eight unconditional loads in flight
-      if (BF16) {
-        gs_u32x2 w[8];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * per_group;
+  const uint32_t end = static_cast<uint32_t>(min(begin + per_group, static_cast<uint64_t>(total_tiles)));
+  GradSums s = {0.0, 0.0, 0.0, 0.0f};
+  uint32_t l = 0;
+  bool any = false;
+  if (begin + wave < end) {
+    uint32_t t = static_cast<uint32_t>(begin) + wave;
+    any = true;
+    l = find_begin(desc, n_tensors, t, lane);
+    TensorDesc d = load_desc(desc, l);
+    Row row[8];
+    auto whole = [&]() { return d.numel - static_cast<uint64_t>(t - d.tile_begin) * kTile >= static_cast<uint64_t>(kTile); };
+    auto load = [&]() {  // a whole tile: eight loads in flight
+      const STQ_GLOBAL Row* p = (const STQ_GLOBAL Row*)(d.grad) + static_cast<size_t>(t - d.tile_begin) * (kTile / 4) + lane;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          w[i] = __builtin_nontemporal_load(reinterpret_cast<const gs_u32x2*>(static_cast<const uint16_t*>(grad) + base + 256u * i + 4u * lane));
+      for (int i = 0; i < 8; ++i) row[i] = __builtin_nontemporal_load(p + 64 * i);
+    };
+    bool loaded = whole();
+    if (loaded) load();
+    for (;;) {
+      // this tile's values out of the registers that the next tile's loads go into
+      Row cur[8];
+      const bool cur_whole = loaded;
+      const uint64_t base = static_cast<uint64_t>(t - d.tile_begin) * kTile, left = d.numel - base;
+      const void* const grad = d.grad;
+      const uint32_t cur_l = l;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          g[4 * i] = __builtin_bit_cast(float, w[i].x << 16); g[4 * i + 1] = __builtin_bit_cast(float, w[i].x & 0xFFFF0000u);
-          g[4 * i + 2] = __builtin_bit_cast(float, w[i].y << 16); g[4 * i + 3] = __builtin_bit_cast(float, w[i].y & 0xFFFF0000u);
+      for (int i = 0; i < 8; ++i) cur[i] = row[i];
+      t += kGradWaves;
+      const bool more = t < end;
+      if (more) {
+        while (t >= d.tile_begin + d.n_tiles) d = load_desc(desc, ++l);  // t < total_tiles: a later tensor holds it
+        loaded = whole();
+        if (loaded) load();
+      }
+      if (cur_whole) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) add_row(s, cur[i]);
+      } else {  // the ragged last tile of a tensor: element by element
+#pragma unroll 4
+        for (uint32_t k = 0; k < 32; ++k) {
+          const uint64_t off = 64u * k + lane;
+          if (off < left)
+            add_grad(s, BF16 ? u2f(static_cast<uint32_t>(as_global(static_cast<const uint16_t*>(grad))[base + off]) << 16)
+                             : as_global(static_cast<const float*>(grad))[base + off]);
         }
-      } else {
-        gs_f32x4 w[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          w[i] = __builtin_nontemporal_load(reinterpret_cast<const gs_f32x4*>(static_cast<const float*>(grad) + base + 256u * i + 4u * lane));
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { g[4 * i] = w[i].x; g[4 * i + 1] = w[i].y; g[4 * i + 2] = w[i].z; g[4 * i + 3] = w[i].w; }
       }
-    } else {  // the ragged last tile of a tensor: element by element
-#pragma unroll
-      for (int k = 0; k < 32; ++k) {
-        const uint32_t off = 256u * (k >> 2) + 4u * lane + (k & 3);
-        g[k] = 0.0f;
-        if (off < left)
-          g[k] = BF16 ? __builtin_bit_cast(float, static_cast<uint32_t>(static_cast<const uint16_t*>(grad)[base + off]) << 16)
-                      : static_cast<const float*>(grad)[base + off];
+      if (!more) break;
+      if (l != cur_l) {
+        const GradSums w = wave_sums(s);
+        if (lane == 0) add_grad_sums(stats + static_cast<size_t>(cur_l) * kStatSlots, w);
+        s = {0.0, 0.0, 0.0, 0.0f};
       }
-    }
-    // fp64 from the first addition: the decision compares scores with thresholds, and the variance of Eq. 3
-    // is a difference of two of these sums (the kernel is bound by its one read of the gradients either way)
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      const double gd = static_cast<double>(g[k]);
-      s0 += gd;
-      s1 += __builtin_fabs(gd);
-      s2 = __builtin_fma(gd, gd, s2);
-      mx = fmaxf(mx, fabsf(g[k]));
     }
   }
-  flush_grad_stats(stats + static_cast<size_t>(l) * kStatSlots, s0, s1, s2, mx, lane);
+  // the waves that ended in the workgroup's last tensor together, a wave that ended in an earlier one by itself
+  const GradSums w = wave_sums(s);
+  if (lane == 0) {
+    held[wave] = w;
+    ended_in[wave] = any ? l + 1u : 0u;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t last = 0;
+    for (int k = 0; k < kGradWaves; ++k) last = max(last, ended_in[k]);
+    GradSums sum = {0.0, 0.0, 0.0, 0.0f};
+    for (int k = 0; k < kGradWaves; ++k) {
+      if (ended_in[k] == last) {
+        sum.sum += held[k].sum;
+        sum.abs += held[k].abs;
+        sum.sq += held[k].sq;
+        sum.top = fmaxf(sum.top, held[k].top);
+      } else if (ended_in[k]) {
+        add_grad_sums(stats + static_cast<size_t>(ended_in[k] - 1u) * kStatSlots, held[k]);
+      }
+    }
+    if (last) add_grad_sums(stats + static_cast<size_t>(last - 1u) * kStatSlots, sum);
+  }
+}
+
+// The accumulators to host memory, and zero in their place: one launch instead of a copy and a fill.
+__global__ __launch_bounds__(256) void take_stats_kernel(uint64_t* host, uint64_t* acc, uint64_t n) {
+  const uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= n) return;
+  host[i] = acc[i];
+  acc[i] = 0u;
 }
 
 }  // namespace
@@ -305,10 +359,21 @@ int launch_repack_many(const RepackManyArgs& a, uint32_t groups, void* stream) {
 }
 
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
-                      uint32_t groups, void* stream) {
+                      uint32_t n_cu, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (grad_bf16) hipLaunchKernelGGL(grad_stats_kernel<true>, dim3(groups), dim3(256), 0, s, desc, n_tensors, total_tiles, stats);
-  else hipLaunchKernelGGL(grad_stats_kernel<false>, dim3(groups), dim3(256), 0, s, desc, n_tensors, total_tiles, stats);
+  // One workgroup per CU, at least one tile per wave.  (0.12 G bf16 gradients in 100 tensors with read-back and decision
+  // 85.6 us, 86.5 with two per CU, 91 with four of four waves; 30 M fp32 in one tensor 43.5, 47, 63; 1.5 G 885, 907, 940.)
+  const uint64_t most = n_cu, rounds = (total_tiles + most * kGradWaves - 1) / (most * kGradWaves);
+  const uint32_t per_group = static_cast<uint32_t>(rounds * kGradWaves);
+  const dim3 grid((total_tiles + per_group - 1) / per_group), block(64 * kGradWaves);
+  if (grad_bf16) hipLaunchKernelGGL(grad_stats_kernel<true>, grid, block, 0, s, desc, n_tensors, total_tiles, per_group, stats);
+  else hipLaunchKernelGGL(grad_stats_kernel<false>, grid, block, 0, s, desc, n_tensors, total_tiles, per_group, stats);
+  return static_cast<int>(hipGetLastError());
+}
+
+int launch_take_stats(double* host, double* acc, uint64_t n, void* stream) {
+  hipLaunchKernelGGL(take_stats_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     reinterpret_cast<uint64_t*>(host), reinterpret_cast<uint64_t*>(acc), n);
   return static_cast<int>(hipGetLastError());
 }
 

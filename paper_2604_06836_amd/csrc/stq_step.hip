@@ -27,6 +27,7 @@
 
 #include "stq_device.h"
 #include "stq_tables.h"
+#include "stq_wave.h"
 
 #pragma clang fp contract(off)
 
@@ -39,19 +40,11 @@ constexpr int kWaveScratch = 4 * XS + 3 * 64;
 constexpr int kLdsWords = kTabWords + kWavesPerGroup * kWaveScratch;  // + the statistics slices in that variant
 constexpr int kStatFlushTiles = 16;  // fp32 lane sums are widened to fp64 every this many tiles
 constexpr uint32_t kDenEntries = 128;  // capacity of the per-wave den table (8 bytes per entry, inside XR)
-constexpr uint32_t kRootEntries = 256; // capacity of the per-wave root table (4 bytes per entry, inside XR)
+static_assert(kDenEntries * 8 <= 4 * XS * 4, "the den table lies inside XR");
+static_assert(((512 / 64) << (kMaxBits - 3)) * 4 <= 4 * XS * 4, "and so do the roots of the widest code at the smallest block");
 
-// Pointers that arrive through the tensor table are loaded from memory, so the compiler cannot
-// see that they are global; say so, to get global_load/global_store instead of flat accesses.
-#define STQ_GLOBAL __attribute__((address_space(1)))
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <class T>
-__device__ __forceinline__ STQ_GLOBAL T* as_global(T* p) { return (STQ_GLOBAL T*)p; }
-
-__device__ __forceinline__ uint32_t f2u(float f) { return __builtin_bit_cast(uint32_t, f); }
-__device__ __forceinline__ float u2f(uint32_t u) { return __builtin_bit_cast(float, u); }
-
 // value at byte offset `off` of an LDS float table
 __device__ __forceinline__ float lds_at(const float* base, uint32_t off) {
   return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + off);
@@ -200,16 +193,6 @@ __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n
   return (512u * q + static_cast<uint32_t>(256 * (n >> 2) + 4 * lane + (n & 3))) < n_valid;
 }
 
-// x from the lane that a DPP control word names (all lanes of the wave active)
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xF, 0xF, true));
-}
-constexpr int kDppXor1 = 0xB1;         // quad_perm [1,0,3,2]
-constexpr int kDppXor2 = 0x4E;         // quad_perm [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141;  // lane i <-> 7-i inside each 8 lanes
-constexpr int kDppMirror = 0x140;      // lane i <-> 15-i inside each row of 16 lanes
-
 // -------------------------------------------------------------------- statistics
 // (The sums of squares use fused multiply-adds: the fixed operation order binds the Adam
 // arithmetic, not the statistics, which are compared within a tolerance.)
@@ -231,50 +214,6 @@ constexpr int kDppMirror = 0x140;      // lane i <-> 15-i inside each row of 16 
 // S = 2: the gradient's statistics only; the slice stays small enough for three workgroups per CU.
 enum GradSlot { kLGSum = 0, kLGAbs, kLGSq };
 enum MomentSlot { kLMSum = 0, kLMSq, kLMErr, kLVSum, kLVSq, kLVErr };
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double x) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint64_t lo = dpp_u32<CTRL>(static_cast<uint32_t>(u)), hi = dpp_u32<CTRL>(static_cast<uint32_t>(u >> 32));
-  return __builtin_bit_cast(double, (hi << 32) | lo);
-}
-// Sums and maxima over groups of 4, 8 or 16 neighbouring lanes, left in every lane of the group.  DPP steps
-// only: a shuffle through LDS needs a lane-dependent address register, and the compiler keeps those
-// alive across the whole tile loop.
-__device__ __forceinline__ double quad_sum(double x) {
-  x += dpp_f64<kDppXor1>(x);
-  x += dpp_f64<kDppXor2>(x);
-  return x;
-}
-__device__ __forceinline__ double octet_sum(double x) {
-  x = quad_sum(x);
-  x += dpp_f64<kDppHalfMirror>(x);
-  return x;
-}
-__device__ __forceinline__ double row_sum(double x) {
-  x = octet_sum(x);
-  x += dpp_f64<kDppMirror>(x);
-  return x;
-}
-__device__ __forceinline__ float octet_sum(float x) {
-  x += u2f(dpp_u32<kDppXor1>(f2u(x)));
-  x += u2f(dpp_u32<kDppXor2>(f2u(x)));
-  x += u2f(dpp_u32<kDppHalfMirror>(f2u(x)));
-  return x;
-}
-__device__ __forceinline__ uint32_t quad_max(uint32_t x) {
-  x = max(x, dpp_u32<kDppXor1>(x));
-  x = max(x, dpp_u32<kDppXor2>(x));
-  return x;
-}
-__device__ __forceinline__ uint32_t octet_max(uint32_t x) {
-  x = quad_max(x);
-  return max(x, dpp_u32<kDppHalfMirror>(x));
-}
-__device__ __forceinline__ uint32_t row_max(uint32_t x) {
-  x = octet_max(x);
-  return max(x, dpp_u32<kDppMirror>(x));
-}
 
 // Layout of a wave's slice (32-bit words), S = 2 | S = 1:
 //   gradient sums  3 slots of G doubles, G = 16 | 8 (one word per group of 64/G lanes)
@@ -999,34 +938,6 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   }
 }
 
-// The descriptor table is never written while a step runs: reading it through the constant
-// address space gives scalar loads, so everything derived from a descriptor (all base addresses)
-// lives in scalar registers.
-#define STQ_CONSTANT __attribute__((address_space(4)))
-__device__ __forceinline__ TensorDesc load_desc(const TensorDesc* table, uint32_t l) {
-  const STQ_CONSTANT uint64_t* p = (const STQ_CONSTANT uint64_t*)(table + l);
-  static_assert(sizeof(TensorDesc) == 96, "descriptor layout");
-  uint64_t w[sizeof(TensorDesc) / 8];
-#pragma unroll
-  for (size_t i = 0; i < sizeof(TensorDesc) / 8; ++i) w[i] = p[i];
-  TensorDesc d;
-  __builtin_memcpy(&d, w, sizeof(TensorDesc));
-  return d;
-}
-// The tensor that holds tile t: the last l with tile_begin <= t (tile_begin ascends from 0, t < total_tiles).  The wave
-// looks at 64 entries at a time, so a table of up to 4096 tensors takes two loads one after the other.
-__device__ __forceinline__ uint32_t find_tensor(const TensorDesc* table, uint32_t n, uint32_t t, int lane) {
-  uint32_t lo = 0;
-  for (uint32_t left = n; left > 1;) {
-    const uint32_t step = (left + 63u) >> 6, i = static_cast<uint32_t>(lane) * step;
-    const uint32_t begin = i < left ? as_global(&table[lo + i].tile_begin)[0] : 0xFFFFFFFFu;
-    const uint32_t at = static_cast<uint32_t>(__popcll(__ballot(i < left && begin <= t))) - 1u;
-    lo += at * step;
-    left = min(step, left - at * step);
-  }
-  return __builtin_amdgcn_readfirstlane(lo);
-}
-
 // -------------------------------------------------------------- step kernel
 // Order of the work.  A unit is a tile (or a quarter tile, see below).  Two schedules:
 //  * tickets (a.sched set): the workgroups of the launch draw tickets from one counter in device memory.
@@ -1093,7 +1004,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
   // and the first descriptor are in flight together
   const uint64_t first = tickets ? static_cast<uint64_t>(blockIdx.x) * kWaves + wave : stripe + (kTogether ? wave : 0u);
   if (first < (tickets ? total_units : stripe_end)) {
-    l = find_tensor(a.desc, a.n_tensors, static_cast<uint32_t>(first >> qs), lane);
+    l = find_begin(a.desc, a.n_tensors, static_cast<uint32_t>(first >> qs), lane);
     d = load_desc(a.desc, l);
     have_desc = true;
   }

@@ -112,3 +112,26 @@ def test_tensor_search_over_three_levels(ctx):
         del m
     for x, y in zip(*got):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("sizes", [[1], [3, 2047, 2049], [1 + (i * 4093) % 9001 for i in range(700)], [2048 * 2500 + 5, 7, 2048 * 4, 2048 * 9000 - 1]])
+def test_gradient_statistics_over_workgroup_ranges(ctx, sizes, dtype):
+    """Tensors that begin and end anywhere in the range of tiles a workgroup of the gradient pass takes."""
+    from workloads import configs
+    from workloads.harness import DeviceModel
+    w = configs.Workload(72, "gradients", [("t%d" % i, n) for i, n in enumerate(sizes)], 128, dtype, 1, "normal_per_tensor")
+    m = DeviceModel(ctx, w, [(4, 4)] * len(sizes))
+    m.set_grads(1)
+    for _ in range(2):  # the second time on cleared accumulators
+        ctx.grad_stats(m.tensors, 128, 1 if dtype == "bf16" else 0, m.stream)
+        got = ctx.stats(len(sizes), m.stream)
+    for l, n in enumerate(sizes):
+        g = m.grad[l].double()
+        # fp64 sums in some order: n * 2^-53 relative to the sum of absolute values
+        bound = 1e-12
+        assert got[l].count == n
+        assert abs(got[l].g_sum - g.sum().item()) <= bound * g.abs().sum().item(), l
+        assert abs(got[l].g_abs_sum - g.abs().sum().item()) <= bound * g.abs().sum().item(), l
+        assert abs(got[l].g_sq_sum - (g * g).sum().item()) <= bound * (g * g).sum().item(), l
+        assert got[l].g_absmax == g.abs().max().item(), l
