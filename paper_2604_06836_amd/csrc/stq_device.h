@@ -5,7 +5,6 @@
 namespace stq {
 
 constexpr int kTile = 2048;         // elements per tile = 64 lanes x 32 codes
-constexpr uint32_t kRepackChunk = 8;  // consecutive tiles a wave of repack_many_kernel converts at a time (1..16 measured alike)
 constexpr int kWavesPerGroup = 8;   // 512-thread workgroups
 constexpr int kGradWaves = 8;       // waves of a workgroup of grad_stats_kernel
 constexpr int kStatSlots = 16;      // 8-byte accumulator slots per tensor
@@ -75,6 +74,7 @@ constexpr uint32_t repack_lut_index(uint32_t state, uint32_t b_old, uint32_t b_n
 struct RepackManyArgs {
   const RepackJob* jobs;
   uint32_t n_jobs, total_tiles;
+  uint32_t chunk;        // consecutive tiles a wave converts, set by the launcher
   const uint32_t* luts;  // [kRepackLuts][256] words
 };
 
@@ -82,7 +82,7 @@ struct RepackManyArgs {
 // stats: 0 none, 1 every statistic, 2 the gradient's only.
 int launch_step(const StepArgs& a, bool grad_bf16, int stats, int mode, uint32_t groups, void* stream);
 int launch_zero(const ZeroArgs& a, void* stream);
-int launch_repack_many(const RepackManyArgs& a, uint32_t groups, void* stream);
+int launch_repack_many(RepackManyArgs a, void* stream);
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
                       uint32_t n_cu, void* stream);
 int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);

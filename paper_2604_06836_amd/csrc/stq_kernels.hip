@@ -57,7 +57,7 @@ __device__ __forceinline__ uint32_t bit_field(uint32_t x) {
 }
 // code N of a lane's stream words
 template <int B, int N>
-__device__ __forceinline__ uint32_t extract(const uint32_t (&w)[B]) {
+__device__ __forceinline__ uint32_t extract(const uint32_t (&w)[8]) {
   constexpr int off = N * B, p = off >> 5, sh = off & 31;
   if constexpr (sh + B <= 32) {
     return bit_field<sh, B>(w[p]);
@@ -66,14 +66,16 @@ __device__ __forceinline__ uint32_t extract(const uint32_t (&w)[B]) {
   }
 }
 template <int B, int... N>
-__device__ __forceinline__ void extract_all(const uint32_t (&w)[B], uint32_t (&code)[32], std::integer_sequence<int, N...>) {
+__device__ __forceinline__ void extract_all(const uint32_t (&w)[8], uint32_t (&code)[32], std::integer_sequence<int, N...>) {
   ((code[N] = extract<B, N>(w)), ...);
 }
 template <int B>
-__device__ __forceinline__ void unpack32(const STQ_GLOBAL uint32_t* src, uint32_t (&code)[32]) {
-  uint32_t w[B];
+__device__ __forceinline__ void load_words(const STQ_GLOBAL uint32_t* src, uint32_t (&w)[8]) {
 #pragma unroll
-  for (int p = 0; p < B; ++p) w[p] = src[64 * p];
+  for (int p = 0; p < B; ++p) w[p] = __builtin_nontemporal_load(src + 64 * p);
+}
+template <int B>
+__device__ __forceinline__ void unpack32(const uint32_t (&w)[8], uint32_t (&code)[32]) {
   extract_all<B>(w, code, std::make_integer_sequence<int, 32>{});
 }
 
@@ -89,7 +91,7 @@ __device__ __forceinline__ void pack32(const uint32_t (&code)[32], STQ_GLOBAL ui
     if (sh + B > 32) w[p + 1] = code[n] >> (32 - sh);  // first bits of the next word
   }
 #pragma unroll
-  for (int p = 0; p < B; ++p) dst[64 * p] = w[p];
+  for (int p = 0; p < B; ++p) __builtin_nontemporal_store(w[p], dst + 64 * p);
 }
 
 #define STQ_SWITCH_WIDTH(bits, CALL)       \
@@ -115,53 +117,30 @@ __device__ __forceinline__ RepackJob load_job(const RepackJob* table, uint32_t j
   __builtin_memcpy(&r, w, sizeof(RepackJob));
   return r;
 }
-__device__ __forceinline__ uint32_t job_tile_begin(const RepackJob* table, uint32_t j) {
-  return *(const STQ_CONSTANT uint32_t*)(&table[j].tile_begin);
-}
-
-// Many width changes in one launch.  One wave per workgroup; wave w of W takes the chunks w, w+W, ... of
-// kRepackChunk consecutive tiles of the launch-wide tile order; when it enters a job with another conversion
-// table it reloads its table.  The table sits at LDS address 0 as 256 bytes (new codes have at most 8 bits), so
+// Many width changes in one launch.  One wave per workgroup and `chunk` consecutive tiles of the launch-wide tile order
+// per wave: handed out by the hardware in order, the waves at work at one time stay closer together than persistent ones.
+// When a wave enters a job with another conversion table it reloads its table.  The table sits at LDS address 0 as 256 bytes (new codes have at most 8 bits), so
 // an old code is the address of its new code as it comes out of the bit-field extraction: one vector
 // instruction per code to unpack, none to look up, one to pack -- the kernel moves (b_old + b_new)/8 bytes per
-// element and was bound by instruction issue with a word table behind a per-wave base address.
+// element and is bound by the memory system: reads and writes, each of which nothing touches again, carry the
+// non-temporal hint, and the loads of two tiles are in flight before the first of them is converted.
+// (2.85 GB of codes of 1.56 G parameters: 523 us with chunks of 4 tiles, 541 with 2, 540 with 8, 772 with 1; 580 with
+// persistent waves that took a tile at a time without the hint.)
 __global__ __launch_bounds__(64) void repack_many_kernel(const RepackManyArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lut[256];  // the kernel's only LDS variable: address 0
   const uint32_t lane = threadIdx.x;
   const uint64_t n_waves = gridDim.x;
-  uint64_t base = static_cast<uint64_t>(blockIdx.x) * kRepackChunk;
+  uint64_t base = static_cast<uint64_t>(blockIdx.x) * a.chunk;
   if (base >= a.total_tiles) return;
-  // job holding the first tile: last j with tile_begin <= base
-  uint32_t lo = 0, hi = a.n_jobs - 1;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (job_tile_begin(a.jobs, mid) <= static_cast<uint32_t>(base)) lo = mid; else hi = mid - 1;
-  }
-  uint32_t j = lo, loaded = 0xFFFFFFFFu;
+  uint32_t j = find_begin(a.jobs, a.n_jobs, static_cast<uint32_t>(base), lane), loaded = 0xFFFFFFFFu;
   RepackJob job = load_job(a.jobs, j);
-  for (; base < a.total_tiles; base += n_waves * kRepackChunk) {
-   const uint32_t c_end = static_cast<uint32_t>(min(base + kRepackChunk, static_cast<uint64_t>(a.total_tiles)));
-   for (uint32_t t = static_cast<uint32_t>(base); t < c_end; ++t) {
-    while (t >= job.tile_begin + job.n_tiles) job = load_job(a.jobs, ++j);  // t < total_tiles: a later job holds it
-    const uint32_t b_old = job.b_old, b_new = job.b_new, which = job.lut;
-    if (loaded != which) {
-      __builtin_amdgcn_wave_barrier();  // the previous tile's table reads are done (same wave, in order)
-      // lane k packs entries 4k .. 4k+3 of the word table in device memory into one LDS word
-      const uint4 e = *reinterpret_cast<const uint4*>(a.luts + which * 256 + 4 * lane);
-      reinterpret_cast<uint32_t*>(lut)[lane] = e.x | (e.y << 8) | (e.z << 16) | (e.w << 24);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      loaded = which;
-    }
-    const uint64_t tile = t - job.tile_begin;
-    const STQ_GLOBAL uint32_t* src = (const STQ_GLOBAL uint32_t*)(job.src + tile * 64 * b_old + lane);
-    STQ_GLOBAL uint32_t* dst = (STQ_GLOBAL uint32_t*)(job.dst + tile * 64 * b_new + lane);
+  // one tile of `job` from its words to its destination
+  auto convert = [&](const uint32_t (&w)[8], uint32_t tile) {
     uint32_t code[32];
-    STQ_SWITCH_WIDTH(b_old, (unpack32<B>(src, code)));
+    STQ_SWITCH_WIDTH(job.b_old, (unpack32<B>(w, code)));
 #pragma unroll
     for (int n = 0; n < 32; ++n) code[n] = lut[code[n]];
-    const uint64_t left = job.numel - tile * kTile;
+    const uint64_t left = job.numel - static_cast<uint64_t>(tile) * kTile;
     if (left < static_cast<uint64_t>(kTile)) {  // ragged last tile: pad codes are 0
       const uint32_t n_valid = static_cast<uint32_t>(left);
       // (the element offsets are computed here, where they are needed: derived from the plain lane index
@@ -172,8 +151,34 @@ __global__ __launch_bounds__(64) void repack_many_kernel(const RepackManyArgs a)
       for (int n = 0; n < 32; ++n)
         if (256u * (n >> 2) + first + (n & 3) >= n_valid) code[n] = 0u;
     }
-    STQ_SWITCH_WIDTH(b_new, (pack32<B>(code, dst)));
-   }
+    STQ_GLOBAL uint32_t* dst = (STQ_GLOBAL uint32_t*)(job.dst + static_cast<size_t>(tile) * 64 * job.b_new + lane);
+    STQ_SWITCH_WIDTH(job.b_new, (pack32<B>(code, dst)));
+  };
+  for (; base < a.total_tiles; base += n_waves * a.chunk) {
+    const uint32_t c_end = static_cast<uint32_t>(min(base + a.chunk, static_cast<uint64_t>(a.total_tiles)));
+    for (uint32_t t = static_cast<uint32_t>(base); t < c_end;) {
+      while (t >= job.tile_begin + job.n_tiles) job = load_job(a.jobs, ++j);  // t < total_tiles: a later job holds it
+      const uint32_t which = job.lut;
+      const uint32_t tile = t - job.tile_begin;
+      const bool two = t + 1u < c_end && tile + 1u < job.n_tiles;
+      const STQ_GLOBAL uint32_t* src = (const STQ_GLOBAL uint32_t*)(job.src + static_cast<size_t>(tile) * 64 * job.b_old + lane);
+      uint32_t w0[8], w1[8];
+      if (two) STQ_SWITCH_WIDTH(job.b_old, (load_words<B>(src, w0), load_words<B>(src + 64 * B, w1)))
+      else STQ_SWITCH_WIDTH(job.b_old, (load_words<B>(src, w0)))
+      if (loaded != which) {
+        __builtin_amdgcn_wave_barrier();  // the previous tile's table reads are done (same wave, in order)
+        // lane k packs entries 4k .. 4k+3 of the word table in device memory into one LDS word
+        const uint4 e = *reinterpret_cast<const uint4*>(a.luts + which * 256 + 4 * lane);
+        reinterpret_cast<uint32_t*>(lut)[lane] = e.x | (e.y << 8) | (e.z << 16) | (e.w << 24);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        loaded = which;
+      }
+      convert(w0, tile);
+      if (two) convert(w1, tile + 1u);
+      t += two ? 2u : 1u;
+    }
   }
 }
 
@@ -353,7 +358,10 @@ int launch_zero(const ZeroArgs& a, void* stream) {
   return static_cast<int>(hipGetLastError());
 }
 
-int launch_repack_many(const RepackManyArgs& a, uint32_t groups, void* stream) {
+int launch_repack_many(RepackManyArgs a, void* stream) {
+  a.chunk = a.total_tiles < 8192u ? 1u : 4u;  // (a launch that single tiles do not fill: every wave one)
+  const uint32_t need = a.total_tiles / a.chunk + (a.total_tiles % a.chunk != 0);
+  const uint32_t groups = need < (1u << 25) ? need : 1u << 25;  // (64 threads each: HIP counts the threads of a launch in 32 bits)
   hipLaunchKernelGGL(repack_many_kernel, dim3(groups), dim3(64), 0, static_cast<hipStream_t>(stream), a);
   return static_cast<int>(hipGetLastError());
 }

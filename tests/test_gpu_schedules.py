@@ -135,3 +135,29 @@ def test_gradient_statistics_over_workgroup_ranges(ctx, sizes, dtype):
         assert abs(got[l].g_abs_sum - g.abs().sum().item()) <= bound * g.abs().sum().item(), l
         assert abs(got[l].g_sq_sum - (g * g).sum().item()) <= bound * (g * g).sum().item(), l
         assert got[l].g_absmax == g.abs().max().item(), l
+
+
+def test_repack_chunks_over_job_boundaries(ctx):
+    """A launch large enough for chunks of four tiles, whose jobs begin and end anywhere in a chunk, against one launch per job."""
+    from paper_2604_06836_amd import binding
+    sizes = [1 + (i * 7919) % 11000 for i in range(2500)] + [2048 * 3000 + 1]
+    rng = np.random.default_rng(73)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(73)
+    jobs, dst, keep = [], [[], []], []
+    for n in sizes:
+        b0, b1, state = (int(x) for x in (rng.integers(2, 9), rng.integers(2, 9), rng.integers(0, 2)))
+        tiles = (n + 2047) // 2048
+        # (any codes will do: the conversion table has an entry for every code of the width)
+        keep.append(torch.randint(-2 ** 31, 2 ** 31 - 1, (tiles * 64 * b0,), generator=gen, device="cuda:0", dtype=torch.int64).to(torch.int32))
+        for d in dst:
+            d.append(torch.full((tiles * 64 * b1,), -1, device="cuda:0", dtype=torch.int32))
+        jobs.append((n, state, keep[-1].data_ptr(), b0, b1))
+    assert sum((n + 2047) // 2048 for n in sizes) > 8192
+    s = torch.cuda.current_stream().cuda_stream
+    ctx.repack_many([(n, st, src, b0, d.data_ptr(), b1) for (n, st, src, b0, b1), d in zip(jobs, dst[0])], 64, s)
+    for (n, st, src, b0, b1), d in zip(jobs, dst[1]):
+        ctx.repack(n, 64, st, src, b0, d.data_ptr(), b1, s)
+    torch.cuda.synchronize()
+    for l, (x, y) in enumerate(zip(*dst)):
+        assert torch.equal(x, y), l
