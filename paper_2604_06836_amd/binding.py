@@ -196,7 +196,7 @@ def decide(ema: DecideState, stats, step: int, *, alpha=0.1, tau=1000.0, phi=7.2
     plan = (Bits * n)()
     scores = (C.c_double * n)()
     _check(load_library().stq_decide(C.byref(ema), stats, n, C.byref(cfg), step, plan, scores), "stq_decide")
-    return [(p.m_bits, p.v_bits) for p in plan], list(scores)
+    return np.frombuffer(plan, BITS_DTYPE).tolist(), scores[:]  # (a list of tuples; field by field it costs 0.2 us a layer)
 
 
 class Context:

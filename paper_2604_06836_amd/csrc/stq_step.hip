@@ -479,6 +479,10 @@ __device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)
 //          and the root of code c is that plus c << (26-b): its exponent counts the whole multiples of P;
 //  kDirect: from the level itself with the IEEE routines, when a scale is out of the range the short forms need.
 // FAST: the short form of the quotient, else the IEEE division.
+// (Vector instructions per parameter with these forms and quantize_v: 58.8 on a 3.5 G-parameter launch at widths 4..8 and
+// 3..6, K = 64, where IEEE-shaped expansions and a 514-entry search table took 67.3.  The launch is bound by the memory
+// system either way; launches that stay in the caches are not: 2.4 M parameters 8.7 us instead of 9.4.  A den table of
+// 256 entries, for levels that serve two elements, changed nothing: 7.51 ms against 7.43.)
 enum UpdateKind { kDenTable, kRoots, kDirect };
 template <int KIND, bool FAST>
 __device__ __forceinline__ void update_params(const float (&mq)[8], const uint32_t (&code)[8], float (&theta)[8], const uint32_t* TAB,
@@ -958,6 +962,9 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
 // STATS 1 (all statistics) and 2 (the gradient's only) stay within the plain kernel's budget of 80 registers
 // and a third of a CU's LDS: their running sums live in LDS and nothing derived from the lane index is kept
 // across the tile loop (see LaneStats).  Only the wide-state variant (MODE 2) runs two workgroups per CU.
+// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 7.45 ms = 6.0 TB/s, where an in-place
+// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 310 us); launches that leave the chip partly
+// idle one pass of latencies (tables, descriptor, loads, three LDS exchanges, stores): 6 us for 0.2 M parameters.
 // QUARTERS: a unit is a quarter tile and a workgroup takes two tiles at a time, in step.  Where the widths are not
 // multiples of 4 bits a quarter shares a word with the next: the waves leave their last bits in LDS, meet at a barrier,
 // and the wave that completes a word puts it together and stores it (its neighbour has read the old word before: its
