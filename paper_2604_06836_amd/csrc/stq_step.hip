@@ -408,12 +408,12 @@ __device__ __forceinline__ float sqrt_rn_safe(float x) {
   const float s = x * y, h = 0.5f * y;
   return __builtin_fmaf(__builtin_fmaf(-s, s, x), h, s);
 }
-// Correctly rounded 1/d for 2^-40 <= d <= 2^40.
+// Correctly rounded 1/d for 2^-70 <= d <= 2^40.
 __device__ __forceinline__ float rcp_rn_safe(float d) {
   const float y = __builtin_amdgcn_rcpf(d);
   return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
 }
-// Correctly rounded n/d from y = the correctly rounded 1/d, for n = 0 or 2^-85 <= |n| <= 2^40 and 2^-40 <= d <= 2^40
+// Correctly rounded n/d from y = the correctly rounded 1/d, for n = 0 or 2^-85 <= |n| <= 2^40 and 2^-70 <= d <= 2^40
 // (the quotient is then normal and every residual exact).
 __device__ __forceinline__ float div_rn_safe(float n, float d, float y) {
   const float q = n * y;
@@ -770,7 +770,8 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   } else {
     bad_v = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(sc_new * a.ibc2) - 0x17800000u <= 0x66800000u - 0x17800000u)) ^ 1;
   }
-  const bool eps_ok = a.eps >= 0x1p-40f && a.eps <= 1.0f;
+  // den = root + eps then lies in [2^-70, 2^40]
+  const bool eps_ok = a.eps >= 0x1p-70f && a.eps <= 0x1p39f;
   bool fast_root = eps_ok && !__any(bad_v);                // the roots (and den) by the short form
   bool fast_m = !__any(bad_m);                             // and, with it, the quotient
   if (fast_root && !wide_v) {
@@ -782,7 +783,7 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       const uint32_t s_bits = f2u(sqrt_rn_safe(vq * a.ibc2));
       if (use_table) {
         for (uint32_t h = e >> lg_roots; h < (1u << (bq - lgP)); h += 64u >> lg_roots) {
-          // (a root of 0 becomes a number below 2^-96 here, which eps >= 2^-40 absorbs)
+          // (a root of 0 becomes a number of at most 2^-96 here, which eps >= 2^-70 absorbs)
           const float den = u2f(s_bits + (((h << lgP) << (26u - bq)))) + a.eps;
           reinterpret_cast<float2*>(XR)[(rg << bq) + (h << lgP) + i] = make_float2(den, rcp_rn_safe(den));
         }

@@ -161,3 +161,31 @@ def test_repack_chunks_over_job_boundaries(ctx):
     torch.cuda.synchronize()
     for l, (x, y) in enumerate(zip(*dst)):
         assert torch.equal(x, y), l
+
+
+@pytest.mark.parametrize("eps", [1e-25, 2.0 ** -70, 1e-20, 1e-15, 1e-12, 0.5, 2.0 ** 39, 1e15])
+def test_epsilon_inside_and_outside_the_short_forms_range(ctx, eps):
+    """The short root and quotient take eps in [2^-70, 2^39], other values the IEEE routines: the oracle's bits either way,
+    also where a block of v is all zero and den is eps alone."""
+    from oracle import stq_oracle as oracle
+    from workloads import configs
+    from workloads.harness import DeviceModel
+    hp = dict(configs.ADAM, eps=float(np.float32(eps)))
+    sizes, plan = [2048 * 3 + 777, 5000], [(8, 4), (5, 8)]
+    w = configs.Workload(74, "eps", [("a", sizes[0]), ("b", sizes[1])], 64, "fp32", 2, "normal_per_tensor", hparams=hp)
+    m = DeviceModel(ctx, w, plan)
+    th = [p.cpu().numpy().copy() for p in m.param]
+    st = [oracle.State.zeros(n, 64, bm, bv) for n, (bm, bv) in zip(sizes, plan)]
+    for t in (1, 2, 3):
+        m.set_grads(t)
+        m.grad[0][64:192] = 1e-30 if t == 1 else 0.0  # squares vanish: v = 0 where m is not
+        m.grad[1][0:64] = 0.0
+        m.step(t)
+        torch.cuda.synchronize()
+        for l in range(2):
+            oracle.step(th[l], m.host_grad(l), st[l], **hp, t=t)
+            p, mw, ms, vw, vs = m.host_state(l)
+            assert np.array_equal(mw, oracle.pack(st[l].um, st[l].bm)) and np.array_equal(vw, oracle.pack(st[l].cv, st[l].bv))
+            assert np.array_equal(ms, oracle.pad_scales(st[l].sm, st[l].numel, 64))
+            assert np.array_equal(vs, oracle.pad_scales(st[l].sv, st[l].numel, 64))
+            assert np.array_equal(p.view(np.uint32), th[l].view(np.uint32)), (t, l)
