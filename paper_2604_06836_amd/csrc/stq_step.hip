@@ -419,15 +419,17 @@ __device__ __forceinline__ float div_rn_safe(float n, float d, float y) {
   const float q = n * y;
   return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
 }
-// Whether every number added is 0 or has its magnitude between two given ones (as bit patterns).
+// Whether every number added is +0 or has its magnitude between two given ones (as bit patterns).  -0 does not pass: the
+// short quotient makes +0 of it, the IEEE one -0, which shows in a parameter that is itself -0.  (A quantized moment is
+// never -0.)
 struct SafeRange {
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   __device__ __forceinline__ void add(float x) {
-    const uint32_t u = f2u(x) & 0x7FFFFFFFu;
-    lo = min(lo, u - 1u);  // 0 passes
+    const uint32_t u = __builtin_rotateleft32(f2u(x), 1);  // the magnitude, below it the sign: +0 is 0 and -0 is 1
+    lo = min(lo, u - 1u);  // +0 passes
     hi = max(hi, u);
   }
-  __device__ __forceinline__ bool within(uint32_t least, uint32_t most) const { return lo >= least - 1u && hi <= most; }
+  __device__ __forceinline__ bool within(uint32_t least, uint32_t most) const { return lo >= 2u * least - 1u && hi <= 2u * most + 1u; }
 };
 // 2^-40 <= x <= 2^40, for x >= 0: positive floats order like their bit patterns
 __device__ __forceinline__ bool in_safe_range(float x) { return f2u(x) - 0x2B800000u <= 0x53800000u - 0x2B800000u; }
