@@ -45,6 +45,8 @@ struct StepArgs {
   float eps, lr, decay;    // decay = 1 - lr*weight_decay
   uint32_t lgK;            // log2 of the block size: 6, 7 or 8
   uint32_t chunk;          // stripes of tiles: consecutive tiles a wave takes at a time; statistics: units of a workgroup
+  uint32_t look_ahead;     // 0: a wave walks from tensor to tensor to that of its next unit; else it searches, this many
+                           // entries of the table first
   uint32_t quarter_units;  // not 0: a unit is a quarter tile (small launches); 2: and some width is not a multiple of
                            // 4 bits, so that quarters share words
   uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters and the count of

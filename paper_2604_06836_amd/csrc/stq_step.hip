@@ -1049,10 +1049,23 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
       const uint32_t t = static_cast<uint32_t>(u >> qs);
       if (t >= d.tile_begin + d.n_tiles) {  // t < total_tiles, so a later tensor holds it
         if (STATS && !tickets) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
-        do {
-          ++l;
+        // (see launch_table; with statistics quarter units have ranges of their own, and the next unit is close)
+        if (!(STATS && QUARTERS) && __builtin_expect(a.look_ahead != 0u, 0)) {
+          int hidden = lane;
+          asm volatile("" : "+v"(hidden));  // no address of the search is worth a register throughout the loop
+          uint32_t window, ahead;
+          do {  // (on to the next window from the last entry of one; the last of all is a window of one)
+            window = min(a.look_ahead, a.n_tensors - l);
+            ahead = find_begin(a.desc + l, window, t, hidden);
+            l += ahead;
+          } while (ahead == window - 1u && window > 1u);
           d = load_desc(a.desc, l);
-        } while (t >= d.tile_begin + d.n_tiles);
+        } else {
+          do {
+            ++l;
+            d = load_desc(a.desc, l);
+          } while (t >= d.tile_begin + d.n_tiles);
+        }
       }
       const uint32_t tile = t - d.tile_begin;
       const uint64_t left = d.numel - static_cast<uint64_t>(tile) * kTile;

@@ -114,6 +114,60 @@ def test_tensor_search_over_three_levels(ctx):
         assert torch.equal(x, y)
 
 
+MANY = {  # (sizes, tensors per launch of the reference: its waves never skip, or walk)
+    # 28,000 tiles, thousands of tensors skipped at once, then none: the search starts with a window of 4096
+    "thousands": ([1 + (i * 7919) % 2048 for i in range(3000)] + [2048 * 13000 - 3, 77, 2048 * 40, 5] +
+                  [2048 * (1 + i % 3) + i for i in range(700)] + [2048 * 9000, 2048, 1] + [900] * 1200, 50),
+    # 20,250 tiles, 38 tensors skipped on average, up to 250: a window of 64, left where it does not reach
+    "dozens": ([2048 * 40 - i for i in range(300)] + [1 + (i * 7919) % 2048 for i in range(250)] + [2048 * 40] * 200, 12)}
+
+
+@pytest.mark.parametrize("many", sorted(MANY))
+@pytest.mark.parametrize("tickets", [False, True])
+def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, many):
+    """Launches whose stripes and tickets skip none, a few, dozens and thousands of tensors, against launches of a few."""
+    sizes, few = MANY[many]
+    plan = [(2 + i % 7, 2 + (i // 7) % 7) for i in range(len(sizes))]
+    got = []
+    for group in (few, len(sizes)):
+        m = model(ctx, sizes, plan, 64, 76)
+        m.set_grads(1)
+        ctx.set_schedule(1 if tickets and group > few else 2 ** 63)
+        for a in range(0, len(sizes), group):
+            launch(ctx, m, 1, list(range(a, min(a + group, len(sizes)))))
+        ctx.set_schedule(0)
+        torch.cuda.synchronize()
+        nm = [m._code_words(n, b) for n, (b, _) in zip(sizes, plan)]
+        nv = [m._code_words(n, b) for n, (_, b) in zip(sizes, plan)]
+        got.append([torch.cat(m.param).view(torch.int32), torch.cat(m.m_scales).view(torch.int32), torch.cat(m.v_scales).view(torch.int32),
+                    torch.cat([c[:k] for c, k in zip(m.m_codes, nm)]), torch.cat([c[:k] for c, k in zip(m.v_codes, nv)])])
+        del m
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
+def test_many_small_tensors_are_not_walked_one_by_one(ctx):
+    """4000 tensors of 16,384 elements: a plain step, whose waves skip hundreds of tensors between their tiles, is no slower
+    than one that also gathers the gradient's statistics, whose waves stay in one range (a walk through all took 4.2 times as
+    long)."""
+    n = 4000
+    m = model(ctx, [16384] * n, [(8, 4)] * n, 128, 77)
+    m.set_grads(1)
+    best = {}
+    for stats in (False, "grad", False, "grad"):
+        launch_all = lambda: m.step(1, stats)  # noqa: E731
+        launch_all()
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            launch_all()
+            b.record()
+            torch.cuda.synchronize()
+            best[stats] = min(best.get(stats, 1e9), a.elapsed_time(b))
+    ctx.stats(n, m.stream)
+    assert best[False] < 1.7 * best["grad"], best
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("sizes", [[1], [3, 2047, 2049], [1 + (i * 4093) % 9001 for i in range(700)], [2048 * 2500 + 5, 7, 2048 * 4, 2048 * 9000 - 1]])
 def test_gradient_statistics_over_workgroup_ranges(ctx, sizes, dtype):
