@@ -475,11 +475,13 @@ __device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)
 
 // The parameter update from the quantized moments (mq: values of the first, code: codes of the second moment).  It needs
 // den = sqrt(vq*ibc2) + eps of the quantized value vq, which takes only 2^b values per block:
-//  kDenTable: den and 1/den come from the wave's table TAB of (den, 1/den), indexed by (row, block, code);
+//  kDenTable: den and 1/den come from the wave's table TAB of (den, 1/den), indexed by (row, block, code) (without FAST
+//          1/den is not there);
 //  kRoots: two octaves of v further down the root is half as large, so a table of the roots of the lowest two octaves'
 //          levels holds them all; TAB keeps, per (row, block, code mod P), the root's bits less (code mod P) << (26-b),
 //          and the root of code c is that plus c << (26-b): its exponent counts the whole multiples of P;
-//  kDirect: from the level itself with the IEEE routines, when a scale is out of the range the short forms need.
+//  kDirect: from the level itself with the IEEE routines, when a scale is out of the range the short forms need and there
+//          is no table of den.
 // FAST: the short form of the quotient, else the IEEE division.
 // (Vector instructions per parameter with these forms and quantize_v: 58.8 on a 3.5 G-parameter launch at widths 4..8 and
 // 3..6, K = 64, where IEEE-shaped expansions and a 514-entry search table took 67.3.  The launch is bound by the memory
@@ -794,6 +796,17 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       }
     }
     wave_lds_sync();
+  } else if (use_table) {
+    // A scale or eps out of the short forms' range (small gradients, an eps such as 1e-30): den by the IEEE routines, still
+    // once per level; the quotients take the IEEE division.  (1.5 G parameters, K = 128, 5 bits, bf16 gradients: 3391 us,
+    // with a root per element 3521, in range 3263.  Where a level serves fewer elements the root is taken per element.)
+    for (uint32_t e = lane; e < (512u >> lgK) << bq; e += 64) {
+      const uint32_t c = e & ((1u << bq) - 1u), rg = e >> bq;
+      const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
+      const float vq = SN[((blk << (lgK - 4)) << 2) + 2 + rw] * lds_at(Lreg, (c << 2) | (4u << bq));
+      reinterpret_cast<float2*>(XR)[e] = make_float2(__builtin_sqrtf(vq * a.ibc2) + a.eps, 0.0f);
+    }
+    wave_lds_sync();
   }
 
   // ---- linear symmetric quantization of m; m is replaced by its quantized value ----
@@ -925,9 +938,9 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     for (int i = 0; i < 2; ++i)
       row[i] = ((static_cast<uint32_t>(i) << (8 - lgK)) + (static_cast<uint32_t>(lane) >> (lgK - 2))) << lg_row;
     const uint32_t* TAB = ws;
-    if (!fast_root) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else if (use_table && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    if (use_table && fast_root && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else if (use_table) update_params<kDenTable, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (!fast_root) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else if (fast_m) update_params<kRoots, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else update_params<kRoots, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
   }
