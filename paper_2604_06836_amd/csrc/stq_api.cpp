@@ -558,7 +558,7 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
   if (!ctx || !jobs || n == 0 || n > 2 * ctx->max_tensors) return STQ_EINVAL;
   if (lg_block(block) < 0) return STQ_EBLOCK;
   std::vector<RepackJob> table(n);
-  uint64_t total = 0;
+  uint64_t total = 0, code_bytes = 0;
   for (uint32_t i = 0; i < n; ++i) {
     const stq_repack_job& j = jobs[i];
     if (!j.src_codes || !j.dst_codes || j.numel == 0 || j.state > 1) return STQ_EINVAL;
@@ -581,6 +581,7 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
     r.lut = repack_lut_index(j.state, j.src_bits, j.dst_bits);
     r.pad = 0;
     total += tiles;
+    code_bytes += tiles * 256 * (j.src_bits + j.dst_bits);
   }
   DeviceGuard g(ctx->device);
   if (!g.ok) return STQ_EHIP;
@@ -597,7 +598,7 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
   a.n_jobs = n;
   a.total_tiles = static_cast<uint32_t>(total);
   a.luts = ctx->d_luts;
-  return launch_repack_many(a, stream) == 0 ? STQ_OK : STQ_EHIP;
+  return launch_repack_many(a, code_bytes, stream) == 0 ? STQ_OK : STQ_EHIP;
 }
 
 }  // extern "C"

@@ -84,7 +84,8 @@ struct RepackManyArgs {
 // stats: 0 none, 1 every statistic, 2 the gradient's only.
 int launch_step(const StepArgs& a, bool grad_bf16, int stats, int mode, uint32_t groups, void* stream);
 int launch_zero(const ZeroArgs& a, void* stream);
-int launch_repack_many(RepackManyArgs a, void* stream);
+constexpr uint64_t kRepackOnceBytes = 350ull << 20;  // see launch_repack_many
+int launch_repack_many(RepackManyArgs a, uint64_t code_bytes, void* stream);  // code_bytes: read and written
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
                       uint32_t n_cu, void* stream);
 int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);

@@ -69,10 +69,10 @@ template <int B, int... N>
 __device__ __forceinline__ void extract_all(const uint32_t (&w)[8], uint32_t (&code)[32], std::integer_sequence<int, N...>) {
   ((code[N] = extract<B, N>(w)), ...);
 }
-template <int B>
+template <int B, bool ONCE>
 __device__ __forceinline__ void load_words(const STQ_GLOBAL uint32_t* src, uint32_t (&w)[8]) {
 #pragma unroll
-  for (int p = 0; p < B; ++p) w[p] = __builtin_nontemporal_load(src + 64 * p);
+  for (int p = 0; p < B; ++p) w[p] = ONCE ? __builtin_nontemporal_load(src + 64 * p) : src[64 * p];
 }
 template <int B>
 __device__ __forceinline__ void unpack32(const uint32_t (&w)[8], uint32_t (&code)[32]) {
@@ -122,10 +122,12 @@ __device__ __forceinline__ RepackJob load_job(const RepackJob* table, uint32_t j
 // When a wave enters a job with another conversion table it reloads its table.  The table sits at LDS address 0 as 256 bytes (new codes have at most 8 bits), so
 // an old code is the address of its new code as it comes out of the bit-field extraction: one vector
 // instruction per code to unpack, none to look up, one to pack -- the kernel moves (b_old + b_new)/8 bytes per
-// element and is bound by the memory system: reads and writes, each of which nothing touches again, carry the
-// non-temporal hint, and the loads of two tiles are in flight before the first of them is converted.
+// element and is bound by the memory system: the writes, which nothing here touches again, carry the non-temporal hint,
+// so do the reads of a launch too large for the caches (ONCE, see launch_repack_many), and the loads of two tiles are in
+// flight before the first of them is converted.
 // (2.85 GB of codes of 1.56 G parameters: 523 us with chunks of 4 tiles, 541 with 2, 540 with 8, 772 with 1; 580 with
 // persistent waves that took a tile at a time without the hint.)
+template <bool ONCE>
 __global__ __launch_bounds__(64) void repack_many_kernel(const RepackManyArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lut[256];  // the kernel's only LDS variable: address 0
   const uint32_t lane = threadIdx.x;
@@ -163,8 +165,8 @@ __global__ __launch_bounds__(64) void repack_many_kernel(const RepackManyArgs a)
       const bool two = t + 1u < c_end && tile + 1u < job.n_tiles;
       const STQ_GLOBAL uint32_t* src = (const STQ_GLOBAL uint32_t*)(job.src + static_cast<size_t>(tile) * 64 * job.b_old + lane);
       uint32_t w0[8], w1[8];
-      if (two) STQ_SWITCH_WIDTH(job.b_old, (load_words<B>(src, w0), load_words<B>(src + 64 * B, w1)))
-      else STQ_SWITCH_WIDTH(job.b_old, (load_words<B>(src, w0)))
+      if (two) STQ_SWITCH_WIDTH(job.b_old, (load_words<B, ONCE>(src, w0), load_words<B, ONCE>(src + 64 * B, w1)))
+      else STQ_SWITCH_WIDTH(job.b_old, (load_words<B, ONCE>(src, w0)))
       if (loaded != which) {
         __builtin_amdgcn_wave_barrier();  // the previous tile's table reads are done (same wave, in order)
         // lane k packs entries 4k .. 4k+3 of the word table in device memory into one LDS word
@@ -358,11 +360,16 @@ int launch_zero(const ZeroArgs& a, void* stream) {
   return static_cast<int>(hipGetLastError());
 }
 
-int launch_repack_many(RepackManyArgs a, void* stream) {
+int launch_repack_many(RepackManyArgs a, uint64_t code_bytes, void* stream) {
   a.chunk = a.total_tiles < 8192u ? 1u : 4u;  // (a launch that single tiles do not fill: every wave one)
   const uint32_t need = a.total_tiles / a.chunk + (a.total_tiles % a.chunk != 0);
   const uint32_t groups = need < (1u << 25) ? need : 1u << 25;  // (64 threads each: HIP counts the threads of a launch in 32 bits)
-  hipLaunchKernelGGL(repack_many_kernel, dim3(groups), dim3(64), 0, static_cast<hipStream_t>(stream), a);
+  // Codes that the 256 MB cache in front of the memory may still hold from the step before are read without the hint, which
+  // would keep them out of it (codes of 4 to 5 bits, two states in turn: 130 M elements, 146 MB of reads and writes, 27.8 us
+  // against 32.1; 200 M 37.6 against 43.2; 300 M, 338 MB, 58.4 against 59.9), those of larger launches with it (340 M, 383 MB,
+  // 65.4 us against 66.4; 2.85 GB 521 against 527).
+  const bool once = code_bytes >= kRepackOnceBytes;
+  hipLaunchKernelGGL(once ? repack_many_kernel<true> : repack_many_kernel<false>, dim3(groups), dim3(64), 0, static_cast<hipStream_t>(stream), a);
   return static_cast<int>(hipGetLastError());
 }
 

@@ -217,6 +217,25 @@ def test_repack_chunks_over_job_boundaries(ctx):
         assert torch.equal(x, y), l
 
 
+@pytest.mark.parametrize("state,b0,b1", [(0, 3, 8), (1, 7, 4)])
+def test_repack_beyond_the_caches(ctx, state, b0, b1):
+    """369 MB of codes and more (read with the non-temporal hint) against two launches of half as much (read without)."""
+    n, half = 2 ** 28 - 1001, 2 ** 27
+    tiles = (n + 2047) // 2048
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(79)
+    src = torch.randint(-2 ** 31, 2 ** 31 - 1, (tiles * 64 * b0,), generator=gen, device="cuda:0", dtype=torch.int64).to(torch.int32)
+    dst = [torch.full((tiles * 64 * b1,), -1, device="cuda:0", dtype=torch.int32) for _ in range(2)]
+    s = torch.cuda.current_stream().cuda_stream
+    assert tiles * 256 * (b0 + b1) > 350 << 20
+    ctx.repack(n, 64, state, src.data_ptr(), b0, dst[0].data_ptr(), b1, s)
+    k = half // 2048 * 256
+    ctx.repack(half, 64, state, src.data_ptr(), b0, dst[1].data_ptr(), b1, s)
+    ctx.repack(n - half, 64, state, src.data_ptr() + k * b0, b0, dst[1].data_ptr() + k * b1, b1, s)
+    torch.cuda.synchronize()
+    assert torch.equal(*dst)
+
+
 @pytest.mark.parametrize("eps", [1e-25, 2.0 ** -70, 1e-20, 1e-15, 1e-12, 0.5, 2.0 ** 39, 1e15])
 def test_epsilon_inside_and_outside_the_short_forms_range(ctx, eps):
     """The short root and quotient take eps in [2^-70, 2^39], other values the IEEE routines: the oracle's bits either way,
