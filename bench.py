@@ -109,7 +109,7 @@ def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2604_06836_amd", "csrc")
-    for name in ("stq_step.hip", "stq_wave.h", "stq_device.h", "stq_tables.h", "stq_tables.cpp"):
+    for name in ("stq_step.hip", "stq_wave.h", "stq_round.h", "stq_device.h", "stq_tables.h", "stq_tables.cpp"):
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()[:16]
 

@@ -49,6 +49,14 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_shared(src: str, out: str) -> str:
+    """One HIP source that includes the kernels' headers -> a shared library of its own (the tests' device code)."""
+    tmp = out + ".tmp.%d" % os.getpid()
+    subprocess.check_call([HIPCC, *COMMON, *DEVICE_FLAGS, "-shared", src, "-o", tmp])
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     build(verbose=True)
     sys.exit(0)
