@@ -6,7 +6,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-# 25,394 tiles with bf16 gradients: whole tiles; each tensor by itself: quarter tiles.  Ragged ends in the first, second and
+# 25,394 tiles: whole tiles (see below); each tensor by itself: quarter tiles.  Ragged ends in the first, second and
 # last quarter of a tile, one tensor of whole tiles only.
 SIZES = [2048 * 6348 + 1, 2048 * 6349 - 900, 2048 * 6347, 2048 * 6348 + 777, 5, 2047]
 PLANS = {"in_place": [(3, 5), (7, 8), (2, 6), (8, 4), (5, 3), (6, 7)],
@@ -22,10 +22,10 @@ def ctx():
     c.close()
 
 
-def model(ctx, sizes, plan, K, seed):
+def model(ctx, sizes, plan, K, seed, dtype="bf16"):
     from workloads import configs
     from workloads.harness import DeviceModel
-    w = configs.Workload(seed, "schedules", [("t%d" % i, n) for i, n in enumerate(sizes)], K, "bf16", 2, "normal_per_tensor")
+    w = configs.Workload(seed, "schedules", [("t%d" % i, n) for i, n in enumerate(sizes)], K, dtype, 2, "normal_per_tensor")
     m = DeviceModel(ctx, w, plan, spare_width=32)
     return m
 
@@ -50,16 +50,17 @@ def outputs(m):
         [[m._spare[(l, s)].clone() for l in range(len(m.param)) for s in (0, 1)]]
 
 
-@pytest.mark.parametrize("kind", ["in_place", "transition", "wide"])
+# (whole tiles under stripes: bf16 gradients and quantized widths only; every other launch of this size takes quarters there)
+@pytest.mark.parametrize("kind,dtype,tickets", [("in_place", "bf16", False), ("transition", "bf16", False)] +
+                         [(kind, dtype, True) for kind in ("in_place", "transition", "wide") for dtype in ("bf16", "fp32")])
 @pytest.mark.parametrize("stats", [False, True, "grad"])
-@pytest.mark.parametrize("tickets", [False, True])
-def test_whole_tiles_and_quarters_give_the_same_bits(ctx, kind, stats, tickets):
+def test_whole_tiles_and_quarters_give_the_same_bits(ctx, kind, dtype, tickets, stats):
     K = {"in_place": 64, "transition": 128, "wide": 256}[kind]
     got, sums = [], []
     for together in (False, True):
         plan = PLANS["in_place"] if kind == "transition" else PLANS[kind]
         new = PLANS["transition"] if kind == "transition" else None
-        m = model(ctx, SIZES, plan, K, 70)
+        m = model(ctx, SIZES, plan, K, 70, dtype)
         for lst in (m.m_codes, m.v_codes):  # nothing undefined behind a state narrower than its buffer
             for l, buf in enumerate(lst):
                 buf[m._code_words(SIZES[l], plan[l][0 if lst is m.m_codes else 1]):] = 0
@@ -123,18 +124,22 @@ MANY = {  # (sizes, tensors per launch of the reference: its waves never skip, o
 
 
 @pytest.mark.parametrize("many", sorted(MANY))
-@pytest.mark.parametrize("tickets", [False, True])
-def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, many):
+@pytest.mark.parametrize("tickets,stats", [(False, False), (True, False), (True, True)])
+def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, stats, many):
     """Launches whose stripes and tickets skip none, a few, dozens and thousands of tensors, against launches of a few."""
     sizes, few = MANY[many]
     plan = [(2 + i % 7, 2 + (i // 7) % 7) for i in range(len(sizes))]
-    got = []
+    got, sums = [], []
     for group in (few, len(sizes)):
+        sums.append([])
         m = model(ctx, sizes, plan, 64, 76)
         m.set_grads(1)
         ctx.set_schedule(1 if tickets and group > few else 2 ** 63)
         for a in range(0, len(sizes), group):
-            launch(ctx, m, 1, list(range(a, min(a + group, len(sizes)))))
+            which = list(range(a, min(a + group, len(sizes))))
+            launch(ctx, m, 1, which, stats=stats)
+            if stats:
+                sums[-1] += [(s.count, s.g_sq_sum, s.g_absmax, s.v_absmax) for s in ctx.stats(len(which), m.stream)]
         ctx.set_schedule(0)
         torch.cuda.synchronize()
         nm = [m._code_words(n, b) for n, (b, _) in zip(sizes, plan)]
@@ -144,6 +149,8 @@ def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, many):
         del m
     for x, y in zip(*got):
         assert torch.equal(x, y)
+    for l, (x, y) in enumerate(zip(*sums)):  # fp64 in another order: n * 2^-53
+        assert x[0] == y[0] and x[2:] == y[2:] and abs(x[1] - y[1]) <= 1e-12 * y[1], l
 
 
 def test_many_small_tensors_are_not_walked_one_by_one(ctx):
