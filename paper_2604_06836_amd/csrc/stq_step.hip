@@ -757,7 +757,7 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   const bool eps_ok = a.eps >= 0x1p-70f && a.eps <= 0x1p39f;
   bool fast_root = eps_ok && !__any(bad_v);                // the roots (and den) by the short form
   bool fast_m = !__any(bad_m);                             // and, with it, the quotient
-  if (fast_root && !wide_v) {
+  if (__builtin_expect(fast_root && !wide_v, 1)) {
     for (uint32_t e = lane; e < (1u << lg_roots) || (use_table && e < 64u); e += 64) {
       const uint32_t root = e & ((1u << lg_roots) - 1u), i = root & ((1u << lgP) - 1u), rg = root >> lgP;
       const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
@@ -775,7 +775,7 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       }
     }
     wave_lds_sync();
-  } else if (use_table) {
+  } else if (__builtin_expect(use_table, 0)) {
     // A scale or eps out of the short forms' range (small gradients, an eps such as 1e-30): den by the IEEE routines, still
     // once per level; the quotients take the IEEE division.  (1.5 G parameters, K = 128, 5 bits, bf16 gradients: 3391 us,
     // with a root per element 3521, in range 3263.  Where a level serves fewer elements the root is taken per element.)
@@ -917,9 +917,9 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     for (int i = 0; i < 2; ++i)
       row[i] = ((static_cast<uint32_t>(i) << (8 - lgK)) + (static_cast<uint32_t>(lane) >> (lgK - 2))) << lg_row;
     const uint32_t* TAB = ws;
-    if (use_table && fast_root && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    if (__builtin_expect(!fast_root && !use_table, 0)) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (use_table && fast_root && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else if (use_table) update_params<kDenTable, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else if (!fast_root) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else if (fast_m) update_params<kRoots, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
     else update_params<kRoots, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
   }
