@@ -291,7 +291,8 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
   const int stats = (hp->flags & STQ_FLAG_STATS) ? 1 : ((hp->flags & STQ_FLAG_STATS_GRAD) ? 2 : 0);
   const bool want_stats = stats != 0;
   const bool fp32_grads = hp->grad_dtype == 0;
-  // every variant fits six waves per SIMD (three workgroups per CU) except the wide-state one (two)
+  // Three workgroups per CU, with wide states two (three there: within 1 % from 0.5 to 300 M parameters, but 3 M, whose
+  // units then all fit at once, 14.1 us instead of 14.9).
   const uint32_t cap_cu = mode == 2 ? 2 : 8;
   const uint32_t per_cu = ctx->groups_per_cu < cap_cu ? ctx->groups_per_cu : cap_cu;
   const uint32_t wpg = kWavesPerGroup;

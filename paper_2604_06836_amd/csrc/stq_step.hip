@@ -7,7 +7,7 @@
 // -ffp-contract=off); division and square root are the correctly rounded ones.
 //
 // Work decomposition: one wavefront owns one 2048-element tile at a time and processes it as four
-// quarters of 2 rows: a quarter's working set fits the 80 registers of six waves per SIMD (68 to 72 in use) with
+// quarters of 2 rows: a quarter's working set fits the 80 registers of six waves per SIMD (69 to 73 in use) with
 // nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.  Small and medium
 // launches hand the quarters of a tile to four waves (see step_kernel).
 // In row i lane j holds the 4 elements 256*i + 4*j + e, so
@@ -39,7 +39,7 @@ constexpr int XS = 68;  // row stride (words) of the transpose scratch: keeps 16
 // per-wave LDS scratch: XR[4][XS] partial maxima (later the den or root table), old scales, new scales, reciprocals
 constexpr int kWaveScratch = 4 * XS + 3 * 64;
 constexpr int kLdsWords = kTabWords + kWavesPerGroup * kWaveScratch;  // + the statistics slices in that variant
-constexpr int kStatFlushTiles = 16;  // fp32 lane sums are widened to fp64 every this many tiles
+constexpr int kStatFlushUnits = 16;  // fp32 lane sums are widened to fp64 every this many units (tiles or quarter tiles)
 constexpr uint32_t kDenEntries = 128;  // capacity of the per-wave den table (8 bytes per entry, inside XR)
 static_assert(kDenEntries * 8 <= 4 * XS * 4, "the den table lies inside XR");
 static_assert(((512 / 64) << (kMaxBits - 3)) * 4 <= 4 * XS * 4, "and so do the roots of the widest code at the smallest block");
@@ -211,7 +211,7 @@ __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n
 //  * S = 1 adds the moments' six fp32 sums (groups of eight lanes, 8-word slots) and two maxima (the owner lanes
 //    of the block scales hold them: lanes 0..31 the first moment's, 32..63 the second's, so a group of four is
 //    of one kind); the sums since the last widening are added to fp64 totals (lane k < 6 of the last slot)
-//    every kStatFlushTiles tiles.
+//    every kStatFlushUnits units.
 // S = 2: the gradient's statistics only; the slice stays small enough for three workgroups per CU.
 enum GradSlot { kLGSum = 0, kLGAbs, kLGSq };
 enum MomentSlot { kLMSum = 0, kLMSq, kLMErr, kLVSum, kLVSq, kLVErr };
@@ -231,7 +231,7 @@ struct LaneStats {
   static constexpr int kMaxOff = 3 * 2 * kG, kMomentOff = kMaxOff + kMaxWords, kWideOff = kMomentOff + 6 * 8;
   static constexpr int kWords = S == 0 ? 0 : (S == 1 ? kWideOff + 2 * 6 + 4 : kMomentOff);
   float* acc;      // this wave's slice, null in the plain kernel
-  uint32_t tiles;  // tiles since the last widening (uniform; stripes only)
+  uint32_t units;  // units since the last widening (uniform; stripes only)
   __device__ __forceinline__ double* grad_sums() const { return reinterpret_cast<double*>(acc); }
   __device__ __forceinline__ uint32_t* maxima() const { return reinterpret_cast<uint32_t*>(acc) + kMaxOff; }
   __device__ __forceinline__ float* moment_sums() const { return acc + kMomentOff; }
@@ -260,7 +260,7 @@ struct LaneStats {
   }
   __device__ __forceinline__ void clear_moment_sums(int lane) {
     if (S == 1 && lane < 48) moment_sums()[lane] = 0.0f;
-    tiles = 0;
+    units = 0;
   }
   __device__ __forceinline__ void clear_grad(int lane) {
     if (lane < 3 * kG) grad_sums()[lane] = 0.0;
@@ -956,7 +956,8 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
 // workgroups that have left), so every launch -- also a replayed one -- finds both at zero.
 // STATS 1 (all statistics) and 2 (the gradient's only) stay within the plain kernel's budget of 80 registers
 // and a third of a CU's LDS: their running sums live in LDS and nothing derived from the lane index is kept
-// across the tile loop (see LaneStats).  Only the wide-state variant (MODE 2) runs two workgroups per CU.
+// across the tile loop (see LaneStats).  They run three workgroups per CU; plain launches whose units do not all fit at
+// once run two, as launches with wide states (MODE 2, 77 to 83 registers) always do (see launch_table).
 // What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 7.45 ms = 6.0 TB/s, where an in-place
 // addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 310 us); launches that leave the chip partly
 // idle one pass of latencies (tables, descriptor, loads, three LDS exchanges, stores): 6 us for 0.2 M parameters.
@@ -1019,7 +1020,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
 
   LaneStats<STATS> st;
   st.acc = STATS ? reinterpret_cast<float*>(lds + kLdsWords + wave * LaneStats<STATS>::kWords) : nullptr;
-  st.tiles = 0;
+  st.units = 0;
   if (STATS) st.clear_all(lane);
   for (;;) {
     uint64_t c_begin, c_end;
@@ -1084,7 +1085,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
           const uint32_t t_first = static_cast<uint32_t>((c_begin - wave) >> qs);
           ticket_stats_tile(st, &ticket_rec[turn][wave], t_first >= d.tile_begin, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
         }
-      } else if (STATS && ++st.tiles == kStatFlushTiles) {
+      } else if (STATS && ++st.units == kStatFlushUnits) {
         widen_stats(st, lane);
       }
     }
