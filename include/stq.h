@@ -146,12 +146,11 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors);
 
 /* Order in which the step kernel takes the tiles of a launch (results do not depend on it, only speed; the
  * statistics' sums differ in the last bits as with any other order of addition).  Launches of at least
- * `ticket_min_tiles` tiles use the ticket schedule: workgroups draw
- * runs of neighbouring tiles from a counter in device memory and their waves work on them in step, so the
- * chip sweeps every array front to back inside one compact window -- worth 10-15 % of bandwidth on
- * multi-gigabyte workloads, a loss on small ones, where the waves keep walking stripes.
- * Steps that gather statistics switch at half of the value.  0 restores the default (about 0.2 G
- * elements); UINT64_MAX never uses tickets.  Host only. */
+ * `ticket_min_tiles` tiles (with bf16 gradients, or 16- or 32-bit states, half as many again) use the ticket
+ * schedule: workgroups draw runs of neighbouring tiles from counters in device memory and their waves work on
+ * them in step, so the chip sweeps every array front to back inside one compact window -- worth 10-20 % of
+ * bandwidth on large workloads, nothing on small ones, where every workgroup takes tickets of its own.
+ * 0 restores the default (about 8 M elements); UINT64_MAX never draws tickets.  Host only. */
 int stq_set_schedule(stq_ctx* ctx, uint64_t ticket_min_tiles);
 
 /* Synchronise the device and free everything the context owns. */

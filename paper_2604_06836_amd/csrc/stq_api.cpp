@@ -70,7 +70,7 @@ namespace {
 
 constexpr uint32_t kStaticMaxTensors = STQ_STATIC_MAX_TENSORS;
 constexpr size_t kStaticTableBytes = sizeof(TensorDesc) * kStaticMaxTensors;
-constexpr size_t kStaticScratchBytes = kStaticTableBytes + 256;  // the table, then the scheduling words
+constexpr size_t kStaticScratchBytes = kStaticTableBytes + 4 * kSchedWords;  // the table, then the ticket counters
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -152,16 +152,6 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   c->device = device;
   c->max_tensors = max_tensors;
   c->n_cu = static_cast<uint32_t>(prop.multiProcessorCount);
-#ifdef STQ_TUNING_ENV  // measurement builds only: launch shape from the environment
-  if (const char* e = std::getenv("STQ_GROUPS_PER_CU")) {
-    const int v = std::atoi(e);
-    if (v >= 1 && v <= 8) c->groups_per_cu = static_cast<uint32_t>(v);
-  }
-  if (const char* e = std::getenv("STQ_CHUNK")) {
-    const long v = std::strtol(e, nullptr, 10);
-    if (v >= 1 && v <= (1 << 20)) c->chunk_override = static_cast<uint32_t>(v);
-  }
-#endif
   DeviceGuard g(device);
   bool ok = g.ok;
   ok = ok && static_scratch_address(device, &c->static_scratch) == STQ_OK;
@@ -169,8 +159,8 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   for (int k = 0; k < kDescTables && ok; ++k)
     ok = ok && hipMalloc(&c->d_desc[k], sizeof(TensorDesc) * max_tensors) == hipSuccess;
   ok = ok && hipMalloc(&c->d_stats, sizeof(double) * kStatSlots * max_tensors) == hipSuccess;
-  ok = ok && hipMalloc(&c->d_sched, 256) == hipSuccess;
-  ok = ok && hipMemset(c->d_sched, 0, 256) == hipSuccess;
+  ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords) == hipSuccess;
+  ok = ok && hipMemset(c->d_sched, 0, 4 * kSchedWords) == hipSuccess;
   ok = ok && hipHostMalloc(&c->h_stats, sizeof(double) * kStatSlots * max_tensors, hipHostMallocDefault) == hipSuccess;
   for (int k = 0; k < kRing && ok; ++k) {
     ok = ok && hipHostMalloc(&c->h_stage[k], sizeof(TensorDesc) * max_tensors, hipHostMallocDefault) == hipSuccess;
@@ -268,7 +258,7 @@ int check_hparams(const stq_hparams* hp) {
 }
 
 int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t total, double* d_stats,
-                 const stq_hparams* hp, int mode, bool quarters_ok, void* stream, uint32_t* sched) {
+                 const stq_hparams* hp, int mode, void* stream, uint32_t* sched) {
   StepArgs a;
   a.desc = d_desc;
   a.n_tensors = n;
@@ -289,62 +279,49 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
 
   // statistics: all of them, or only the gradient's (the flag for all wins)
   const int stats = (hp->flags & STQ_FLAG_STATS) ? 1 : ((hp->flags & STQ_FLAG_STATS_GRAD) ? 2 : 0);
-  const bool want_stats = stats != 0;
-  const bool fp32_grads = hp->grad_dtype == 0;
-  // Three workgroups per CU, with wide states two (three there: within 1 % from 0.5 to 300 M parameters, but 3 M, whose
-  // units then all fit at once, 14.1 us instead of 14.9).
-  const uint32_t cap_cu = mode == 2 ? 2 : 8;
-  const uint32_t per_cu = ctx->groups_per_cu < cap_cu ? ctx->groups_per_cu : cap_cu;
+  const bool fp32_grads = hp->grad_dtype == 0, wide = mode == 2;
   const uint32_t wpg = kWavesPerGroup;
-  uint32_t max_groups = ctx->n_cu * per_cu;
-  // Tickets (see step_kernel) for large launches: 0.33 G parameters 849 us against 905 (fp32 gradients) and 732 against
-  // 762 (bf16), 0.2 G the same within 1 %, 0.13 G slower (358 against 355; 314 against 308).  With statistics from half
-  // of that size on (0.2 G 584 us against 599, 90 M 303 against 281).
-  const uint64_t min_tiles = want_stats ? ctx->ticket_min_tiles / 2 : ctx->ticket_min_tiles;
-  bool tickets = total >= min_tiles;
-#ifdef STQ_TUNING_ENV
-  if (std::getenv("STQ_NO_TICKETS")) tickets = false;
-  if (std::getenv("STQ_TICKETS")) tickets = true;
+  // Units (see step_kernel): half tiles, which two workgroups per CU take with 128 registers a wave.  Quarter tiles, with
+  // three workgroups per CU, in launches whose quarters all fit at once, where a wave with half the work is done sooner
+  // (1 M parameters 5.8 us, with halves 6.9; 3.0 M 9.0 and 10.3, 3.2 M 11.4 and 10.4).  With statistics only the smallest
+  // (0.5 M 25.4 and 25.6, 1.0 M 28.9 and 27.7, 3.0 M 41.6 and 34.7): what a unit leaves of them costs as much for a quarter.
+  const bool quarters = total * 4ull <= static_cast<uint64_t>(ctx->n_cu) * (stats ? 4 : 3 * wpg);
+  // Tickets drawn, in one order over the chip, or every workgroup's own (see step_kernel).  fp32 gradients: 9.0 M
+  // parameters 24.5 us drawn and 25.1 not, 16 M 39.2 and 41.1, 60 M 145 and 153; bf16: 12.5 M 28.0 and 27.4, 16 M 33.7
+  // and 35.0, 60 M 114 and 117; wide states: 12.5 M 47.8 and 48.1, 9.0 M 38.1 and 37.1.
+  const bool draws = (fp32_grads && !wide ? total : total * 2ull / 3) >= ctx->ticket_min_tiles;
+  // Workgroups per CU.  States of 16 and 32 bits beside fp32 gradients have twice the bytes of others per element: one
+  // workgroup has enough of them in flight, and keeps the window narrower (16- and 32-bit states, 90 M: 357 us, 389 with
+  // two; 8 and 16 bits 130 M: 386 and 402, but 30 M 94 and 86; with bf16 gradients 130 M 360 and 356).
+  uint32_t per_cu = quarters ? 3 : (wide && fp32_grads && draws && total >= 30000u ? 1 : 2);
+  uint32_t lg_parts = quarters ? 2 : 1;
+#ifdef STQ_TUNING_ENV  // measurement builds only: launch shape from the environment
+  if (const char* e = std::getenv("STQ_LG_PARTS")) { lg_parts = std::strtoul(e, nullptr, 10) == 2 ? 2 : 1; per_cu = lg_parts == 2 ? 3 : 2; }
+  if (const char* e = std::getenv("STQ_GROUPS_PER_CU")) per_cu = std::strtoul(e, nullptr, 10);
 #endif
-  a.sched = !tickets ? nullptr : (sched ? sched : ctx->d_sched);
-  // Units of scheduling (see step_kernel): quarter tiles in a launch that whole tiles would not fill (2.4 M parameters
-  // 8.0 us against 14.7, 12.6 M 33 against 40), and under stripes also in larger ones: the last round is shorter and the
-  // chip's window on each array a quarter as wide.  With bf16 gradients up to 25,000 tiles (30 M 73.5 us against 75.5,
-  // 45 M 107 against 108.5, but 60 M 143 against 141); with fp32 gradients or wide states up to the ticket schedule
-  // (fp32: 45 M 107 against 119, 90 M 234 against 252; 60 M of 16- and 32-bit states 266 against 295).
-  bool quarters = total < static_cast<uint64_t>(max_groups) * wpg || (!tickets && (fp32_grads || mode == 2 || total < 25000u));
-#ifdef STQ_TUNING_ENV
-  if (const char* e = std::getenv("STQ_QUARTER_BELOW")) quarters = total < std::strtoull(e, nullptr, 10);
-#endif
-  a.quarter_units = quarters ? (quarters_ok ? 1u : 2u) : 0u;
-  const uint64_t units = static_cast<uint64_t>(total) << (quarters ? 2 : 0);
-  const uint64_t need_groups = (units + wpg - 1) / wpg;
-  // The plain step is bound by the memory system once its waves have several units each, and fewer waves in flight keep
-  // the chip's accesses closer together: two workgroups per CU instead of three take 3404 us instead of 3497 on 1.56 G
-  // parameters (K = 128, bf16), 345 instead of 360 on 124 M.  A launch whose units all fit at once wants every wave
-  // (2.4 M parameters: 8.8 us with three, 10.0 with two), and the variants with statistics have arithmetic to hide
-  // (3525 us with three, 3620 with two).
-  if (!want_stats && need_groups > max_groups && per_cu > 2) max_groups = ctx->n_cu * 2;
+  a.sched = !draws ? nullptr : (sched ? sched : ctx->d_sched);
+  a.unit_rows = 8u >> lg_parts;
+  const uint64_t units = static_cast<uint64_t>(total) << lg_parts;
+  const uint64_t need_groups = (units + wpg - 1) / wpg, max_groups = static_cast<uint64_t>(ctx->n_cu) * per_cu;
   const uint32_t groups = static_cast<uint32_t>(need_groups < max_groups ? need_groups : max_groups);
-  // Order of the units under stripes (see step_kernel).  Quarters: the workgroups take eight at a time in turn.  Tiles:
-  // interleaved chunks, pairs of tiles once a wave has at least four (a wave then owns whole cache lines of the scale
-  // arrays: 345 us instead of 348 with single tiles on 124 M parameters, 360 with four at a time), four at a time from
-  // 24 on.  With statistics one range of units per workgroup, whose waves take them in turn: the fewer tensors a
-  // workgroup meets, the fewer of its sums go to the global slots.
-  const uint64_t n_waves = static_cast<uint64_t>(groups) * wpg;
-  const uint64_t per_wave = (units + n_waves - 1) / n_waves;
-  if (want_stats) a.chunk = static_cast<uint32_t>(per_wave * wpg);
-  else a.chunk = per_wave >= 24 ? 4 : (per_wave >= 4 ? 2 : 1);
-  if (ctx->chunk_override && !want_stats) a.chunk = ctx->chunk_override;
+  // Eight counters (where every one has as many workgroups: fewer CUs than the card has, or a small launch) as long as the
+  // draws of the start count, one in larger launches, where the classes would drift apart (9 M parameters 22.5 us with
+  // eight and 26.9 with one, 130 M 267.5 and 270.5, 300 M 616 and 613; 3.5 G 7.20 ms and 7.00).
+  a.lg_classes = total < 100000u && groups % (8u << kLgTicketClasses) == 0 ? kLgTicketClasses : 0;
+#ifdef STQ_TUNING_ENV
+  if (const char* e = std::getenv("STQ_CLASSES")) a.lg_classes = std::strtoul(e, nullptr, 10);
+#endif
   // How a wave finds the tensor of its next unit (see step_kernel).  A walk costs one scalar load after the other for each
-  // tensor it passes, a search one or two vector loads, which take as long as ten to twenty of them while the memory
-  // system is busy.  With at most 16 tensors to the next unit on average a wave walks (fp32 gradients, 300 tensors of
-  // 204,800 elements, ten to pass: 150 us, with a search 154); beyond, it searches a window of 64 entries first (1000 of
-  // 67,591, 31 to pass: 181 us, walking 237), from 40 on one of 4096 (4000 of 16,384: 190 us, with 64 first 210, walking
-  // 843; 4000 of 768: 26, walking 636).
-  const uint64_t tiles_on = (want_stats && !tickets ? wpg : n_waves * (tickets || quarters ? 1 : a.chunk)) >> (quarters ? 2 : 0);
-  const uint64_t passed = tiles_on * n / total;
-  a.look_ahead = passed <= 16 ? 0u : (passed <= 40 ? 64u : 4096u);
+  // tensor it passes, a search one or two vector loads, which take as long as some of them while the memory system is busy.
+  // With at most 8 tensors to the next unit on average a wave walks (148 tensors of 124 M elements, 5 to pass: 256 us, with
+  // a search 258); beyond, it searches a window of 64 entries first (600 of 131,072 elements, 32 to pass: 193 us, walking
+  // 222; 1000 of 67,591, 60 to pass: 170 and 318), from 64 on one of 4096 (4000 of 16,384, 256 to pass: 157 us, with 64
+  // first 164, walking 1089; 4000 of 768: 22, 35 and 449).
+  const uint64_t passed = (static_cast<uint64_t>(groups) * wpg >> lg_parts) * n / total;
+  a.look_ahead = passed <= 8 ? 0u : (passed < 64 ? 64u : 4096u);
+#ifdef STQ_TUNING_ENV
+  if (const char* e = std::getenv("STQ_LOOK")) a.look_ahead = std::strtoul(e, nullptr, 10);
+#endif
   return launch_step(a, hp->grad_dtype == 1, stats, mode, groups, stream) == 0 ? STQ_OK : STQ_EHIP;
 }
 
@@ -394,15 +371,13 @@ int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream
 }
 
 // Kernel variant for a set of descriptors: 0 in place, 1 widths change, 2 some state is (or becomes)
-// 16 or 32 bits wide; and whether every width keeps quarter tiles word-aligned.
-void classify(const TensorDesc* descs, uint32_t n, bool changes, int* mode, bool* quarters_ok) {
-  *mode = changes ? 1 : 0;
-  *quarters_ok = true;
+// 16 or 32 bits wide.
+int mode_of(const TensorDesc* descs, uint32_t n, bool changes) {
   for (uint32_t l = 0; l < n; ++l) {
     const TensorDesc& d = descs[l];
-    if (is_wide(d.bm) || is_wide(d.bv) || is_wide(d.bm_out) || is_wide(d.bv_out)) *mode = 2;
-    *quarters_ok = *quarters_ok && ((d.bm | d.bv | d.bm_out | d.bv_out) & 3u) == 0;
+    if (is_wide(d.bm) || is_wide(d.bv) || is_wide(d.bm_out) || is_wide(d.bv_out)) return 2;
   }
+  return changes ? 1 : 0;
 }
 
 // One launch of the step kernel.  new_plan/new_codes are null for the in-place step.
@@ -443,10 +418,8 @@ int step_impl(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const stq_bit
   int table = -1;
   if (int e = resident_table(ctx, descs, s, &table)) return e;
 
-  int mode;
-  bool quarters_ok;
-  classify(descs.data(), n, new_plan != nullptr, &mode, &quarters_ok);
-  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, quarters_ok, stream)) return e;
+  const int mode = mode_of(descs.data(), n, new_plan != nullptr);
+  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, stream)) return e;
   if ((hp->flags & (STQ_FLAG_STATS | STQ_FLAG_STATS_GRAD)) != 0)
     for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;
@@ -482,16 +455,14 @@ int stq_step_static(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const s
   if (int e = next_stage_slot(ctx, &k)) return e;
   uint32_t total = 0;
   if (int e = fill_descs(ctx, tensors, n, plan, hp->block, true, ctx->h_stage[k], &total)) return e;
-  int mode;
-  bool quarters_ok;
-  classify(ctx->h_stage[k], n, false, &mode, &quarters_ok);
+  const int mode = mode_of(ctx->h_stage[k], n, false);
   TensorDesc* table = static_cast<TensorDesc*>(ctx->static_scratch);
   uint32_t* sched = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ctx->static_scratch) + kStaticTableBytes);
   if (int e = upload_descs(ctx, k, nullptr, n, table, s)) return e;
   // the scheduling words must be zero when the kernel starts: a kernel leaves them so, but the array is shared
   // by every caller on this GPU and may hold what an aborted launch left
   if (launch_fill_zero(sched, kSchedWords, stream) != 0) return STQ_EHIP;
-  if (int e = launch_table(ctx, table, n, total, ctx->d_stats, hp, mode, quarters_ok, stream, sched)) return e;
+  if (int e = launch_table(ctx, table, n, total, ctx->d_stats, hp, mode, stream, sched)) return e;
   if ((hp->flags & (STQ_FLAG_STATS | STQ_FLAG_STATS_GRAD)) != 0)
     for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;

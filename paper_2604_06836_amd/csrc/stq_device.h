@@ -8,7 +8,9 @@ constexpr int kTile = 2048;         // elements per tile = 64 lanes x 32 codes
 constexpr int kWavesPerGroup = 8;   // 512-thread workgroups
 constexpr int kGradWaves = 8;       // waves of a workgroup of grad_stats_kernel
 constexpr int kStatSlots = 16;      // 8-byte accumulator slots per tensor
-constexpr uint32_t kSchedWords = 2;  // the ticket counter of a launch and the count of workgroups that have left
+constexpr uint32_t kLgTicketClasses = 3;  // the ticket counters of a launch, at most (see step_kernel)
+constexpr uint32_t kSchedStride = 64;   // words from one counter to the next: each has cache lines of its own
+constexpr uint32_t kSchedWords = kSchedStride << kLgTicketClasses;
 
 // Device-resident description of one tensor for the step kernel.
 struct TensorDesc {
@@ -44,14 +46,12 @@ struct StepArgs {
   float ibc1, ibc2;        // reciprocal bias corrections 1/(1-beta^t)
   float eps, lr, decay;    // decay = 1 - lr*weight_decay
   uint32_t lgK;            // log2 of the block size: 6, 7 or 8
-  uint32_t chunk;          // stripes of tiles: consecutive tiles a wave takes at a time; statistics: units of a workgroup
   uint32_t look_ahead;     // 0: a wave walks from tensor to tensor to that of its next unit; else it searches, this many
                            // entries of the table first
-  uint32_t quarter_units;  // not 0: a unit is a quarter tile (small launches); 2: and some width is not a multiple of
-                           // 4 bits, so that quarters share words
-  uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters and the count of
-                           // workgroups that have left; null: no tickets, every wave walks its own stripes
-                           // (see step_kernel)
+  uint32_t unit_rows;      // rows of a unit of scheduling: 2 (a quarter tile) or 4 (a half)
+  uint32_t lg_classes;     // log2 of the number of ticket counters
+  uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters; null: nothing is drawn (see
+                           // step_kernel)
 };
 
 struct ZeroArgs {

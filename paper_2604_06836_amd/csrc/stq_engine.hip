@@ -123,7 +123,6 @@ struct stq_engine {
   stq_ctx* ctx = nullptr;
   uint32_t n = 0, total_tiles = 0, block = 0;
   bool wide = false;      // some state may be 16 or 32 bits wide: the kernel variant that handles them
-  bool quarters_ok = true;  // every width the loop can take is a multiple of 4 bits
   bool alg1_order = false;  // decide from a pass over the gradients before the step, as Algorithm 1 is written
   bool stepped = false;     // a step has been enqueued
   uint32_t capacity_bits = 0;
@@ -180,18 +179,16 @@ int stq_engine_create(stq_ctx* ctx, stq_engine** out, const stq_tensor* tensors,
   std::vector<TensorDesc> descs;
   uint32_t total = 0;
   if (int err = build_descs(ctx, tensors, n, initial_plan, block, true, descs, &total)) return err;
-  bool wide = false, quarters_ok = true;
+  bool wide = false;
   for (uint32_t i = 0; i <= cfg->n_thr; ++i) {
     if (int err = check_bits_stored(cfg->bits[i])) return err;
     if (cfg->bits[i] > capacity_bits) return STQ_EINVAL;
     wide = wide || is_wide(cfg->bits[i]);
-    quarters_ok = quarters_ok && (cfg->bits[i] & 3u) == 0;
   }
   std::vector<uint32_t*> spare(2 * static_cast<size_t>(n));
   for (uint32_t l = 0; l < n; ++l) {
     if (initial_plan[l].m_bits > capacity_bits || initial_plan[l].v_bits > capacity_bits) return STQ_EINVAL;
     wide = wide || is_wide(initial_plan[l].m_bits) || is_wide(initial_plan[l].v_bits);
-    quarters_ok = quarters_ok && ((initial_plan[l].m_bits | initial_plan[l].v_bits) & 3u) == 0;
     // the second buffers: distinct from the first over the whole capacity
     const uintptr_t span = static_cast<uintptr_t>(descs[l].n_tiles) * 256 * capacity_bits;
     const void* first[2] = {tensors[l].m_codes, tensors[l].v_codes};
@@ -212,7 +209,6 @@ int stq_engine_create(stq_ctx* ctx, stq_engine** out, const stq_tensor* tensors,
   e->total_tiles = total;
   e->block = block;
   e->wide = wide;
-  e->quarters_ok = quarters_ok;
   e->capacity_bits = capacity_bits;
   e->h_desc = descs;
   e->h_spare = spare;
@@ -335,7 +331,7 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
       if (int err = plan(true)) return err;
     }
     const int mode = e->wide ? 2 : (due ? 1 : 0);
-    if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, e->quarters_ok, stream)) return err;
+    if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream)) return err;
     if (due) return plan(false);  // the states now are what the step wrote
     return STQ_OK;
   }
@@ -343,7 +339,7 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
   h.flags = due ? STQ_FLAG_STATS_GRAD : 0u;  // the decision reads the gradient's sums only
   // kernel variant: the widths in the table differ from the stored ones only in the step after a decision
   const int mode = e->wide ? 2 : (e->pending ? 1 : 0);
-  if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, e->quarters_ok, stream)) return err;
+  if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream)) return err;
   if (due || e->pending) {
     if (int err = plan(due)) return err;
     e->pending = due;

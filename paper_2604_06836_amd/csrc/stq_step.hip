@@ -6,17 +6,15 @@
 // Arithmetic contract: IEEE binary32, every operation rounded on its own (build with
 // -ffp-contract=off); division and square root are the correctly rounded ones.
 //
-// Work decomposition: one wavefront owns one 2048-element tile at a time and processes it as four
-// quarters of 2 rows: a quarter's working set fits the 80 registers of six waves per SIMD (69 to 73 in use) with
-// nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.  Small and medium
-// launches hand the quarters of a tile to four waves (see step_kernel).
+// Work decomposition: one wavefront works on one part of a 2048-element tile at a time, a half (4 rows) or, in small
+// launches, a quarter (2 rows).  A half's working set fits the 128 registers of four waves per SIMD (108 to 125 in use), a
+// quarter's the 80 of six, with nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.
 // In row i lane j holds the 4 elements 256*i + 4*j + e, so
 // every parameter and gradient access is a coalesced 16-byte (8-byte for bf16) per-lane access,
 // and a block of K = 64/128/256 consecutive elements is 16/32/64 neighbouring lanes of one row.
 // The lane's 32 codes of a state are exactly b 32-bit words; word p of all lanes is one contiguous
-// 256-byte row of the code buffer.  A quarter reads the words that hold its 8 codes and writes
-// the words it completes; the bits of a word shared with the next quarter travel in a register (or, where the next
-// quarter is another wave's, through LDS).
+// 256-byte row of the code buffer.  A part reads the words that hold its codes and writes the words, or the bytes of
+// words that it shares with its neighbours, that are its own: a part's codes start and end on a byte.
 //
 // Only the bit-stream unpack and pack are specialised per width (small switch arms); all
 // arithmetic is width-generic and takes the width through table offsets and constants.
@@ -24,6 +22,7 @@
 
 #include <cfloat>
 #include <cstdint>
+#include <utility>
 
 #include "stq_device.h"
 #include "stq_round.h"
@@ -36,14 +35,22 @@ namespace stq {
 namespace {
 
 constexpr int XS = 68;  // row stride (words) of the transpose scratch: keeps 16-byte alignment, shifts banks
-// per-wave LDS scratch: XR[4][XS] partial maxima (later the den or root table), old scales, new scales, reciprocals
-constexpr int kWaveScratch = 4 * XS + 3 * 64;
-constexpr int kLdsWords = kTabWords + kWavesPerGroup * kWaveScratch;  // + the statistics slices in that variant
-constexpr int kStatFlushUnits = 16;  // fp32 lane sums are widened to fp64 every this many units (tiles or quarter tiles)
-constexpr uint32_t kDenEntries = 128;  // capacity of the per-wave den table (8 bytes per entry, inside XR)
-static_assert(kDenEntries * 8 <= 4 * XS * 4, "the den table lies inside XR");
-static_assert(((512 / 64) << (kMaxBits - 3)) * 4 <= 4 * XS * 4, "and so do the roots of the widest code at the smallest block");
-
+// The part of a tile that a wave works on at a time: ROWS rows of 256 elements, 4*ROWS elements per lane.
+template <int ROWS>
+struct Part {
+  static constexpr int kLgRows = ROWS == 2 ? 1 : 2;
+  static constexpr int kElems = 4 * ROWS;          // per lane
+  static constexpr int kPairs = 2 * ROWS;          // (state, row) pairs; a pair's block scales belong to 64/kPairs lanes
+  static constexpr int kLgPairs = kLgRows + 1;
+  // per-wave LDS scratch: XR[kPairs][XS] partial maxima (later the den or root table), old scales, new scales, reciprocals
+  static constexpr int kTableWords = kPairs * XS;
+  static constexpr int kScratch = kTableWords + 3 * 64;
+  static constexpr uint32_t kDenEntries = 64u * ROWS;  // capacity of the per-wave den table (8 bytes per entry, inside XR)
+  static_assert(ROWS == 2 || ROWS == 4, "quarters and halves of a tile");
+  static_assert(kDenEntries * 2 <= kTableWords, "the den table lies inside XR");
+  static_assert((4 * ROWS) << (kMaxBits - 3) <= kTableWords, "and so do the roots of the widest code at the smallest block");
+};
+constexpr int kStatFlushRows = 8;  // fp32 lane sums are widened to fp64 every this many rows of a wave
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // value at byte offset `off` of an LDS float table
@@ -60,8 +67,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // ---------------------------------------------------------------- bit streams
-// Within a quarter, code n (0..7) of width B sits at bits [n*B, n*B+B) of the quarter's local stream
-// (at most 64 bits, words w[0], w[1]).
+// Within a part, code n of width B sits at bits [n*B, n*B+B) of the part's local stream.
 // Bits [SH, SH+B) of x in one instruction.  Written as the instruction itself: from the plain expression
 // the compiler makes a shift and a mask, and then cannot fold the table offset that follows into either.
 template <int SH, int B>
@@ -71,12 +77,12 @@ __device__ __forceinline__ uint32_t bit_field(uint32_t x) {
   return r;
 }
 
-template <int B, int N>
-__device__ __forceinline__ uint32_t extract(const uint32_t (&w)[3]) {
+template <int B, int N, int W>
+__device__ __forceinline__ uint32_t extract(const uint32_t (&w)[W]) {
   constexpr int off = N * B, p = off >> 5, sh = off & 31;
-  if (sh + B <= 32) return bit_field<sh, B>(w[p]);
+  if constexpr (sh + B <= 32) return bit_field<sh, B>(w[p]);
   // a code that straddles two words: align it first
-  return bit_field<0, B>(__builtin_amdgcn_alignbit(w[p + 1], w[p], static_cast<uint32_t>(sh)));
+  else return bit_field<0, B>(__builtin_amdgcn_alignbit(w[p + 1], w[p], static_cast<uint32_t>(sh)));
 }
 
 // Byte N of x, times 4; byte N of x masked: one instruction each (the byte is selected by the operand).
@@ -99,82 +105,123 @@ __device__ __forceinline__ uint32_t byte_and(uint32_t x, uint32_t mask) {
   return r;
 }
 
-// The 8 codes of a quarter, times 4: byte offsets into the width's value table.
-// lw holds the lane's words from the one that contains the quarter's first bit; s0 (0, 8, 16 or
-// 24) is the position of that bit in lw[0] (always 0 at widths 4 and 8).
-template <int B>
-__device__ __forceinline__ void unpack_offsets(const uint32_t* lw, uint32_t s0, uint32_t (&off)[8]) {
+template <int B, int W, int... N>
+__device__ __forceinline__ void extract_offsets(const uint32_t (&w)[W], uint32_t* off, std::integer_sequence<int, N...>) {
+  ((off[N] = extract<B, N>(w) << 2), ...);
+}
+
+// The codes of a part, times 4: byte offsets into the width's value table.
+// lw holds the lane's words from the one that contains the part's first bit; s0 is the position of that bit in lw[0]
+// (0, 8, 16 or 24 for a quarter, 0 or 16 for a half; always 0 where kWordAligned).
+template <int ROWS, int B>
+constexpr bool kWordAligned = (4 * ROWS * B) % 32 == 0;
+template <int ROWS, int B, int W>
+__device__ __forceinline__ void unpack_offsets(const uint32_t (&lw)[W], uint32_t s0, uint32_t (&off)[4 * ROWS]) {
   if constexpr (B == 8) {
     uint32_t two = 2u;
     asm("" : "+v"(two));
-    off[0] = byte_times4<0>(lw[0], two); off[1] = byte_times4<1>(lw[0], two);
-    off[2] = byte_times4<2>(lw[0], two); off[3] = byte_times4<3>(lw[0], two);
-    off[4] = byte_times4<0>(lw[1], two); off[5] = byte_times4<1>(lw[1], two);
-    off[6] = byte_times4<2>(lw[1], two); off[7] = byte_times4<3>(lw[1], two);
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      off[4 * k + 0] = byte_times4<0>(lw[k], two); off[4 * k + 1] = byte_times4<1>(lw[k], two);
+      off[4 * k + 2] = byte_times4<2>(lw[k], two); off[4 * k + 3] = byte_times4<3>(lw[k], two);
+    }
   } else if constexpr (B == 4) {
-    const uint32_t even = lw[0] << 2, odd = lw[0] >> 2;  // code 2k / 2k+1 at bits 2..5 of byte k
-    off[0] = byte_and<0>(even, 0x3Cu); off[1] = byte_and<0>(odd, 0x3Cu);
-    off[2] = byte_and<1>(even, 0x3Cu); off[3] = byte_and<1>(odd, 0x3Cu);
-    off[4] = byte_and<2>(even, 0x3Cu); off[5] = byte_and<2>(odd, 0x3Cu);
-    off[6] = byte_and<3>(even, 0x3Cu); off[7] = byte_and<3>(odd, 0x3Cu);
+#pragma unroll
+    for (int k = 0; k < ROWS / 2; ++k) {
+      const uint32_t even = lw[k] << 2, odd = lw[k] >> 2;  // code 2i / 2i+1 at bits 2..5 of byte i
+      off[8 * k + 0] = byte_and<0>(even, 0x3Cu); off[8 * k + 1] = byte_and<0>(odd, 0x3Cu);
+      off[8 * k + 2] = byte_and<1>(even, 0x3Cu); off[8 * k + 3] = byte_and<1>(odd, 0x3Cu);
+      off[8 * k + 4] = byte_and<2>(even, 0x3Cu); off[8 * k + 5] = byte_and<2>(odd, 0x3Cu);
+      off[8 * k + 6] = byte_and<3>(even, 0x3Cu); off[8 * k + 7] = byte_and<3>(odd, 0x3Cu);
+    }
   } else {
-    uint32_t w[3];
-    w[0] = __builtin_amdgcn_alignbit(lw[1], lw[0], s0);
-    w[1] = __builtin_amdgcn_alignbit(lw[2], lw[1], s0);
-    w[2] = 0u;
-    off[0] = extract<B, 0>(w) << 2;
-    off[1] = extract<B, 1>(w) << 2;
-    off[2] = extract<B, 2>(w) << 2;
-    off[3] = extract<B, 3>(w) << 2;
-    off[4] = extract<B, 4>(w) << 2;
-    off[5] = extract<B, 5>(w) << 2;
-    off[6] = extract<B, 6>(w) << 2;
-    off[7] = extract<B, 7>(w) << 2;
+    constexpr int kWords = (4 * ROWS * B + 31) / 32;
+    uint32_t w[kWords + 1];
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) w[k] = kWordAligned<ROWS, B> ? lw[k] : __builtin_amdgcn_alignbit(k + 1 < W ? lw[k + 1] : 0u, lw[k], s0);
+    w[kWords] = 0u;
+    extract_offsets<B>(w, off, std::make_integer_sequence<int, 4 * ROWS>{});
   }
 }
 
-// Pack the low B bits of the 8 codes of a quarter behind the s0 bits that `carry` holds of the current word,
-// store the words this completes (at C, word stride 64) and keep the rest in `carry`.  Each code enters its
-// word from the top with one v_alignbit, which needs no masking of what lies above the code; MINUS1: the
-// codes given are all one too large (and at least 1), which one subtraction per word of whole codes undoes.
-// HOLD: another wave has the quarter before this one, so the first word, which the two share when s0 > 0, is left in
-// `held` instead of being stored.  (A quarter that starts inside a word always completes it, and what it leaves in
-// `carry` is then its own bits only: 8B >= 16 and s0 + 8B is 32 for the widths below 4 whose quarters are shorter.)
-template <int B, bool MINUS1, bool HOLD>
-__device__ __forceinline__ void pack_store(const uint32_t (&code)[8], STQ_GLOBAL uint32_t* C, uint32_t s0,
-                                           uint32_t& carry, uint32_t& held, uint32_t lane) {
-  constexpr int kPer = B <= 4 ? 8 : 4;                       // codes per packed word, kPer * B bits of it
-  constexpr uint32_t kOnes = (B == 2 ? 0x5555u : B == 3 ? 0x249249u : B == 4 ? 0x11111111u : B == 5 ? 0x8421u
-                              : B == 6 ? 0x41041u : B == 7 ? 0x204081u : 0x1010101u);
-  uint32_t w[8 / kPer];
+// Bytes [FIRST, END) of x to the same bytes of the word at p.
+template <int FIRST, int END>
+__device__ __forceinline__ void store_bytes(STQ_GLOBAL uint32_t* p, uint32_t x) {
+  STQ_GLOBAL uint8_t* b = reinterpret_cast<STQ_GLOBAL uint8_t*>(p);
+  STQ_GLOBAL uint16_t* h = reinterpret_cast<STQ_GLOBAL uint16_t*>(p);
+  if constexpr (FIRST == 0 && END == 4) *p = x;
+  else if constexpr (FIRST == 0 && END >= 2) h[0] = static_cast<uint16_t>(x);
+  else if constexpr (FIRST <= 2 && END == 4) h[1] = static_cast<uint16_t>(x >> 16);
+  if constexpr (FIRST == 0 && END == 1) b[0] = static_cast<uint8_t>(x);
+  if constexpr (FIRST == 1) b[1] = static_cast<uint8_t>(x >> 8);
+  if constexpr (FIRST == 0 && END == 3) b[2] = static_cast<uint8_t>(x >> 16);
+  if constexpr (FIRST == 3) b[3] = static_cast<uint8_t>(x >> 24);
+  static_assert((FIRST == 0 && END >= 1) || (FIRST >= 1 && END == 4), "a part starts or ends with its word");
+}
+
+// Pack the low B bits of the codes of a part and store them from bit s0 of the word at C on (word stride 64).
+// Each code enters its word from the top with one v_alignbit, which needs no masking of what lies above the code; MINUS1:
+// the codes given are all one too large (and at least 1), which one subtraction per word undoes (and one per code that
+// straddles two words).
+// Other waves have the parts before and after this one: of the words that it shares with them it writes its own bytes (a
+// part starts and ends on a byte; their waves read these words as a whole, but use no byte that is not theirs).
+template <int ROWS, int B, bool MINUS1>
+__device__ __forceinline__ void pack_store(const uint32_t (&code)[4 * ROWS], STQ_GLOBAL uint32_t* C, uint32_t s0, uint32_t lane) {
+  constexpr int N = 4 * ROWS, kBits = N * B, kWhole = kBits / 32, kWords = (kBits + 31) / 32;
+  uint32_t w[kWords], ones[kWords];  // the part's bits, and a 1 for each of its codes that lies in one word
 #pragma unroll
-  for (int k = 0; k < 8 / kPer; ++k) {
-    uint32_t x = code[k * kPer] << (32 - B);
+  for (int k = 0; k < kWords; ++k) ones[k] = 0u;
+  {
+    uint32_t x = 0u;
 #pragma unroll
-    for (int n = 1; n < kPer; ++n) x = __builtin_amdgcn_alignbit(code[k * kPer + n], x, B);
-    if (kPer * B < 32) x >>= 32 - kPer * B;
-    w[k] = MINUS1 ? x - kOnes : x;
+    for (int n = 0; n < N; ++n) {
+      const int p = (n * B) >> 5, at = (n * B) & 31, in_word = 32 - at;  // bits left in word p
+      if (B <= in_word) {
+        ones[p] |= 1u << at;
+        x = at == 0 ? code[n] << (32 - B) : __builtin_amdgcn_alignbit(code[n], x, B);
+        if (B == in_word) w[p] = x;
+      } else {
+        const uint32_t c = MINUS1 ? code[n] - 1u : code[n];
+        w[p] = __builtin_amdgcn_alignbit(c, x, in_word);
+        x = c << (32 - B);  // (its lowest bits, which are in w[p], leave the word at the bottom again)
+      }
+    }
+    if (kBits % 32 != 0) w[kWords - 1] = x >> (32 - kBits % 32);
   }
-  // the quarter's 8B bits as a pair of words
-  uint32_t lo, hi;
-  if constexpr (B <= 4) { lo = w[0]; hi = 0u; }
-  else if constexpr (B == 8) { lo = w[0]; hi = w[1]; }
-  else { lo = (w[1] << (4 * B)) | w[0]; hi = w[1] >> (32 - 4 * B); }
-  if (B == 4 || B == 8 || s0 == 0) {  // (a quarter of 4- or 8-bit codes always starts on a word)
-    if (B >= 4) C[lane] = lo;
-    if (B == 8) C[64u + lane] = hi;
-    carry = B < 4 ? lo : hi;  // (not used at widths 4 and 8)
+  if (MINUS1) {
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) w[k] -= ones[k];
+  }
+  C += lane;
+  if (kWordAligned<ROWS, B> || s0 == 0) {
+#pragma unroll
+    for (int k = 0; k < kWhole; ++k) C[64u * k] = w[k];
+    if constexpr (kWhole < kWords) store_bytes<0, kBits % 32 / 8>(C + 64 * kWhole, w[kWhole]);
     return;
   }
-  const uint32_t m0 = HOLD ? lo << s0 : (lo << s0) | carry;
-  const uint32_t m1 = __builtin_amdgcn_alignbit(hi, lo, 32u - s0);
-  const uint32_t done = (s0 + 8u * B) >> 5;  // complete words: 0, 1 or 2
-  if (!HOLD && done == 0) { carry = m0; return; }
-  if (HOLD) held = m0; else C[lane] = m0;
-  carry = m1;
-  if (done == 2) {
-    C[64u + lane] = m1;
-    carry = hi >> (32u - s0);
+  if constexpr (!kWordAligned<ROWS, B>) {
+    const uint32_t m0 = w[0] << s0;
+    if constexpr (ROWS == 4) {  // the second half of a tile, from the middle of a word to the end of one
+      store_bytes<2, 4>(C, m0);
+#pragma unroll
+      for (int k = 1; k < kWords; ++k) C[64u * k] = __builtin_amdgcn_alignbit(w[k], w[k - 1], 16u);
+    } else {  // a quarter in the middle or at the end of a tile: of three words at most
+      const uint32_t hi = kWords == 2 ? w[kWords - 1] : 0u;
+      const uint32_t m1 = __builtin_amdgcn_alignbit(hi, w[0], 32u - s0), m2 = hi >> (32u - s0);
+      const uint32_t end = s0 + kBits, done = end >> 5;  // words that end within the part: 1 or 2
+      if (s0 == 8) store_bytes<1, 4>(C, m0);
+      else if (s0 == 16) store_bytes<2, 4>(C, m0);
+      else store_bytes<3, 4>(C, m0);
+      if (done == 2) C[64] = m1;
+      const uint32_t rest = done == 2 ? m2 : m1;
+      STQ_GLOBAL uint32_t* last = C + 64u * done;
+      switch (end & 31u) {
+        case 8: store_bytes<0, 1>(last, rest); break;
+        case 16: store_bytes<0, 2>(last, rest); break;
+        case 24: store_bytes<0, 3>(last, rest); break;
+        default: break;
+      }
+    }
   }
 }
 
@@ -189,9 +236,10 @@ __device__ __forceinline__ void pack_store(const uint32_t (&code)[8], STQ_GLOBAL
     default: { constexpr int B = 8; CALL; } break; \
   }
 
-// element n (0..7) of this lane in quarter q is real (not pad) in a tile with n_valid elements
+// element n of this lane in part q is real (not pad) in a tile with n_valid elements
+template <int ROWS>
 __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n_valid) {
-  return (512u * q + static_cast<uint32_t>(256 * (n >> 2) + 4 * lane + (n & 3))) < n_valid;
+  return (256u * ROWS * q + static_cast<uint32_t>(256 * (n >> 2) + 4 * lane + (n & 3))) < n_valid;
 }
 
 // -------------------------------------------------------------------- statistics
@@ -200,7 +248,7 @@ __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n
 // Running statistics of one wave, kept in its LDS slice so that they cost no registers between the places
 // that add to them.  A contribution is first combined over a few neighbouring lanes with DPP steps, then one
 // lane of the group adds it to the group's word with an LDS atomic that returns nothing: the wave does not
-// wait for it, where a read-modify-write would put an LDS round trip into every quarter's dependency chain
+// wait for it, where a read-modify-write would put an LDS round trip into every part's dependency chain
 // (that latency, not the arithmetic, was most of the statistics' cost: it showed when fewer waves were
 // resident to hide it).  The atomics are issued from 8 or 16 lanes: from all 64 they are several times slower.
 //  * The gradient's three sums (all that the bit-width decision reads, Eq. 2, 3, 8) are taken in fp64 from the
@@ -211,8 +259,8 @@ __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n
 //  * S = 1 adds the moments' six fp32 sums (groups of eight lanes, 8-word slots) and two maxima (the owner lanes
 //    of the block scales hold them: lanes 0..31 the first moment's, 32..63 the second's, so a group of four is
 //    of one kind); the sums since the last widening are added to fp64 totals (lane k < 6 of the last slot)
-//    every kStatFlushUnits units.
-// S = 2: the gradient's statistics only; the slice stays small enough for three workgroups per CU.
+//    every kStatFlushRows rows.
+// S = 2: the gradient's statistics only.
 enum GradSlot { kLGSum = 0, kLGAbs, kLGSq };
 enum MomentSlot { kLMSum = 0, kLMSq, kLMErr, kLVSum, kLVSq, kLVErr };
 
@@ -231,7 +279,7 @@ struct LaneStats {
   static constexpr int kMaxOff = 3 * 2 * kG, kMomentOff = kMaxOff + kMaxWords, kWideOff = kMomentOff + 6 * 8;
   static constexpr int kWords = S == 0 ? 0 : (S == 1 ? kWideOff + 2 * 6 + 4 : kMomentOff);
   float* acc;      // this wave's slice, null in the plain kernel
-  uint32_t units;  // units since the last widening (uniform; stripes only)
+  uint32_t units;  // units since the last widening (uniform)
   __device__ __forceinline__ double* grad_sums() const { return reinterpret_cast<double*>(acc); }
   __device__ __forceinline__ uint32_t* maxima() const { return reinterpret_cast<uint32_t*>(acc) + kMaxOff; }
   __device__ __forceinline__ float* moment_sums() const { return acc + kMomentOff; }
@@ -309,7 +357,7 @@ __device__ __forceinline__ void widen_stats(LaneStats<S>& s, int lane) {
   s.clear_moment_sums(lane);
 }
 
-// the wave's statistics -> the tensor's global slots; the slice is cleared  (stripes)
+// the wave's statistics -> the tensor's global slots; the slice is cleared
 template <int S>
 __device__ __forceinline__ void flush_stats(LaneStats<S>& s, double* slot, int lane) {
   asm volatile("" : "+v"(lane));
@@ -328,74 +376,50 @@ __device__ __forceinline__ void flush_stats(LaneStats<S>& s, double* slot, int l
   s.clear_all(lane);
 }
 
-// ---- statistics under the ticket schedule ----
-// A wave changes tensor with almost every tile there, so it cannot keep sums per tensor.  Instead, after every
-// tile, the wave reduces its values over its lanes, clears its slice and leaves the values in its record of
-// the current ticket in LDS.  After the ticket's barrier wave 0 adds up the records of the workgroup's waves
-// and adds the result to the tensor's global slots: one set of global atomics per workgroup and ticket.  The
-// records belong to the tensor of the ticket's first unit; a wave whose tile lies in another tensor (a ticket
-// that straddles a tensor boundary) adds to that tensor's global slots itself and leaves an empty record.
+// ---- the workgroup's statistics ----
+// The waves of a workgroup keep their sums while the workgroup's units stay in one tensor (that of the first unit of each
+// ticket).  When it goes on to another, each wave reduces its values over its lanes into its record, and after a barrier
+// wave 0 adds up the records and adds the result to the tensor's global slots: one set of global atomics per workgroup
+// and tensor.  A wave whose unit lies in a later tensor than the first unit of its ticket adds to the global slots itself.
 template <int S>
-struct TicketRecord {
+struct StatRecord {
   double sum[S == 1 ? 9 : 3];           // in the order of the global slots from kGSum on
   uint32_t max_bits[S == 1 ? 4 : 2];    // max|g|, (max|m|, max v,) pad
 };
 
-// after a tile: the wave's values -> its record (or, for a straddling tile, the tensor's global slots)
+// the wave's statistics -> its record; the slice is cleared
 template <int S>
-__device__ __forceinline__ void ticket_stats_tile(LaneStats<S>& s, TicketRecord<S>* rec, bool in_wg_tensor, double* slot, int lane) {
-  asm volatile("" : "+v"(lane));
-  wave_lds_sync();
-  double g = s.reduced_grad(lane);
-  double mo = S == 1 ? s.reduced_moment(lane) : 0.0;
-  uint32_t mx = s.reduced_max(lane);
-  s.clear_grad(lane);
-  s.clear_moment_sums(lane);
-  int kg, km, kx;
-  const bool lg = LaneStats<S>::grad_lead(lane, kg), lm = LaneStats<S>::moment_lead(lane, km), lx = LaneStats<S>::max_lead(lane, kx);
-  if (!in_wg_tensor) {
-    if (lg) atomicAdd(&slot[kGSum + kg], g);
-    if (lm) atomicAdd(&slot[kMSum + km], mo);
-    if (lx) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]) + kx, mx);
-    g = 0.0;
-    mo = 0.0;
-    mx = 0u;
-  }
-  if (lg) rec->sum[kg] = g;
-  if (lm) rec->sum[3 + km] = mo;
-  if (lx) rec->max_bits[kx] = mx;
-}
-
-// stripes, at the end: the wave's statistics -> its record, or an empty record
-template <int S>
-__device__ __forceinline__ void record_stats(LaneStats<S>& s, TicketRecord<S>* rec, bool full, int lane) {
+__device__ __forceinline__ void record_stats(LaneStats<S>& s, StatRecord<S>* rec, int lane) {
   asm volatile("" : "+v"(lane));
   if (S == 1) widen_stats(s, lane);
   wave_lds_sync();
-  const double g = full ? s.reduced_grad(lane) : 0.0;
-  const uint32_t mx = full ? s.reduced_max(lane) : 0u;
+  const double g = s.reduced_grad(lane);
+  const uint32_t mx = s.reduced_max(lane);
   int k;
   if (LaneStats<S>::grad_lead(lane, k)) rec->sum[k] = g;
-  if (S == 1 && lane < 6) rec->sum[3 + lane] = full ? s.wide(lane) : 0.0;
+  if (S == 1 && lane < 6) rec->sum[3 + lane] = s.wide(lane);
   if (LaneStats<S>::max_lead(lane, k)) rec->max_bits[k] = mx;
+  s.clear_all(lane);
 }
 
-// wave 0, after the ticket's (or the last) barrier: the records of the workgroup's waves -> the tensor's global slots
+// wave 0, after a barrier: the records of the workgroup's waves -> the tensor's global slots
 template <int S>
-__device__ __forceinline__ void ticket_stats_flush(const TicketRecord<S>* recs, double* slot, int lane) {
-  static_assert(kWavesPerGroup == 8, "lane 8k + w takes value k of wave w's record");
+__device__ __forceinline__ void flush_records(const StatRecord<S>* recs, double* slot, int lane) {
+  static_assert(kWavesPerGroup == 4 || kWavesPerGroup == 8, "lane k * waves + w takes value k of wave w's record");
   asm volatile("" : "+v"(lane));
-  constexpr int kSums = S == 1 ? 9 : 3, kMaxima = S == 1 ? 3 : 1;
-  const TicketRecord<S>& r = recs[lane & 7];
-  const int k = lane >> 3;
-  const double x = octet_sum(k < kSums ? r.sum[k] : 0.0);  // sums 0..7
-  if ((lane & 7) == 0 && k < kSums) atomicAdd(&slot[kGSum + k], x);
-  if (S == 1) {
+  constexpr int kSums = S == 1 ? 9 : 3, kMaxima = S == 1 ? 3 : 1, kAtOnce = 64 / kWavesPerGroup;
+  constexpr bool kOctets = kWavesPerGroup == 8;
+  const StatRecord<S>& r = recs[lane & (kWavesPerGroup - 1)];
+  const int k = lane / kWavesPerGroup;
+  const bool lead = (lane & (kWavesPerGroup - 1)) == 0;
+  const double mine = k < kSums ? r.sum[k] : 0.0, x = kOctets ? octet_sum(mine) : quad_sum(mine);
+  if (lead && k < kSums) atomicAdd(&slot[kGSum + k], x);
+  if (kSums > kAtOnce) {
     const double y = octet_sum(lane < 8 ? r.sum[kSums - 1] : 0.0);  // the ninth
     if (lane == 0) atomicAdd(&slot[kGSum + 8], y);
   }
-  const uint32_t mx = octet_max(k < kMaxima ? r.max_bits[k] : 0u);
-  if ((lane & 7) == 0 && k < kMaxima) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]) + k, mx);
+  const uint32_t top = k < kMaxima ? r.max_bits[k] : 0u, mx = kOctets ? octet_max(top) : quad_max(top);
+  if (lead && k < kMaxima) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]) + k, mx);
 }
 
 // Whether every number added is +0 or has its magnitude between two given ones (as bit patterns).  -0 does not pass: the
@@ -428,18 +452,19 @@ __device__ __forceinline__ float updated_param(float theta, float ratio, const U
 // Codes of the second moment: the number of thresholds at or below rho = v/blockmax, as one subtraction and one shift
 // of rho's bit pattern (see stq_tables.h).  The subtrahend is the same for every mantissa at widths up to 4; wider
 // codes look it up by the top five mantissa bits (32 words: a wave's reads never meet in a bank).
-template <bool TAIL>
-__device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)[8], const float (&inv)[2], uint32_t b,
+template <int ROWS, bool TAIL>
+__device__ __forceinline__ void quantize_v(const float (&v)[4 * ROWS], uint32_t (&code)[4 * ROWS], const float (&inv)[ROWS], uint32_t b,
                                            const uint32_t* vq, uint32_t q, int lane, uint32_t n_valid) {
+  constexpr int N = 4 * ROWS;
   const uint32_t sh = 27u - b;
   if (b <= 4) {
     const uint32_t D = b == 4 ? kVqConst4 : (b == 3 ? kVqConst3 : kVqConst2);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) code[n] = __builtin_elementwise_sub_sat(f2u(v[n] * inv[n >> 2]), D) >> sh;
+    for (int n = 0; n < N; ++n) code[n] = __builtin_elementwise_sub_sat(f2u(v[n] * inv[n >> 2]), D) >> sh;
   } else {
     const char* D = reinterpret_cast<const char*>(vq + (b - kMinBits) * kVqBuckets);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const uint32_t bits = f2u(v[n] * inv[n >> 2]);
       const uint32_t d = *reinterpret_cast<const uint32_t*>(D + ((bits >> (kVqShift - 2)) & (4u * (kVqBuckets - 1))));
       code[n] = __builtin_elementwise_sub_sat(bits, d) >> sh;
@@ -447,8 +472,8 @@ __device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)
   }
   if (TAIL) {
 #pragma unroll
-    for (int n = 0; n < 8; ++n)
-      if (!is_valid(n, q, lane, n_valid)) code[n] = 0u;
+    for (int n = 0; n < N; ++n)
+      if (!is_valid<ROWS>(n, q, lane, n_valid)) code[n] = 0u;
   }
 }
 
@@ -467,13 +492,13 @@ __device__ __forceinline__ void quantize_v(const float (&v)[8], uint32_t (&code)
 // system either way; launches that stay in the caches are not: 2.4 M parameters 8.7 us instead of 9.4.  A den table of
 // 256 entries, for levels that serve two elements, changed nothing: 7.51 ms against 7.43.)
 enum UpdateKind { kDenTable, kRoots, kDirect };
-template <int KIND, bool FAST>
-__device__ __forceinline__ void update_params(const float (&mq)[8], const uint32_t (&code)[8], float (&theta)[8], const uint32_t* TAB,
-                                              const uint32_t (&row)[2], uint32_t b, const float (&sn)[2], const float* Lreg,
-                                              const UpdateArgs& u) {
+template <int KIND, bool FAST, int ROWS>
+__device__ __forceinline__ void update_params(const float (&mq)[4 * ROWS], const uint32_t (&code)[4 * ROWS], float (&theta)[4 * ROWS],
+                                              const uint32_t* TAB, const uint32_t (&row)[ROWS], uint32_t b, const float (&sn)[ROWS],
+                                              const float* Lreg, const UpdateArgs& u) {
   const uint32_t below = b > 3 ? (1u << (b - 3)) - 1u : 0u;  // P - 1 (kRoots)
 #pragma unroll
-  for (int n = 0; n < 8; ++n) {
+  for (int n = 0; n < 4 * ROWS; ++n) {
     const int i = n >> 2;
     const float mt = mq[n] * u.ibc1;
     float den, rden = 0.0f;
@@ -492,10 +517,11 @@ __device__ __forceinline__ void update_params(const float (&mq)[8], const uint32
   }
 }
 
-// ------------------------------------------------------------------ one quarter tile
-// Lane L = (value vL = L>>4, lane group qL = L&15) owns one (state, row) pair's block scale:
-// state = vL>>1, row = 2q + (vL&1), block within the row = qL >> (lgK-4).  A block's owners are
-// 4, 8 or 16 neighbouring lanes of one 16-lane row, so their maxima combine by DPP lane swaps.
+// ------------------------------------------------------------------ one part of a tile
+// ROWS rows, a quarter (2) or a half (4) of the tile.  The 2*ROWS (state, row) pairs belong to 64/(2*ROWS) lanes each:
+// lane L owns a block scale of pair vL, state = vL / ROWS, row = ROWS*q + vL % ROWS, as the qL-th of the pair's lanes; it
+// stands for 2*ROWS lanes of the row, 8*ROWS elements.  A block's owners are K/(8*ROWS), i.e. 2 to 16, neighbouring lanes
+// of one 16-lane row, so their maxima combine by DPP lane swaps.
 // bfloat16 rounding (to nearest, ties to even) of a finite float, kept as a float
 __device__ __forceinline__ float bf16_rne(float x) {
   uint32_t u = f2u(x);
@@ -503,64 +529,64 @@ __device__ __forceinline__ float bf16_rne(float x) {
   return u2f(u & 0xFFFF0000u);
 }
 
-// The words a quarter shares with its neighbours, for both states: the bits it leaves of its last word (for the next
-// quarter) and, when another wave has the previous quarter, its part of its first word.
-struct SharedWords {
-  uint32_t carry_m, carry_v, held_m, held_v;
-};
-
 // MODE 0: widths stay as they are; 1: the launch changes widths (other destination buffers);
 // 2: as 1, and states may have the wide formats: 32 bits = the fp32 value, 16 bits = its bfloat16
 // rounding, stored in the same tile format with 32- or 16-bit codes and without scales.
-template <bool BF16, int STATS, bool TAIL, int MODE, bool HOLD>
-__device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t tile, uint32_t q, uint32_t n_valid,
-                                                const StepArgs& a, const uint32_t* lds, uint32_t* ws, int lane,
-                                                SharedWords& sw, LaneStats<STATS>& st) {
+template <bool BF16, int STATS, bool TAIL, int MODE, int ROWS>
+__device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile, uint32_t q, uint32_t n_valid,
+                                             const StepArgs& a, const uint32_t* lds, uint32_t* ws, int lane,
+                                             LaneStats<STATS>& st) {
   // Everything derived from the lane index and the block size is cheap to recompute.  Hide the two
   // from loop-invariant code motion, which would otherwise keep dozens of such values live across
   // the whole tile loop and spill them.
   asm volatile("" : "+v"(lane));
   uint32_t lgK = a.lgK;
-  asm volatile("" : "+s"(lgK));
+  asm volatile("" : "+s"(lgK), "+s"(q));
   constexpr bool XW = MODE >= 1, WIDE = MODE == 2;
+  typedef Part<ROWS> P_;
+  constexpr int N = P_::kElems;
   const uint32_t bm = d.bm, bv = d.bv;              // widths of the stored codes
   // widths this step writes: the same, unless the launch changes widths (XW)
   const uint32_t bmo = XW ? d.bm_out : bm, bvo = XW ? d.bv_out : bv;
-  const size_t e0 = static_cast<size_t>(tile) * kTile + 512u * q;
+  const size_t e0 = static_cast<size_t>(tile) * kTile + 256u * ROWS * q;
   STQ_GLOBAL float* P = as_global(d.param + e0);
-  // the quarter's first bit: word (q*b)>>2 of the lane's b words, bit 8*((q*b)&3)
-  const uint32_t s0m = 8u * ((q * bm) & 3u), s0v = 8u * ((q * bv) & 3u);
-  STQ_GLOBAL uint32_t* CM = as_global(d.m_codes + static_cast<size_t>(tile) * 64u * bm) + ((q * bm) >> 2) * 64;
-  STQ_GLOBAL uint32_t* CV = as_global(d.v_codes + static_cast<size_t>(tile) * 64u * bv) + ((q * bv) >> 2) * 64;
+  // the part's first bit: bit s0 of word first_word of the lane's b words
+  auto first_bit = [&](uint32_t b) { return (4u * ROWS * q * b) & 31u; };
+  auto first_word = [&](uint32_t b) { return ((4u * ROWS * q * b) >> 5) * 64u; };
+  const uint32_t s0m = first_bit(bm), s0v = first_bit(bv);
+  STQ_GLOBAL uint32_t* CM = as_global(d.m_codes + static_cast<size_t>(tile) * 64u * bm) + first_word(bm);
+  STQ_GLOBAL uint32_t* CV = as_global(d.v_codes + static_cast<size_t>(tile) * 64u * bv) + first_word(bv);
   // where the new codes go: the same buffers at the same widths, or other buffers at the new widths
-  const uint32_t s0mo = 8u * ((q * bmo) & 3u), s0vo = 8u * ((q * bvo) & 3u);
-  STQ_GLOBAL uint32_t* CMO = XW ? as_global(d.m_out + static_cast<size_t>(tile) * 64u * bmo) + ((q * bmo) >> 2) * 64 : CM;
-  STQ_GLOBAL uint32_t* CVO = XW ? as_global(d.v_out + static_cast<size_t>(tile) * 64u * bvo) + ((q * bvo) >> 2) * 64 : CV;
+  const uint32_t s0mo = first_bit(bmo), s0vo = first_bit(bvo);
+  STQ_GLOBAL uint32_t* CMO = XW ? as_global(d.m_out + static_cast<size_t>(tile) * 64u * bmo) + first_word(bmo) : CM;
+  STQ_GLOBAL uint32_t* CVO = XW ? as_global(d.v_out + static_cast<size_t>(tile) * 64u * bvo) + first_word(bvo) : CV;
   const size_t sbase = static_cast<size_t>(tile) << (11 - lgK);  // scales per tile = 2048/K
   // the lane index as a 6-bit unsigned offset: global addresses become uniform base + 32-bit offset
   const uint32_t ul = static_cast<uint32_t>(lane) & 63u;
-  const int vL = lane >> 4, qL = lane & 15;
-  const uint32_t sidx = ((2u * q + static_cast<uint32_t>(vL & 1)) << (8 - lgK)) + (static_cast<uint32_t>(qL) >> (lgK - 4));
-  STQ_GLOBAL float* SC = as_global((vL >> 1) ? d.v_scales : d.m_scales);
+  constexpr int kLgOwners = 6 - P_::kLgPairs, kLgSpan = P_::kLgPairs + 2;  // lanes of a pair; elements an owner stands for
+  const int vL = lane >> kLgOwners, qL = lane & ((1 << kLgOwners) - 1);
+  const uint32_t sidx = ((ROWS * q + static_cast<uint32_t>(vL & (ROWS - 1))) << (8 - lgK)) + (static_cast<uint32_t>(qL) >> (lgK - kLgSpan));
+  STQ_GLOBAL float* SC = as_global((vL >> P_::kLgRows) ? d.v_scales : d.m_scales);
 
   // ---- loads for the moment phase --------------------------------------------
   const float sc_old = SC[sbase + sidx];
-  constexpr int kMaxWords = WIDE ? 8 : 3;  // a quarter of a wide state is 4 or 8 whole words
+  // (a quarter of 7-bit codes may touch three words, a half four; a part of a wide state is N/2 or N whole words)
+  constexpr int kMaxWords = WIDE ? N : (ROWS == 2 ? 3 : 4);
   uint32_t lwm[kMaxWords], lwv[kMaxWords];
   {
-    const uint32_t nwm = (s0m + 8u * bm + 31u) >> 5, nwv = (s0v + 8u * bv + 31u) >> 5;  // 1..3 words (4, 8 wide)
+    const uint32_t nwm = (s0m + N * bm + 31u) >> 5, nwv = (s0v + N * bv + 31u) >> 5;
 #pragma unroll
     for (int k = 0; k < kMaxWords; ++k) lwm[k] = (static_cast<uint32_t>(k) < nwm) ? CM[k * 64u + ul] : 0u;
 #pragma unroll
     for (int k = 0; k < kMaxWords; ++k) lwv[k] = (static_cast<uint32_t>(k) < nwv) ? CV[k * 64u + ul] : 0u;
   }
-  float g[8];
+  float g[N];
   {
     STQ_GLOBAL const float* G32 = as_global(static_cast<const float*>(d.grad) + e0);
     STQ_GLOBAL const uint16_t* G16 = as_global(static_cast<const uint16_t*>(d.grad) + e0);
     if (!TAIL) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < ROWS; ++i) {
         if (BF16) {
           const u32x2 r = __builtin_nontemporal_load(&reinterpret_cast<STQ_GLOBAL const u32x2*>(G16 + 256 * i)[ul]);
           g[4 * i + 0] = u2f(r.x << 16); g[4 * i + 1] = u2f(r.x & 0xFFFF0000u);
@@ -572,9 +598,9 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       }
     } else {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) {
+      for (int n = 0; n < N; ++n) {
         float x = 0.0f;
-        if (is_valid(n, q, lane, n_valid)) {
+        if (is_valid<ROWS>(n, q, lane, n_valid)) {
           const uint32_t idx = 256u * (n >> 2) + 4u * ul + (n & 3);
           x = BF16 ? u2f(static_cast<uint32_t>(G16[idx]) << 16) : G32[idx];
         }
@@ -583,25 +609,34 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     }
   }
 
-  // old scales to every lane that needs them: lane j reads the 4 values of its lane group
+  // old scales to every lane that needs them: lane j reads the values of its lane group
   float* wsf = reinterpret_cast<float*>(ws);
-  float* XR = wsf;                // [4][XS]
-  float* SO = wsf + 4 * XS;       // [64] old scales at [lane group * 4 + value]
-  float* SN = SO + 64;            // [64] new scales
-  float* SI = SN + 64;            // [64] reciprocals of the new scales
-  SO[qL * 4 + vL] = sc_old;
+  float* XR = wsf;                          // [kPairs][XS]
+  float* SO = wsf + P_::kTableWords;        // [64] old scales at [lane group * kPairs + pair]
+  float* SN = SO + 64;                      // [64] new scales
+  float* SI = SN + 64;                      // [64] reciprocals of the new scales
+  SO[qL * P_::kPairs + vL] = sc_old;
   wave_lds_sync();
-  float som[2], sov[2];
-  {
-    const float4 a0 = *reinterpret_cast<const float4*>(SO + (lane >> 2) * 4);
-    som[0] = a0.x; som[1] = a0.y; sov[0] = a0.z; sov[1] = a0.w;
-  }
+  // the values of state `state` (0 first, 1 second moment) at the lane's blocks, from one of these arrays
+  auto of_rows = [&](const float* S, int state, float (&x)[ROWS]) {
+    const float* at = S + (lane >> P_::kLgPairs) * P_::kPairs + state * ROWS;
+    if (ROWS == 2) {
+      const float2 y = *reinterpret_cast<const float2*>(at);
+      x[0] = y.x; x[1] = y.y;
+    } else {
+      const float4 y = *reinterpret_cast<const float4*>(at);
+      x[0] = y.x; x[1] = y.y; x[ROWS - 2] = y.z; x[ROWS - 1] = y.w;
+    }
+  };
+  float som[ROWS], sov[ROWS];
+  of_rows(SO, 0, som);
+  of_rows(SO, 1, sov);
 
   if (STATS) {
     double sg_sum = 0.0, sg_abs = 0.0, sg_sq = 0.0;  // fp64 from the first addition (pads are zeros)
     float sg_max = 0.0f;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const double gd = static_cast<double>(g[n]);
       sg_sum += gd;
       sg_abs += __builtin_fabs(gd);
@@ -617,37 +652,37 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   // ---- moments: m_t = beta1*m_{t-1} + (1-beta1)*g ; v_t = beta2*v_{t-1} + (1-beta2)*g^2 ----
   const float* Rreg = reinterpret_cast<const float*>(lds) + kTabROff;  // value tables, see stq_tables.h
   const float* Lreg = reinterpret_cast<const float*>(lds) + kTabLOff;
-  float m[8], v[8];
+  float m[N], v[N];
   {
-    uint32_t off[8];
-    float old[8];  // the stored moments m_{t-1}, then v_{t-1}
+    uint32_t off[N];
+    float old[N];  // the stored moments m_{t-1}, then v_{t-1}
     if (WIDE && bm >= 16) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n)
+      for (int n = 0; n < N; ++n)
         old[n] = bm == 32 ? u2f(lwm[n]) : u2f((n & 1) ? (lwm[n >> 1] & 0xFFFF0000u) : (lwm[n >> 1] << 16));
     } else {
       const float* R = Rreg + (1u << bm);
-      STQ_SWITCH_BITS(bm, (unpack_offsets<B>(lwm, s0m, off)));
+      STQ_SWITCH_BITS(bm, (unpack_offsets<ROWS, B>(lwm, s0m, off)));
 #pragma unroll
-      for (int n = 0; n < 8; ++n) old[n] = som[n >> 2] * lds_at(R, off[n]);
+      for (int n = 0; n < N; ++n) old[n] = som[n >> 2] * lds_at(R, off[n]);
     }
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const float x = a.beta1 * old[n], y = a.omb1 * g[n];
       m[n] = x + y;
     }
     if (WIDE && bv >= 16) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n)
+      for (int n = 0; n < N; ++n)
         old[n] = bv == 32 ? u2f(lwv[n]) : u2f((n & 1) ? (lwv[n >> 1] & 0xFFFF0000u) : (lwv[n >> 1] << 16));
     } else {
       const float* L = Lreg + (1u << bv);
-      STQ_SWITCH_BITS(bv, (unpack_offsets<B>(lwv, s0v, off)));
+      STQ_SWITCH_BITS(bv, (unpack_offsets<ROWS, B>(lwv, s0v, off)));
 #pragma unroll
-      for (int n = 0; n < 8; ++n) old[n] = sov[n >> 2] * lds_at(L, off[n]);
+      for (int n = 0; n < N; ++n) old[n] = sov[n >> 2] * lds_at(L, off[n]);
     }
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const float gg = g[n] * g[n];
       const float x = a.beta2 * old[n], y = a.omb2 * gg;
       v[n] = x + y;
@@ -655,8 +690,8 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   }
   if (TAIL) {
 #pragma unroll
-    for (int n = 0; n < 8; ++n)
-      if (!is_valid(n, q, lane, n_valid)) { m[n] = 0.0f; v[n] = 0.0f; }
+    for (int n = 0; n < N; ++n)
+      if (!is_valid<ROWS>(n, q, lane, n_valid)) { m[n] = 0.0f; v[n] = 0.0f; }
   }
 
   if (STATS == 1) {
@@ -664,7 +699,7 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     // errors follow in the quantizer loops)
     float sm_sum = 0.0f, sm_sq = 0.0f, sv_sum = 0.0f, sv_sq = 0.0f;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       sm_sum += m[n];
       sm_sq = __builtin_fmaf(m[n], m[n], sm_sq);
       sv_sum += v[n];
@@ -680,37 +715,47 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   // Parameters and gradients are touched once per step: non-temporal accesses keep them from
   // displacing the code and scale lines in the caches (measured: both the load and the store of
   // the parameters must carry the hint; on the code and scale streams it loses).
-  float theta[8];
+  float theta[N];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     if (!TAIL) {
       const f32x4 t = __builtin_nontemporal_load(&reinterpret_cast<STQ_GLOBAL const f32x4*>(P + 256 * i)[ul]);
       theta[4 * i] = t.x; theta[4 * i + 1] = t.y; theta[4 * i + 2] = t.z; theta[4 * i + 3] = t.w;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        theta[4 * i + e] = is_valid(4 * i + e, q, lane, n_valid) ? P[256u * i + 4u * ul + e] : 0.0f;
+        theta[4 * i + e] = is_valid<ROWS>(4 * i + e, q, lane, n_valid) ? P[256u * i + 4u * ul + e] : 0.0f;
     }
   }
 
   // ---- block maxima: lane partials -> LDS transpose -> one owner lane per (state,row,block)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     const float pm = fmaxf(fmaxf(fabsf(m[4 * i]), fabsf(m[4 * i + 1])), fmaxf(fabsf(m[4 * i + 2]), fabsf(m[4 * i + 3])));
     const float pv = fmaxf(fmaxf(v[4 * i], v[4 * i + 1]), fmaxf(v[4 * i + 2], v[4 * i + 3]));
     XR[i * XS + lane] = pm;
-    XR[(2 + i) * XS + lane] = pv;
+    XR[(ROWS + i) * XS + lane] = pv;
   }
   wave_lds_sync();
   // the maxima are non-negative, so they order like their bit patterns: integer max, no NaN handling
   float r;
   {
-    const uint4 t0 = *reinterpret_cast<const uint4*>(XR + vL * XS + qL * 4);
-    uint32_t rb = max(max(t0.x, t0.y), max(t0.z, t0.w));
-    rb = max(rb, dpp_u32<kDppXor1>(rb));
-    rb = max(rb, dpp_u32<kDppXor2>(rb));
-    if (lgK >= 7) rb = max(rb, dpp_u32<kDppHalfMirror>(rb));
-    if (lgK == 8) rb = max(rb, dpp_u32<kDppMirror>(rb));
+    uint32_t rb = 0u;
+#pragma unroll
+    for (int k = 0; k < P_::kPairs; k += 4) {
+      const uint4 t0 = *reinterpret_cast<const uint4*>(XR + vL * XS + qL * P_::kPairs + k);
+      rb = max(max(max(rb, t0.x), max(t0.y, t0.z)), t0.w);
+    }
+    if (ROWS == 2) {
+      rb = max(rb, dpp_u32<kDppXor1>(rb));
+      rb = max(rb, dpp_u32<kDppXor2>(rb));
+      if (lgK >= 7) rb = max(rb, dpp_u32<kDppHalfMirror>(rb));
+      if (lgK == 8) rb = max(rb, dpp_u32<kDppMirror>(rb));
+    } else {
+      rb = max(rb, dpp_u32<kDppXor1>(rb));
+      if (lgK >= 7) rb = max(rb, dpp_u32<kDppXor2>(rb));
+      if (lgK == 8) rb = max(rb, dpp_u32<kDppHalfMirror>(rb));
+    }
     r = u2f(rb);
   }
   if (STATS == 1) {
@@ -724,44 +769,44 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   } else {
     sc_inv = (sc_new > 0.0f) ? 1.0f / sc_new : 0.0f;
   }
-  SN[qL * 4 + vL] = sc_new;
-  SI[qL * 4 + vL] = sc_inv;
+  SN[qL * P_::kPairs + vL] = sc_new;
+  SI[qL * P_::kPairs + vL] = sc_inv;
   {
     // a wide state has no scales: its owners store nothing
-    const bool has_scale = !WIDE || (vL < 2 ? bmo : bvo) < 16;
-    if (has_scale && (static_cast<uint32_t>(qL) & ((1u << (lgK - 4)) - 1u)) == 0u) SC[sbase + sidx] = sc_new;
+    const bool has_scale = !WIDE || (vL < ROWS ? bmo : bvo) < 16;
+    if (has_scale && (static_cast<uint32_t>(qL) & ((1u << (lgK - kLgSpan)) - 1u)) == 0u) SC[sbase + sidx] = sc_new;
   }
   wave_lds_sync();
 
   // ---- table of den = sqrt(vq*ibc2) + eps and 1/den, or of the roots (see update_params) ----
   // Levels P codes apart (P = 2^(b-3), 1 below b = 4) lie a whole number of octaves pairs apart, so their roots differ by
-  // a power of two: one root per (row, block, code mod P), roots = (512/K)*P.  When a level serves at least four
-  // elements, entries = (512/K) << bv_out <= 128, the lanes go on to den and its reciprocal; 64/roots lanes share the
+  // a power of two: one root per (row, block, code mod P), roots = (256*ROWS/K)*P.  When a level serves at least four
+  // elements, entries = (256*ROWS/K) << bv_out <= 64*ROWS, the lanes go on to den and its reciprocal; 64/roots lanes share the
   // multiples of a root.  The table takes the place of XR, whose last readers have finished.
   const UpdateArgs ua = {a.ibc1, a.ibc2, a.eps, a.lr, a.decay};
   const bool wide_m = WIDE && bmo >= 16, wide_v = WIDE && bvo >= 16;
   const uint32_t bq = wide_v ? 8u : bvo;
-  const bool use_table = !wide_v && ((512u >> lgK) << bq) <= kDenEntries;
-  const uint32_t lgP = bq > 3 ? bq - 3 : 0, lg_roots = 9u - lgK + lgP;
+  const bool use_table = !wide_v && ((256u * ROWS >> lgK) << bq) <= P_::kDenEntries;
+  const uint32_t lgP = bq > 3 ? bq - 3 : 0, lg_roots = 8u + P_::kLgRows - lgK + lgP;
   // The short forms need every operand in a range where no intermediate underflows or overflows.  The owner lanes
   // check their scales: m~ = (s_m*R)*ibc1 is 0 or at least s_m*ibc1/127, in [2^-85, 2^40] when s_m*ibc1 lies in
   // [2^-78, 2^40]; v~ = (s_v*L)*ibc2 is 0 or at least s_v*ibc2*2^-16, in [2^-96, 2^78] when s_v*ibc2 lies in
   // [2^-80, 2^78], and a root is then at most 2^39.
   int bad_m = 0, bad_v = 0;
-  if (vL < 2) {
+  if (vL < ROWS) {
     bad_m = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(sc_new * a.ibc1) - 0x18800000u <= 0x53800000u - 0x18800000u)) ^ 1;
   } else {
     bad_v = (static_cast<int>(sc_new == 0.0f) | static_cast<int>(f2u(sc_new * a.ibc2) - 0x17800000u <= 0x66800000u - 0x17800000u)) ^ 1;
   }
   // den = root + eps then lies in [2^-70, 2^40]
-  const bool eps_ok = a.eps >= 0x1p-70f && a.eps <= 0x1p39f;
+  const bool eps_ok = f2u(a.eps) - 0x1C800000u <= 0x53000000u - 0x1C800000u;  // (eps > 0)
   bool fast_root = eps_ok && !__any(bad_v);                // the roots (and den) by the short form
   bool fast_m = !__any(bad_m);                             // and, with it, the quotient
   if (__builtin_expect(fast_root && !wide_v, 1)) {
     for (uint32_t e = lane; e < (1u << lg_roots) || (use_table && e < 64u); e += 64) {
       const uint32_t root = e & ((1u << lg_roots) - 1u), i = root & ((1u << lgP) - 1u), rg = root >> lgP;
       const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
-      const float sv = SN[((blk << (lgK - 4)) << 2) + 2 + rw];
+      const float sv = SN[((blk << (lgK - kLgSpan)) << P_::kLgPairs) + ROWS + rw];
       const float vq = sv * lds_at(Lreg, (i << 2) | (4u << bq));
       const uint32_t s_bits = f2u(sqrt_rn_safe(vq * a.ibc2));
       if (use_table) {
@@ -779,10 +824,10 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     // A scale or eps out of the short forms' range (small gradients, an eps such as 1e-30): den by the IEEE routines, still
     // once per level; the quotients take the IEEE division.  (1.5 G parameters, K = 128, 5 bits, bf16 gradients: 3391 us,
     // with a root per element 3521, in range 3263.  Where a level serves fewer elements the root is taken per element.)
-    for (uint32_t e = lane; e < (512u >> lgK) << bq; e += 64) {
+    for (uint32_t e = lane; e < (256u * ROWS >> lgK) << bq; e += 64) {
       const uint32_t c = e & ((1u << bq) - 1u), rg = e >> bq;
       const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
-      const float vq = SN[((blk << (lgK - 4)) << 2) + 2 + rw] * lds_at(Lreg, (c << 2) | (4u << bq));
+      const float vq = SN[((blk << (lgK - kLgSpan)) << P_::kLgPairs) + ROWS + rw] * lds_at(Lreg, (c << 2) | (4u << bq));
       reinterpret_cast<float2*>(XR)[e] = make_float2(__builtin_sqrtf(vq * a.ibc2) + a.eps, 0.0f);
     }
     wave_lds_sync();
@@ -791,10 +836,10 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
   // ---- linear symmetric quantization of m; m is replaced by its quantized value ----
   if (wide_m) {
     float sm_err = 0.0f;
-    uint32_t kept[8];
+    uint32_t kept[N];
     SafeRange range;  // the elements are not multiples of a block scale: look at each
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const float mq = bmo == 32 ? m[n] : bf16_rne(m[n]);  // pads are 0 and stay 0
       range.add(mq * ua.ibc1);
       if (STATS == 1) {
@@ -808,18 +853,15 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     if (STATS == 1) st.add(kLMErr, lane, sm_err);
     if (bmo == 32) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) CMO[n * 64u + ul] = kept[n];
+      for (int n = 0; n < N; ++n) CMO[n * 64u + ul] = kept[n];
     } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) CMO[k * 64u + ul] = (kept[2 * k] >> 16) | (kept[2 * k + 1] & 0xFFFF0000u);
+      for (int k = 0; k < N / 2; ++k) CMO[k * 64u + ul] = (kept[2 * k] >> 16) | (kept[2 * k + 1] & 0xFFFF0000u);
     }
   } else {
-    float sn[2], inv[2];
-    {
-      const float4 a0 = *reinterpret_cast<const float4*>(SN + (lane >> 2) * 4);
-      const float4 b0 = *reinterpret_cast<const float4*>(SI + (lane >> 2) * 4);
-      sn[0] = a0.x; sn[1] = a0.y; inv[0] = b0.x; inv[1] = b0.y;
-    }
+    float sn[ROWS], inv[ROWS];
+    of_rows(SN, 0, sn);
+    of_rows(SI, 0, inv);
     const int qmax = (1 << (bmo - 1)) - 1;
     const float qmaxf = static_cast<float>(qmax);
     // Round half to even by adding 1.5*2^23, which leaves the integer q in the low mantissa bits (|t| <= 127.5); with
@@ -829,34 +871,34 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     const float magic = 12582912.0f + static_cast<float>(qmax + 1);
     const uint32_t magic_code = 0x4B400001u;  // bits of (magic + q), less the code
     const uint32_t r_base = (4u << bmo) - 4u * magic_code;
-    uint32_t code[8];  // low bits: code + 1
-    float sm_err = 0.0f;  // this quarter's part of the lane's sum of squared quantization errors
+    uint32_t code[N];  // low bits: code + 1
+    float sm_err = 0.0f;  // this part's share of the lane's sum of squared quantization errors
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const int i = n >> 2;
       const float t = (m[n] * inv[i]) * qmaxf;
       uint32_t u = f2u(t + magic);
-      if (TAIL && !is_valid(n, q, lane, n_valid)) u = magic_code;
+      if (TAIL && !is_valid<ROWS>(n, q, lane, n_valid)) u = magic_code;
       code[n] = u;
       float mq = sn[i] * lds_at(Rreg, (u << 2) + r_base);
       if (STATS == 1) {
-        if (TAIL && !is_valid(n, q, lane, n_valid)) mq = 0.0f;
+        if (TAIL && !is_valid<ROWS>(n, q, lane, n_valid)) mq = 0.0f;
         const float dd = m[n] - mq;
         sm_err = __builtin_fmaf(dd, dd, sm_err);
       }
       m[n] = mq;
     }
     if (STATS == 1) st.add(kLMErr, lane, sm_err);
-    STQ_SWITCH_BITS(bmo, (pack_store<B, true, HOLD>(code, CMO, s0mo, sw.carry_m, sw.held_m, ul)));
+    STQ_SWITCH_BITS(bmo, (pack_store<ROWS, B, true>(code, CMO, s0mo, ul)));
   }
 
   // ---- logarithmic quantization of v and the parameter update ----
   if (wide_v) {
     float sv_err = 0.0f;
-    uint32_t kept[8];
+    uint32_t kept[N];
     SafeRange range;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < N; ++n) {
       const float vq = bvo == 32 ? v[n] : bf16_rne(v[n]);
       if (STATS == 1) {
         const float dd = v[n] - vq;
@@ -866,17 +908,17 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
       v[n] = vq * ua.ibc2;
       range.add(v[n]);
     }
-    // The short forms where every element of the wave's quarter allows them (124 M parameters at widths drawn from
+    // The short forms where every element of the wave's part allows them (124 M parameters at widths drawn from
     // {4, 8, 16, 32}: 468 us instead of 472 with the IEEE routines)
     if (eps_ok && __all(range.within(0x0F800000u, 0x66800000u)) && fast_m) {  // 2^-96, 2^78
 #pragma unroll
-      for (int n = 0; n < 8; ++n) {
+      for (int n = 0; n < N; ++n) {
         const float den = sqrt_rn_safe(v[n]) + ua.eps;
         theta[n] = updated_param(theta[n], div_rn_safe(m[n] * ua.ibc1, den, rcp_rn_safe(den)), ua);
       }
     } else {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) {
+      for (int n = 0; n < N; ++n) {
         const float den = __builtin_sqrtf(v[n]) + ua.eps;
         theta[n] = updated_param(theta[n], (m[n] * ua.ibc1) / den, ua);
       }
@@ -884,98 +926,91 @@ __device__ __forceinline__ void process_quarter(const TensorDesc& d, uint32_t ti
     if (STATS == 1) st.add(kLVErr, lane, sv_err);
     if (bvo == 32) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) CVO[n * 64u + ul] = kept[n];
+      for (int n = 0; n < N; ++n) CVO[n * 64u + ul] = kept[n];
     } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) CVO[k * 64u + ul] = (kept[2 * k] >> 16) | (kept[2 * k + 1] & 0xFFFF0000u);
+      for (int k = 0; k < N / 2; ++k) CVO[k * 64u + ul] = (kept[2 * k] >> 16) | (kept[2 * k + 1] & 0xFFFF0000u);
     }
   } else {
-    float sn[2], inv[2];
-    {
-      const float4 a1 = *reinterpret_cast<const float4*>(SN + (lane >> 2) * 4);
-      const float4 b1 = *reinterpret_cast<const float4*>(SI + (lane >> 2) * 4);
-      sn[0] = a1.z; sn[1] = a1.w; inv[0] = b1.z; inv[1] = b1.w;
-    }
-    uint32_t code[8];
-    quantize_v<TAIL>(v, code, inv, bvo, lds + kTabVqOff, q, lane, n_valid);
+    float sn[ROWS], inv[ROWS];
+    of_rows(SN, 1, sn);
+    of_rows(SI, 1, inv);
+    uint32_t code[N];
+    quantize_v<ROWS, TAIL>(v, code, inv, bvo, lds + kTabVqOff, q, lane, n_valid);
     if (STATS == 1) {
-      float sv_err = 0.0f;  // this quarter's part of the lane's sum of squared quantization errors
+      float sv_err = 0.0f;  // this part's share of the lane's sum of squared quantization errors
 #pragma unroll
-      for (int n = 0; n < 8; ++n) {
+      for (int n = 0; n < N; ++n) {
         float vq = sn[n >> 2] * lds_at(Lreg, (code[n] << 2) | (4u << bvo));
-        if (TAIL && !is_valid(n, q, lane, n_valid)) vq = 0.0f;
+        if (TAIL && !is_valid<ROWS>(n, q, lane, n_valid)) vq = 0.0f;
         const float dd = v[n] - vq;
         sv_err = __builtin_fmaf(dd, dd, sv_err);
       }
       st.add(kLVErr, lane, sv_err);
     }
-    STQ_SWITCH_BITS(bvo, (pack_store<B, false, HOLD>(code, CVO, s0vo, sw.carry_v, sw.held_v, ul)));
+    STQ_SWITCH_BITS(bvo, (pack_store<ROWS, B, false>(code, CVO, s0vo, ul)));
     // first table entry of the lane's two blocks: ((row*G + block) << bv_out, or << lgP for the roots), G = 256/K blocks per row
     const uint32_t lg_row = use_table ? bvo : lgP;
-    uint32_t row[2];
+    uint32_t row[ROWS];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < ROWS; ++i)
       row[i] = ((static_cast<uint32_t>(i) << (8 - lgK)) + (static_cast<uint32_t>(lane) >> (lgK - 2))) << lg_row;
     const uint32_t* TAB = ws;
-    if (__builtin_expect(!fast_root && !use_table, 0)) update_params<kDirect, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else if (use_table && fast_root && fast_m) update_params<kDenTable, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else if (use_table) update_params<kDenTable, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else if (fast_m) update_params<kRoots, true>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
-    else update_params<kRoots, false>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    if (__builtin_expect(!fast_root && !use_table, 0)) update_params<kDirect, false, ROWS>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (use_table && fast_root && fast_m) update_params<kDenTable, true, ROWS>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (use_table) update_params<kDenTable, false, ROWS>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else if (fast_m) update_params<kRoots, true, ROWS>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
+    else update_params<kRoots, false, ROWS>(m, code, theta, TAB, row, bvo, sn, Lreg, ua);
   }
 
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     if (!TAIL) {
       __builtin_nontemporal_store(f32x4{theta[4 * i], theta[4 * i + 1], theta[4 * i + 2], theta[4 * i + 3]},
                                   &reinterpret_cast<STQ_GLOBAL f32x4*>(P + 256 * i)[ul]);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (is_valid(4 * i + e, q, lane, n_valid)) P[256u * i + 4u * ul + e] = theta[4 * i + e];
+        if (is_valid<ROWS>(4 * i + e, q, lane, n_valid)) P[256u * i + 4u * ul + e] = theta[4 * i + e];
     }
   }
 }
 
 // -------------------------------------------------------------- step kernel
-// Order of the work.  A unit is a tile (or a quarter tile, see below).  Two schedules:
-//  * tickets (a.sched set): the workgroups of the launch draw tickets from one counter in device memory.
-//    Ticket k stands for the kWaves consecutive units k*kWaves .. k*kWaves + kWaves-1, one per wave; the
-//    waves of a workgroup meet at a barrier before they go on to the next ticket (drawn while they work on
-//    the current one, so its latency is hidden; a workgroup's first ticket is its own index).  The waves of a
-//    workgroup then read and write neighbouring tiles at the same time, and the chip as a whole works inside
-//    one compact window of the launch-wide order that moves forward in order.  On multi-gigabyte workloads the
-//    memory system gives 10-15 % more bandwidth to this than to waves that each walk their own stripe of the
-//    arrays at their own pace; on small ones the barrier costs more than the order gains.
-//  * stripes (a.sched null): wave w of W takes the chunks w, w+W, w+2W, ... of `chunk` consecutive tiles; quarter tiles
-//    go to the workgroups eight at a time in turn.  With statistics a workgroup has one range of units, which its waves
-//    take in turn: a wave adds its sums to a tensor's global slots when its next unit lies in another tensor, and what
-//    the waves hold at the end goes there together (one wave after the other had each other's atomics to wait for: 3 M
-//    parameters of one tensor with every statistic took 170 us, now 44; 90 M 356, now 281).
-// The ticket counter resets itself: the last workgroup to leave the kernel clears it (and the count of
-// workgroups that have left), so every launch -- also a replayed one -- finds both at zero.
-// STATS 1 (all statistics) and 2 (the gradient's only) stay within the plain kernel's budget of 80 registers
-// and a third of a CU's LDS: their running sums live in LDS and nothing derived from the lane index is kept
-// across the tile loop (see LaneStats).  They run three workgroups per CU; plain launches whose units do not all fit at
-// once run two, as launches with wide states (MODE 2, 77 to 83 registers) always do (see launch_table).
-// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 7.45 ms = 6.0 TB/s, where an in-place
-// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 310 us); launches that leave the chip partly
+// Order of the work.  A unit is a part of a tile: a half (ROWS = 4), or a quarter (ROWS = 2) in launches that halves would
+// not fill.  Ticket k stands for the kWaves consecutive units k*kWaves .. k*kWaves + kWaves-1, one per wave of a workgroup.
+//  * Drawn (a.sched set): the workgroups draw tickets from counters in device memory and their waves meet at a barrier
+//    before they go on to the next one, which was drawn while they worked.  The chip as a whole then sweeps the arrays in
+//    order, and the narrower the window in which it works at one time, the more the memory system gives: 1.56 G parameters
+//    (bf16 gradients) 3.09 ms with half tiles in one order, 3.36 with whole tiles (tickets twice as long), 3.39 with two
+//    half tiles one after the other per draw, 3.82 with every workgroup walking its own tickets.
+//    One counter alone is drawn from at most every 12 ns or so, which 512 workgroups starting together feel (9 M
+//    parameters: 26.9 us, with eight counters 22.5; 130 M: 268.8 and 266.9; 1.56 G: 3092 and 3120).  The workgroups of a
+//    counter have to be spread over the XCDs: with a counter for each XCD, which do not run at the same pace, the classes
+//    drift apart (1.56 G: 3590 us).
+//  * Else workgroup g takes the tickets g, g + G, ...: launches up to 16 M parameters, where there is nothing to keep in order.
+// With statistics a workgroup's waves keep their sums as long as its tickets start in the same tensor (see StatRecord).
+// Counters that start anew by themselves leave nothing to clear: every launch -- also a replayed one -- finds them at zero.
+// (A count of the workgroups that have left, with acquire and release, cost 20 us: each one writes back its L2.)
+// Why halves: what a part needs besides its elements (addresses, scales, the exchange of maxima, the table of roots, the
+// sums of the statistics over the lanes) is a third of a quarter's vector instructions, and one chain of latencies; with
+// four rows it is shared by twice the elements, and the waves that 128 registers leave, 16 per CU, keep as many bytes in
+// flight.  bf16 gradients, static order: 30 M parameters 73.8 us with quarters, 61.1 with halves; 12.5 M 33.3 and 27.7.
+// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 7.0 ms = 6.4 TB/s, where an in-place
+// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 300 us); launches that leave the chip partly
 // idle one pass of latencies (tables, descriptor, loads, three LDS exchanges, stores): 6 us for 0.2 M parameters.
-// QUARTERS: a unit is a quarter tile and a workgroup takes two tiles at a time, in step.  Where the widths are not
-// multiples of 4 bits a quarter shares a word with the next: the waves leave their last bits in LDS, meet at a barrier,
-// and the wave that completes a word puts it together and stores it (its neighbour has read the old word before: its
-// moments, which the barrier follows, depend on it).
-template <bool BF16, int STATS, int MODE, bool QUARTERS>
-__global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_kernel(const StepArgs a) {
+// the class of ticket counter that a workgroup belongs to
+__device__ __forceinline__ uint32_t class_of(uint32_t group, uint32_t lg_classes) { return (group >> 3) & ((1u << lg_classes) - 1u); }
+
+template <bool BF16, int STATS, int MODE, int ROWS>
+__global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6) void step_kernel(const StepArgs a) {
   constexpr int kWaves = kWavesPerGroup;
-  __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsWords + kWavesPerGroup * LaneStats<STATS>::kWords];
+  constexpr int kWaveScratch = Part<ROWS>::kScratch, kLdsWords = kTabWords + kWaves * kWaveScratch;
+  constexpr uint32_t kLgParts = 3u - Part<ROWS>::kLgRows, kParts = 1u << kLgParts;  // of a tile
+  __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsWords + kWaves * LaneStats<STATS>::kWords];
   __shared__ uint32_t drawn[2];  // the ticket being worked on and the next one, alternating
-  // statistics of the two tickets in flight, one record per wave
-  __shared__ TicketRecord<STATS> ticket_rec[2][kWavesPerGroup];
-  __shared__ uint32_t ended_in[kWavesPerGroup];  // statistics under stripes: the tensor a wave ended in, plus one
-  __shared__ uint32_t shared_bits[QUARTERS ? 2 * kWaves * 2 * 64 : 1];  // [round & 1][wave][state][lane]
-  const bool tickets = a.sched != nullptr;
-  if (threadIdx.x == 0) drawn[0] = blockIdx.x;
+  __shared__ StatRecord<STATS> records[kWaves];
+  __shared__ uint32_t group_end[2];  // statistics: where the tensor ends that the first unit of the ticket lies in, alternating
   constexpr int kTabLoads = (kTabWords + 64 * kWaves - 1) / (64 * kWaves);  // the tables: 5 KB
   uint32_t tab[kTabLoads];
 #pragma unroll
@@ -984,32 +1019,23 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* ws = lds + kTabWords + wave * kWaveScratch;
-  const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * kWaves;
-  constexpr uint32_t qs = QUARTERS ? 2u : 0u;
-  const uint64_t total_units = static_cast<uint64_t>(a.total_tiles) << qs;
-  // Stripes.  kTogether: the waves of a workgroup take consecutive units, round by round (next unit: stripe + wave, the
-  // workgroup's first one being the same for its waves); else each wave walks chunks of its own.
-  constexpr bool kTogether = QUARTERS || STATS != 0;
-  const uint64_t C = kTogether ? 1 : a.chunk;
-  const uint64_t stripe_step = STATS ? kWaves : n_waves * C;
-  const uint64_t stripe_end = STATS ? min(total_units, (static_cast<uint64_t>(blockIdx.x) + 1) * a.chunk) : total_units;
-  uint64_t stripe = STATS ? static_cast<uint64_t>(blockIdx.x) * a.chunk
-                          : (kTogether ? static_cast<uint64_t>(blockIdx.x) * kWaves
-                                       : (static_cast<uint64_t>(blockIdx.x) * kWaves + wave) * C);
+  const bool draws = a.sched != nullptr;
+  const uint64_t total_units = static_cast<uint64_t>(a.total_tiles) << kLgParts;
   const uint32_t n_tickets = static_cast<uint32_t>((total_units + kWaves - 1) / kWaves);
-  uint32_t turn = 0;         // which of drawn[] is current (tickets)
-  uint32_t next_ticket = 0;  // thread 0: the ticket drawn for the next round
+  uint32_t turn = 0;  // which of drawn[] is current
+  // Ticket k belongs to class k mod C, each with a counter; so does a workgroup, to one class with its seven neighbours,
+  // which are on the other XCDs (C > 1 only if this gives every class as many).  Its first ticket is the one of its own index
+  // within the class; the counter hands out those that follow and starts anew after as many draws as the class has
+  // tickets: every workgroup draws until it gets a number past the end, one draw for each ticket that it works on.
+  uint32_t cur = blockIdx.x;
+  if (draws) cur = ((((blockIdx.x >> 3) >> a.lg_classes) << 3) + (blockIdx.x & 7u)) << a.lg_classes | class_of(blockIdx.x, a.lg_classes);
 
-  uint32_t l = 0;
-  bool have_desc = false;
+  // tensor holding the wave's first unit: the table's loads, the search and the first descriptor are in flight together
+  uint32_t l = 0, held_l = 0;
   TensorDesc d;
-  // tensor holding the wave's first tile (a workgroup's first ticket is its own index): the table's loads, the search
-  // and the first descriptor are in flight together
-  const uint64_t first = tickets ? static_cast<uint64_t>(blockIdx.x) * kWaves + wave : stripe + (kTogether ? wave : 0u);
-  if (first < (tickets ? total_units : stripe_end)) {
-    l = find_begin(a.desc, a.n_tensors, static_cast<uint32_t>(first >> qs), lane);
+  if (static_cast<uint64_t>(cur) * kWaves + wave < total_units) {
+    l = find_begin(a.desc, a.n_tensors, static_cast<uint32_t>((static_cast<uint64_t>(cur) * kWaves + wave) >> kLgParts), lane);
     d = load_desc(a.desc, l);
-    have_desc = true;
   }
 #pragma unroll
   for (int k = 0; k < kTabLoads; ++k) {
@@ -1021,29 +1047,25 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
   LaneStats<STATS> st;
   st.acc = STATS ? reinterpret_cast<float*>(lds + kLdsWords + wave * LaneStats<STATS>::kWords) : nullptr;
   st.units = 0;
-  if (STATS) st.clear_all(lane);
-  for (;;) {
-    uint64_t c_begin, c_end;
-    if (tickets) {
-      const uint32_t cur = __builtin_amdgcn_readfirstlane(drawn[turn]);
-      if (cur >= n_tickets) break;  // the same for every wave of the workgroup
-      // the counter hands out the tickets from gridDim.x on
-      if (threadIdx.x == 0) next_ticket = gridDim.x + __hip_atomic_fetch_add(a.sched, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      c_begin = static_cast<uint64_t>(cur) * kWaves + wave;
-      c_end = min(c_begin + 1, total_units);
-    } else {
-      if (stripe >= stripe_end) break;  // (kTogether: the same for every wave of the workgroup)
-      c_begin = stripe + (kTogether ? wave : 0u);
-      c_end = min(c_begin + C, stripe_end);
-      stripe += stripe_step;
+  if (STATS) {
+    held_l = l;  // the tensor that the wave's sums belong to
+    st.clear_all(lane);
+  }
+  auto slots_of = [&](uint32_t tensor) { return a.stats + static_cast<size_t>(tensor) * kStatSlots; };
+  while (cur < n_tickets) {  // the same for every wave of the workgroup
+    uint32_t next_ticket = 0;
+    if (draws && threadIdx.x == 0) {
+      uint32_t group = blockIdx.x;
+      asm volatile("" : "+s"(group));  // nothing of this is worth a register throughout the loop
+      const uint32_t cls = class_of(group, a.lg_classes), tickets = (n_tickets + (1u << a.lg_classes) - 1u - cls) >> a.lg_classes;
+      next_ticket = atomicInc(a.sched + cls * kSchedStride, tickets - 1u);
+      next_ticket = ((gridDim.x >> a.lg_classes) + next_ticket) << a.lg_classes | cls;
     }
-    SharedWords sw = {0u, 0u, 0u, 0u};
-    for (uint64_t u = c_begin; u < c_end; ++u) {
-      const uint32_t t = static_cast<uint32_t>(u >> qs);
+    const uint64_t u = static_cast<uint64_t>(cur) * kWaves + wave;
+    if (u < total_units) {
+      const uint32_t t = static_cast<uint32_t>(u >> kLgParts), q = static_cast<uint32_t>(u) & (kParts - 1u);
       if (t >= d.tile_begin + d.n_tiles) {  // t < total_tiles, so a later tensor holds it
-        if (STATS && !tickets) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
-        // (see launch_table; with statistics quarter units have ranges of their own, and the next unit is close)
-        if (!(STATS && QUARTERS) && __builtin_expect(a.look_ahead != 0u, 0)) {
+        if (__builtin_expect(a.look_ahead != 0u, 0)) {
           int hidden = lane;
           asm volatile("" : "+v"(hidden));  // no address of the search is worth a register throughout the loop
           uint32_t window, ahead;
@@ -1060,106 +1082,51 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, MODE == 2 ? 4 : 6) void step_k
           } while (t >= d.tile_begin + d.n_tiles);
         }
       }
+      bool in_group = true;  // the unit lies in the tensor of the ticket's first unit (it cannot lie behind it)
+      if (STATS) {
+        in_group = static_cast<uint32_t>((u - wave) >> kLgParts) >= d.tile_begin;
+        if (!in_group) flush_stats(st, slots_of(held_l), lane);
+        else held_l = l;
+      }
       const uint32_t tile = t - d.tile_begin;
       const uint64_t left = d.numel - static_cast<uint64_t>(tile) * kTile;
-      if (QUARTERS) {
-        const uint32_t q = static_cast<uint32_t>(u & 3u);
-        if (left >= 512u * (q + 1u))
-          process_quarter<BF16, STATS, false, MODE, true>(d, tile, q, kTile, a, lds, ws, lane, sw, st);
-        else
-          process_quarter<BF16, STATS, true, MODE, true>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, sw, st);
-      } else if (left >= static_cast<uint64_t>(kTile)) {
-        sw.carry_m = sw.carry_v = 0u;
-#pragma nounroll
-        for (uint32_t q = 0; q < 4; ++q)
-          process_quarter<BF16, STATS, false, MODE, false>(d, tile, q, kTile, a, lds, ws, lane, sw, st);
-      } else {
-        sw.carry_m = sw.carry_v = 0u;
-#pragma nounroll
-        for (uint32_t q = 0; q < 4; ++q)
-          process_quarter<BF16, STATS, true, MODE, false>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, sw, st);
-      }
-      if (STATS && tickets) {
-        if constexpr (STATS != 0) {
-          // does the ticket's first unit lie in this wave's tensor?  (it cannot lie behind it: units only grow)
-          const uint32_t t_first = static_cast<uint32_t>((c_begin - wave) >> qs);
-          ticket_stats_tile(st, &ticket_rec[turn][wave], t_first >= d.tile_begin, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
-        }
-      } else if (STATS && ++st.units == kStatFlushUnits) {
-        widen_stats(st, lane);
+      if (left >= 256u * ROWS * (q + 1u))
+        process_part<BF16, STATS, false, MODE, ROWS>(d, tile, q, kTile, a, lds, ws, lane, st);
+      else
+        process_part<BF16, STATS, true, MODE, ROWS>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, st);
+      if (STATS) {
+        if (!in_group) flush_stats(st, slots_of(l), lane);
+        else if (++st.units == kStatFlushRows / ROWS) widen_stats(st, lane);
+        if (wave == 0 && lane == 0) group_end[turn] = d.tile_begin + d.n_tiles;
       }
     }
-    if (QUARTERS && a.quarter_units == 2) {
-      uint32_t* mine = shared_bits + ((turn * kWaves + wave) * 2) * 64;
-      if (c_begin < c_end) {
-        mine[lane] = sw.carry_m;
-        mine[64 + lane] = sw.carry_v;
+    if (draws && threadIdx.x == 0) drawn[turn] = next_ticket;
+    if (STATS || draws) __syncthreads();  // the workgroup goes on together
+    cur = draws ? __builtin_amdgcn_readfirstlane(drawn[turn]) : cur + gridDim.x;
+    if constexpr (STATS != 0) {
+      const uint32_t end = __builtin_amdgcn_readfirstlane(group_end[turn]);
+      if (cur >= n_tickets || static_cast<uint32_t>(static_cast<uint64_t>(cur) * kWaves >> kLgParts) >= end) {
+        record_stats(st, &records[wave], lane);
+        __syncthreads();
+        if (wave == 0) flush_records(records, slots_of(l), lane);  // (wave 0 has the first unit of every ticket)
       }
-      __syncthreads();
-      if (c_begin < c_end) {
-        const uint32_t* before = mine - 2 * 64;  // the wave with the previous quarter (read for q > 0 only)
-        const uint32_t q = static_cast<uint32_t>(c_begin & 3u), tile = static_cast<uint32_t>(c_begin >> 2) - d.tile_begin;
-        const uint32_t bmo = MODE >= 1 ? d.bm_out : d.bm, bvo = MODE >= 1 ? d.bv_out : d.bv;
-        uint32_t* cm = (MODE >= 1 ? d.m_out : d.m_codes) + (static_cast<size_t>(tile) * bmo + ((q * bmo) >> 2)) * 64;
-        uint32_t* cv = (MODE >= 1 ? d.v_out : d.v_codes) + (static_cast<size_t>(tile) * bvo + ((q * bvo) >> 2)) * 64;
-        if ((q * bmo) & 3u) as_global(cm)[lane] = sw.held_m | before[lane];
-        if ((q * bvo) & 3u) as_global(cv)[lane] = sw.held_v | before[64 + lane];
-      }
-      if (!tickets) turn ^= 1u;  // (the next round's bits go into the other half: a wave is at most one barrier ahead)
     }
-    if (tickets) {
-      if constexpr (STATS != 0) {
-        // a wave without a unit in this ticket (the launch's last one) leaves an empty record
-        constexpr int kRecordDoubles = sizeof(TicketRecord<STATS>) / 8;
-        if (c_begin >= c_end && lane < kRecordDoubles) reinterpret_cast<double*>(&ticket_rec[turn][wave])[lane] = 0.0;
-      }
-      if (threadIdx.x == 0) drawn[turn ^ 1u] = next_ticket;
-      __syncthreads();  // the workgroup goes on together
-      if constexpr (STATS != 0) {
-        // wave 0 worked on the ticket's first unit: its l is that unit's tensor
-        if (wave == 0) ticket_stats_flush(ticket_rec[turn], a.stats + static_cast<size_t>(l) * kStatSlots, lane);
-      }
-      turn ^= 1u;
-    }
-  }
-  if constexpr (STATS != 0) {
-    if (!tickets) {
-      // The workgroup's sums go to the global slots together: those of the waves that ended in its last tensor by one set
-      // of atomics, a wave that ended in an earlier one by itself.
-      if (lane == 0) ended_in[wave] = have_desc ? l + 1u : 0u;
-      __syncthreads();
-      uint32_t last = 0;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) last = max(last, ended_in[w]);
-      last = __builtin_amdgcn_readfirstlane(last);
-      const bool with_last = have_desc && l + 1u == last;
-      if (have_desc && !with_last) flush_stats(st, a.stats + static_cast<size_t>(l) * kStatSlots, lane);
-      record_stats(st, &ticket_rec[0][wave], with_last, lane);
-      __syncthreads();
-      if (wave == 0 && last) ticket_stats_flush(ticket_rec[0], a.stats + static_cast<size_t>(last - 1u) * kStatSlots, lane);
-    }
-  }
-  if (tickets && threadIdx.x == 0) {
-    // every ticket this workgroup drew precedes its leaving; the last one to leave has seen all others leave
-    const uint32_t left_before = __hip_atomic_fetch_add(a.sched + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    if (left_before == gridDim.x - 1u) {
-      __hip_atomic_store(a.sched, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.sched + 1, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    turn ^= 1u;  // (what the next round leaves goes into the other half: a wave is at most one barrier ahead)
   }
 }
 
 }  // namespace
 
+template <int MODE, int STATS, int ROWS>
+static void launch_grads(const StepArgs& a, bool grad_bf16, dim3 grid, dim3 block, hipStream_t s) {
+  if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE, ROWS>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((step_kernel<false, STATS, MODE, ROWS>), grid, block, 0, s, a);
+}
+
 template <int MODE, int STATS>
 static void launch_variant(const StepArgs& a, bool grad_bf16, dim3 grid, dim3 block, hipStream_t s) {
-  if (a.quarter_units) {
-    if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((step_kernel<false, STATS, MODE, true>), grid, block, 0, s, a);
-  } else {
-    if (grad_bf16) hipLaunchKernelGGL((step_kernel<true, STATS, MODE, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((step_kernel<false, STATS, MODE, false>), grid, block, 0, s, a);
-  }
+  if (a.unit_rows == 2) launch_grads<MODE, STATS, 2>(a, grad_bf16, grid, block, s);
+  else launch_grads<MODE, STATS, 4>(a, grad_bf16, grid, block, s);
 }
 
 template <int MODE>
