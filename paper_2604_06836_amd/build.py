@@ -17,7 +17,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -ffp-contract=off: every fp32 operation of the step is rounded on its own (the packed codes
 # must be reproducible bit for bit).  Packed-fp32 instructions are disabled.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-ffp-contract=off",
-                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                # a kernel's first scalar arguments are in registers when its waves start (up to 16 words)
+                "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
           "-Wall", "-Wextra", "-Wno-unused-parameter"]
 

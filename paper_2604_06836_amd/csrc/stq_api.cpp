@@ -259,11 +259,12 @@ int check_hparams(const stq_hparams* hp) {
 
 int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t total, double* d_stats,
                  const stq_hparams* hp, int mode, void* stream, uint32_t* sched) {
+  StepWork w;
   StepArgs a;
-  a.desc = d_desc;
-  a.n_tensors = n;
-  a.total_tiles = total;
-  a.tables = ctx->d_tables;
+  w.desc = d_desc;
+  w.n_tensors = n;
+  w.total_tiles = total;
+  w.tables = ctx->d_tables;
   a.stats = d_stats;
   a.beta1 = hp->beta1;
   a.omb1 = 1.0f - hp->beta1;
@@ -299,17 +300,17 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
   if (const char* e = std::getenv("STQ_LG_PARTS")) { lg_parts = std::strtoul(e, nullptr, 10) == 2 ? 2 : 1; per_cu = lg_parts == 2 ? 3 : 2; }
   if (const char* e = std::getenv("STQ_GROUPS_PER_CU")) per_cu = std::strtoul(e, nullptr, 10);
 #endif
-  a.sched = !draws ? nullptr : (sched ? sched : ctx->d_sched);
-  a.unit_rows = 8u >> lg_parts;
+  w.sched = !draws ? nullptr : (sched ? sched : ctx->d_sched);
+  w.unit_rows = 8u >> lg_parts;
   const uint64_t units = static_cast<uint64_t>(total) << lg_parts;
   const uint64_t need_groups = (units + wpg - 1) / wpg, max_groups = static_cast<uint64_t>(ctx->n_cu) * per_cu;
   const uint32_t groups = static_cast<uint32_t>(need_groups < max_groups ? need_groups : max_groups);
   // Eight counters (where every one has as many workgroups: fewer CUs than the card has, or a small launch) as long as the
   // draws of the start count, one in larger launches, where the classes would drift apart (9 M parameters 22.5 us with
   // eight and 26.9 with one, 130 M 267.5 and 270.5, 300 M 616 and 613; 3.5 G 7.20 ms and 7.00).
-  a.lg_classes = total < 100000u && groups % (8u << kLgTicketClasses) == 0 ? kLgTicketClasses : 0;
+  w.lg_classes = total < 100000u && groups % (8u << kLgTicketClasses) == 0 ? kLgTicketClasses : 0;
 #ifdef STQ_TUNING_ENV
-  if (const char* e = std::getenv("STQ_CLASSES")) a.lg_classes = std::strtoul(e, nullptr, 10);
+  if (const char* e = std::getenv("STQ_CLASSES")) w.lg_classes = std::strtoul(e, nullptr, 10);
 #endif
   // How a wave finds the tensor of its next unit (see step_kernel).  A walk costs one scalar load after the other for each
   // tensor it passes, a search one or two vector loads, which take as long as some of them while the memory system is busy.
@@ -322,7 +323,7 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
 #ifdef STQ_TUNING_ENV
   if (const char* e = std::getenv("STQ_LOOK")) a.look_ahead = std::strtoul(e, nullptr, 10);
 #endif
-  return launch_step(a, hp->grad_dtype == 1, stats, mode, groups, stream) == 0 ? STQ_OK : STQ_EHIP;
+  return launch_step(w, a, hp->grad_dtype == 1, stats, mode, groups, stream) == 0 ? STQ_OK : STQ_EHIP;
 }
 
 }  // namespace stq

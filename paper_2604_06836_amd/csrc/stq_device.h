@@ -36,11 +36,19 @@ enum StatSlot {
   kMaxV     // low uint32: bit pattern of max v
 };
 
-struct StepArgs {
+// A launch of the step kernel: its work ...
+struct StepWork {
   const TensorDesc* desc;
+  const uint32_t* tables;  // kTabWords words, see stq_tables.h
+  uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters; null: nothing is drawn (see
+                           // step_kernel)
   uint32_t n_tensors;
   uint32_t total_tiles;
-  const uint32_t* tables;  // kTabWords words, see stq_tables.h
+  uint32_t lg_classes;     // log2 of the number of ticket counters
+  uint32_t unit_rows;      // rows of a unit of scheduling: 2 (a quarter tile) or 4 (a half)
+};
+// ... and the rest of its arguments.
+struct StepArgs {
   double* stats;           // [n_tensors][kStatSlots]
   float beta1, omb1, beta2, omb2;
   float ibc1, ibc2;        // reciprocal bias corrections 1/(1-beta^t)
@@ -48,10 +56,6 @@ struct StepArgs {
   uint32_t lgK;            // log2 of the block size: 6, 7 or 8
   uint32_t look_ahead;     // 0: a wave walks from tensor to tensor to that of its next unit; else it searches, this many
                            // entries of the table first
-  uint32_t unit_rows;      // rows of a unit of scheduling: 2 (a quarter tile) or 4 (a half)
-  uint32_t lg_classes;     // log2 of the number of ticket counters
-  uint32_t* sched;         // kSchedWords words, zero between launches: the ticket counters; null: nothing is drawn (see
-                           // step_kernel)
 };
 
 struct ZeroArgs {
@@ -82,7 +86,7 @@ struct RepackManyArgs {
 
 // Launchers implemented in stq_step.hip and stq_kernels.hip.  `stream` is a hipStream_t.  Return a hipError_t as int.
 // stats: 0 none, 1 every statistic, 2 the gradient's only.
-int launch_step(const StepArgs& a, bool grad_bf16, int stats, int mode, uint32_t groups, void* stream);
+int launch_step(const StepWork& w, const StepArgs& a, bool grad_bf16, int stats, int mode, uint32_t groups, void* stream);
 int launch_zero(const ZeroArgs& a, void* stream);
 constexpr uint64_t kRepackOnceBytes = 350ull << 20;  // see launch_repack_many
 int launch_repack_many(RepackManyArgs a, uint64_t code_bytes, void* stream);  // code_bytes: read and written
