@@ -164,7 +164,11 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   ok = ok && hipHostMalloc(&c->h_stats, sizeof(double) * kStatSlots * max_tensors, hipHostMallocDefault) == hipSuccess;
   for (int k = 0; k < kRing && ok; ++k) {
     ok = ok && hipHostMalloc(&c->h_stage[k], sizeof(TensorDesc) * max_tensors, hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipHostMalloc(&c->h_jobs[k], sizeof(RepackJob) * 2 * max_tensors, hipHostMallocDefault) == hipSuccess;
+  }
+  for (int k = 0; k < 2 && ok; ++k) {
     ok = ok && hipEventCreateWithFlags(&c->stage_done[k], hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&c->jobs_done[k], hipEventDisableTiming) == hipSuccess;
   }
   ok = ok && hipMemcpy(c->d_tables, img.data(), img.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
   // every conversion table of the re-pack: (state, old width, new width) -> 256 codes, one word each
@@ -180,10 +184,6 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   ok = ok && hipMalloc(&c->d_luts, luts.size() * 4) == hipSuccess;
   ok = ok && hipMemcpy(c->d_luts, luts.data(), luts.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
   ok = ok && hipMalloc(&c->d_jobs, sizeof(RepackJob) * 2 * max_tensors) == hipSuccess;
-  for (int k = 0; k < kRing && ok; ++k) {
-    ok = ok && hipHostMalloc(&c->h_jobs[k], sizeof(RepackJob) * 2 * max_tensors, hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&c->jobs_done[k], hipEventDisableTiming) == hipSuccess;
-  }
   ok = ok && hipMemset(c->d_stats, 0, sizeof(double) * kStatSlots * max_tensors) == hipSuccess;
   ok = ok && hipDeviceSynchronize() == hipSuccess;
   if (!ok) { stq_destroy(c); return STQ_EHIP; }
@@ -214,10 +214,10 @@ int stq_destroy(stq_ctx* c) {
   if (c->d_jobs) (void)hipFree(c->d_jobs);
   for (int k = 0; k < kRing; ++k) {
     if (c->h_jobs[k]) (void)hipHostFree(c->h_jobs[k]);
-    if (c->jobs_done[k]) (void)hipEventDestroy(c->jobs_done[k]);
-  }
-  for (int k = 0; k < kRing; ++k) {
     if (c->h_stage[k]) (void)hipHostFree(c->h_stage[k]);
+  }
+  for (int k = 0; k < 2; ++k) {
+    if (c->jobs_done[k]) (void)hipEventDestroy(c->jobs_done[k]);
     if (c->stage_done[k]) (void)hipEventDestroy(c->stage_done[k]);
   }
   delete c;
@@ -333,18 +333,9 @@ namespace {
 // Stage n descriptors (already in pinned slot k, or copied there from `src`) into `dst` in stream order.
 int upload_descs(stq_ctx* ctx, int k, const TensorDesc* src, size_t n, TensorDesc* dst, hipStream_t s) {
   if (src) std::memcpy(ctx->h_stage[k], src, sizeof(TensorDesc) * n);
-  if (hipMemcpyAsync(dst, ctx->h_stage[k], sizeof(TensorDesc) * n, hipMemcpyHostToDevice, s) != hipSuccess) return STQ_EHIP;
-  if (hipEventRecord(ctx->stage_done[k], s) != hipSuccess) return STQ_EHIP;
-  return STQ_OK;
-}
-
-// The next pinned staging slot, free again (its upload of kRing calls ago has finished).
-int next_stage_slot(stq_ctx* ctx, int* out) {
-  const int k = ctx->ring_pos;
-  if (int e = wait_slot_free(ctx->stage_done[k])) return e;
-  ctx->ring_pos = (k + 1) % kRing;
-  *out = k;
-  return STQ_OK;
+  const int launched = launch_upload(dst, ctx->h_stage[k], sizeof(TensorDesc) * n, s);
+  if (int e = slot_in_use(ctx->stage_done, k, s)) return e;
+  return launched == 0 ? STQ_OK : STQ_EHIP;
 }
 
 // Index of a device-resident tensor table that holds `descs`: one that already does (uploaded on this
@@ -360,7 +351,7 @@ int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream
   if (table < 0) {
     table = ctx->desc_pos;
     int k = -1;
-    if (int e = next_stage_slot(ctx, &k)) return e;
+    if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
     ctx->uploaded[table].clear();  // whatever happens below, the old contents are no longer claimed
     if (int e = upload_descs(ctx, k, descs.data(), n, ctx->d_desc[table], s)) return e;
     ctx->desc_pos = (table + 1) % kDescTables;
@@ -453,9 +444,12 @@ int stq_step_static(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const s
   hipStream_t s = static_cast<hipStream_t>(stream);
   // descriptors straight into a pinned staging slot, from there into this device's static table
   int k = -1;
-  if (int e = next_stage_slot(ctx, &k)) return e;
+  if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
   uint32_t total = 0;
-  if (int e = fill_descs(ctx, tensors, n, plan, hp->block, true, ctx->h_stage[k], &total)) return e;
+  if (int e = fill_descs(ctx, tensors, n, plan, hp->block, true, ctx->h_stage[k], &total)) {
+    (void)slot_in_use(ctx->stage_done, k, s);  // (the other slots of its half may be)
+    return e;
+  }
   const int mode = mode_of(ctx->h_stage[k], n, false);
   TensorDesc* table = static_cast<TensorDesc*>(ctx->static_scratch);
   uint32_t* sched = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ctx->static_scratch) + kStaticTableBytes);
@@ -559,13 +553,12 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
   DeviceGuard g(ctx->device);
   if (!g.ok) return STQ_EHIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int k = ctx->jobs_pos;
-  ctx->jobs_pos = (k + 1) % kRing;
-  if (int e = wait_slot_free(ctx->jobs_done[k])) return e;
+  int k = -1;
+  if (int e = take_slot(ctx->jobs_done, &ctx->jobs_pos, &k)) return e;
   std::memcpy(ctx->h_jobs[k], table.data(), sizeof(RepackJob) * n);
-  if (hipMemcpyAsync(ctx->d_jobs, ctx->h_jobs[k], sizeof(RepackJob) * n, hipMemcpyHostToDevice, s) != hipSuccess)
-    return STQ_EHIP;
-  if (hipEventRecord(ctx->jobs_done[k], s) != hipSuccess) return STQ_EHIP;
+  const int launched = launch_upload(ctx->d_jobs, ctx->h_jobs[k], sizeof(RepackJob) * n, stream);
+  if (int e = slot_in_use(ctx->jobs_done, k, s)) return e;
+  if (launched != 0) return STQ_EHIP;
   RepackManyArgs a;
   a.jobs = ctx->d_jobs;
   a.n_jobs = n;

@@ -93,6 +93,7 @@ int launch_repack_many(RepackManyArgs a, uint64_t code_bytes, void* stream);  //
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
                       uint32_t n_cu, void* stream);
 int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);
+int launch_upload(void* dst, const void* pinned, uint64_t bytes, void* stream);  // a multiple of 16 bytes
 int launch_fill_zero(uint32_t* p, uint64_t words, void* stream);
 
 }  // namespace stq

@@ -12,7 +12,7 @@
 
 namespace stq {
 
-constexpr int kRing = 16;       // pinned staging slots for descriptor uploads
+constexpr int kRing = 16;       // pinned staging slots of a kind of upload, in two halves with an event each (see take_slot)
 constexpr uint64_t kTicketMinTiles = 4096;  // launches of at least this many tiles, 8.4 M elements, draw tickets (see launch_table)
 constexpr int kDescTables = 4;  // device-resident tensor tables kept: a caller that alternates between a
                                 // few argument sets (two gradient buffers, say) uploads each only once
@@ -29,12 +29,12 @@ struct stq_ctx {
   double* d_stats = nullptr;
   uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches)
   stq::TensorDesc* h_stage[stq::kRing] = {};  // pinned
-  hipEvent_t stage_done[stq::kRing] = {};
+  hipEvent_t stage_done[2] = {};
   int ring_pos = 0;
   uint32_t* d_luts = nullptr;                // every conversion table of the re-pack, kRepackLuts x 256 words
   stq::RepackJob* d_jobs = nullptr;          // 2 * max_tensors
   stq::RepackJob* h_jobs[stq::kRing] = {};  // pinned
-  hipEvent_t jobs_done[stq::kRing] = {};
+  hipEvent_t jobs_done[2] = {};
   int jobs_pos = 0;
   double* h_stats = nullptr;                 // pinned, max_tensors * kStatSlots
   std::vector<stq::TensorDesc> uploaded[stq::kDescTables];  // what each d_desc currently holds
@@ -58,15 +58,28 @@ inline int lg_block(uint32_t K) {
   switch (K) { case 64: return 6; case 128: return 7; case 256: return 8; default: return -1; }
 }
 
-// A pinned staging slot may be written again once the upload it last fed has finished.  Asking is cheap and
-// almost always enough (the ring is long); waiting is the rare fallback -- on this runtime a wait on an event
+// The next slot of a ring, to be written by the host.  Half of the ring's slots are free again once the event that followed
+// the last upload from one of them has passed (an event for each would put a barrier behind every upload).  Asking is cheap
+// and almost always enough (the ring is long); waiting is the rare fallback -- on this runtime a wait on an event
 // can take as long as the work queued behind it.
-inline int wait_slot_free(hipEvent_t done) {
-  const hipError_t q = hipEventQuery(done);
-  if (q == hipSuccess) return STQ_OK;
-  if (q != hipErrorNotReady) { (void)hipGetLastError(); return STQ_EHIP; }
-  (void)hipGetLastError();
-  return hipEventSynchronize(done) == hipSuccess ? STQ_OK : STQ_EHIP;
+inline int take_slot(hipEvent_t* done, int* pos, int* slot) {
+  const int k = *pos;
+  if (k % (kRing / 2) == 0) {
+    const hipEvent_t half = done[k / (kRing / 2)];
+    const hipError_t q = hipEventQuery(half);
+    if (q != hipSuccess) {
+      (void)hipGetLastError();
+      if (q != hipErrorNotReady || hipEventSynchronize(half) != hipSuccess) return STQ_EHIP;
+    }
+  }
+  *pos = (k + 1) % kRing;
+  *slot = k;
+  return STQ_OK;
+}
+// After the upload from `slot` has been enqueued on s.
+inline int slot_in_use(hipEvent_t* done, int slot, hipStream_t s) {
+  if (slot % (kRing / 2) != kRing / 2 - 1) return STQ_OK;
+  return hipEventRecord(done[slot / (kRing / 2)], s) == hipSuccess ? STQ_OK : STQ_EHIP;
 }
 
 struct DeviceGuard {  // makes the context's device current for the duration of a call

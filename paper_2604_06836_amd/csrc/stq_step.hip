@@ -1031,11 +1031,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
   // which are on the other XCDs (C > 1 only if this gives every class as many).  Its first ticket is the one of its own index
   // within the class; the counter hands out those that follow and starts anew after as many draws as the class has
   // tickets: every workgroup draws until it gets a number past the end, one draw for each ticket that it works on.
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
   uint32_t cur = blockIdx.x;
   if (draws) cur = ((((blockIdx.x >> 3) >> lg_classes) << 3) + (blockIdx.x & 7u)) << lg_classes | class_of(blockIdx.x, lg_classes);
 
   // tensor holding the wave's first unit: the table's loads, the search and the first descriptor are in flight together
-  uint32_t l = 0, held_l = 0;
+  uint32_t l = 0, held_l = kNone;  // held_l, with statistics: the tensor that the wave's sums belong to, if it has any
   TensorDesc d;
   if (static_cast<uint64_t>(cur) * kWaves + wave < total_units) {
     l = find_begin(desc, n_tensors, static_cast<uint32_t>((static_cast<uint64_t>(cur) * kWaves + wave) >> kLgParts), lane);
@@ -1052,7 +1053,6 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
   st.acc = STATS ? reinterpret_cast<float*>(lds + kLdsWords + wave * LaneStats<STATS>::kWords) : nullptr;
   st.units = 0;
   if (STATS) {
-    held_l = l;  // the tensor that the wave's sums belong to
     st.clear_all(lane);
   }
   auto slots_of = [&](uint32_t tensor) { return a.stats + static_cast<size_t>(tensor) * kStatSlots; };
@@ -1063,7 +1063,6 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
       asm volatile("" : "+s"(group));  // nothing of this is worth a register throughout the loop
       const uint32_t cls = class_of(group, lg_classes), tickets = (n_tickets + (1u << lg_classes) - 1u - cls) >> lg_classes;
       next_ticket = atomicInc(sched + cls * kSchedStride, tickets - 1u);
-      next_ticket = ((gridDim.x >> lg_classes) + next_ticket) << lg_classes | cls;
     }
     const uint64_t u = static_cast<uint64_t>(cur) * kWaves + wave;
     if (u < total_units) {
@@ -1089,8 +1088,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
       bool in_group = true;  // the unit lies in the tensor of the ticket's first unit (it cannot lie behind it)
       if (STATS) {
         in_group = static_cast<uint32_t>((u - wave) >> kLgParts) >= d.tile_begin;
-        if (!in_group) flush_stats(st, slots_of(held_l), lane);
-        else held_l = l;
+        if (!in_group && held_l != kNone) flush_stats(st, slots_of(held_l), lane);
+        held_l = in_group ? l : kNone;
       }
       const uint32_t tile = t - d.tile_begin;
       const uint64_t left = d.numel - static_cast<uint64_t>(tile) * kTile;
@@ -1104,13 +1103,18 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
         if (wave == 0 && lane == 0) group_end[turn] = d.tile_begin + d.n_tiles;
       }
     }
-    if (draws && threadIdx.x == 0) drawn[turn] = next_ticket;
+    if (draws && threadIdx.x == 0) {
+      uint32_t group = blockIdx.x;
+      asm volatile("" : "+s"(group));
+      drawn[turn] = ((gridDim.x >> lg_classes) + next_ticket) << lg_classes | class_of(group, lg_classes);
+    }
     if (STATS || draws) __syncthreads();  // the workgroup goes on together
     cur = draws ? __builtin_amdgcn_readfirstlane(drawn[turn]) : cur + gridDim.x;
     if constexpr (STATS != 0) {
       const uint32_t end = __builtin_amdgcn_readfirstlane(group_end[turn]);
       if (cur >= n_tickets || static_cast<uint32_t>(static_cast<uint64_t>(cur) * kWaves >> kLgParts) >= end) {
         record_stats(st, &records[wave], lane);
+        held_l = kNone;
         __syncthreads();
         if (wave == 0) flush_records(records, slots_of(l), lane);  // (wave 0 has the first unit of every ticket)
       }
