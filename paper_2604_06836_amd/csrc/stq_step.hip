@@ -50,7 +50,6 @@ struct Part {
   static_assert(kDenEntries * 2 <= kTableWords, "the den table lies inside XR");
   static_assert((4 * ROWS) << (kMaxBits - 3) <= kTableWords, "and so do the roots of the widest code at the smallest block");
 };
-constexpr int kStatFlushRows = 8;  // fp32 lane sums are widened to fp64 every this many rows of a wave
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // value at byte offset `off` of an LDS float table
@@ -256,10 +255,10 @@ __device__ __forceinline__ bool is_valid(int n, uint32_t q, int lane, uint32_t n
 //    score with a threshold should not hinge on the rounding of a sum (the variance in Eq. 3 is a difference of
 //    two such sums).  Groups of four lanes, 16-word slots; the gradient's maximum likewise in a 16-word slot of
 //    bit patterns (all maxima are non-negative, so they order like their bit patterns).
-//  * S = 1 adds the moments' six fp32 sums (groups of eight lanes, 8-word slots) and two maxima (the owner lanes
-//    of the block scales hold them: lanes 0..31 the first moment's, 32..63 the second's, so a group of four is
-//    of one kind); the sums since the last widening are added to fp64 totals (lane k < 6 of the last slot)
-//    every kStatFlushRows rows.
+//  * S = 1 adds the moments' six sums (groups of eight lanes, 8-word slots): that of the first moments, whose terms cancel, in
+//    fp64 like the gradient's, the others, of terms that are not negative, in fp32 over the eight elements that a lane has in
+//    two rows and in fp64 from there on; and two maxima (the owner lanes of the block scales hold them: lanes 0..31 the first
+//    moment's, 32..63 the second's, so a group of four is of one kind).
 // S = 2: the gradient's statistics only.
 enum GradSlot { kLGSum = 0, kLGAbs, kLGSq };
 enum MomentSlot { kLMSum = 0, kLMSq, kLMErr, kLVSum, kLVSq, kLVErr };
@@ -268,22 +267,18 @@ enum MomentSlot { kLMSum = 0, kLMSq, kLMErr, kLVSum, kLVSq, kLVErr };
 //   gradient sums  3 slots of G doubles, G = 16 | 8 (one word per group of 64/G lanes)
 //   maxima         16 | 32 words: [0, G) max|g|; S = 1: [16, 24) max|m| (lanes 0..31 own the first moment's
 //                  block scales), [24, 32) max v (lanes 32..63); words [8, 16) stay 0
-//   S = 1 only     moment sums: 6 slots of 8 floats; fp64 totals of the six since the last flush (+ pad)
-// S = 1 takes the smaller gradient slots so that three workgroups still fit a CU's LDS.
+//   S = 1 only     moment sums: 6 slots of 8 doubles
 template <int S>
 struct LaneStats {
   static constexpr int kGShift = S == 1 ? 3 : 2;  // log2 of the lanes that share a gradient word
   static constexpr int kG = 64 >> kGShift;        // words per gradient slot
   static constexpr int kMaxWords = S == 1 ? 32 : 16;
-  static constexpr int kMomentSums = S == 1 ? 6 : 0;
-  static constexpr int kMaxOff = 3 * 2 * kG, kMomentOff = kMaxOff + kMaxWords, kWideOff = kMomentOff + 6 * 8;
-  static constexpr int kWords = S == 0 ? 0 : (S == 1 ? kWideOff + 2 * 6 + 4 : kMomentOff);
+  static constexpr int kMaxOff = 3 * 2 * kG, kMomentOff = kMaxOff + kMaxWords;
+  static constexpr int kWords = S == 0 ? 0 : (S == 1 ? kMomentOff + 6 * 8 * 2 : kMomentOff);
   float* acc;      // this wave's slice, null in the plain kernel
-  uint32_t units;  // units since the last widening (uniform)
   __device__ __forceinline__ double* grad_sums() const { return reinterpret_cast<double*>(acc); }
   __device__ __forceinline__ uint32_t* maxima() const { return reinterpret_cast<uint32_t*>(acc) + kMaxOff; }
-  __device__ __forceinline__ float* moment_sums() const { return acc + kMomentOff; }
-  __device__ __forceinline__ double& wide(int k) const { return reinterpret_cast<double*>(acc + kWideOff)[k]; }
+  __device__ __forceinline__ double* moment_sums() const { return reinterpret_cast<double*>(acc + kMomentOff); }
 
   __device__ __forceinline__ void add_grad(int k, int lane, double x) {
     x = S == 1 ? octet_sum(x) : quad_sum(x);
@@ -295,7 +290,14 @@ struct LaneStats {
     if ((lane & ((1 << kGShift) - 1)) == 0)
       __hip_atomic_fetch_max(maxima() + (lane >> kGShift), xb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
-  __device__ __forceinline__ void add(int slot, int lane, float x) {
+  // parts: the fp32 sums of two rows each
+  template <int PAIRS>
+  __device__ __forceinline__ void add(int slot, int lane, const float (&parts)[PAIRS]) {
+    double x = static_cast<double>(parts[0]);
+    if (PAIRS == 2) x += static_cast<double>(parts[PAIRS - 1]);
+    add(slot, lane, x);
+  }
+  __device__ __forceinline__ void add(int slot, int lane, double x) {
     x = octet_sum(x);
     if ((lane & 7) == 0)
       __hip_atomic_fetch_add(&moment_sums()[slot * 8 + (lane >> 3)], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -306,20 +308,10 @@ struct LaneStats {
     if ((lane & 3) == 0)
       __hip_atomic_fetch_max(maxima() + 16 + (lane >> 2), xb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
-  __device__ __forceinline__ void clear_moment_sums(int lane) {
-    if (S == 1 && lane < 48) moment_sums()[lane] = 0.0f;
-    units = 0;
-  }
-  __device__ __forceinline__ void clear_grad(int lane) {
+  __device__ __forceinline__ void clear(int lane) {
     if (lane < 3 * kG) grad_sums()[lane] = 0.0;
     if (lane < kMaxWords) maxima()[lane] = 0u;
-  }
-  __device__ __forceinline__ void clear_all(int lane) {
-    clear_grad(lane);
-    if (S == 1) {
-      clear_moment_sums(lane);
-      if (lane < 6) wide(lane) = 0.0;
-    }
+    if (S == 1 && lane < 48) moment_sums()[lane] = 0.0;
   }
   // The reductions of a slice, for the flushes below (call wave_lds_sync() first).
   // Gradient sum k (0..2), complete, in the lanes [k*kG, (k+1)*kG); zero in the lanes from 3*kG on.
@@ -327,10 +319,8 @@ struct LaneStats {
     const double x = lane < 3 * kG ? grad_sums()[lane] : 0.0;
     return S == 1 ? octet_sum(x) : row_sum(x);
   }
-  // Moment sum k (0..5) since the last clearing, in the lanes [8k, 8k+8); zero from lane 48 on.
-  __device__ __forceinline__ double reduced_moment(int lane) const {
-    return octet_sum(lane < 48 ? static_cast<double>(moment_sums()[lane]) : 0.0);
-  }
+  // Moment sum k (0..5) in the lanes [8k, 8k+8); zero from lane 48 on.
+  __device__ __forceinline__ double reduced_moment(int lane) const { return octet_sum(lane < 48 ? moment_sums()[lane] : 0.0); }
   // max|g| in lane 0; S = 1: max|m| in lane 16, max v in lane 24.
   __device__ __forceinline__ uint32_t reduced_max(int lane) const {
     const uint32_t x = lane < kMaxWords ? maxima()[lane] : 0u;
@@ -345,18 +335,6 @@ struct LaneStats {
   }
 };
 
-// S = 1: the moments' fp32 sums -> the wave's fp64 totals
-template <int S>
-__device__ __forceinline__ void widen_stats(LaneStats<S>& s, int lane) {
-  if (S != 1) return;
-  asm volatile("" : "+v"(lane));  // nothing derived from the lane index is worth keeping across the tile loop
-  wave_lds_sync();                // the atomics of every lane before the reads below
-  const double t = s.reduced_moment(lane);
-  int k;
-  if (LaneStats<S>::moment_lead(lane, k)) s.wide(k) += t;
-  s.clear_moment_sums(lane);
-}
-
 // the wave's statistics -> the tensor's global slots; the slice is cleared
 template <int S>
 __device__ __forceinline__ void flush_stats(LaneStats<S>& s, double* slot, int lane) {
@@ -369,11 +347,10 @@ __device__ __forceinline__ void flush_stats(LaneStats<S>& s, double* slot, int l
   if (LaneStats<S>::grad_lead(lane, k)) atomicAdd(&slot[kGSum + k], g);
   if (LaneStats<S>::max_lead(lane, k)) atomicMax(&out[k], mx);
   if (S == 1) {
-    widen_stats(s, lane);
-    wave_lds_sync();
-    if (lane < 6) atomicAdd(&slot[kMSum + lane], s.wide(lane));
+    const double mo = s.reduced_moment(lane);
+    if (LaneStats<S>::moment_lead(lane, k)) atomicAdd(&slot[kMSum + k], mo);
   }
-  s.clear_all(lane);
+  s.clear(lane);
 }
 
 // ---- the workgroup's statistics ----
@@ -391,15 +368,14 @@ struct StatRecord {
 template <int S>
 __device__ __forceinline__ void record_stats(LaneStats<S>& s, StatRecord<S>* rec, int lane) {
   asm volatile("" : "+v"(lane));
-  if (S == 1) widen_stats(s, lane);
   wave_lds_sync();
-  const double g = s.reduced_grad(lane);
+  const double g = s.reduced_grad(lane), mo = S == 1 ? s.reduced_moment(lane) : 0.0;
   const uint32_t mx = s.reduced_max(lane);
   int k;
   if (LaneStats<S>::grad_lead(lane, k)) rec->sum[k] = g;
-  if (S == 1 && lane < 6) rec->sum[3 + lane] = s.wide(lane);
+  if (LaneStats<S>::moment_lead(lane, k)) rec->sum[3 + k] = mo;
   if (LaneStats<S>::max_lead(lane, k)) rec->max_bits[k] = mx;
-  s.clear_all(lane);
+  s.clear(lane);
 }
 
 // wave 0, after a barrier: the records of the workgroup's waves -> the tensor's global slots
@@ -697,13 +673,15 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
   if (STATS == 1) {
     // the moments' sums and sums of squares, taken here where few other values are live (their quantization
     // errors follow in the quantizer loops)
-    float sm_sum = 0.0f, sm_sq = 0.0f, sv_sum = 0.0f, sv_sq = 0.0f;
+    double sm_sum = 0.0;
+    float sm_sq[ROWS / 2] = {}, sv_sum[ROWS / 2] = {}, sv_sq[ROWS / 2] = {};
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      sm_sum += m[n];
-      sm_sq = __builtin_fmaf(m[n], m[n], sm_sq);
-      sv_sum += v[n];
-      sv_sq = __builtin_fmaf(v[n], v[n], sv_sq);
+      const int p = n >> 3;
+      sm_sum += static_cast<double>(m[n]);
+      sm_sq[p] = __builtin_fmaf(m[n], m[n], sm_sq[p]);
+      sv_sum[p] += v[n];
+      sv_sq[p] = __builtin_fmaf(v[n], v[n], sv_sq[p]);
     }
     st.add(kLMSum, lane, sm_sum);
     st.add(kLMSq, lane, sm_sq);
@@ -835,7 +813,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 
   // ---- linear symmetric quantization of m; m is replaced by its quantized value ----
   if (wide_m) {
-    float sm_err = 0.0f;
+    float sm_err[ROWS / 2] = {};
     uint32_t kept[N];
     SafeRange range;  // the elements are not multiples of a block scale: look at each
 #pragma unroll
@@ -844,7 +822,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       range.add(mq * ua.ibc1);
       if (STATS == 1) {
         const float dd = m[n] - mq;
-        sm_err = __builtin_fmaf(dd, dd, sm_err);
+        sm_err[n >> 3] = __builtin_fmaf(dd, dd, sm_err[n >> 3]);
       }
       m[n] = mq;
       kept[n] = f2u(mq);
@@ -872,7 +850,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
     const uint32_t magic_code = 0x4B400001u;  // bits of (magic + q), less the code
     const uint32_t r_base = (4u << bmo) - 4u * magic_code;
     uint32_t code[N];  // low bits: code + 1
-    float sm_err = 0.0f;  // this part's share of the lane's sum of squared quantization errors
+    float sm_err[ROWS / 2] = {};  // sums of squared quantization errors of two rows each
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const int i = n >> 2;
@@ -884,7 +862,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       if (STATS == 1) {
         if (TAIL && !is_valid<ROWS>(n, q, lane, n_valid)) mq = 0.0f;
         const float dd = m[n] - mq;
-        sm_err = __builtin_fmaf(dd, dd, sm_err);
+        sm_err[n >> 3] = __builtin_fmaf(dd, dd, sm_err[n >> 3]);
       }
       m[n] = mq;
     }
@@ -894,7 +872,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 
   // ---- logarithmic quantization of v and the parameter update ----
   if (wide_v) {
-    float sv_err = 0.0f;
+    float sv_err[ROWS / 2] = {};
     uint32_t kept[N];
     SafeRange range;
 #pragma unroll
@@ -902,7 +880,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       const float vq = bvo == 32 ? v[n] : bf16_rne(v[n]);
       if (STATS == 1) {
         const float dd = v[n] - vq;
-        sv_err = __builtin_fmaf(dd, dd, sv_err);
+        sv_err[n >> 3] = __builtin_fmaf(dd, dd, sv_err[n >> 3]);
       }
       kept[n] = f2u(vq);
       v[n] = vq * ua.ibc2;
@@ -938,13 +916,13 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
     uint32_t code[N];
     quantize_v<ROWS, TAIL>(v, code, inv, bvo, lds + kTabVqOff, q, lane, n_valid);
     if (STATS == 1) {
-      float sv_err = 0.0f;  // this part's share of the lane's sum of squared quantization errors
+      float sv_err[ROWS / 2] = {};  // sums of squared quantization errors of two rows each
 #pragma unroll
       for (int n = 0; n < N; ++n) {
         float vq = sn[n >> 2] * lds_at(Lreg, (code[n] << 2) | (4u << bvo));
         if (TAIL && !is_valid<ROWS>(n, q, lane, n_valid)) vq = 0.0f;
         const float dd = v[n] - vq;
-        sv_err = __builtin_fmaf(dd, dd, sv_err);
+        sv_err[n >> 3] = __builtin_fmaf(dd, dd, sv_err[n >> 3]);
       }
       st.add(kLVErr, lane, sv_err);
     }
@@ -1051,9 +1029,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
 
   LaneStats<STATS> st;
   st.acc = STATS ? reinterpret_cast<float*>(lds + kLdsWords + wave * LaneStats<STATS>::kWords) : nullptr;
-  st.units = 0;
   if (STATS) {
-    st.clear_all(lane);
+    st.clear(lane);
   }
   auto slots_of = [&](uint32_t tensor) { return a.stats + static_cast<size_t>(tensor) * kStatSlots; };
   while (cur < n_tickets) {  // the same for every wave of the workgroup
@@ -1099,7 +1076,6 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
         process_part<BF16, STATS, true, MODE, ROWS>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, st);
       if (STATS) {
         if (!in_group) flush_stats(st, slots_of(l), lane);
-        else if (++st.units == kStatFlushRows / ROWS) widen_stats(st, lane);
         if (wave == 0 && lane == 0) group_end[turn] = d.tile_begin + d.n_tiles;
       }
     }
