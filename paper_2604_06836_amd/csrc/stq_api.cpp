@@ -284,9 +284,11 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
   const uint32_t wpg = kWavesPerGroup;
   // Units (see step_kernel): half tiles, which two workgroups per CU take with 128 registers a wave.  Quarter tiles, with
   // three workgroups per CU, in launches whose quarters all fit at once, where a wave with half the work is done sooner
-  // (1 M parameters 5.8 us, with halves 6.9; 3.0 M 9.0 and 10.3, 3.2 M 11.4 and 10.4).  With statistics only the smallest
-  // (0.5 M 25.4 and 25.6, 1.0 M 28.9 and 27.7, 3.0 M 41.6 and 34.7): what a unit leaves of them costs as much for a quarter.
-  const bool quarters = total * 4ull <= static_cast<uint64_t>(ctx->n_cu) * (stats ? 4 : 3 * wpg);
+  // (1 M parameters 5.8 us, with halves 6.9; 3.0 M 9.0 and 10.3, 3.2 M 11.4 and 10.4).  With statistics only the smallest of
+  // these (0.5 M 25.4 and 25.6, 1.0 M 28.9 and 27.7, 3.0 M 41.6 and 34.7: what a unit leaves of them costs as much for a
+  // quarter) and those of small tensors, each of which is left by itself (300 tensors of 3000 elements 31.6 and 34.3, 1000 of
+  // 768 40.2 and 42.4).
+  const bool quarters = total * 4ull <= static_cast<uint64_t>(ctx->n_cu) * 3 * wpg && (!stats || total <= ctx->n_cu || total < 16ull * n);
   // Tickets drawn, in one order over the chip, or every workgroup's own (see step_kernel).  fp32 gradients: 9.0 M
   // parameters 24.5 us drawn and 25.1 not, 16 M 39.2 and 41.1, 60 M 145 and 153; bf16: 12.5 M 28.0 and 27.4, 16 M 33.7
   // and 35.0, 60 M 114 and 117; wide states: 12.5 M 47.8 and 48.1, 9.0 M 38.1 and 37.1.
