@@ -103,7 +103,7 @@ int build_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_b
 
 // Launches the step kernel over the device-resident table `d_desc` of n tensors / total_tiles tiles.
 // mode: 0 in place, 1 widths change, 2 some state is (or may become) 16 or 32 bits wide.
-// sched: the two scheduling words the launch uses (null: the context's own).
+// sched: the kSchedWords ticket counters the launch uses (null: the context's own).
 int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t total_tiles, double* d_stats,
                  const stq_hparams* hp, int mode, void* stream,
                  uint32_t* sched = nullptr);
