@@ -23,9 +23,10 @@
  *     equal one of those, on the same stream, is one kernel launch and nothing else
  *     (no upload, no wait, no allocation).  Any other call, and every stq_repack and
  *     stq_repack_many, first uploads a small table from pinned host memory (sixteen staging slots
- *     in turn; a slot whose last upload has not finished yet is waited for); such a
- *     call cannot be recorded into a HIP graph.  (The step number reaches the kernel as launch arguments, so a
- *     recorded launch repeats its own step.)  stq_engine_step is asynchronous too; with
+ *     in turn; a slot whose last upload has not finished yet is waited for).  While hip_stream is
+ *     being captured the table travels in the arguments of small kernel launches instead, so a
+ *     recorded call is kernel launches only as well, and its replays do not depend on later calls'
+ *     tables.  (The step number reaches the kernel as launch arguments, so a recorded launch repeats its own step.)  stq_engine_step is asynchronous too; with
  *     grads = NULL it consists of kernel launches only.
  *   - One context serves one stream at a time.  Calls on one context must not
  *     overlap from several host threads.  A context may move to another stream after
@@ -180,7 +181,8 @@ int stq_step(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n,
  * and the scheduling words of large launches -- lives in a static device array of the library
  * (STQ_STATIC_MAX_TENSORS entries of 96 bytes + 256 bytes, about 96 KiB per GPU, held until the
  * process ends) instead of the context's buffers.  The call allocates nothing on host or device:
- * it fills a pinned staging slot of the context, copies it to the static table in stream order,
+ * it fills a pinned staging slot of the context (under capture: the arguments of small launches),
+ * copies it to the static table in stream order,
  * clears the scheduling words with a small kernel and launches.  n above STQ_STATIC_MAX_TENSORS gives STQ_ELIMIT
  * (n above the context's max_tensors STQ_EINVAL).  Every call on a GPU, from any context, uses
  * that GPU's one table: calls that overlap on one GPU (two streams, two contexts) race; on one

@@ -13,9 +13,10 @@ using namespace stq;
 
 namespace stq {
 
-int fill_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bits* plan, uint32_t K,
-               bool need_param_grad, TensorDesc* out, uint32_t* total_tiles) {
+int build_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bits* plan, uint32_t K,
+                bool need_param_grad, std::vector<TensorDesc>& out, uint32_t* total_tiles) {
   if (!ctx || !t || !plan || n == 0 || n > ctx->max_tensors) return STQ_EINVAL;
+  out.resize(n);
   if (lg_block(K) < 0) return STQ_EBLOCK;
   uint64_t tiles = 0;
   for (uint32_t l = 0; l < n; ++l) {
@@ -50,13 +51,6 @@ int fill_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bi
   }
   *total_tiles = static_cast<uint32_t>(tiles);
   return STQ_OK;
-}
-
-int build_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bits* plan, uint32_t K,
-                bool need_param_grad, std::vector<TensorDesc>& out, uint32_t* total_tiles) {
-  if (!ctx || n == 0 || n > ctx->max_tensors) return STQ_EINVAL;
-  out.resize(n);
-  return fill_descs(ctx, t, n, plan, K, need_param_grad, out.data(), total_tiles);
 }
 
 }  // namespace stq
@@ -156,7 +150,7 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   bool ok = g.ok;
   ok = ok && static_scratch_address(device, &c->static_scratch) == STQ_OK;
   ok = ok && hipMalloc(&c->d_tables, img.size() * 4) == hipSuccess;
-  for (int k = 0; k < kDescTables && ok; ++k)
+  for (int k = 0; k <= kRecordedTable && ok; ++k)
     ok = ok && hipMalloc(&c->d_desc[k], sizeof(TensorDesc) * max_tensors) == hipSuccess;
   ok = ok && hipMalloc(&c->d_stats, sizeof(double) * kStatSlots * max_tensors) == hipSuccess;
   ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords) == hipSuccess;
@@ -205,8 +199,8 @@ int stq_destroy(stq_ctx* c) {
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
   if (c->d_tables) (void)hipFree(c->d_tables);
-  for (int k = 0; k < kDescTables; ++k)
-    if (c->d_desc[k]) (void)hipFree(c->d_desc[k]);
+  for (TensorDesc* table : c->d_desc)
+    if (table) (void)hipFree(table);
   if (c->d_stats) (void)hipFree(c->d_stats);
   if (c->d_sched) (void)hipFree(c->d_sched);
   if (c->h_stats) (void)hipHostFree(c->h_stats);
@@ -332,17 +326,21 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
 
 namespace {
 
-// Stage n descriptors (already in pinned slot k, or copied there from `src`) into `dst` in stream order.
-int upload_descs(stq_ctx* ctx, int k, const TensorDesc* src, size_t n, TensorDesc* dst, hipStream_t s) {
-  if (src) std::memcpy(ctx->h_stage[k], src, sizeof(TensorDesc) * n);
-  const int launched = launch_upload(dst, ctx->h_stage[k], sizeof(TensorDesc) * n, s);
+// n descriptors into `dst` in stream order, through a pinned staging slot.
+int upload_descs(stq_ctx* ctx, const std::vector<TensorDesc>& descs, TensorDesc* dst, hipStream_t s) {
+  const size_t bytes = sizeof(TensorDesc) * descs.size();
+  if (recording(s)) return launch_upload_by_value(dst, descs.data(), bytes, s) == 0 ? STQ_OK : STQ_EHIP;
+  int k = -1;
+  if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
+  std::memcpy(ctx->h_stage[k], descs.data(), bytes);
+  const int launched = launch_upload(dst, ctx->h_stage[k], bytes, s);
   if (int e = slot_in_use(ctx->stage_done, k, s)) return e;
   return launched == 0 ? STQ_OK : STQ_EHIP;
 }
 
 // Index of a device-resident tensor table that holds `descs`: one that already does (uploaded on this
 // same stream, so the kernel is ordered after the upload), else the oldest, overwritten in stream order
-// (after the kernels that read it).
+// (after the kernels that read it).  A recorded upload has not happened yet: its table is one that no call takes to be there.
 int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream_t s, int* out) {
   const size_t n = descs.size();
   int table = -1;
@@ -350,12 +348,13 @@ int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream
     if (ctx->uploaded_on[k] == s && ctx->uploaded[k].size() == n &&
         std::memcmp(ctx->uploaded[k].data(), descs.data(), sizeof(TensorDesc) * n) == 0)
       table = k;
-  if (table < 0) {
+  if (table < 0 && recording(s)) {
+    table = kRecordedTable;
+    if (int e = upload_descs(ctx, descs, ctx->d_desc[table], s)) return e;
+  } else if (table < 0) {
     table = ctx->desc_pos;
-    int k = -1;
-    if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
     ctx->uploaded[table].clear();  // whatever happens below, the old contents are no longer claimed
-    if (int e = upload_descs(ctx, k, descs.data(), n, ctx->d_desc[table], s)) return e;
+    if (int e = upload_descs(ctx, descs, ctx->d_desc[table], s)) return e;
     ctx->desc_pos = (table + 1) % kDescTables;
     ctx->uploaded[table] = descs;
     ctx->uploaded_on[table] = s;
@@ -444,18 +443,13 @@ int stq_step_static(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const s
   DeviceGuard g(ctx->device);
   if (!g.ok) return STQ_EHIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // descriptors straight into a pinned staging slot, from there into this device's static table
-  int k = -1;
-  if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
+  std::vector<TensorDesc>& descs = ctx->descs;  // reserved at stq_init: no allocation per call
   uint32_t total = 0;
-  if (int e = fill_descs(ctx, tensors, n, plan, hp->block, true, ctx->h_stage[k], &total)) {
-    (void)slot_in_use(ctx->stage_done, k, s);  // (the other slots of its half may be)
-    return e;
-  }
-  const int mode = mode_of(ctx->h_stage[k], n, false);
+  if (int e = build_descs(ctx, tensors, n, plan, hp->block, true, descs, &total)) return e;
+  const int mode = mode_of(descs.data(), n, false);
   TensorDesc* table = static_cast<TensorDesc*>(ctx->static_scratch);
   uint32_t* sched = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ctx->static_scratch) + kStaticTableBytes);
-  if (int e = upload_descs(ctx, k, nullptr, n, table, s)) return e;
+  if (int e = upload_descs(ctx, descs, table, s)) return e;
   // the scheduling words must be zero when the kernel starts: a kernel leaves them so, but the array is shared
   // by every caller on this GPU and may hold what an aborted launch left
   if (launch_fill_zero(sched, kSchedWords, stream) != 0) return STQ_EHIP;
@@ -555,12 +549,16 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
   DeviceGuard g(ctx->device);
   if (!g.ok) return STQ_EHIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int k = -1;
-  if (int e = take_slot(ctx->jobs_done, &ctx->jobs_pos, &k)) return e;
-  std::memcpy(ctx->h_jobs[k], table.data(), sizeof(RepackJob) * n);
-  const int launched = launch_upload(ctx->d_jobs, ctx->h_jobs[k], sizeof(RepackJob) * n, stream);
-  if (int e = slot_in_use(ctx->jobs_done, k, s)) return e;
-  if (launched != 0) return STQ_EHIP;
+  if (recording(s)) {
+    if (launch_upload_by_value(ctx->d_jobs, table.data(), sizeof(RepackJob) * n, stream) != 0) return STQ_EHIP;
+  } else {
+    int k = -1;
+    if (int e = take_slot(ctx->jobs_done, &ctx->jobs_pos, &k)) return e;
+    std::memcpy(ctx->h_jobs[k], table.data(), sizeof(RepackJob) * n);
+    const int launched = launch_upload(ctx->d_jobs, ctx->h_jobs[k], sizeof(RepackJob) * n, stream);
+    if (int e = slot_in_use(ctx->jobs_done, k, s)) return e;
+    if (launched != 0) return STQ_EHIP;
+  }
   RepackManyArgs a;
   a.jobs = ctx->d_jobs;
   a.n_jobs = n;

@@ -94,6 +94,7 @@ int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total
                       uint32_t n_cu, void* stream);
 int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);
 int launch_upload(void* dst, const void* pinned, uint64_t bytes, void* stream);  // a multiple of 16 bytes
+int launch_upload_by_value(void* dst, const void* host, uint64_t bytes, void* stream);  // the same, for a stream being recorded
 int launch_fill_zero(uint32_t* p, uint64_t words, void* stream);
 
 }  // namespace stq

@@ -175,6 +175,14 @@ __global__ void set_grads_kernel(TensorDesc* desc, const void* const* grads, uin
   const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
   if (l < n) desc[l].grad = grads[l];
 }
+// The same from the launch's own arguments, for a launch that is recorded into a graph (see recording()).
+struct GradChunk {
+  const void* grad[480];  // (3840 bytes: a launch takes 4096 bytes of arguments)
+};
+constexpr uint32_t kChunkGrads = sizeof(GradChunk) / sizeof(void*);
+__global__ void set_grads_by_value_kernel(TensorDesc* desc, uint32_t n, const GradChunk chunk) {
+  if (threadIdx.x < n) desc[threadIdx.x].grad = chunk.grad[threadIdx.x];
+}
 
 }  // namespace
 
@@ -347,7 +355,15 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
   DeviceGuard g(e->ctx->device);
   if (!g.ok) return STQ_EHIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (grads) {
+  if (grads && recording(s)) {
+    for (uint32_t l = 0; l < e->n; l += kChunkGrads) {
+      GradChunk chunk;
+      const uint32_t here = e->n - l < kChunkGrads ? e->n - l : kChunkGrads;
+      std::memcpy(&chunk, grads + l, sizeof(void*) * here);
+      hipLaunchKernelGGL(set_grads_by_value_kernel, dim3(1), dim3(512), 0, s, e->d_desc + l, here, chunk);
+      if (hipGetLastError() != hipSuccess) return STQ_EHIP;
+    }
+  } else if (grads) {
     int k = -1;
     if (int err = take_slot(e->grads_done, &e->grads_pos, &k)) return err;
     std::memcpy(e->h_grads[k], grads, sizeof(void*) * e->n);

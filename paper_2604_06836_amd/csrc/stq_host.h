@@ -16,6 +16,7 @@ constexpr int kRing = 16;       // pinned staging slots of a kind of upload, in 
 constexpr uint64_t kTicketMinTiles = 4096;  // launches of at least this many tiles, 8.4 M elements, draw tickets (see launch_table)
 constexpr int kDescTables = 4;  // device-resident tensor tables kept: a caller that alternates between a
                                 // few argument sets (two gradient buffers, say) uploads each only once
+constexpr int kRecordedTable = kDescTables;  // one more, written by recorded launches only, each of which uploads it anew
 
 }  // namespace stq
 
@@ -25,7 +26,7 @@ struct stq_ctx {
   uint32_t n_cu = 0;
   uint64_t ticket_min_tiles = stq::kTicketMinTiles;  // see stq_set_schedule
   uint32_t* d_tables = nullptr;
-  stq::TensorDesc* d_desc[stq::kDescTables] = {nullptr, nullptr, nullptr, nullptr};
+  stq::TensorDesc* d_desc[stq::kDescTables + 1] = {};
   double* d_stats = nullptr;
   uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches)
   stq::TensorDesc* h_stage[stq::kRing] = {};  // pinned
@@ -82,6 +83,16 @@ inline int slot_in_use(hipEvent_t* done, int slot, hipStream_t s) {
   return hipEventRecord(done[slot / (kRing / 2)], s) == hipSuccess ? STQ_OK : STQ_EHIP;
 }
 
+// Whether work enqueued on s is recorded into a graph instead of run.  What a recorded launch reads at its replays must not
+// be memory that later calls write again: not a staging slot, nor a table that is kept for one argument set after the other.
+// (The default stream cannot be captured.)
+inline bool recording(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (!s) return false;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return status == hipStreamCaptureStatusActive;
+}
+
 struct DeviceGuard {  // makes the context's device current for the duration of a call
   int prev = -1; bool ok = false;
   explicit DeviceGuard(int dev) {
@@ -96,8 +107,6 @@ struct DeviceGuard {  // makes the context's device current for the duration of 
 int check_hparams(const stq_hparams* hp);
 
 // Fills the descriptors of n tensors at the widths of `plan` (new codes in place) and the launch-wide tile count.
-int fill_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bits* plan, uint32_t K,
-               bool need_param_grad, TensorDesc* out, uint32_t* total_tiles);
 int build_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_bits* plan, uint32_t K,
                 bool need_param_grad, std::vector<TensorDesc>& out, uint32_t* total_tiles);
 

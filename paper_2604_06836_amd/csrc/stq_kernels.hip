@@ -4,9 +4,9 @@
 // The step kernel itself is in stq_step.hip.
 #include <hip/hip_runtime.h>
 
-#include <utility>
-
 #include <cstdint>
+#include <cstring>
+#include <utility>
 
 #include "stq_device.h"
 #include "stq_tables.h"
@@ -194,6 +194,17 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, uint64_t wo
 __global__ __launch_bounds__(256) void upload_kernel(uint4* dst, const uint4* pinned, uint64_t n) {
   const uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i < n) dst[i] = pinned[i];
+}
+
+// The same with the table in the launch's own arguments, for a launch that is recorded into a graph: a replay finds them
+// unchanged, where a staging slot would by then hold a later call's table.
+struct UploadChunk {
+  uint4 part[240];  // (3840 bytes: a launch takes 4096 bytes of arguments)
+};
+constexpr uint64_t kChunkParts = sizeof(UploadChunk) / sizeof(uint4);
+static_assert(kChunkParts <= 256, "a thread for each");
+__global__ __launch_bounds__(256) void upload_by_value_kernel(uint4* dst, uint32_t n, const UploadChunk chunk) {
+  if (threadIdx.x < n) dst[threadIdx.x] = chunk.part[threadIdx.x];
 }
 
 // --------------------------------------------------- gradient statistics kernel
@@ -404,6 +415,18 @@ int launch_upload(void* dst, const void* pinned, uint64_t bytes, void* stream) {
   hipLaunchKernelGGL(upload_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
                      static_cast<uint4*>(dst), static_cast<const uint4*>(pinned), n);
   return static_cast<int>(hipGetLastError());
+}
+
+int launch_upload_by_value(void* dst, const void* host, uint64_t bytes, void* stream) {
+  for (uint64_t at = 0; at < bytes; at += sizeof(UploadChunk)) {
+    UploadChunk chunk;
+    const uint64_t here = bytes - at < sizeof(UploadChunk) ? bytes - at : sizeof(UploadChunk);
+    std::memcpy(&chunk, static_cast<const char*>(host) + at, here);
+    hipLaunchKernelGGL(upload_by_value_kernel, dim3(1), dim3(256), 0, static_cast<hipStream_t>(stream),
+                       reinterpret_cast<uint4*>(static_cast<char*>(dst) + at), static_cast<uint32_t>(here / sizeof(uint4)), chunk);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return static_cast<int>(e);
+  }
+  return 0;
 }
 
 int launch_fill_zero(uint32_t* p, uint64_t words, void* stream) {

@@ -63,3 +63,122 @@ def test_recorded_step_replays_like_the_eager_step(tickets, kind):
     finally:
         for c in ctxs:
             c.close()
+
+
+# Calls that bring a table with them: recorded, then many calls of the same kind with tables of their own (as many as there are
+# staging slots and more), then replays.  Everything else in the two contexts is alike, call for call.  The other calls' tables
+# have the same sizes.  90 tensors: two launches' arguments and a part of a third; 500: two of gradient addresses.
+def uploading_models(ctx, n, seed):
+    w = configs.Workload(seed, "graph", [("t%d" % l, 1 + (977 * l) % 3000) for l in range(n)], 64, "fp32", 1, "normal_per_tensor")
+    dm = DeviceModel(ctx, w, [(2 + l % 7, 2 + l % 5) for l in range(n)], spare_width=8)
+    for lst in (dm.m_codes, dm.v_codes):
+        for l, buf in enumerate(lst):
+            buf[dm._code_words(dm.numel[l], dm.plan[l][0 if lst is dm.m_codes else 1]):] = 0
+    for s in dm._spare.values():
+        s.zero_()
+    dm.set_grads(1)
+    return dm
+
+
+def buffers(dm):
+    lists = (dm.param, dm.m_scales, dm.v_scales, dm.m_codes, dm.v_codes)
+    return [t.view(torch.int32).clone() for lst in lists for t in lst] + [t.clone() for t in dm._spare.values()]
+
+
+class Uploading:
+    """One kind of call on a context, with a model of its own for every set of arguments."""
+
+    def __init__(self, kind, n, stream):
+        self.kind, self.n, self.s = kind, n, stream.cuda_stream
+        self.ctx = stq.Context(0, 512)
+        self.dm, self.other = uploading_models(self.ctx, n, 86), [uploading_models(self.ctx, n, 87 + k) for k in range(2 if kind == "engine" else 6)]
+        if kind == "engine":
+            dm = self.dm
+            second = [(dm._spare[(l, 0)].data_ptr(), dm._spare[(l, 1)].data_ptr()) for l in range(n)]
+            self.eng = self.ctx.engine(dm.tensors, second, dm.cplan, 8, 64, thr=(6.8,), bits=(4, 8), stream=self.s)
+
+    def call(self, dm, t):
+        if self.kind == "step":
+            self.ctx.step(dm.tensors, dm.cplan, hparams(dm.w, t), self.s)
+        elif self.kind == "static":
+            self.ctx.step_static(dm.tensors, dm.cplan, hparams(dm.w, t), self.s)
+        elif self.kind == "grad":
+            self.ctx.grad_stats(dm.tensors, 64, 0, self.s)
+        elif self.kind == "engine":  # (a step without a decision)
+            self.eng.step(hparams(self.dm.w, t + 4), 0, [g.data_ptr() for g in dm.grad], self.s)
+        else:
+            new = [(2 + (m + l) % 7, 2 + (v + l) % 7) for l, (m, v) in enumerate(dm.plan)]
+            if self.kind == "transition":
+                dst = [tuple(dm._spare[(l, k)].data_ptr() if new[l][k] != dm.plan[l][k] else None for k in (0, 1)) for l in range(self.n)]
+                self.ctx.step_transition(dm.tensors, dm.cplan, stq.binding.make_plan(new), dst, hparams(dm.w, t), self.s)
+            else:
+                self.ctx.repack_many([(dm.numel[l], k, cur[l].data_ptr(), dm.plan[l][k], dm._spare[(l, k)].data_ptr(), new[l][k])
+                                      for l in range(self.n) for k, cur in ((0, dm.m_codes), (1, dm.v_codes))], 64, self.s)
+
+    def results(self):
+        torch.cuda.synchronize()
+        out = [b for dm in [self.dm] + self.other for b in buffers(dm)]
+        if self.kind == "grad":
+            out.append(torch.tensor([(s.g_sum, s.g_abs_sum, s.g_sq_sum, s.g_absmax) for s in self.ctx.stats(self.n, self.s)], dtype=torch.float64))
+        return out
+
+
+def same_results(a, b, tag):
+    for l, (x, y) in enumerate(zip(a, b)):
+        if x.dtype != torch.float64:
+            assert torch.equal(x, y), (tag, l)
+        else:  # sums in fp64 in another order: n * 2^-53 of the sum of absolute values, n <= 3000
+            assert torch.equal(x[:, 3], y[:, 3]) and (x[:, 3] > 0).all(), tag
+            assert ((x - y)[:, :2].abs() <= 1e-12 * x[:, 1:2]).all() and ((x - y)[:, 2].abs() <= 1e-12 * x[:, 2]).all(), tag
+
+
+@pytest.mark.parametrize("kind,n", [("step", 3), ("step", 90), ("transition", 90), ("static", 3), ("static", 90), ("grad", 90), ("repack", 90),
+                                    ("engine", 3), ("engine", 500)])
+def test_recorded_uploads_outlive_the_calls_that_follow(kind, n):
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ref, rec = Uploading(kind, n, side), Uploading(kind, n, side)
+        try:
+            side.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                rec.call(rec.dm, 7)
+            if kind != "grad":
+                same_results(ref.results(), rec.results(), "recording alone does nothing")
+            for replay in range(3):
+                for u in (ref, rec):  # 40 uploads
+                    for k in range(40):
+                        u.call(u.other[k % len(u.other)], 8 + k)
+                if kind == "grad":  # clear the accumulators: what follows is the recorded call's, and a count for it
+                    for u in (ref, rec):
+                        u.ctx.stats(n, u.s)
+                        for g in u.other[0].grad:
+                            g.zero_()
+                        u.call(u.other[0], 1)
+                graph.replay()
+                ref.call(ref.dm, 7)
+                same_results(ref.results(), rec.results(), replay)
+                junk = torch.ones(1 << 20, device="cuda")  # eager work of the program between the replays
+                junk.mul_(2.0)
+                side.synchronize()
+        finally:
+            for u in (ref, rec):
+                if kind == "engine":
+                    u.eng.close()
+                u.ctx.close()
+
+
+def test_a_table_that_was_only_recorded_is_uploaded_by_the_next_call():
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ref, rec = Uploading("step", 3, side), Uploading("step", 3, side)
+        try:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                rec.call(rec.dm, 1)
+            for u in (ref, rec):
+                u.call(u.dm, 1)
+            same_results(ref.results(), rec.results(), "the eager call")
+        finally:
+            for u in (ref, rec):
+                u.ctx.close()
