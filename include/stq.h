@@ -19,9 +19,10 @@
  *     stq_zero_state, stq_step, stq_step_transition, stq_repack and stq_repack_many
  *     are asynchronous on that stream; stq_stats synchronises it.  stq_step,
  *     stq_step_transition and stq_grad_stats keep the tensor tables of the last four
- *     distinct argument sets on the device: a call whose tensors, plan and block size
+ *     distinct argument sets (or more) on the device: a call whose tensors, plan and block size
  *     equal one of those, on the same stream, is one kernel launch and nothing else
- *     (no upload, no wait, no allocation).  Any other call, and every stq_repack and
+ *     (no upload, no wait, no allocation).  Recorded into a HIP graph it keeps its table for as long as the
+ *     context lives (the first four tables that are recorded; launches with others bring theirs along, as follows).  Any other call, and every stq_repack and
  *     stq_repack_many, first uploads a small table from pinned host memory (sixteen staging slots
  *     in turn; a slot whose last upload has not finished yet is waited for).  While hip_stream is
  *     being captured the table travels in the arguments of small kernel launches instead, so a

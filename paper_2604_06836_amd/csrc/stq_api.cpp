@@ -150,8 +150,8 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   bool ok = g.ok;
   ok = ok && static_scratch_address(device, &c->static_scratch) == STQ_OK;
   ok = ok && hipMalloc(&c->d_tables, img.size() * 4) == hipSuccess;
-  for (int k = 0; k <= kRecordedTable && ok; ++k)
-    ok = ok && hipMalloc(&c->d_desc[k], sizeof(TensorDesc) * max_tensors) == hipSuccess;
+  ok = ok && hipMalloc(&c->d_desc[0], sizeof(TensorDesc) * max_tensors * (kRecordedTable + 1)) == hipSuccess;
+  for (int k = 1; k <= kRecordedTable && ok; ++k) c->d_desc[k] = c->d_desc[0] + static_cast<size_t>(max_tensors) * k;
   ok = ok && hipMalloc(&c->d_stats, sizeof(double) * kStatSlots * max_tensors) == hipSuccess;
   ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords) == hipSuccess;
   ok = ok && hipMemset(c->d_sched, 0, 4 * kSchedWords) == hipSuccess;
@@ -199,8 +199,7 @@ int stq_destroy(stq_ctx* c) {
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
   if (c->d_tables) (void)hipFree(c->d_tables);
-  for (TensorDesc* table : c->d_desc)
-    if (table) (void)hipFree(table);
+  if (c->d_desc[0]) (void)hipFree(c->d_desc[0]);
   if (c->d_stats) (void)hipFree(c->d_stats);
   if (c->d_sched) (void)hipFree(c->d_sched);
   if (c->h_stats) (void)hipHostFree(c->h_stats);
@@ -340,7 +339,9 @@ int upload_descs(stq_ctx* ctx, const std::vector<TensorDesc>& descs, TensorDesc*
 
 // Index of a device-resident tensor table that holds `descs`: one that already does (uploaded on this
 // same stream, so the kernel is ordered after the upload), else the oldest, overwritten in stream order
-// (after the kernels that read it).  A recorded upload has not happened yet: its table is one that no call takes to be there.
+// (after the kernels that read it).  A launch that is recorded reads its table at every replay, so one on the device is held
+// from then on, and where that cannot be, the table is uploaded with the launch, into one that no call takes to be there
+// (recording it uploads nothing yet).
 int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream_t s, int* out) {
   const size_t n = descs.size();
   int table = -1;
@@ -348,10 +349,17 @@ int resident_table(stq_ctx* ctx, const std::vector<TensorDesc>& descs, hipStream
     if (ctx->uploaded_on[k] == s && ctx->uploaded[k].size() == n &&
         std::memcmp(ctx->uploaded[k].data(), descs.data(), sizeof(TensorDesc) * n) == 0)
       table = k;
-  if (table < 0 && recording(s)) {
-    table = kRecordedTable;
-    if (int e = upload_descs(ctx, descs, ctx->d_desc[table], s)) return e;
+  if (recording(s)) {
+    if (table >= 0 && !ctx->held[table] && ctx->n_held < kHeldTables) {
+      ctx->held[table] = true;
+      ++ctx->n_held;
+    }
+    if (table < 0 || !ctx->held[table]) {
+      table = kRecordedTable;
+      if (int e = upload_descs(ctx, descs, ctx->d_desc[table], s)) return e;
+    }
   } else if (table < 0) {
+    while (ctx->held[ctx->desc_pos]) ctx->desc_pos = (ctx->desc_pos + 1) % kDescTables;
     table = ctx->desc_pos;
     ctx->uploaded[table].clear();  // whatever happens below, the old contents are no longer claimed
     if (int e = upload_descs(ctx, descs, ctx->d_desc[table], s)) return e;

@@ -14,8 +14,9 @@ namespace stq {
 
 constexpr int kRing = 16;       // pinned staging slots of a kind of upload, in two halves with an event each (see take_slot)
 constexpr uint64_t kTicketMinTiles = 4096;  // launches of at least this many tiles, 8.4 M elements, draw tickets (see launch_table)
-constexpr int kDescTables = 4;  // device-resident tensor tables kept: a caller that alternates between a
+constexpr int kDescTables = 8;  // device-resident tensor tables kept: a caller that alternates between a
                                 // few argument sets (two gradient buffers, say) uploads each only once
+constexpr int kHeldTables = 4;  // of these, at most so many are never written again, since a recorded launch reads them
 constexpr int kRecordedTable = kDescTables;  // one more, written by recorded launches only, each of which uploads it anew
 
 }  // namespace stq
@@ -26,7 +27,7 @@ struct stq_ctx {
   uint32_t n_cu = 0;
   uint64_t ticket_min_tiles = stq::kTicketMinTiles;  // see stq_set_schedule
   uint32_t* d_tables = nullptr;
-  stq::TensorDesc* d_desc[stq::kDescTables + 1] = {};
+  stq::TensorDesc* d_desc[stq::kDescTables + 1] = {};  // parts of one allocation
   double* d_stats = nullptr;
   uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches)
   stq::TensorDesc* h_stage[stq::kRing] = {};  // pinned
@@ -39,7 +40,9 @@ struct stq_ctx {
   int jobs_pos = 0;
   double* h_stats = nullptr;                 // pinned, max_tensors * kStatSlots
   std::vector<stq::TensorDesc> uploaded[stq::kDescTables];  // what each d_desc currently holds
-  hipStream_t uploaded_on[stq::kDescTables] = {nullptr, nullptr, nullptr, nullptr};  // the stream that uploaded it
+  hipStream_t uploaded_on[stq::kDescTables] = {};            // the stream that uploaded it
+  bool held[stq::kDescTables] = {};                          // a recorded launch reads it
+  int n_held = 0;
   std::vector<stq::TensorDesc> descs;        // descriptors of the call in progress (capacity max_tensors)
   void* static_scratch = nullptr;            // this device's static table of stq_step_static
   int desc_pos = 0;                          // next table to replace

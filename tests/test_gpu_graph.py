@@ -182,3 +182,33 @@ def test_a_table_that_was_only_recorded_is_uploaded_by_the_next_call():
         finally:
             for u in (ref, rec):
                 u.ctx.close()
+
+
+def test_recorded_launches_keep_their_resident_tables():
+    """Six argument sets that are on the device when they are recorded (more than the context holds for recordings), then calls
+    with more other sets than there are tables, then replays."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ref, rec = Uploading("step", 3, side), Uploading("step", 3, side)
+        others = [uploading_models(ref.ctx, 3, 95 + k) for k in range(9)], [uploading_models(rec.ctx, 3, 95 + k) for k in range(9)]
+        try:
+            graphs = [torch.cuda.CUDAGraph() for _ in range(6)]
+            for k, graph in enumerate(graphs):
+                for u in (ref, rec):
+                    u.call(u.other[k], 1)  # eager: uploads the table
+                with torch.cuda.graph(graph, stream=side):
+                    rec.call(rec.other[k], 2)
+            for replay in range(2):
+                for u, more in zip((ref, rec), others):
+                    for _ in range(2):
+                        for dm in more:
+                            u.call(dm, 3)
+                for k, graph in enumerate(graphs):
+                    graph.replay()
+                    ref.call(ref.other[k], 2)
+                same_results(ref.results(), rec.results(), replay)
+                for a, b in zip(*others):
+                    same_results(buffers(a), buffers(b), replay)
+        finally:
+            for u in (ref, rec):
+                u.ctx.close()
