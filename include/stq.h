@@ -30,7 +30,9 @@
  *     tables.  (The step number reaches the kernel as launch arguments, so a recorded launch repeats its own step.)  stq_engine_step is asynchronous too; with
  *     grads = NULL it consists of kernel launches only.
  *   - One context serves one stream at a time.  Calls on one context must not
- *     overlap from several host threads.  A context may move to another stream after
+ *     overlap from several host threads.  (Calls that overlap on several streams all the same share the
+ *     tables, staging slots and accumulators: a step may run on another call's tensors, and no error
+ *     is returned.  The engines of a context each have their own, so steps of several engines may overlap on several streams.)  A context may move to another stream after
  *     the caller has ordered the new stream behind the old one's work; tensor tables
  *     are then uploaded again on the new stream.
  *   - Gradients, parameters and hyper-parameters must be finite.  A non-finite

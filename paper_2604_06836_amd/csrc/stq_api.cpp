@@ -153,8 +153,8 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   ok = ok && hipMalloc(&c->d_desc[0], sizeof(TensorDesc) * max_tensors * (kRecordedTable + 1)) == hipSuccess;
   for (int k = 1; k <= kRecordedTable && ok; ++k) c->d_desc[k] = c->d_desc[0] + static_cast<size_t>(max_tensors) * k;
   ok = ok && hipMalloc(&c->d_stats, sizeof(double) * kStatSlots * max_tensors) == hipSuccess;
-  ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords) == hipSuccess;
-  ok = ok && hipMemset(c->d_sched, 0, 4 * kSchedWords) == hipSuccess;
+  ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords * (kRecordedTable + 1)) == hipSuccess;
+  ok = ok && hipMemset(c->d_sched, 0, 4 * kSchedWords * (kRecordedTable + 1)) == hipSuccess;
   ok = ok && hipHostMalloc(&c->h_stats, sizeof(double) * kStatSlots * max_tensors, hipHostMallocDefault) == hipSuccess;
   for (int k = 0; k < kRing && ok; ++k) {
     ok = ok && hipHostMalloc(&c->h_stage[k], sizeof(TensorDesc) * max_tensors, hipHostMallocDefault) == hipSuccess;
@@ -295,7 +295,7 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
   if (const char* e = std::getenv("STQ_LG_PARTS")) { lg_parts = std::strtoul(e, nullptr, 10) == 2 ? 2 : 1; per_cu = lg_parts == 2 ? 3 : 2; }
   if (const char* e = std::getenv("STQ_GROUPS_PER_CU")) per_cu = std::strtoul(e, nullptr, 10);
 #endif
-  w.sched = !draws ? nullptr : (sched ? sched : ctx->d_sched);
+  w.sched = draws ? sched : nullptr;
   w.unit_rows = 8u >> lg_parts;
   const uint64_t units = static_cast<uint64_t>(total) << lg_parts;
   const uint64_t need_groups = (units + wpg - 1) / wpg, max_groups = static_cast<uint64_t>(ctx->n_cu) * per_cu;
@@ -420,7 +420,8 @@ int step_impl(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, const stq_bit
   if (int e = resident_table(ctx, descs, s, &table)) return e;
 
   const int mode = mode_of(descs.data(), n, new_plan != nullptr);
-  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, stream)) return e;
+  uint32_t* const sched = ctx->d_sched + static_cast<size_t>(table) * kSchedWords;
+  if (int e = launch_table(ctx, ctx->d_desc[table], n, total, ctx->d_stats, hp, mode, stream, sched)) return e;
   if ((hp->flags & (STQ_FLAG_STATS | STQ_FLAG_STATS_GRAD)) != 0)
     for (uint32_t l = 0; l < n; ++l) ctx->stat_count[l] += tensors[l].numel;
   return STQ_OK;

@@ -201,6 +201,7 @@ struct stq_engine {
   TensorDesc* d_desc = nullptr;
   double* d_stats = nullptr;
   double* d_fac = nullptr;
+  uint32_t* d_sched = nullptr;  // ticket counters of its launches (see stq_ctx)
   double* d_ema = nullptr;
   double* d_score = nullptr;
   uint32_t** d_spare = nullptr;
@@ -219,6 +220,7 @@ int stq_engine_destroy(stq_engine* e) {
   if (e->d_desc) (void)hipFree(e->d_desc);
   if (e->d_stats) (void)hipFree(e->d_stats);
   if (e->d_fac) (void)hipFree(e->d_fac);
+  if (e->d_sched) (void)hipFree(e->d_sched);
   if (e->d_ema) (void)hipFree(e->d_ema);
   if (e->d_score) (void)hipFree(e->d_score);
   if (e->d_spare) (void)hipFree(e->d_spare);
@@ -293,6 +295,7 @@ int stq_engine_create(stq_ctx* ctx, stq_engine** out, const stq_tensor* tensors,
   ok = ok && hipMalloc(&e->d_desc, sizeof(TensorDesc) * n) == hipSuccess;
   ok = ok && hipMalloc(&e->d_stats, sizeof(double) * kStatSlots * n) == hipSuccess;
   ok = ok && hipMalloc(&e->d_fac, sizeof(double) * 3 * n) == hipSuccess;
+  ok = ok && hipMalloc(&e->d_sched, 4 * kSchedWords) == hipSuccess;
   ok = ok && hipMalloc(&e->d_ema, sizeof(double) * 3) == hipSuccess;
   ok = ok && hipMalloc(&e->d_score, sizeof(double) * n) == hipSuccess;
   ok = ok && hipMalloc(&e->d_spare, sizeof(uint32_t*) * 2 * n) == hipSuccess;
@@ -304,6 +307,7 @@ int stq_engine_create(stq_ctx* ctx, stq_engine** out, const stq_tensor* tensors,
   ok = ok && hipMemcpyAsync(e->d_desc, descs.data(), sizeof(TensorDesc) * n, hipMemcpyHostToDevice, s) == hipSuccess;
   ok = ok && hipMemcpyAsync(e->d_spare, spare.data(), sizeof(uint32_t*) * 2 * n, hipMemcpyHostToDevice, s) == hipSuccess;
   ok = ok && hipMemcpyAsync(e->d_ema, ema0, sizeof(ema0), hipMemcpyHostToDevice, s) == hipSuccess;
+  ok = ok && launch_fill_zero(e->d_sched, kSchedWords, stream) == 0;
   ok = ok && launch_fill_zero(reinterpret_cast<uint32_t*>(e->d_stats), sizeof(double) * kStatSlots * n / 4, stream) == 0;
   ok = ok && launch_fill_zero(reinterpret_cast<uint32_t*>(e->d_score), sizeof(double) * n / 4, stream) == 0;
   ok = ok && hipStreamSynchronize(s) == hipSuccess;
@@ -400,7 +404,7 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
       if (int err = plan(true)) return err;
     }
     const int mode = e->wide ? 2 : (due ? 1 : 0);
-    if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream)) return err;
+    if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream, e->d_sched)) return err;
     if (due) return plan(false);  // the states now are what the step wrote
     return STQ_OK;
   }
@@ -408,7 +412,7 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
   h.flags = due ? STQ_FLAG_STATS_GRAD : 0u;  // the decision reads the gradient's sums only
   // kernel variant: the widths in the table differ from the stored ones only in the step after a decision
   const int mode = e->wide ? 2 : (e->pending ? 1 : 0);
-  if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream)) return err;
+  if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream, e->d_sched)) return err;
   if (due || e->pending) {
     if (int err = plan(due)) return err;
     e->pending = due;

@@ -29,7 +29,8 @@ struct stq_ctx {
   uint32_t* d_tables = nullptr;
   stq::TensorDesc* d_desc[stq::kDescTables + 1] = {};  // parts of one allocation
   double* d_stats = nullptr;
-  uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches)
+  uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches), kSchedWords for each of d_desc:
+                                 // launches that overlap although they should not then have counters of their own
   stq::TensorDesc* h_stage[stq::kRing] = {};  // pinned
   hipEvent_t stage_done[2] = {};
   int ring_pos = 0;
@@ -115,9 +116,8 @@ int build_descs(const stq_ctx* ctx, const stq_tensor* t, uint32_t n, const stq_b
 
 // Launches the step kernel over the device-resident table `d_desc` of n tensors / total_tiles tiles.
 // mode: 0 in place, 1 widths change, 2 some state is (or may become) 16 or 32 bits wide.
-// sched: the kSchedWords ticket counters the launch uses (null: the context's own).
+// sched: the kSchedWords ticket counters the launch uses, those of its table.
 int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t total_tiles, double* d_stats,
-                 const stq_hparams* hp, int mode, void* stream,
-                 uint32_t* sched = nullptr);
+                 const stq_hparams* hp, int mode, void* stream, uint32_t* sched);
 
 }  // namespace stq

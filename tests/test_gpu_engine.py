@@ -337,3 +337,59 @@ def test_checkpoint_with_a_waiting_decision(oracle, ctx):
         assert e.value.code == -7
     finally:
         eng2.close()
+
+
+def overlapping_models(ctx):
+    """Two models of different sizes, each large enough to keep the chip busy for a while."""
+    out = []
+    for k, sizes in enumerate(([2048 * 4000 + 5, 700, 2048 * 300], [2048 * 1500 - 1, 2048 * 900 + 77])):
+        plan = [(4, 8), (8, 4), (6, 4)][:len(sizes)]
+        mdl = Model(ctx, sizes, 128, plan, 8, False, 500 + k)
+        for i in range(2):
+            mdl.upload_grads(i, grads_of_step(sizes, False, 510 + 10 * k + i)(1))
+        out.append((mdl, plan))
+    torch.cuda.synchronize()
+    return out
+
+
+def all_buffers(mdl):
+    return [t.view(torch.int32) for t in mdl.param + [b for c in mdl.codes for b in c] + [s for pair in mdl.scales for s in pair]]
+
+
+@pytest.mark.parametrize("engines", [True, False])
+def test_launches_that_overlap_do_not_take_each_others_tiles(engines):
+    """Engines of one context that step on a stream each; and steps of the context itself with resident tables on two
+    streams that the caller did not order, which shall not leave tiles out either.  Tiles are drawn in both."""
+    got = []
+    for overlap in (False, True):
+        ctx = stq.Context(0, 8)
+        try:
+            ctx.set_schedule(1)
+            models = overlapping_models(ctx)
+            streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+            calls, engs = [], []
+            for (mdl, plan), st in zip(models, streams):
+                s = st.cuda_stream
+                if engines:
+                    eng = ctx.engine(mdl.tensors, mdl.second, mdl.cplan, 8, 128, thr=(6.8,), bits=(4, 8), stream=s)
+                    engs.append(eng)
+                    calls.append(lambda t, eng=eng, mdl=mdl, s=s: eng.step(binding.HParams(*HP.values(), t, 128, 0, 0), 3, mdl.grad_ptrs(t % 2), s))
+                else:
+                    calls.append(lambda t, mdl=mdl, s=s: ctx.step(mdl.tensors, mdl.cplan, binding.HParams(*HP.values(), t, 128, 0, 0), s))
+                calls[-1](1)
+                torch.cuda.synchronize()
+            for t in range(2, 14):
+                for call in calls:
+                    call(t)
+                    if not overlap:
+                        torch.cuda.synchronize()
+            torch.cuda.synchronize()
+            got.append([x.clone() for mdl, _ in models for x in all_buffers(mdl)])
+            if engines:
+                got[-1].append(torch.tensor([w for e in engs for pair in e.read()["stored"] for w in pair]))
+        finally:
+            for e in engs:
+                e.close()
+            ctx.close()
+    for l, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), l
