@@ -19,22 +19,25 @@
  *     stq_zero_state, stq_step, stq_step_transition, stq_repack and stq_repack_many
  *     are asynchronous on that stream; stq_stats synchronises it.  stq_step,
  *     stq_step_transition and stq_grad_stats keep the tensor tables of the last four
- *     distinct argument sets (or more) on the device: a call whose tensors, plan and block size
- *     equal one of those, on the same stream, is one kernel launch and nothing else
- *     (no upload, no wait, no allocation).  Recorded into a HIP graph it keeps its table for as long as the
- *     context lives (the first four tables that are recorded; launches with others bring theirs along, as follows).  Any other call, and every stq_repack and
- *     stq_repack_many, first uploads a small table from pinned host memory (sixteen staging slots
- *     in turn; a slot whose last upload has not finished yet is waited for).  While hip_stream is
- *     being captured the table travels in the arguments of small kernel launches instead, so a
- *     recorded call is kernel launches only as well, and its replays do not depend on later calls'
- *     tables.  (The step number reaches the kernel as launch arguments, so a recorded launch repeats its own step.)  stq_engine_step is asynchronous too; with
+ *     distinct argument sets (or more) on the device: a call whose tensors, plan and
+ *     block size equal one of those, on the same stream, is one kernel launch and
+ *     nothing else (no upload, no wait, no allocation).  Any other call, and every
+ *     stq_repack and stq_repack_many, first uploads a small table from pinned host
+ *     memory (staging slots in turn; the call waits only if more than sixteen uploads
+ *     of its kind are still under way).  stq_engine_step is asynchronous too; with
  *     grads = NULL it consists of kernel launches only.
+ *   - All of these calls but stq_stats can be recorded into a HIP graph as kernel launches,
+ *     whose replays do not depend on later calls: a table on the device that a recorded
+ *     launch reads is kept for as long as the context lives (up to four of them); any other
+ *     table travels in the arguments of launches of its own.  (The step number reaches the
+ *     kernel as launch arguments too, so a recorded launch repeats its own step.)
  *   - One context serves one stream at a time.  Calls on one context must not
- *     overlap from several host threads.  (Calls that overlap on several streams all the same share the
- *     tables, staging slots and accumulators: a step may run on another call's tensors, and no error
- *     is returned.  The engines of a context each have their own, so steps of several engines may overlap on several streams.)  A context may move to another stream after
+ *     overlap from several host threads.  A context may move to another stream after
  *     the caller has ordered the new stream behind the old one's work; tensor tables
- *     are then uploaded again on the new stream.
+ *     are then uploaded again on the new stream.  (Calls that overlap on several streams
+ *     all the same share tables, staging slots and accumulators: a step may then run on
+ *     another call's tensors, and no error says so.  The engines of a context each have
+ *     their own: steps of several engines may overlap on several streams.)
  *   - Gradients, parameters and hyper-parameters must be finite.  A non-finite
  *     gradient makes the codes of its tile meaningless (only the tensors' own
  *     buffers are written; no address depends on data).  It shows in the statistics:

@@ -156,11 +156,9 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors) {
   ok = ok && hipMalloc(&c->d_sched, 4 * kSchedWords * (kRecordedTable + 1)) == hipSuccess;
   ok = ok && hipMemset(c->d_sched, 0, 4 * kSchedWords * (kRecordedTable + 1)) == hipSuccess;
   ok = ok && hipHostMalloc(&c->h_stats, sizeof(double) * kStatSlots * max_tensors, hipHostMallocDefault) == hipSuccess;
-  for (int k = 0; k < kRing && ok; ++k) {
-    ok = ok && hipHostMalloc(&c->h_stage[k], sizeof(TensorDesc) * max_tensors, hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipHostMalloc(&c->h_jobs[k], sizeof(RepackJob) * 2 * max_tensors, hipHostMallocDefault) == hipSuccess;
-  }
-  for (int k = 0; k < 2 && ok; ++k) {
+  ok = ok && hipHostMalloc(&c->h_stage, sizeof(TensorDesc) * max_tensors * kRing, hipHostMallocDefault) == hipSuccess;
+  ok = ok && hipHostMalloc(&c->h_jobs, sizeof(RepackJob) * 2 * max_tensors * kRing, hipHostMallocDefault) == hipSuccess;
+  for (int k = 0; k < kRingGroups && ok; ++k) {
     ok = ok && hipEventCreateWithFlags(&c->stage_done[k], hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&c->jobs_done[k], hipEventDisableTiming) == hipSuccess;
   }
@@ -205,11 +203,9 @@ int stq_destroy(stq_ctx* c) {
   if (c->h_stats) (void)hipHostFree(c->h_stats);
   if (c->d_luts) (void)hipFree(c->d_luts);
   if (c->d_jobs) (void)hipFree(c->d_jobs);
-  for (int k = 0; k < kRing; ++k) {
-    if (c->h_jobs[k]) (void)hipHostFree(c->h_jobs[k]);
-    if (c->h_stage[k]) (void)hipHostFree(c->h_stage[k]);
-  }
-  for (int k = 0; k < 2; ++k) {
+  if (c->h_jobs) (void)hipHostFree(c->h_jobs);
+  if (c->h_stage) (void)hipHostFree(c->h_stage);
+  for (int k = 0; k < kRingGroups; ++k) {
     if (c->jobs_done[k]) (void)hipEventDestroy(c->jobs_done[k]);
     if (c->stage_done[k]) (void)hipEventDestroy(c->stage_done[k]);
   }
@@ -331,8 +327,9 @@ int upload_descs(stq_ctx* ctx, const std::vector<TensorDesc>& descs, TensorDesc*
   if (recording(s)) return launch_upload_by_value(dst, descs.data(), bytes, s) == 0 ? STQ_OK : STQ_EHIP;
   int k = -1;
   if (int e = take_slot(ctx->stage_done, &ctx->ring_pos, &k)) return e;
-  std::memcpy(ctx->h_stage[k], descs.data(), bytes);
-  const int launched = launch_upload(dst, ctx->h_stage[k], bytes, s);
+  TensorDesc* const slot = ctx->h_stage + static_cast<size_t>(ctx->max_tensors) * k;
+  std::memcpy(slot, descs.data(), bytes);
+  const int launched = launch_upload(dst, slot, bytes, s);
   if (int e = slot_in_use(ctx->stage_done, k, s)) return e;
   return launched == 0 ? STQ_OK : STQ_EHIP;
 }
@@ -563,8 +560,9 @@ int stq_repack_many(stq_ctx* ctx, const stq_repack_job* jobs, uint32_t n, uint32
   } else {
     int k = -1;
     if (int e = take_slot(ctx->jobs_done, &ctx->jobs_pos, &k)) return e;
-    std::memcpy(ctx->h_jobs[k], table.data(), sizeof(RepackJob) * n);
-    const int launched = launch_upload(ctx->d_jobs, ctx->h_jobs[k], sizeof(RepackJob) * n, stream);
+    RepackJob* const slot = ctx->h_jobs + 2 * static_cast<size_t>(ctx->max_tensors) * k;
+    std::memcpy(slot, table.data(), sizeof(RepackJob) * n);
+    const int launched = launch_upload(ctx->d_jobs, slot, sizeof(RepackJob) * n, stream);
     if (int e = slot_in_use(ctx->jobs_done, k, s)) return e;
     if (launched != 0) return STQ_EHIP;
   }

@@ -205,8 +205,8 @@ struct stq_engine {
   double* d_ema = nullptr;
   double* d_score = nullptr;
   uint32_t** d_spare = nullptr;
-  const void** h_grads[kRing] = {};  // pinned
-  hipEvent_t grads_done[2] = {};
+  const void** h_grads = nullptr;  // pinned, kRing slots of n
+  hipEvent_t grads_done[kRingGroups] = {};
   int grads_pos = 0;
   void* h_read = nullptr;  // pinned staging of stq_engine_read
 };
@@ -224,9 +224,7 @@ int stq_engine_destroy(stq_engine* e) {
   if (e->d_ema) (void)hipFree(e->d_ema);
   if (e->d_score) (void)hipFree(e->d_score);
   if (e->d_spare) (void)hipFree(e->d_spare);
-  for (int k = 0; k < kRing; ++k) {
-    if (e->h_grads[k]) (void)hipHostFree(e->h_grads[k]);
-  }
+  if (e->h_grads) (void)hipHostFree(e->h_grads);
   for (hipEvent_t done : e->grads_done)
     if (done) (void)hipEventDestroy(done);
   if (e->h_read) (void)hipHostFree(e->h_read);
@@ -299,7 +297,7 @@ int stq_engine_create(stq_ctx* ctx, stq_engine** out, const stq_tensor* tensors,
   ok = ok && hipMalloc(&e->d_ema, sizeof(double) * 3) == hipSuccess;
   ok = ok && hipMalloc(&e->d_score, sizeof(double) * n) == hipSuccess;
   ok = ok && hipMalloc(&e->d_spare, sizeof(uint32_t*) * 2 * n) == hipSuccess;
-  for (int k = 0; k < kRing; ++k) ok = ok && hipHostMalloc(&e->h_grads[k], sizeof(void*) * n, hipHostMallocDefault) == hipSuccess;
+  ok = ok && hipHostMalloc(&e->h_grads, sizeof(void*) * n * kRing, hipHostMallocDefault) == hipSuccess;
   for (hipEvent_t& done : e->grads_done) ok = ok && hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess;
   ok = ok && hipHostMalloc(&e->h_read, read_bytes, hipHostMallocDefault) == hipSuccess;
   // the uploads come from pageable host memory, so each call returns only after its source was read
@@ -370,8 +368,9 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
   } else if (grads) {
     int k = -1;
     if (int err = take_slot(e->grads_done, &e->grads_pos, &k)) return err;
-    std::memcpy(e->h_grads[k], grads, sizeof(void*) * e->n);
-    hipLaunchKernelGGL(set_grads_kernel, dim3((e->n + 255) / 256), dim3(256), 0, s, e->d_desc, e->h_grads[k], e->n);
+    const void** const slot = e->h_grads + static_cast<size_t>(e->n) * k;
+    std::memcpy(slot, grads, sizeof(void*) * e->n);
+    hipLaunchKernelGGL(set_grads_kernel, dim3((e->n + 255) / 256), dim3(256), 0, s, e->d_desc, slot, e->n);
     const bool launched = hipGetLastError() == hipSuccess;
     if (int err = slot_in_use(e->grads_done, k, s)) return err;
     if (!launched) return STQ_EHIP;

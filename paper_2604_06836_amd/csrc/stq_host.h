@@ -12,7 +12,8 @@
 
 namespace stq {
 
-constexpr int kRing = 16;       // pinned staging slots of a kind of upload, in two halves with an event each (see take_slot)
+constexpr int kRingGroups = 3, kRingGroup = 8;   // pinned staging slots of a kind of upload: groups with an event each (see
+constexpr int kRing = kRingGroups * kRingGroup;  // take_slot).  All but one group, sixteen uploads, may always be under way.
 constexpr uint64_t kTicketMinTiles = 4096;  // launches of at least this many tiles, 8.4 M elements, draw tickets (see launch_table)
 constexpr int kDescTables = 8;  // device-resident tensor tables kept: a caller that alternates between a
                                 // few argument sets (two gradient buffers, say) uploads each only once
@@ -31,13 +32,13 @@ struct stq_ctx {
   double* d_stats = nullptr;
   uint32_t* d_sched = nullptr;   // ticket counters of the step kernel (zero between launches), kSchedWords for each of d_desc:
                                  // launches that overlap although they should not then have counters of their own
-  stq::TensorDesc* h_stage[stq::kRing] = {};  // pinned
-  hipEvent_t stage_done[2] = {};
+  stq::TensorDesc* h_stage = nullptr;        // pinned, kRing slots of max_tensors
+  hipEvent_t stage_done[stq::kRingGroups] = {};
   int ring_pos = 0;
   uint32_t* d_luts = nullptr;                // every conversion table of the re-pack, kRepackLuts x 256 words
   stq::RepackJob* d_jobs = nullptr;          // 2 * max_tensors
-  stq::RepackJob* h_jobs[stq::kRing] = {};  // pinned
-  hipEvent_t jobs_done[2] = {};
+  stq::RepackJob* h_jobs = nullptr;          // pinned, kRing slots of 2 * max_tensors
+  hipEvent_t jobs_done[stq::kRingGroups] = {};
   int jobs_pos = 0;
   double* h_stats = nullptr;                 // pinned, max_tensors * kStatSlots
   std::vector<stq::TensorDesc> uploaded[stq::kDescTables];  // what each d_desc currently holds
@@ -63,18 +64,18 @@ inline int lg_block(uint32_t K) {
   switch (K) { case 64: return 6; case 128: return 7; case 256: return 8; default: return -1; }
 }
 
-// The next slot of a ring, to be written by the host.  Half of the ring's slots are free again once the event that followed
-// the last upload from one of them has passed (an event for each would put a barrier behind every upload).  Asking is cheap
+// The next slot of a ring, to be written by the host.  A group's slots are free again once the event that followed
+// the upload from the last of them has passed (an event for each slot would put a barrier behind every upload).  Asking is cheap
 // and almost always enough (the ring is long); waiting is the rare fallback -- on this runtime a wait on an event
 // can take as long as the work queued behind it.
 inline int take_slot(hipEvent_t* done, int* pos, int* slot) {
   const int k = *pos;
-  if (k % (kRing / 2) == 0) {
-    const hipEvent_t half = done[k / (kRing / 2)];
-    const hipError_t q = hipEventQuery(half);
+  if (k % kRingGroup == 0) {
+    const hipEvent_t group = done[k / kRingGroup];
+    const hipError_t q = hipEventQuery(group);
     if (q != hipSuccess) {
       (void)hipGetLastError();
-      if (q != hipErrorNotReady || hipEventSynchronize(half) != hipSuccess) return STQ_EHIP;
+      if (q != hipErrorNotReady || hipEventSynchronize(group) != hipSuccess) return STQ_EHIP;
     }
   }
   *pos = (k + 1) % kRing;
@@ -83,8 +84,8 @@ inline int take_slot(hipEvent_t* done, int* pos, int* slot) {
 }
 // After the upload from `slot` has been enqueued on s.
 inline int slot_in_use(hipEvent_t* done, int slot, hipStream_t s) {
-  if (slot % (kRing / 2) != kRing / 2 - 1) return STQ_OK;
-  return hipEventRecord(done[slot / (kRing / 2)], s) == hipSuccess ? STQ_OK : STQ_EHIP;
+  if (slot % kRingGroup != kRingGroup - 1) return STQ_OK;
+  return hipEventRecord(done[slot / kRingGroup], s) == hipSuccess ? STQ_OK : STQ_EHIP;
 }
 
 // Whether work enqueued on s is recorded into a graph instead of run.  What a recorded launch reads at its replays must not

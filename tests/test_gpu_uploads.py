@@ -56,3 +56,59 @@ def test_job_tables(ctx, n):
     torch.cuda.synchronize()
     for l, (x, y) in enumerate(zip(*dst)):
         assert torch.equal(x, y), l
+
+
+@pytest.mark.parametrize("kind", ["step", "repack", "engine"])
+def test_sixteen_uploads_ahead_of_the_device(kind):
+    """Sixteen calls that upload a table each return while the stream is still busy with earlier work, whichever staging slot
+    they begin at, and their results are those of calls that were waited for."""
+    import paper_2604_06836_amd as stq
+    from paper_2604_06836_amd import binding
+    from workloads.harness import hparams
+    n, K, got = 3, 64, []
+    for ahead in (False, True):
+        c = stq.Context(0, 8)
+        m = model(c, [700, 2049, 5], [(4, 4)] * n, K, 93, "fp32")
+        for lst in (m.m_codes, m.v_codes):  # nothing undefined behind the codes
+            for l, buf in enumerate(lst):
+                buf[m._code_words(m.numel[l], 4):] = 0
+        grads = []
+        for k in range(7):
+            m.set_grads(k + 1)
+            grads.append([g.clone() for g in m.grad])
+        out = [[torch.zeros_like(m.m_codes[l]) for l in range(n)] for _ in range(17)]
+        eng = None
+        if kind == "engine":
+            eng = c.engine(m.tensors, [(m._spare[(l, 0)].data_ptr(), m._spare[(l, 1)].data_ptr()) for l in range(n)], m.cplan, 8, K,
+                           thr=(6.8,), bits=(4, 8), stream=m.stream)
+
+        def call(k, t):
+            if kind == "engine":  # (no decisions: past the first steps)
+                eng.step(hparams(m.w, t), 0, [g.data_ptr() for g in grads[t % 7]], m.stream)
+            elif kind == "repack":
+                c.repack_many([(m.numel[l], 0, m.m_codes[l].data_ptr(), 4, out[k][l].data_ptr(), 2 + t % 7) for l in range(n)], K, m.stream)
+            else:  # 21 argument sets in turn, more than there are tables
+                which = ([0, 1, 2], [0, 1], [1, 2])[t % 3]
+                sub = (binding.Tensor * len(which))(*[m.tensors[l] for l in which])
+                for x, l in zip(sub, which):
+                    x.grad = grads[t % 7][l].data_ptr()
+                c.step(sub, binding.make_plan([m.plan[l] for l in which]), hparams(m.w, t), m.stream)
+
+        for phase in range(24):  # 17 uploads each, so that every slot is the first of the sixteen once
+            if ahead:
+                torch.cuda._sleep(10_000_000)  # some milliseconds or more
+                busy = torch.cuda.Event()
+                busy.record()
+            for k in range(17):
+                if ahead and k == 16:
+                    assert not busy.query(), phase
+                if not ahead or k == 16:
+                    torch.cuda.synchronize()
+                call(k, 5 + 17 * phase + k)
+            torch.cuda.synchronize()
+        got.append([x.view(torch.int32).clone() for x in [*m.param, *m.m_codes, *m.v_codes, *m.m_scales, *m.v_scales, *sum(out, [])]])
+        if eng:
+            eng.close()
+        c.close()
+    for l, (x, y) in enumerate(zip(*got)):
+        assert torch.equal(x, y), l
