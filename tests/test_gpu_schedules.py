@@ -1,13 +1,15 @@
-"""The result of a step does not depend on how a launch cuts its tiles up: whole tiles under stripes or tickets, and quarter
-tiles (which the other GPU tests compare with the oracle on small inputs), give the same bits."""
+"""The result of a step does not depend on how a launch cuts its tiles up or on the order in which it takes them: drawn
+tickets, every workgroup's own, and launches of a tensor each give the same bits.  (The tests' names are older than the half
+and quarter tiles that launches consist of now.)"""
 import numpy as np
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
-# 25,394 tiles: whole tiles (see below); each tensor by itself: quarter tiles.  Ragged ends in the first, second and
-# last quarter of a tile, one tensor of whole tiles only.
+# 25,394 tiles in halves; by themselves the four large tensors are launches of halves too, of another number of workgroups and
+# tickets, the two small ones of quarters (test_gpu_units.py compares halves with quarters).  Ragged ends in the first, second
+# and last quarter of a tile, one tensor of whole tiles only.
 SIZES = [2048 * 6348 + 1, 2048 * 6349 - 900, 2048 * 6347, 2048 * 6348 + 777, 5, 2047]
 PLANS = {"in_place": [(3, 5), (7, 8), (2, 6), (8, 4), (5, 3), (6, 7)],
          "transition": [(5, 3), (8, 7), (6, 2), (4, 5), (3, 3), (7, 6)],
@@ -50,7 +52,6 @@ def outputs(m):
         [[m._spare[(l, s)].clone() for l in range(len(m.param)) for s in (0, 1)]]
 
 
-# (whole tiles under stripes: bf16 gradients and quantized widths only; every other launch of this size takes quarters there)
 @pytest.mark.parametrize("kind,dtype,tickets", [("in_place", "bf16", False), ("transition", "bf16", False)] +
                          [(kind, dtype, True) for kind in ("in_place", "transition", "wide") for dtype in ("bf16", "fp32")])
 @pytest.mark.parametrize("stats", [False, True, "grad"])
@@ -83,7 +84,7 @@ def test_whole_tiles_and_quarters_give_the_same_bits(ctx, kind, dtype, tickets, 
                             assert a == b, (l, f)
                         elif f == "g_sum":   # fp64 in another order: n * 2^-53 of the sum of absolute values
                             assert abs(a - b) <= 1e-12 * ref[2], (l, f)
-                        elif f == "m_sum":   # fp32 over a tile: 1e-5 of sqrt(n * sum of squares) >= the sum of absolute values
+                        elif f == "m_sum":   # of sqrt(n * sum of squares) >= the sum of absolute values (closer in test_gpu_units.py)
                             assert abs(a - b) <= 1e-5 * np.sqrt(SIZES[l] * ref[6]), (l, f)
                         else:
                             assert abs(a - b) <= (1e-12 if f.startswith("g_") else 1e-5) * abs(b) + SIZES[l] * 1.2e-38, (l, f)
@@ -126,7 +127,7 @@ MANY = {  # (sizes, tensors per launch of the reference: its waves never skip, o
 @pytest.mark.parametrize("many", sorted(MANY))
 @pytest.mark.parametrize("tickets,stats", [(False, False), (True, False), (True, True)])
 def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, stats, many):
-    """Launches whose stripes and tickets skip none, a few, dozens and thousands of tensors, against launches of a few."""
+    """Launches whose waves skip none, a few, dozens and thousands of tensors, drawn or not, against launches of a few."""
     sizes, few = MANY[many]
     plan = [(2 + i % 7, 2 + (i // 7) % 7) for i in range(len(sizes))]
     got, sums = [], []
@@ -154,25 +155,26 @@ def test_a_unit_lies_any_number_of_tensors_after_the_last(ctx, tickets, stats, m
 
 
 def test_many_small_tensors_are_not_walked_one_by_one(ctx):
-    """4000 tensors of 16,384 elements: a plain step, whose waves skip hundreds of tensors between their tiles, is no slower
-    than one that also gathers the gradient's statistics, whose waves stay in one range (a walk through all took 4.2 times as
-    long)."""
-    n = 4000
-    m = model(ctx, [16384] * n, [(8, 4)] * n, 128, 77)
-    m.set_grads(1)
+    """4000 tensors of 16,384 elements, of which a wave skips hundreds between its tiles, against the same number of elements
+    in four tensors, where there is nothing to skip (156 us against 125; a walk through all takes 849)."""
     best = {}
-    for stats in (False, "grad", False, "grad"):
-        launch_all = lambda: m.step(1, stats)  # noqa: E731
-        launch_all()
-        for _ in range(5):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            a.record()
-            launch_all()
-            b.record()
-            torch.cuda.synchronize()
-            best[stats] = min(best.get(stats, 1e9), a.elapsed_time(b))
-    ctx.stats(n, m.stream)
-    assert best[False] < 1.7 * best["grad"], best
+    for n in (4000, 4):
+        m = model(ctx, [16384 * (4000 // n)] * n, [(8, 4)] * n, 128, 77)
+        m.set_grads(1)
+        for stats in (False, "grad"):
+            for k in range(8):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                m.step(1, stats)
+                b.record()
+                torch.cuda.synchronize()
+                if k > 1:
+                    best[n, stats] = min(best.get((n, stats), 1e9), a.elapsed_time(b))
+        if stats:
+            ctx.stats(n, m.stream)
+        del m
+    for stats in (False, "grad"):
+        assert best[4000, stats] < 2.5 * best[4, stats], best
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])

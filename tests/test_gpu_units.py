@@ -1,6 +1,6 @@
-"""Half and quarter tiles give the same bits, on both sides of every line at which the launch changes its units or its order:
-each tensor by itself is a launch of quarter tiles (which the other GPU tests compare with the oracle), all together one of the
-size asked for."""
+"""Half and quarter tiles give the same bits, on both sides of every line at which the launch changes its units, its order, its
+counters or its workgroups: each tensor by itself is a launch of quarter tiles (which the other GPU tests compare with the
+oracle), all together one of the size asked for."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +15,7 @@ WIDTHS = {"in_place": [2, 3, 4, 5, 6, 7, 8], "transition": [2, 3, 4, 5, 6, 7, 8]
 @pytest.fixture(scope="module")
 def ctx():
     import paper_2604_06836_amd as stq
-    c = stq.Context(0, 256)
+    c = stq.Context(0, 2048)
     yield c
     c.close()
 
@@ -36,7 +36,26 @@ def sizes_of(tiles, n_cu):
                                                 ("transition", "bf16", 64, "grad"), ("wide", "fp32", 64, False), ("wide", "bf16", 128, True)])
 def test_halves_and_quarters_give_the_same_bits(ctx, per_cu, more, kind, dtype, K, stats):
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    sizes = sizes_of(per_cu * n_cu + more, n_cu)
+    compare(ctx, sizes_of(per_cu * n_cu + more, n_cu), kind, dtype, K, stats)
+
+
+# wide states with fp32 gradients: two workgroups per CU below 30,000 tiles, one from there on; eight counters below 100,000
+# tiles, then one
+@pytest.mark.parametrize("tiles,kind,dtype,K,stats", [(29_999, "wide", "fp32", 64, False), (30_000, "wide", "fp32", 64, False),
+                                                      (30_000, "wide", "fp32", 256, True), (99_999, "in_place", "bf16", 128, False),
+                                                      (100_000, "in_place", "bf16", 128, False), (100_000, "in_place", "fp32", 64, "grad")])
+def test_lines_of_large_launches(ctx, tiles, kind, dtype, K, stats):
+    compare(ctx, sizes_of(tiles, torch.cuda.get_device_properties(0).multi_processor_count), kind, dtype, K, stats)
+
+
+# with statistics, above one tile per CU: quarters below 16 tiles a tensor on average
+@pytest.mark.parametrize("stats", [True, "grad"])
+@pytest.mark.parametrize("tiles", [15, 16])
+def test_statistics_of_small_tensors(ctx, tiles, stats):
+    compare(ctx, [2048 * tiles - (l * 97) % 2048 for l in range(60)], "in_place", "fp32", 128, stats)
+
+
+def compare(ctx, sizes, kind, dtype, K, stats):
     w = WIDTHS[kind]
     plan = [(w[i % len(w)], w[(i // len(w) + 2 * i) % len(w)]) for i in range(len(sizes))]
     new = [(b, a) for a, b in plan] if kind != "in_place" else None
@@ -54,7 +73,8 @@ def test_halves_and_quarters_give_the_same_bits(ctx, per_cu, more, kind, dtype, 
             for g in [list(range(len(sizes)))] if together else [[l] for l in range(len(sizes))]:
                 launch(ctx, m, t, g, new, stats)
                 if stats:
-                    sums[-1] += [(s.count, s.g_absmax, s.m_absmax, s.v_absmax, s.g_sq_sum, s.m_sq_sum, s.v_err_sq) for s in ctx.stats(len(g), m.stream)]
+                    sums[-1] += [(s.count, s.g_absmax, s.m_absmax, s.v_absmax, s.g_sum, s.m_sum, s.g_abs_sum, s.g_sq_sum, s.m_sq_sum, s.m_err_sq,
+                                  s.v_sum, s.v_sq_sum, s.v_err_sq) for s in ctx.stats(len(g), m.stream)]
         got.append(outputs(m))
         del m
     for a, b in zip(*got):
@@ -62,6 +82,10 @@ def test_halves_and_quarters_give_the_same_bits(ctx, per_cu, more, kind, dtype, 
             assert torch.equal(x.view(torch.int32), y.view(torch.int32)), l
     for i, (a, b) in enumerate(zip(*sums)):
         assert a[:4] == b[:4], i
-        # non-negative terms: fp64 in another order, n * 2^-53; the moments' in fp32 over eight rows of a lane and eight lanes
-        assert abs(a[4] - b[4]) <= 1e-12 * a[4], i
-        assert np.allclose(a[5:], b[5:], rtol=1e-5, atol=2048 * n_cu * 1.2e-38), i
+        # Sums of the same numbers in another order, in fp64 (those of the moments' squares, of v and of the errors over eight
+        # elements of a lane in fp32 first, the same eight in halves and quarters).  No chain of additions is longer than 2000
+        # (a lane's elements, its units, the waves, the workgroups): 2000 * 2^-53 = 2.2e-13 of the sum of absolute values,
+        # for that of the first moments at most sqrt(n * sum of squares).
+        assert abs(a[4] - b[4]) <= 1e-12 * a[6] and abs(a[5] - b[5]) <= 1e-12 * np.sqrt(a[0] * a[8]), i
+        for x, y in zip(a[6:], b[6:]):
+            assert abs(x - y) <= 1e-12 * x, i

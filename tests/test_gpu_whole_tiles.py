@@ -1,6 +1,7 @@
-"""The whole-tile kernels against the oracle.  Launches as small as the other parity tests use take quarter tiles; here a filler
-tensor makes them large enough for whole ones: under tickets from 24 tiles per CU on, under stripes (bf16 gradients, quantized
-widths) from 25,000 tiles on.  The filler itself is compared with a launch of its own, which takes quarter tiles."""
+"""The kernels of half tiles against the oracle.  Launches as small as the other parity tests use take quarter tiles; here a
+filler tensor makes them large enough for halves, with tickets drawn ("tickets") or every workgroup's own ("stripes", on 25,400
+tiles).  The filler itself is compared with a launch of its own, whose tickets are its workgroups' own.  (The names here are older
+than half tiles.)"""
 import numpy as np
 import pytest
 import torch
