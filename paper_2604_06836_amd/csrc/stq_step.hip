@@ -381,20 +381,19 @@ __device__ __forceinline__ void record_stats(LaneStats<S>& s, StatRecord<S>* rec
 // wave 0, after a barrier: the records of the workgroup's waves -> the tensor's global slots
 template <int S>
 __device__ __forceinline__ void flush_records(const StatRecord<S>* recs, double* slot, int lane) {
-  static_assert(kWavesPerGroup == 4 || kWavesPerGroup == 8, "lane k * waves + w takes value k of wave w's record");
+  static_assert(kWavesPerGroup == 8, "lane 8 k + w takes value k of wave w's record");
   asm volatile("" : "+v"(lane));
-  constexpr int kSums = S == 1 ? 9 : 3, kMaxima = S == 1 ? 3 : 1, kAtOnce = 64 / kWavesPerGroup;
-  constexpr bool kOctets = kWavesPerGroup == 8;
-  const StatRecord<S>& r = recs[lane & (kWavesPerGroup - 1)];
-  const int k = lane / kWavesPerGroup;
-  const bool lead = (lane & (kWavesPerGroup - 1)) == 0;
-  const double mine = k < kSums ? r.sum[k] : 0.0, x = kOctets ? octet_sum(mine) : quad_sum(mine);
+  constexpr int kSums = S == 1 ? 9 : 3, kMaxima = S == 1 ? 3 : 1;
+  const StatRecord<S>& r = recs[lane & 7];
+  const int k = lane >> 3;
+  const bool lead = (lane & 7) == 0;
+  const double x = octet_sum(k < kSums ? r.sum[k] : 0.0);
   if (lead && k < kSums) atomicAdd(&slot[kGSum + k], x);
-  if (kSums > kAtOnce) {
+  if (kSums > 8) {
     const double y = octet_sum(lane < 8 ? r.sum[kSums - 1] : 0.0);  // the ninth
     if (lane == 0) atomicAdd(&slot[kGSum + 8], y);
   }
-  const uint32_t top = k < kMaxima ? r.max_bits[k] : 0u, mx = kOctets ? octet_max(top) : quad_max(top);
+  const uint32_t mx = octet_max(k < kMaxima ? r.max_bits[k] : 0u);
   if (lead && k < kMaxima) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]) + k, mx);
 }
 

@@ -54,12 +54,6 @@ __device__ __forceinline__ double row_sum(double x) {
   x += dpp_f64<kDppMirror>(x);
   return x;
 }
-__device__ __forceinline__ float octet_sum(float x) {
-  x += u2f(dpp_u32<kDppXor1>(f2u(x)));
-  x += u2f(dpp_u32<kDppXor2>(f2u(x)));
-  x += u2f(dpp_u32<kDppHalfMirror>(f2u(x)));
-  return x;
-}
 __device__ __forceinline__ uint32_t quad_max(uint32_t x) {
   x = max(x, dpp_u32<kDppXor1>(x));
   x = max(x, dpp_u32<kDppXor2>(x));
