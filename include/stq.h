@@ -30,7 +30,9 @@
  *     whose replays do not depend on later calls: a table on the device that a recorded
  *     launch reads is kept for as long as the context lives (up to four of them); any other
  *     table travels in the arguments of launches of its own.  (The step number reaches the
- *     kernel as launch arguments too, so a recorded launch repeats its own step.)
+ *     kernel as launch arguments too, so a recorded launch repeats its own step; a recorded
+ *     stq_engine_step repeats the kernels of the step it was recorded at, so in the default
+ *     order record steps at which no decision is due or waiting.)
  *   - One context serves one stream at a time.  Calls on one context must not
  *     overlap from several host threads.  A context may move to another stream after
  *     the caller has ordered the new stream behind the old one's work; tensor tables
@@ -112,8 +114,8 @@ typedef struct {
 } stq_hparams;
 #define STQ_FLAG_STATS 1u      /* accumulate every per-layer statistic of stq_layer_stats during this step */
 #define STQ_FLAG_STATS_GRAD 2u /* accumulate only the gradient's (count, g_sum, g_abs_sum, g_sq_sum, g_absmax:
-                                  all that stq_decide reads); the moments' fields stay 0.  Cheaper (1 to 2 % of a
-                                  step against 7 %).  STQ_FLAG_STATS wins if both are set. */
+                                  all that stq_decide reads); the moments' fields stay 0.  Cheaper (4 to 8 % of a
+                                  step against 20 %).  STQ_FLAG_STATS wins if both are set. */
 
 /* Host copy of one layer's accumulated statistics (Section 3.3 inputs plus the
  * moments' own statistics and quantization error).  m and v are the new moments
@@ -155,7 +157,7 @@ int stq_init(stq_ctx** out, int device, uint32_t max_tensors);
  * statistics' sums differ in the last bits as with any other order of addition).  Launches of at least
  * `ticket_min_tiles` tiles (with bf16 gradients, or 16- or 32-bit states, half as many again) use the ticket
  * schedule: workgroups draw runs of neighbouring tiles from counters in device memory and their waves work on
- * them in step, so the chip sweeps every array front to back inside one compact window -- worth 10-20 % of
+ * them in step, so the chip sweeps every array front to back inside one compact window -- worth 10-25 % of
  * bandwidth on large workloads, nothing on small ones, where every workgroup takes tickets of its own.
  * 0 restores the default (about 8 M elements); UINT64_MAX never draws tickets.  Host only. */
 int stq_set_schedule(stq_ctx* ctx, uint64_t ticket_min_tiles);
@@ -185,11 +187,11 @@ int stq_step(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n,
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same step, the
  * same kernel and the same results, but the kernel's scratch memory -- the tensor table it reads
  * and the scheduling words of large launches -- lives in a static device array of the library
- * (STQ_STATIC_MAX_TENSORS entries of 96 bytes + 256 bytes, about 96 KiB per GPU, held until the
+ * (STQ_STATIC_MAX_TENSORS entries of 96 bytes + 2 KiB of counters, 98 KiB per GPU, held until the
  * process ends) instead of the context's buffers.  The call allocates nothing on host or device:
  * it fills a pinned staging slot of the context (under capture: the arguments of small launches),
- * copies it to the static table in stream order,
- * clears the scheduling words with a small kernel and launches.  n above STQ_STATIC_MAX_TENSORS gives STQ_ELIMIT
+ * copies it to the static table in stream order, clears the scheduling words with a small
+ * kernel and launches.  n above STQ_STATIC_MAX_TENSORS gives STQ_ELIMIT
  * (n above the context's max_tensors STQ_EINVAL).  Every call on a GPU, from any context, uses
  * that GPU's one table: calls that overlap on one GPU (two streams, two contexts) race; on one
  * stream they are ordered.  Statistics flags work as in stq_step (the context's accumulators). */

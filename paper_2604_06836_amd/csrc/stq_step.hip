@@ -7,7 +7,7 @@
 // -ffp-contract=off); division and square root are the correctly rounded ones.
 //
 // Work decomposition: one wavefront works on one part of a 2048-element tile at a time, a half (4 rows) or, in small
-// launches, a quarter (2 rows).  A half's working set fits the 128 registers of four waves per SIMD (108 to 125 in use), a
+// launches, a quarter (2 rows).  A half's working set fits the 128 registers of four waves per SIMD (107 to 124 in use), a
 // quarter's the 80 of six, with nothing spilled to scratch memory, so the kernel's HBM traffic is the algorithmic traffic.
 // In row i lane j holds the 4 elements 256*i + 4*j + e, so
 // every parameter and gradient access is a coalesced 16-byte (8-byte for bf16) per-lane access,
@@ -462,10 +462,10 @@ __device__ __forceinline__ void quantize_v(const float (&v)[4 * ROWS], uint32_t 
 //  kDirect: from the level itself with the IEEE routines, when a scale is out of the range the short forms need and there
 //          is no table of den.
 // FAST: the short form of the quotient, else the IEEE division.
-// (Vector instructions per parameter with these forms and quantize_v: 58.8 on a 3.5 G-parameter launch at widths 4..8 and
-// 3..6, K = 64, where IEEE-shaped expansions and a 514-entry search table took 67.3.  The launch is bound by the memory
-// system either way; launches that stay in the caches are not: 2.4 M parameters 8.7 us instead of 9.4.  A den table of
-// 256 entries, for levels that serve two elements, changed nothing: 7.51 ms against 7.43.)
+// (Vector instructions per parameter on a 3.5 G-parameter launch at widths 4..8 and 3..6, K = 64: 51.5.  What these forms and
+// quantize_v gave was measured when a wave took whole tiles: 58.8 instructions, with IEEE-shaped expansions and a 514-entry
+// search table 67.3; 2.4 M parameters, which stay in the caches, 8.7 us instead of 9.4, and the large launch, which the memory
+// system bounds, as before.  A den table of twice the entries, for levels that serve two elements, changed nothing then.)
 enum UpdateKind { kDenTable, kRoots, kDirect };
 template <int KIND, bool FAST, int ROWS>
 __device__ __forceinline__ void update_params(const float (&mq)[4 * ROWS], const uint32_t (&code)[4 * ROWS], float (&theta)[4 * ROWS],
@@ -799,8 +799,9 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
     wave_lds_sync();
   } else if (__builtin_expect(use_table, 0)) {
     // A scale or eps out of the short forms' range (small gradients, an eps such as 1e-30): den by the IEEE routines, still
-    // once per level; the quotients take the IEEE division.  (1.5 G parameters, K = 128, 5 bits, bf16 gradients: 3391 us,
-    // with a root per element 3521, in range 3263.  Where a level serves fewer elements the root is taken per element.)
+    // once per level; the quotients take the IEEE division.  (1.5 G parameters, K = 128, 5 bits, bf16 gradients: 3270 us,
+    // in range 3116; with a root per element it was 4 % more when a wave took whole tiles.  Where a level serves fewer elements
+    // the root is taken per element.)
     for (uint32_t e = lane; e < (256u * ROWS >> lgK) << bq; e += 64) {
       const uint32_t c = e & ((1u << bq) - 1u), rg = e >> bq;
       const uint32_t rw = rg >> (8 - lgK), blk = rg & ((1u << (8 - lgK)) - 1u);
@@ -886,7 +887,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       range.add(v[n]);
     }
     // The short forms where every element of the wave's part allows them (124 M parameters at widths drawn from
-    // {4, 8, 16, 32}: 468 us instead of 472 with the IEEE routines)
+    // {4, 8, 16, 32}: 390 us; 406 with an eps out of range, for which all states take the IEEE routines)
     if (eps_ok && __all(range.within(0x0F800000u, 0x66800000u)) && fast_m) {  // 2^-96, 2^78
 #pragma unroll
       for (int n = 0; n < N; ++n) {
@@ -965,7 +966,8 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 //    parameters: 26.9 us, with eight counters 22.5; 130 M: 268.8 and 266.9; 1.56 G: 3092 and 3120).  The workgroups of a
 //    counter have to be spread over the XCDs: with a counter for each XCD, which do not run at the same pace, the classes
 //    drift apart (1.56 G: 3590 us).
-//  * Else workgroup g takes the tickets g, g + G, ...: launches up to 16 M parameters, where there is nothing to keep in order.
+//  * Else workgroup g takes the tickets g, g + G, ...: launches below 8.4 M parameters (with bf16 gradients or wide states
+//    12.6 M; see launch_table), where there is nothing to keep in order.
 // With statistics a workgroup's waves keep their sums as long as its tickets start in the same tensor (see StatRecord).
 // Counters that start anew by themselves leave nothing to clear: every launch -- also a replayed one -- finds them at zero.
 // (A count of the workgroups that have left, with acquire and release, cost 20 us: each one writes back its L2.)
