@@ -30,9 +30,8 @@
  *     whose replays do not depend on later calls: a table on the device that a recorded
  *     launch reads is kept for as long as the context lives (up to four of them); any other
  *     table travels in the arguments of launches of its own.  (The step number reaches the
- *     kernel as launch arguments too, so a recorded launch repeats its own step; a recorded
- *     stq_engine_step repeats the kernels of the step it was recorded at, so in the default
- *     order record steps at which no decision is due or waiting.)
+ *     kernel as launch arguments too, so a recorded launch repeats its own step, and a recorded
+ *     stq_engine_step decides at every replay if it did so when it was recorded.)
  *   - One context serves one stream at a time.  Calls on one context must not
  *     overlap from several host threads.  A context may move to another stream after
  *     the caller has ordered the new stream behind the old one's work; tensor tables

@@ -196,6 +196,7 @@ struct stq_engine {
   std::vector<TensorDesc> h_desc;   // the table as created (for stq_engine_set_next, before the first step)
   std::vector<uint32_t*> h_spare;
   bool pending = false;   // the table holds widths/destinations that differ from the stored ones
+  bool replays_decide = false;  // ... or may do so without the host's knowledge: a step with a decision has been recorded
   double tau = 0.0;
   PlanCfg cfg;
   TensorDesc* d_desc = nullptr;
@@ -409,12 +410,18 @@ int stq_engine_step(stq_engine* e, const stq_hparams* hp, uint32_t update_every,
   }
   // by-product order: the step gathers the statistics, the decision takes effect in the next step
   h.flags = due ? STQ_FLAG_STATS_GRAD : 0u;  // the decision reads the gradient's sums only
+  // What a graph replays the host does not see.  Once a decision has been recorded, every step takes the one that may be waiting;
+  // so does a recorded step of the variant that writes to the table's destinations whether one is waiting or not.  (A recorded
+  // in-place step leaves it waiting.)
+  const bool rec = recording(s);
+  if (rec && due) e->replays_decide = true;
+  const bool pending = e->pending || e->replays_decide || (rec && e->wide);
   // kernel variant: the widths in the table differ from the stored ones only in the step after a decision
-  const int mode = e->wide ? 2 : (e->pending ? 1 : 0);
+  const int mode = e->wide ? 2 : (pending ? 1 : 0);
   if (int err = launch_table(e->ctx, e->d_desc, e->n, e->total_tiles, e->d_stats, &h, mode, stream, e->d_sched)) return err;
-  if (due || e->pending) {
+  if (due || pending) {
     if (int err = plan(due)) return err;
-    e->pending = due;
+    if (!rec) e->pending = due;
   }
   return STQ_OK;
 }

@@ -212,3 +212,95 @@ def test_recorded_launches_keep_their_resident_tables():
         finally:
             for u in (ref, rec):
                 u.ctx.close()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("alg1", [False, True])
+def test_recorded_steps_of_the_loop(alg1, wide):
+    """Steps with and without a decision, recorded while one was waiting or not, replayed in an order of their own among eager
+    steps: the same as the eager calls."""
+    bits = (4, 8, 16, 32) if wide else (3, 4, 6, 8)
+    side = torch.cuda.Stream()
+    sizes = [700, 2048 * 3, 5000, 9, 4097, 2048 * 2 + 1]
+    with torch.cuda.stream(side):
+        s = side.cuda_stream
+        both = []
+        for _ in range(2):
+            ctx = stq.Context(0, 8)
+            w = configs.Workload(97, "loop", [("t%d" % l, n) for l, n in enumerate(sizes)], 64, "fp32", 1, "normal_per_tensor")
+            dm = DeviceModel(ctx, w, [(4, 8)] * len(sizes), spare_width=32)
+            grads = []
+            for k in range(2):
+                dm.set_grads(k + 1)
+                grads.append([g.clone() for g in dm.grad])
+            second = [(dm._spare[(l, 0)].data_ptr(), dm._spare[(l, 1)].data_ptr()) for l in range(len(sizes))]
+            eng = ctx.engine(dm.tensors, second, dm.cplan, 32, 64, thr=(8.0, 11.0, 14.0), bits=bits, alg1_order=alg1, stream=s)
+            both.append((ctx, dm, eng, grads))
+        by_ptr = [{b.data_ptr(): b for b in [*dm.m_codes, *dm.v_codes, *dm._spare.values()]} for _, dm, _, _ in both]
+        widths = set()
+
+        def step(i, t, every, k):
+            _, dm, eng, grads = both[i]
+            eng.step(hparams(dm.w, t), every, [g.data_ptr() for g in grads[k]], s)
+
+        def check(tag):
+            side.synchronize()
+            a, b = (eng.read(s) for _, _, eng, _ in both)
+            assert a["stored"] == b["stored"] and a["next"] == b["next"], tag
+            widths.update(a["stored"])
+            for l, n in enumerate(sizes):
+                for k in (0, 1):
+                    words = both[0][1]._code_words(n, a["stored"][l][k])
+                    assert torch.equal(by_ptr[0][a["current"][l][k]][:words], by_ptr[1][b["current"][l][k]][:words]), (tag, l, k)
+                for x, y in ((both[i][1] for i in (0, 1)),):
+                    for name in ("param", "m_scales", "v_scales"):
+                        assert torch.equal(getattr(x, name)[l].view(torch.int32), getattr(y, name)[l].view(torch.int32)), (tag, l, name)
+
+        try:
+            graphs = {}
+
+            def record(name, t, every, k):
+                graphs[name] = (torch.cuda.CUDAGraph(), t, every, k)
+                with torch.cuda.graph(graphs[name][0], stream=side):
+                    step(1, t, every, k)
+
+            def replay(name):
+                graph, t, every, k = graphs[name]
+                graph.replay()
+                step(0, t, every, k)
+
+            def eager(*a):
+                step(0, *a)
+                step(1, *a)
+
+            record("plain", 11, 0, 0)             # nothing waits
+            eager(10, 10, 0)                      # a decision, which then waits (default order)
+            record("waiting", 12, 0, 1)
+            eager(13, 0, 0)                       # takes it, though the recorded step came first
+            check("eager")
+            eager(20, 10, 1)
+            if alg1 or wide:                      # (a recorded in-place step leaves the decision waiting, which no eager step does)
+                replay("plain")
+            replay("waiting")
+            check("a waiting decision")
+            record("decides", 30, 10, 1)
+            for n in range(3):
+                replay("decides")
+                check("decides %d" % n)
+            eager(31, 0, 0)
+            check("eager after a replayed decision")
+            replay("decides")
+            eager(40, 10, 0)
+            replay("waiting")
+            check("a decision after a replayed one")
+            replay("decides")
+            replay("decides")
+            eager(41, 0, 1)
+            eager(42, 0, 1)
+            replay("plain")
+            check("end")
+            assert len(widths) > 2, widths
+        finally:
+            for ctx, _, eng, _ in both:
+                eng.close()
+                ctx.close()
