@@ -213,14 +213,18 @@ __global__ __launch_bounds__(256) void upload_by_value_kernel(uint4* dst, uint32
 // precedes that step's layer loop.  One read of the gradients, and bound by it as long as the sums do not wait for each
 // other: a workgroup takes one contiguous range of tiles, its eight waves in turn, with the next tile's loads in flight
 // while a tile is added up; a lane keeps fp64 totals; what the waves hold at the end goes to the layer's accumulators
-// by one set of atomics per workgroup (one set per wave, 8192 of them on the
-// same words, took 127 us for 0.25 GB of bf16 gradients; now 45).
+// by one set of atomics per workgroup.
+// With read-back and decision, us: 0.12 G bf16 gradients in 148 tensors 78.5 before, now 75.5, 30 M fp32 in one tensor 42.5 and
+// 38.8, 400 ragged tensors of up to 0.4 M 98 and 93.5: the atomics of a workgroup's three sums were an instruction each (see
+// add_grad_sums), one lane added up the waves' sums, and a ragged tile was read four elements a lane at a time.  (Two tiles in
+// flight, with 16-byte loads: the same there, but 1.5 G bf16 gradients 482 where this takes 462; one set of atomics per
+// wave, 8192 of them on the same words, 127 for 0.12 G.)
 struct GradSums {
   double sum, abs, sq;
   float top;
 };
 
-// over the wave; complete in lane 0
+// over the wave; complete in every lane
 __device__ __forceinline__ GradSums wave_sums(GradSums s) {
   s.sum = row_sum(s.sum);
   s.abs = row_sum(s.abs);
@@ -237,11 +241,14 @@ __device__ __forceinline__ GradSums wave_sums(GradSums s) {
   return s;
 }
 
-__device__ __forceinline__ void add_grad_sums(double* slot, const GradSums& s) {
-  atomicAdd(&slot[kGSum], s.sum);
-  atomicAdd(&slot[kGAbsSum], s.abs);
-  atomicAdd(&slot[kGSqSum], s.sq);
-  atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]), f2u(s.top));
+// Sums that every lane holds -> the tensor's accumulators, by one instruction for the three sums: what adds to the same
+// cache line at the same time is taken in turn, at about 10 ns an instruction whatever the number of its lanes (256
+// workgroups: 2 us, and 11 with one lane adding four values one after the other).
+__device__ __forceinline__ void add_grad_sums(double* slot, const GradSums& s, int lane) {
+  static_assert(kGAbsSum == kGSum + 1 && kGSqSum == kGSum + 2, "neighbours");
+  const double x = lane == 0 ? s.sum : (lane == 1 ? s.abs : s.sq);
+  if (lane < 3) atomicAdd(&slot[kGSum + lane], x);
+  if (lane == 3) atomicMax(reinterpret_cast<uint32_t*>(&slot[kMaxGM]), f2u(s.top));
 }
 
 typedef uint32_t gs_u32x2 __attribute__((ext_vector_type(2)));
@@ -283,12 +290,10 @@ __global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const Tenso
   const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * per_group;
   const uint32_t end = static_cast<uint32_t>(min(begin + per_group, static_cast<uint64_t>(total_tiles)));
   GradSums s = {0.0, 0.0, 0.0, 0.0f};
-  uint32_t l = 0;
-  bool any = false;
+  uint32_t sum_of = 0;  // the tensor that s belongs to, plus one
   if (begin + wave < end) {
     uint32_t t = static_cast<uint32_t>(begin) + wave;
-    any = true;
-    l = find_begin(desc, n_tensors, t, lane);
+    uint32_t l = find_begin(desc, n_tensors, t, lane);
     TensorDesc d = load_desc(desc, l);
     Row row[8];
     auto whole = [&]() { return d.numel - static_cast<uint64_t>(t - d.tile_begin) * kTile >= static_cast<uint64_t>(kTile); };
@@ -305,7 +310,7 @@ __global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const Tenso
       const bool cur_whole = loaded;
       const uint64_t base = static_cast<uint64_t>(t - d.tile_begin) * kTile, left = d.numel - base;
       const void* const grad = d.grad;
-      const uint32_t cur_l = l;
+      sum_of = l + 1u;
 #pragma unroll
       for (int i = 0; i < 8; ++i) cur[i] = row[i];
       t += kGradWaves;
@@ -318,19 +323,27 @@ __global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const Tenso
       if (cur_whole) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) add_row(s, cur[i]);
-      } else {  // the ragged last tile of a tensor: element by element
-#pragma unroll 4
-        for (uint32_t k = 0; k < 32; ++k) {
-          const uint64_t off = 64u * k + lane;
-          if (off < left)
-            add_grad(s, BF16 ? u2f(static_cast<uint32_t>(as_global(static_cast<const uint16_t*>(grad))[base + off]) << 16)
-                             : as_global(static_cast<const float*>(grad))[base + off]);
+      } else {  // the ragged last tile of a tensor: whole rows of four at once, the up to three elements behind them by a lane each
+        const STQ_GLOBAL Row* p = (const STQ_GLOBAL Row*)(grad) + base / 4 + lane;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          cur[i] = Row{};
+          if (4u * (64u * i + lane) + 4u <= left) cur[i] = p[64 * i];
         }
+        const uint32_t rest = static_cast<uint32_t>(left) & 3u;
+        uint32_t last = 0u;
+        if (static_cast<uint32_t>(lane) < rest) {
+          const uint64_t at = base + left - rest + lane;
+          last = BF16 ? as_global(static_cast<const uint16_t*>(grad))[at] : as_global(static_cast<const uint32_t*>(grad))[at];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) add_row(s, cur[i]);
+        add_grad(s, u2f(BF16 ? last << 16 : last));
+        asm volatile("");  // (keeps these additions apart from a whole tile's, which must not wait for all loads)
       }
       if (!more) break;
-      if (l != cur_l) {
-        const GradSums w = wave_sums(s);
-        if (lane == 0) add_grad_sums(stats + static_cast<size_t>(cur_l) * kStatSlots, w);
+      if (l + 1u != sum_of) {
+        add_grad_sums(stats + static_cast<size_t>(sum_of - 1u) * kStatSlots, wave_sums(s), lane);
         s = {0.0, 0.0, 0.0, 0.0f};
       }
     }
@@ -339,25 +352,19 @@ __global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const Tenso
   const GradSums w = wave_sums(s);
   if (lane == 0) {
     held[wave] = w;
-    ended_in[wave] = any ? l + 1u : 0u;
+    ended_in[wave] = sum_of;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t last = 0;
-    for (int k = 0; k < kGradWaves; ++k) last = max(last, ended_in[k]);
-    GradSums sum = {0.0, 0.0, 0.0, 0.0f};
-    for (int k = 0; k < kGradWaves; ++k) {
-      if (ended_in[k] == last) {
-        sum.sum += held[k].sum;
-        sum.abs += held[k].abs;
-        sum.sq += held[k].sq;
-        sum.top = fmaxf(sum.top, held[k].top);
-      } else if (ended_in[k]) {
-        add_grad_sums(stats + static_cast<size_t>(ended_in[k] - 1u) * kStatSlots, held[k]);
-      }
-    }
-    if (last) add_grad_sums(stats + static_cast<size_t>(last - 1u) * kStatSlots, sum);
+  static_assert(kGradWaves == 8, "a lane of an octet for each wave");
+  const uint32_t mine = ended_in[lane & 7], last = octet_max(mine);
+  if (wave == 0) {
+    const GradSums& h = held[lane & 7];
+    const bool in = mine == last;
+    const GradSums sum = {octet_sum(in ? h.sum : 0.0), octet_sum(in ? h.abs : 0.0), octet_sum(in ? h.sq : 0.0),
+                          u2f(octet_max(in ? f2u(h.top) : 0u))};
+    if (last) add_grad_sums(stats + static_cast<size_t>(last - 1u) * kStatSlots, sum, lane);
   }
+  if (sum_of && sum_of != last) add_grad_sums(stats + static_cast<size_t>(sum_of - 1u) * kStatSlots, w, lane);
 }
 
 // The accumulators to host memory, and zero in their place: one launch instead of a copy and a fill.

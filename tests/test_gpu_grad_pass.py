@@ -1,0 +1,40 @@
+"""The gradients' statistics of stq_grad_stats at the edges of its loads (16 or 8 bytes a lane, whole tiles apart from ragged
+ones) and of its division of the work, against numpy's float64."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SIZES = {
+    # one tile a wave: every remainder of a load, of a row, of a tile
+    "edges": [1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 259, 1023, 1024, 1791, 2044, 2045, 2047, 2048, 2049, 2051, 4095, 4096, 4099],
+    # several tiles a wave: waves that end in different tensors of their workgroup's range, ragged tiles between whole ones
+    "ranges": [700_001, 2048 * 3, 5, 2048 * 1999 + 1, 2048 * 41 + 2046, 1, 2_500_003] + [2048 * 2 + 7 * k for k in range(9)],
+    "one": [2048 * 4100],
+}
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("which", SIZES)
+def test_edges_of_the_gradient_pass(which, dtype):
+    import paper_2604_06836_amd as stq
+    from workloads import configs
+    from workloads.harness import DeviceModel
+    sizes = SIZES[which]
+    ctx = stq.Context(0, 64)
+    w = configs.Workload(97, "gpass-%s-%s" % (which, dtype), [("t%d" % i, n) for i, n in enumerate(sizes)], 128, dtype, 1, "normal_per_tensor")
+    m = DeviceModel(ctx, w, [(4, 4)] * len(sizes))
+    m.set_grads(1)
+    for _ in range(2):  # the second call finds the accumulators cleared
+        ctx.grad_stats(m.tensors, w.K, 1 if dtype == "bf16" else 0, m.stream)
+        got = ctx.stats(len(sizes), m.stream)
+        for l, g in enumerate(got):
+            x = m.grad[l].double().cpu().numpy()
+            total = np.abs(x).sum()
+            assert g.count == sizes[l] and g.g_absmax == np.abs(x).max(), l
+            # fp64 additions in another order: no chain is longer than 3000 (a lane's elements, the lanes, the workgroups),
+            # 3000 * 2^-53 = 3.4e-13 of the sum of absolute values
+            for a, b, scale in ((g.g_sum, x.sum(), total), (g.g_abs_sum, total, total), (g.g_sq_sum, (x * x).sum(), (x * x).sum())):
+                assert abs(a - b) <= 1e-12 * scale, (l, a, b)
+    ctx.close()
