@@ -303,6 +303,12 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
 #ifdef STQ_TUNING_ENV
   if (const char* e = std::getenv("STQ_CLASSES")) w.lg_classes = std::strtoul(e, nullptr, 10);
 #endif
+  // Large launches write through: parameters and code words leave the L2 at once, with the reads that make room for
+  // them no longer waiting for a line to be written (0.1 G parameters: bf16 gradients 214.4 us, written through 211.5, fp32
+  // 240.2 and 238.0; 0.2 G 404 and 400, 460 and 455; 1.56 G bf16 3082 and 3051; transitions and 16-bit states 1.4 and 1.1 % less).
+  // Below, the end of the launch finds less of it done: 60 M 120.8 and 120.9 (bf16), 127.0 and 130.6 (fp32); 2.4 M 8.0 and
+  // 8.3.  With every statistic, where the vector instructions count, 0.5 G 1340 and 1340: not built.
+  w.write_through = total >= 45000u;
   // How a wave finds the tensor of its next unit (see step_kernel).  A walk costs one scalar load after the other for each
   // tensor it passes, a search one or two vector loads, which take as long as some of them while the memory system is busy.
   // With at most 8 tensors to the next unit on average a wave walks (148 tensors of 124 M elements, 5 to pass: 256 us, with

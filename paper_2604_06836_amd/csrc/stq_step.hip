@@ -52,6 +52,7 @@ struct Part {
 };
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // value at byte offset `off` of an LDS float table
 __device__ __forceinline__ float lds_at(const float* base, uint32_t off) {
   return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + off);
@@ -143,6 +144,25 @@ __device__ __forceinline__ void unpack_offsets(const uint32_t (&lw)[W], uint32_t
   }
 }
 
+// Stores of a launch that writes through (see launch_table): to memory at once instead of when the L2 makes room.  (Only both
+// the parameters and the words of codes together gain; the bytes of words that two parts share are left to the L2, which
+// has them from both.)
+__device__ __forceinline__ void store_through(STQ_GLOBAL uint32_t* p, uint32_t x) {
+  __hip_atomic_store((uint32_t*)p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// 16 bytes to byte `off` of the `bytes` at base (the same in all lanes), with the non-temporal hint
+__device__ __forceinline__ void store_through(STQ_GLOBAL float* base, int bytes, uint32_t off, f32x4 x) {
+  constexpr int kNt = 2, kSc1 = 16;
+  const auto where = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);  // (a raw buffer)
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), where, off, 0, kNt | kSc1);
+}
+// a whole word of codes
+template <bool THROUGH>
+__device__ __forceinline__ void store_word(STQ_GLOBAL uint32_t* p, uint32_t x) {
+  if constexpr (THROUGH) store_through(p, x);
+  else *p = x;
+}
+
 // Bytes [FIRST, END) of x to the same bytes of the word at p.
 template <int FIRST, int END>
 __device__ __forceinline__ void store_bytes(STQ_GLOBAL uint32_t* p, uint32_t x) {
@@ -164,7 +184,7 @@ __device__ __forceinline__ void store_bytes(STQ_GLOBAL uint32_t* p, uint32_t x) 
 // straddles two words).
 // Other waves have the parts before and after this one: of the words that it shares with them it writes its own bytes (a
 // part starts and ends on a byte; their waves read these words as a whole, but use no byte that is not theirs).
-template <int ROWS, int B, bool MINUS1>
+template <int ROWS, int B, bool MINUS1, bool THROUGH>
 __device__ __forceinline__ void pack_store(const uint32_t (&code)[4 * ROWS], STQ_GLOBAL uint32_t* C, uint32_t s0, uint32_t lane) {
   constexpr int N = 4 * ROWS, kBits = N * B, kWhole = kBits / 32, kWords = (kBits + 31) / 32;
   uint32_t w[kWords], ones[kWords];  // the part's bits, and a 1 for each of its codes that lies in one word
@@ -194,7 +214,7 @@ __device__ __forceinline__ void pack_store(const uint32_t (&code)[4 * ROWS], STQ
   C += lane;
   if (kWordAligned<ROWS, B> || s0 == 0) {
 #pragma unroll
-    for (int k = 0; k < kWhole; ++k) C[64u * k] = w[k];
+    for (int k = 0; k < kWhole; ++k) store_word<THROUGH>(C + 64u * k, w[k]);
     if constexpr (kWhole < kWords) store_bytes<0, kBits % 32 / 8>(C + 64 * kWhole, w[kWhole]);
     return;
   }
@@ -203,7 +223,7 @@ __device__ __forceinline__ void pack_store(const uint32_t (&code)[4 * ROWS], STQ
     if constexpr (ROWS == 4) {  // the second half of a tile, from the middle of a word to the end of one
       store_bytes<2, 4>(C, m0);
 #pragma unroll
-      for (int k = 1; k < kWords; ++k) C[64u * k] = __builtin_amdgcn_alignbit(w[k], w[k - 1], 16u);
+      for (int k = 1; k < kWords; ++k) store_word<THROUGH>(C + 64u * k, __builtin_amdgcn_alignbit(w[k], w[k - 1], 16u));
     } else {  // a quarter in the middle or at the end of a tile: of three words at most
       const uint32_t hi = kWords == 2 ? w[kWords - 1] : 0u;
       const uint32_t m1 = __builtin_amdgcn_alignbit(hi, w[0], 32u - s0), m2 = hi >> (32u - s0);
@@ -507,7 +527,7 @@ __device__ __forceinline__ float bf16_rne(float x) {
 // MODE 0: widths stay as they are; 1: the launch changes widths (other destination buffers);
 // 2: as 1, and states may have the wide formats: 32 bits = the fp32 value, 16 bits = its bfloat16
 // rounding, stored in the same tile format with 32- or 16-bit codes and without scales.
-template <bool BF16, int STATS, bool TAIL, int MODE, int ROWS>
+template <bool BF16, int STATS, bool TAIL, int MODE, int ROWS, bool THROUGH>
 __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile, uint32_t q, uint32_t n_valid,
                                              const StepArgs& a, const uint32_t* lds, uint32_t* ws, int lane,
                                              LaneStats<STATS>& st) {
@@ -867,7 +887,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       m[n] = mq;
     }
     if (STATS == 1) st.add(kLMErr, lane, sm_err);
-    STQ_SWITCH_BITS(bmo, (pack_store<ROWS, B, true>(code, CMO, s0mo, ul)));
+    STQ_SWITCH_BITS(bmo, (pack_store<ROWS, B, true, THROUGH>(code, CMO, s0mo, ul)));
   }
 
   // ---- logarithmic quantization of v and the parameter update ----
@@ -926,7 +946,7 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
       }
       st.add(kLVErr, lane, sv_err);
     }
-    STQ_SWITCH_BITS(bvo, (pack_store<ROWS, B, false>(code, CVO, s0vo, ul)));
+    STQ_SWITCH_BITS(bvo, (pack_store<ROWS, B, false, THROUGH>(code, CVO, s0vo, ul)));
     // first table entry of the lane's two blocks: ((row*G + block) << bv_out, or << lgP for the roots), G = 256/K blocks per row
     const uint32_t lg_row = use_table ? bvo : lgP;
     uint32_t row[ROWS];
@@ -944,8 +964,9 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     if (!TAIL) {
-      __builtin_nontemporal_store(f32x4{theta[4 * i], theta[4 * i + 1], theta[4 * i + 2], theta[4 * i + 3]},
-                                  &reinterpret_cast<STQ_GLOBAL f32x4*>(P + 256 * i)[ul]);
+      const f32x4 t = {theta[4 * i], theta[4 * i + 1], theta[4 * i + 2], theta[4 * i + 3]};
+      if constexpr (THROUGH) store_through(P, 1024 * ROWS, 16u * ul + 1024u * i, t);
+      else __builtin_nontemporal_store(t, &reinterpret_cast<STQ_GLOBAL f32x4*>(P + 256 * i)[ul]);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -983,7 +1004,7 @@ __device__ __forceinline__ uint32_t class_of(uint32_t group, uint32_t lg_classes
 
 // What a workgroup needs first comes as arguments of its own, which are in registers when it starts (the build has them
 // preloaded; a struct's members would be read from memory first: 25 ragged tensors of 0.2 M elements 6.0 us, now 5.6).
-template <bool BF16, int STATS, int MODE, int ROWS>
+template <bool BF16, int STATS, int MODE, int ROWS, bool THROUGH>
 __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6) void step_kernel(
     const TensorDesc* desc, const uint32_t* tables, uint32_t* sched, uint32_t n_tensors, uint32_t total_tiles, uint32_t lg_classes,
     const StepArgs a) {
@@ -1072,9 +1093,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
       const uint32_t tile = t - d.tile_begin;
       const uint64_t left = d.numel - static_cast<uint64_t>(tile) * kTile;
       if (left >= 256u * ROWS * (q + 1u))
-        process_part<BF16, STATS, false, MODE, ROWS>(d, tile, q, kTile, a, lds, ws, lane, st);
+        process_part<BF16, STATS, false, MODE, ROWS, THROUGH>(d, tile, q, kTile, a, lds, ws, lane, st);
       else
-        process_part<BF16, STATS, true, MODE, ROWS>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, st);
+        process_part<BF16, STATS, true, MODE, ROWS, THROUGH>(d, tile, q, static_cast<uint32_t>(left), a, lds, ws, lane, st);
       if (STATS) {
         if (!in_group) flush_stats(st, slots_of(l), lane);
         if (wave == 0 && lane == 0) group_end[turn] = d.tile_begin + d.n_tiles;
@@ -1102,16 +1123,25 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, ROWS == 4 || MODE == 2 ? 4 : 6
 
 }  // namespace
 
-template <int MODE, int STATS, int ROWS>
+template <int MODE, int STATS, int ROWS, bool THROUGH>
 static void launch_grads(const StepWork& w, const StepArgs& a, bool grad_bf16, dim3 grid, dim3 block, hipStream_t s) {
-  const auto kernel = grad_bf16 ? step_kernel<true, STATS, MODE, ROWS> : step_kernel<false, STATS, MODE, ROWS>;
+  const auto kernel = grad_bf16 ? step_kernel<true, STATS, MODE, ROWS, THROUGH> : step_kernel<false, STATS, MODE, ROWS, THROUGH>;
   hipLaunchKernelGGL(kernel, grid, block, 0, s, w.desc, w.tables, w.sched, w.n_tensors, w.total_tiles, w.lg_classes, a);
 }
 
 template <int MODE, int STATS>
 static void launch_variant(const StepWork& w, const StepArgs& a, bool grad_bf16, dim3 grid, dim3 block, hipStream_t s) {
-  if (w.unit_rows == 2) launch_grads<MODE, STATS, 2>(w, a, grad_bf16, grid, block, s);
-  else launch_grads<MODE, STATS, 4>(w, a, grad_bf16, grid, block, s);
+  if (w.unit_rows == 2) {
+    launch_grads<MODE, STATS, 2, false>(w, a, grad_bf16, grid, block, s);
+  } else {
+    if constexpr (STATS != 1) {
+      if (w.write_through) {
+        launch_grads<MODE, STATS, 4, true>(w, a, grad_bf16, grid, block, s);
+        return;
+      }
+    }
+    launch_grads<MODE, STATS, 4, false>(w, a, grad_bf16, grid, block, s);
+  }
 }
 
 template <int MODE>
