@@ -1,5 +1,6 @@
 """The gradients' statistics of stq_grad_stats at the edges of its loads (16 or 8 bytes a lane, whole tiles apart from ragged
-ones) and of its division of the work, against numpy's float64."""
+ones) and of its division of the work, against numpy's float64; and their
+read-back, whose parts arrive one by one."""
 import numpy as np
 import pytest
 import torch
@@ -37,4 +38,27 @@ def test_edges_of_the_gradient_pass(which, dtype):
             # 3000 * 2^-53 = 3.4e-13 of the sum of absolute values
             for a, b, scale in ((g.g_sum, x.sum(), total), (g.g_abs_sum, total, total), (g.g_sq_sum, (x * x).sum(), (x * x).sum())):
                 assert abs(a - b) <= 1e-12 * scale, (l, a, b)
+    ctx.close()
+
+
+@pytest.mark.parametrize("busy", [False, True])
+def test_read_back(busy):
+    """Parts of 16 tensors each; calls for more and for fewer than the call before; behind work that takes longer than the
+    host looks for the parts."""
+    import paper_2604_06836_amd as stq
+    from workloads import configs
+    from workloads.harness import DeviceModel
+    counts = [1, 16, 17, 40, 33, 32, 1, 40]
+    ctx = stq.Context(0, 40)
+    w = configs.Workload(98, "read-back", [("t%d" % i, 100 + i) for i in range(40)], 64, "fp32", 1, "normal_per_tensor")
+    m = DeviceModel(ctx, w, [(4, 4)] * 40)
+    m.set_grads(1)
+    x = [g.double().abs().cpu().numpy() for g in m.grad]
+    big = torch.zeros(1 << 30, dtype=torch.uint8, device="cuda") if busy else None
+    for n in counts:
+        for _ in range(40 if busy else 0):  # 40 passes over 1 GiB: 10 ms
+            big.add_(1)
+        ctx.grad_stats((type(m.tensors[0]) * n)(*m.tensors[:n]), w.K, 0, m.stream)
+        for l, g in enumerate(ctx.stats(n, m.stream)):
+            assert g.count == x[l].size and g.g_absmax == x[l].max() and abs(g.g_abs_sum - x[l].sum()) <= 1e-12 * x[l].sum(), (n, l)
     ctx.close()
