@@ -112,3 +112,40 @@ def test_sixteen_uploads_ahead_of_the_device(kind):
         c.close()
     for l, (x, y) in enumerate(zip(*got)):
         assert torch.equal(x, y), l
+
+
+# up to 480 addresses of gradients travel in the launch's arguments, more through a staging slot
+@pytest.mark.parametrize("n", [1, 480, 481])
+def test_addresses_of_the_gradients(n):
+    import paper_2604_06836_amd as stq
+    from workloads.harness import hparams
+    sizes, K, got = [1 + (977 * l) % 300 for l in range(n)], 64, []
+    for by_address in (False, True):
+        c = stq.Context(0, 512)
+        m = model(c, sizes, [(4, 4)] * n, K, 94, "fp32")
+        for lst in (m.m_codes, m.v_codes):
+            for l, buf in enumerate(lst):
+                buf[m._code_words(sizes[l], 4):] = 0
+        for x in m._spare.values():
+            x.zero_()
+        eng = c.engine(m.tensors, [(m._spare[(l, 0)].data_ptr(), m._spare[(l, 1)].data_ptr()) for l in range(n)], m.cplan, 8, K,
+                       thr=(6.8,), bits=(4, 8), stream=m.stream)
+        grads = []
+        for k in range(3):
+            m.set_grads(k + 1)
+            grads.append([g.clone() for g in m.grad])
+        for t in range(1, 31):  # (24 slots; decisions up to step 4; every third step keeps the addresses it has)
+            g = grads[(t - t % 3) % 9 // 3]
+            if by_address:
+                eng.step(hparams(m.w, t), 0, [x.data_ptr() for x in g] if t % 3 == 0 or t == 1 else None, m.stream)
+            else:
+                for x, y in zip(m.grad, g):
+                    x.copy_(y)
+                eng.step(hparams(m.w, t), 0, None, m.stream)
+        torch.cuda.synchronize()
+        spare = [m._spare[k] for k in sorted(m._spare)]
+        got.append([x.view(torch.int32).clone() for x in [*m.param, *m.m_codes, *m.v_codes, *spare, *m.m_scales, *m.v_scales]])
+        eng.close()
+        c.close()
+    for l, (x, y) in enumerate(zip(*got)):
+        assert torch.equal(x, y), l
