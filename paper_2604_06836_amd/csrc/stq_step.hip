@@ -982,7 +982,8 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 //    before they go on to the next one, which was drawn while they worked.  The chip as a whole then sweeps the arrays in
 //    order, and the narrower the window in which it works at one time, the more the memory system gives: 1.56 G parameters
 //    (bf16 gradients) 3.09 ms with half tiles in one order, 3.36 with whole tiles (tickets twice as long), 3.39 with two
-//    half tiles one after the other per draw, 3.82 with every workgroup walking its own tickets.
+//    half tiles one after the other per draw, 3.82 with every workgroup walking its own tickets.  (Without writing
+//    through, which makes 3.05 of the 3.09.)
 //    One counter alone is drawn from at most every 12 ns or so, which 512 workgroups starting together feel (9 M
 //    parameters: 26.9 us, with eight counters 22.5; 130 M: 268.8 and 266.9; 1.56 G: 3092 and 3120).  The workgroups of a
 //    counter have to be spread over the XCDs: with a counter for each XCD, which do not run at the same pace, the classes
@@ -996,8 +997,8 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 // sums of the statistics over the lanes) is a third of a quarter's vector instructions, and one chain of latencies; with
 // four rows it is shared by twice the elements, and the waves that 128 registers leave, 16 per CU, keep as many bytes in
 // flight.  bf16 gradients, static order: 30 M parameters 73.8 us with quarters, 61.1 with halves; 12.5 M 33.3 and 27.7.
-// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 7.0 ms = 6.4 TB/s, where an in-place
-// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 300 us); launches that leave the chip partly
+// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 6.96 ms = 6.4 TB/s, where an in-place
+// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 292 us); launches that leave the chip partly
 // idle one pass of latencies (tables, descriptor, loads, three LDS exchanges, stores): 6 us for 0.2 M parameters.
 // the class of ticket counter that a workgroup belongs to
 __device__ __forceinline__ uint32_t class_of(uint32_t group, uint32_t lg_classes) { return (group >> 3) & ((1u << lg_classes) - 1u); }
