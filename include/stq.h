@@ -17,8 +17,7 @@
  *     stq_engine_destroy free.  "host" pointers are ordinary process memory.
  *   - hip_stream is a hipStream_t passed as void* (NULL = the default stream).
  *     stq_zero_state, stq_step, stq_step_transition, stq_repack and stq_repack_many
- *     are asynchronous on that stream; stq_stats returns when all that was enqueued
- *     on it before has run.  stq_step,
+ *     are asynchronous on that stream; stq_stats synchronises it.  stq_step,
  *     stq_step_transition and stq_grad_stats keep the tensor tables of the last four
  *     distinct argument sets (or more) on the device: a call whose tensors, plan and
  *     block size equal one of those, on the same stream, is one kernel launch and
@@ -227,8 +226,8 @@ int stq_step_transition(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n,
 int stq_grad_stats(stq_ctx* ctx, const stq_tensor* tensors, uint32_t n, uint32_t block,
                    uint32_t grad_dtype, void* hip_stream);
 
-/* Copy accumulators 0..n-1 to `out` (host, n entries), once all that was enqueued
- * on the stream before has run, and clear them on the device.  Sums are order-dependent in the last bits; the maxima
+/* Copy accumulators 0..n-1 to `out` (host, n entries), synchronise, and clear
+ * them on the device.  Sums are order-dependent in the last bits; the maxima
  * are exact. */
 int stq_stats(stq_ctx* ctx, stq_layer_stats* out, uint32_t n, void* hip_stream);
 

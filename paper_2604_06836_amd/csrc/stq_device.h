@@ -93,10 +93,7 @@ constexpr uint64_t kRepackOnceBytes = 350ull << 20;  // see launch_repack_many
 int launch_repack_many(RepackManyArgs a, uint64_t code_bytes, void* stream);  // code_bytes: read and written
 int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total_tiles, double* stats, bool grad_bf16,
                       uint32_t n_cu, void* stream);
-constexpr uint32_t kTakeThreads = 256;
-constexpr uint32_t take_groups(uint64_t n) { return static_cast<uint32_t>((n + kTakeThreads - 1) / kTakeThreads); }
-// n accumulators to host memory, then `call` to the first take_groups(n) words of `taken` (host memory too)
-int launch_take_stats(double* host, double* acc, uint64_t n, uint64_t* taken, uint64_t call, void* stream);
+int launch_take_stats(double* host, double* acc, uint64_t n, void* stream);
 int launch_upload(void* dst, const void* pinned, uint64_t bytes, void* stream);  // a multiple of 16 bytes
 int launch_upload_by_value(void* dst, const void* host, uint64_t bytes, void* stream);  // the same, for a stream being recorded
 int launch_fill_zero(uint32_t* p, uint64_t words, void* stream);

@@ -41,8 +41,6 @@ struct stq_ctx {
   hipEvent_t jobs_done[stq::kRingGroups] = {};
   int jobs_pos = 0;
   double* h_stats = nullptr;                 // pinned, max_tensors * kStatSlots
-  uint64_t* h_taken = nullptr;               // pinned, behind h_stats: which call each part of it is from (see stq_stats)
-  uint64_t stats_calls = 0;
   std::vector<stq::TensorDesc> uploaded[stq::kDescTables];  // what each d_desc currently holds
   hipStream_t uploaded_on[stq::kDescTables] = {};            // the stream that uploaded it
   bool held[stq::kDescTables] = {};                          // a recorded launch reads it

@@ -367,17 +367,12 @@ __global__ __launch_bounds__(64 * kGradWaves) void grad_stats_kernel(const Tenso
   if (sum_of && sum_of != last) add_grad_sums(stats + static_cast<size_t>(sum_of - 1u) * kStatSlots, w, lane);
 }
 
-// The accumulators to host memory, and zero in their place: one launch instead of a copy and a fill.  Each workgroup then says
-// that its part is there: the host reads the words as soon as they have arrived, which is before the launch has been found to
-// have ended (see stq_stats).
-__global__ __launch_bounds__(kTakeThreads) void take_stats_kernel(uint64_t* host, uint64_t* acc, uint64_t n, uint64_t* taken, uint64_t call) {
-  const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kTakeThreads + threadIdx.x;
-  if (i < n) {
-    host[i] = acc[i];
-    acc[i] = 0u;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(taken + blockIdx.x, call, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+// The accumulators to host memory, and zero in their place: one launch instead of a copy and a fill.
+__global__ __launch_bounds__(256) void take_stats_kernel(uint64_t* host, uint64_t* acc, uint64_t n) {
+  const uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= n) return;
+  host[i] = acc[i];
+  acc[i] = 0u;
 }
 
 }  // namespace
@@ -416,9 +411,9 @@ int launch_grad_stats(const TensorDesc* desc, uint32_t n_tensors, uint32_t total
   return static_cast<int>(hipGetLastError());
 }
 
-int launch_take_stats(double* host, double* acc, uint64_t n, uint64_t* taken, uint64_t call, void* stream) {
-  hipLaunchKernelGGL(take_stats_kernel, dim3(take_groups(n)), dim3(kTakeThreads), 0, static_cast<hipStream_t>(stream),
-                     reinterpret_cast<uint64_t*>(host), reinterpret_cast<uint64_t*>(acc), n, taken, call);
+int launch_take_stats(double* host, double* acc, uint64_t n, void* stream) {
+  hipLaunchKernelGGL(take_stats_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     reinterpret_cast<uint64_t*>(host), reinterpret_cast<uint64_t*>(acc), n);
   return static_cast<int>(hipGetLastError());
 }
 

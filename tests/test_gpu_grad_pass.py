@@ -1,6 +1,6 @@
 """The gradients' statistics of stq_grad_stats at the edges of its loads (16 or 8 bytes a lane, whole tiles apart from ragged
 ones) and of its division of the work, against numpy's float64; and their
-read-back, whose parts arrive one by one."""
+read-back, which waits for the stream."""
 import numpy as np
 import pytest
 import torch
@@ -27,7 +27,7 @@ def test_edges_of_the_gradient_pass(which, dtype):
     w = configs.Workload(97, "gpass-%s-%s" % (which, dtype), [("t%d" % i, n) for i, n in enumerate(sizes)], 128, dtype, 1, "normal_per_tensor")
     m = DeviceModel(ctx, w, [(4, 4)] * len(sizes))
     m.set_grads(1)
-    for _ in range(2):  # the second call finds the accumulators cleared
+    for _ in range(2):  # the second call finds the accumulators cleared, and gradients of twice the size
         ctx.grad_stats(m.tensors, w.K, 1 if dtype == "bf16" else 0, m.stream)
         got = ctx.stats(len(sizes), m.stream)
         for l, g in enumerate(got):
@@ -38,13 +38,15 @@ def test_edges_of_the_gradient_pass(which, dtype):
             # 3000 * 2^-53 = 3.4e-13 of the sum of absolute values
             for a, b, scale in ((g.g_sum, x.sum(), total), (g.g_abs_sum, total, total), (g.g_sq_sum, (x * x).sum(), (x * x).sum())):
                 assert abs(a - b) <= 1e-12 * scale, (l, a, b)
+        for g in m.grad:
+            g.mul_(2)  # exact in both types
     ctx.close()
 
 
 @pytest.mark.parametrize("busy", [False, True])
 def test_read_back(busy):
-    """Parts of 16 tensors each; calls for more and for fewer than the call before; behind work that takes longer than the
-    host looks for the parts."""
+    """Calls for more tensors and for fewer than the call before, each with other gradients; also behind some milliseconds of
+    work.  A call returns when its stream is idle."""
     import paper_2604_06836_amd as stq
     from workloads import configs
     from workloads.harness import DeviceModel
@@ -55,10 +57,18 @@ def test_read_back(busy):
     m.set_grads(1)
     x = [g.double().abs().cpu().numpy() for g in m.grad]
     big = torch.zeros(1 << 30, dtype=torch.uint8, device="cuda") if busy else None
-    for n in counts:
-        for _ in range(40 if busy else 0):  # 40 passes over 1 GiB: 10 ms
-            big.add_(1)
-        ctx.grad_stats((type(m.tensors[0]) * n)(*m.tensors[:n]), w.K, 0, m.stream)
-        for l, g in enumerate(ctx.stats(n, m.stream)):
-            assert g.count == x[l].size and g.g_absmax == x[l].max() and abs(g.g_abs_sum - x[l].sum()) <= 1e-12 * x[l].sum(), (n, l)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for call, n in enumerate(counts):
+            for _ in range(40 if busy else 0):  # 40 passes over 1 GiB: 10 ms
+                big.add_(1)
+            for g in m.grad:
+                g.mul_(2)  # exact
+            ctx.grad_stats((type(m.tensors[0]) * n)(*m.tensors[:n]), w.K, 0, m.stream)
+            got = ctx.stats(n, m.stream)
+            assert side.query(), call
+            for l, g in enumerate(got):
+                y = x[l] * 2.0 ** (call + 1)
+                assert g.count == y.size and g.g_absmax == y.max() and abs(g.g_abs_sum - y.sum()) <= 1e-12 * y.sum(), (call, l)
     ctx.close()
