@@ -58,17 +58,19 @@ def test_job_tables(ctx, n):
         assert torch.equal(x, y), l
 
 
-@pytest.mark.parametrize("kind", ["step", "repack", "engine"])
+@pytest.mark.parametrize("kind", ["step", "repack", "engine", "engine-481"])
 def test_sixteen_uploads_ahead_of_the_device(kind):
     """Sixteen calls that upload a table each return while the stream is still busy with earlier work, whichever staging slot
-    they begin at, and their results are those of calls that were waited for."""
+    they begin at, and their results are those of calls that were waited for.  (An engine of up to 480 tensors has no slots: its
+    addresses are the launch's arguments.)"""
     import paper_2604_06836_amd as stq
     from paper_2604_06836_amd import binding
     from workloads.harness import hparams
-    n, K, got = 3, 64, []
+    sizes = [700, 2049, 5] if kind != "engine-481" else [1 + (977 * l) % 300 for l in range(481)]
+    n, K, got = len(sizes), 64, []
     for ahead in (False, True):
-        c = stq.Context(0, 8)
-        m = model(c, [700, 2049, 5], [(4, 4)] * n, K, 93, "fp32")
+        c = stq.Context(0, 512 if n > 8 else 8)
+        m = model(c, sizes, [(4, 4)] * n, K, 93, "fp32")
         for lst in (m.m_codes, m.v_codes):  # nothing undefined behind the codes
             for l, buf in enumerate(lst):
                 buf[m._code_words(m.numel[l], 4):] = 0
@@ -76,15 +78,16 @@ def test_sixteen_uploads_ahead_of_the_device(kind):
         for k in range(7):
             m.set_grads(k + 1)
             grads.append([g.clone() for g in m.grad])
-        out = [[torch.zeros_like(m.m_codes[l]) for l in range(n)] for _ in range(17)]
+        addresses = [[g.data_ptr() for g in gs] for gs in grads]
+        out = [[torch.zeros_like(m.m_codes[l]) for l in range(n)] for _ in range(17 if kind == "repack" else 0)]
         eng = None
-        if kind == "engine":
+        if kind.startswith("engine"):
             eng = c.engine(m.tensors, [(m._spare[(l, 0)].data_ptr(), m._spare[(l, 1)].data_ptr()) for l in range(n)], m.cplan, 8, K,
                            thr=(6.8,), bits=(4, 8), stream=m.stream)
 
         def call(k, t):
-            if kind == "engine":  # (no decisions: past the first steps)
-                eng.step(hparams(m.w, t), 0, [g.data_ptr() for g in grads[t % 7]], m.stream)
+            if kind.startswith("engine"):  # (no decisions: past the first steps)
+                eng.step(hparams(m.w, t), 0, addresses[t % 7], m.stream)
             elif kind == "repack":
                 c.repack_many([(m.numel[l], 0, m.m_codes[l].data_ptr(), 4, out[k][l].data_ptr(), 2 + t % 7) for l in range(n)], K, m.stream)
             else:  # 21 argument sets in turn, more than there are tables
@@ -114,7 +117,8 @@ def test_sixteen_uploads_ahead_of_the_device(kind):
         assert torch.equal(x, y), l
 
 
-# up to 480 addresses of gradients travel in the launch's arguments, more through a staging slot
+# Up to 480 addresses of gradients travel in the launch's arguments, more through a staging slot.  (Eleven uploads: the slots come
+# round in test_sixteen_uploads_ahead_of_the_device.)
 @pytest.mark.parametrize("n", [1, 480, 481])
 def test_addresses_of_the_gradients(n):
     import paper_2604_06836_amd as stq
@@ -134,7 +138,7 @@ def test_addresses_of_the_gradients(n):
         for k in range(3):
             m.set_grads(k + 1)
             grads.append([g.clone() for g in m.grad])
-        for t in range(1, 31):  # (24 slots; decisions up to step 4; every third step keeps the addresses it has)
+        for t in range(1, 31):  # (decisions up to step 4; two of three steps keep the addresses they have)
             g = grads[(t - t % 3) % 9 // 3]
             if by_address:
                 eng.step(hparams(m.w, t), 0, [x.data_ptr() for x in g] if t % 3 == 0 or t == 1 else None, m.stream)
