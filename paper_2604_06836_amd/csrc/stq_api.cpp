@@ -303,11 +303,14 @@ int launch_table(stq_ctx* ctx, const TensorDesc* d_desc, uint32_t n, uint32_t to
 #ifdef STQ_TUNING_ENV
   if (const char* e = std::getenv("STQ_CLASSES")) w.lg_classes = std::strtoul(e, nullptr, 10);
 #endif
-  // Large launches write through: parameters and code words leave the L2 at once, with the reads that make room for
-  // them no longer waiting for a line to be written (0.1 G parameters: bf16 gradients 214.4 us, written through 211.5, fp32
-  // 240.2 and 238.0; 0.2 G 404 and 400, 460 and 455; 1.56 G bf16 3082 and 3051; transitions and 16-bit states 1.4 and 1.1 % less).
-  // Below, the end of the launch finds less of it done: 60 M 120.8 and 120.9 (bf16), 127.0 and 130.6 (fp32); 2.4 M 8.0 and
-  // 8.3.  With every statistic, where the vector instructions count, 0.5 G 1340 and 1340: not built.
+  // Large launches write through: parameters and the code words of quantized states leave the L2 at once, with the reads that
+  // make room for them no longer waiting for a line to be written (0.1 G parameters: bf16 gradients 214.4 us, written through
+  // 211.5, fp32 240.2 and 238.0; 0.2 G 404 and 400, 460 and 455; 1.56 G bf16 3082 and 3051; transitions 1.4 % less, 16-bit states,
+  // of which only the parameters are, 1.0 %).  The line lies above the launches that lose by it, fp32 gradients of 40 to 60 M
+  // parameters (one tensor: 40 M 88.0 and 89.5, 60 M 129.1 and 133.2; 50 tensors of 62 M 136.7 and 137.6; why is not known).
+  // Others below it would have up to 1 % less (50 tensors: fp32 81 M 196.9 and 195.8, 31 M 72.5 and 71.7, bf16 62 M 122.3 and
+  // 121.7; wide states 30 M 127.9 and 126.7) or nothing (bf16, 50 tensors of 81 M 171.8 and 171.8, one of 30 M 60.9 and 61.1).
+  // With every statistic, where the vector instructions count, 0.5 G 1340 and 1340: not built.
   w.write_through = total >= 45000u;
   // How a wave finds the tensor of its next unit (see step_kernel).  A walk costs one scalar load after the other for each
   // tensor it passes, a search one or two vector loads, which take as long as some of them while the memory system is busy.

@@ -46,7 +46,7 @@ struct StepWork {
   uint32_t total_tiles;
   uint32_t lg_classes;     // log2 of the number of ticket counters
   uint32_t unit_rows;      // rows of a unit of scheduling: 2 (a quarter tile) or 4 (a half)
-  bool write_through;      // with halves: what the kernel writes goes through the L2 to memory at once
+  bool write_through;      // with halves: parameters and whole words of 2- to 8-bit codes go through the L2 to memory at once
 };
 // ... and the rest of its arguments.
 struct StepArgs {

@@ -146,7 +146,7 @@ __device__ __forceinline__ void unpack_offsets(const uint32_t (&lw)[W], uint32_t
 
 // Stores of a launch that writes through (see launch_table): to memory at once instead of when the L2 makes room.  (Only both
 // the parameters and the words of codes together gain; the bytes of words that two parts share are left to the L2, which
-// has them from both.)
+// has them from both.  The words of 16- and 32-bit states are plain stores in every variant.)
 __device__ __forceinline__ void store_through(STQ_GLOBAL uint32_t* p, uint32_t x) {
   __hip_atomic_store((uint32_t*)p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -997,8 +997,8 @@ __device__ __forceinline__ void process_part(const TensorDesc& d, uint32_t tile,
 // sums of the statistics over the lanes) is a third of a quarter's vector instructions, and one chain of latencies; with
 // four rows it is shared by twice the elements, and the waves that 128 registers leave, 16 per CU, keep as many bytes in
 // flight.  bf16 gradients, static order: 30 M parameters 73.8 us with quarters, 61.1 with halves; 12.5 M 33.3 and 27.7.
-// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 6.96 ms = 6.4 TB/s, where an in-place
-// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 292 us); launches that leave the chip partly
+// What bounds it: large launches the memory system (3.5 G parameters, 44.65 GB in 6.98 ms = 6.4 TB/s, where an in-place
+// addition of one array reaches 5.9), as do launches of 0.1 G (1.81 GB in 291 us); launches that leave the chip partly
 // idle one pass of latencies (tables, descriptor, loads, three LDS exchanges, stores): 6 us for 0.2 M parameters.
 // the class of ticket counter that a workgroup belongs to
 __device__ __forceinline__ uint32_t class_of(uint32_t group, uint32_t lg_classes) { return (group >> 3) & ((1u << lg_classes) - 1u); }
